@@ -7,12 +7,12 @@
 // once, then a handful of short phases between workgroup barriers.  Two measured facts shape it:
 //   * one compute unit pulls only about 20 GB/s out of a cold HBM (the chip's bandwidth is the sum
 //     over its 256 units), so the 64-128 KiB of centroid rows per level are the largest single cost;
-//   * with one workgroup per compute unit every instruction of the chain costs 8-9 cycles, so the
-//     chain is kept short: the products run on the fp64 matrix pipe, every thread then owns ONE entry
-//     (no loops at the benchmark's sizes), one exponential per (entry, head), no logarithm, and what
-//     is the same for the whole workgroup (one value per head) is worked out once per wave, the heads
-//     side by side in the lanes.  (More waves would shorten the per-entry part and lengthen that one:
-//     512 threads is where the two balance for levels of 256-512 entries.)
+//   * with two waves per SIMD a wave issues one instruction in 5 cycles, a dependent one 8 cycles after its
+//     predecessor (fp32 and fp64 alike; DPP 12, permlane swap 24, LDS read 67, fp64 division 70; a barrier 15;
+//     code that runs for the first time is no slower), so the chain is kept short: the products run on the
+//     fp64 matrix pipe and everything about an entry stays in the registers the product leaves it in (the
+//     register path below).  (More waves would shorten the per-entry part and lengthen what every wave
+//     does for itself: 512 threads is where the two balance for levels of 256-512 entries.)
 //
 // Logits l[h,i] = scale * q_h . Kc_i are accumulated in fp64 (products of bf16 numbers are exact,
 // so the sum carries ~1e-16 relative error and the ranking agrees with an fp64 reference except on
@@ -26,9 +26,9 @@
 // comparison among the entries of the boundary bucket (a most-significant-digit radix search takes
 // over where that bucket is crowded).
 //
-// Per-entry working arrays (logits, keys, counts, ids, row starts, flags) live in LDS when a level
-// has at most lds_cap entries and in a global scratch area otherwise (separate template
-// instantiations: LDS instructions and LDS-only barriers in the first case).
+// A level of at most lds_cap entries takes the register path (fast_level): its per-entry values live in
+// registers, the candidate list and the compact list of selected clusters in LDS, and its barriers wait for LDS
+// only.  Any other level works on arrays in a global scratch area, one entry per thread at a time (score_level).
 //
 // Shadow workgroups: with spare compute units (2 U <= units of the chip, U a multiple of eight: the
 // blocks of a launch go round the eight L2 slices), a second workgroup per unit, placed on the same
@@ -75,6 +75,9 @@ struct Scratch {
     double wm[kWaves][8];             // per wave and head: largest logit of an entry that takes part
     double ws[kWaves][8];             // per wave and head: sum of N e^{l - M_h}
     double bm[8], bs[8];              // what stayed behind at the coarse level, per head: shift and sum of N e^{l - shift}
+    double bw[kWaves][8];             // ... the same sum by wave (register path: bs is its column sums)
+    uint32_t far[2];                  // register path, per level: some logit needs a shift
+    uint32_t tiny;                    // register path: some score left the range of a double
     // extremes of the keys, token total, "some score too small" flag and boundary-list length of the
     // level in progress, maintained with LDS atomics
     unsigned long long key_min, key_max;
@@ -107,6 +110,15 @@ __device__ __forceinline__ void phase_sync()
     }
 }
 
+// Inclusive prefix sum over lanes 0..7 (the same DPP row; what lies above them is of no interest).
+__device__ __forceinline__ uint32_t eight_incl_scan_u32(uint32_t v)
+{
+    static_assert(kWaves == 8, "one lane per wave");
+    v += dpp_u32_or0<0x111, 0xf>(v);
+    v += dpp_u32_or0<0x112, 0xf>(v);
+    v += dpp_u32_or0<0x114, 0xf>(v);
+    return v;
+}
 // Exclusive prefix sums of two values per thread over one chunk of kThreads threads, with running
 // totals carried in registers (every thread adds the same chunk totals, so they stay uniform).
 // One barrier per call: the per-wave totals are double-buffered by the parity of `calls`; after the
@@ -128,7 +140,7 @@ __device__ __forceinline__ void chunk_excl_scan2(uint32_t a, uint32_t b, Scratch
     }
     phase_sync<kLds>();
     const uint32_t wa = lane < kWaves ? s.wsum[par][lane][0] : 0u, wb = lane < kWaves ? s.wsum[par][lane][1] : 0u;
-    const uint32_t sa = wave_incl_scan_u32(wa), sb = wave_incl_scan_u32(wb);
+    const uint32_t sa = eight_incl_scan_u32(wa), sb = eight_incl_scan_u32(wb);
     const int w = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t off_a = (uint32_t)__builtin_amdgcn_readlane((int)(sa - wa), w);
     const uint32_t off_b = (uint32_t)__builtin_amdgcn_readlane((int)(sb - wb), w);
@@ -313,14 +325,14 @@ __device__ __forceinline__ Lds carve_lds(unsigned char* lds, int cap)
     L.qB = reinterpret_cast<double*>(lds);
     L.hist = reinterpret_cast<unsigned long long*>(L.qB + GH * 512);
     L.blist = L.hist + kHistBuckets;
-    L.A.lg = reinterpret_cast<double*>(L.blist + 2 * kListCap);
-    L.A.lg_stride = cap;
-    L.A.keys = reinterpret_cast<uint64_t*>(L.A.lg + (size_t)G * cap);
+    L.A.lg = nullptr;            // (logits, row starts and flags of such a level stay in registers)
+    L.A.lg_stride = 0;
+    L.A.keys = reinterpret_cast<uint64_t*>(L.blist + 2 * kListCap);
     L.A.wts = reinterpret_cast<uint32_t*>(L.A.keys + cap);
     L.A.ids = reinterpret_cast<int32_t*>(L.A.wts + cap);
-    L.A.aux = L.A.ids + cap;
-    L.A.aux2 = L.A.aux + cap;
-    L.A.flags = reinterpret_cast<uint8_t*>(L.A.aux2 + cap);
+    L.A.aux2 = L.A.ids + cap;
+    L.A.aux = nullptr;
+    L.A.flags = nullptr;
     return L;
 }
 
@@ -353,29 +365,82 @@ __device__ __forceinline__ Arrays global_arrays(const ScoreParams& p, int u)
 // After the product lane (i, b, j) owns the logit of entry 4b + i and head j.
 // ------------------------------------------------------------------------------------------------
 template <int G>
-__device__ __forceinline__ double query_operand_element(const ScoreParams& p, int u, int x)
+__device__ __forceinline__ uint16_t query_operand_element(const ScoreParams& p, int u, int x)
 {
     const int hg = x >> 9, s = (x >> 4) & 31, k = (x >> 2) & 3, j = x & 3;
     const int h = 4 * hg + j, d = 32 * (s >> 3) + 8 * k + (s & 7);
-    return h < G ? (double)bf16_to_f32(p.q[((long long)u * G + h) * kHeadDim + d]) : 0.0;
+    return h < G ? p.q[((long long)u * G + h) * kHeadDim + d] : (uint16_t)0;
 }
 
-__device__ __forceinline__ double shfl_xor_f64(double v, int m)
+constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
+// The two halves of a pairwise exchange across rows of 16 lanes (kSpan = 16: rows 0/1 and 2/3; 32: the halves of
+// the wave), as one vector instruction per 32 bits: op(first, second) is the same in all lanes concerned.
+template <int kSpan>
+__device__ __forceinline__ void exchange_u32(uint32_t v, uint32_t& first, uint32_t& second)
+{
+    const auto r = kSpan == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                               : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    first = r[0];
+    second = r[1];
+}
+template <int kSpan, typename Op>
+__device__ __forceinline__ double across_rows(double v, Op op)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    uint32_t l0, l1, h0, h1;
+    exchange_u32<kSpan>((uint32_t)b, l0, l1);
+    exchange_u32<kSpan>((uint32_t)(b >> 32), h0, h1);
+    return op(__longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0)),
+              __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1)));
+}
+// Combination over the 16 lanes of a wave that are equal modulo 4 (matrix layout: the same head); every one of
+// them receives the result.
+template <typename Op>
+__device__ __forceinline__ double same_head(double x, Op op)
+{
+    x = op(x, dpp_f64<kDppRowRor4>(x));
+    x = op(x, dpp_f64<kDppRowRor8>(x));
+    x = across_rows<16>(x, op);
+    return across_rows<32>(x, op);
+}
+struct MaxOp { __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); } };
+struct MinOp { __device__ __forceinline__ double operator()(double a, double b) const { return fmin(a, b); } };
+struct AddOp { __device__ __forceinline__ double operator()(double a, double b) const { return a + b; } };
+// Sum over the wave; every lane receives it.
+__device__ __forceinline__ uint32_t wave_total_u32(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppXor1, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppXor2, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowRor4, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowRor8, 0xf, 0xf, true);
+    uint32_t a, b;
+    exchange_u32<16>(v, a, b);
+    v = a + b;
+    exchange_u32<32>(v, a, b);
+    return a + b;
+}
+// Combination over aligned groups of 8 lanes.
+template <typename Op>
+__device__ __forceinline__ double eight_lanes(double x, Op op)
+{
+    x = op(x, dpp_f64<kDppXor1>(x));
+    x = op(x, dpp_f64<kDppXor2>(x));
+    return op(x, dpp_f64<kDppHalfMirror>(x));
+}
+// The value lane t of each group of four holds.
+template <int t>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, t * 0x55, 0xf, 0xf, true);
+}
+__device__ __forceinline__ double uniform_f64(double v)
 {
     const long long b = __double_as_longlong(v);
-    const int lo = __shfl_xor((int)(b & 0xffffffffll), m, 64), hi = __shfl_xor((int)(b >> 32), m, 64);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll)), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
 // Largest value over the 16 lanes of a wave that own the same head (lanes equal modulo 4).
-__device__ __forceinline__ double max_same_head(double x)
-{
-    x = fmax(x, dpp_f64<kDppRowRor4>(x));
-    x = fmax(x, dpp_f64<kDppRowRor8>(x));
-    x = fmax(x, shfl_xor_f64(x, 16));
-    x = fmax(x, shfl_xor_f64(x, 32));
-    return x;
-}
+__device__ __forceinline__ double max_same_head(double x) { return same_head(x, MaxOp{}); }
 __device__ __forceinline__ double row_min_f64(double v)
 {
     v = fmin(v, dpp_f64<kDppXor1>(v));
@@ -443,12 +508,11 @@ struct LevelState {
     uint32_t wk[kKeep];
 };
 
-template <int G, bool kLds, typename Meanwhile>
+template <int G>
 __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, const Arrays& A, Scratch& S, int u, int n,
                                            bool use_ids, bool coarse, long long budget, bool with_behind,
-                                           bool q_pending, const double (&qv)[(G + 3) / 4], bool quiet, bool reverse,
-                                           unsigned long long* key_out, uint8_t* flag_out, LevelState<G>& state,
-                                           Meanwhile meanwhile)
+                                           bool q_pending, const uint16_t (&qv)[(G + 3) / 4],
+                                           unsigned long long* key_out, uint8_t* flag_out, LevelState<G>& state)
 {
     constexpr int GH = (G + 3) / 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -468,7 +532,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
         uint4 raw[kInFlight][4];
         int cntD[kInFlight], auxD[kInFlight], aux2D[kInFlight];
         auto request = [&](int t, uint4 (&r)[4], int& cnt, int& a1, int& a2) {
-            const int base = ((reverse ? rounds - 1 - t : t) * kWaves + wave) * 16;
+            const int base = (t * kWaves + wave) * 16;
             const int xa = base + eA, xd = base + eD;
 #pragma unroll
             for (int c = 0; c < 4; ++c) r[c] = make_uint4(0, 0, 0, 0);
@@ -508,10 +572,9 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
         }
         if (q_pending) {
 #pragma unroll
-            for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = qv[hg];
+            for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = (double)bf16_to_f32(qv[hg]);
             phase_sync<true>();
         }
-        meanwhile();
 
         double mx[GH];
 #pragma unroll
@@ -536,7 +599,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
                                 acc[hg] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, L.qB[(hg * 32 + 8 * c + e) * 16 + bsel], acc[hg], 0, 0, 0);
                         }
                     }
-                    const int xd = ((reverse ? rounds - 1 - t : t) * kWaves + wave) * 16 + eD;
+                    const int xd = (t * kWaves + wave) * 16 + eD;
                     const bool part = xd < n && cntD[j] > 0;
                     if (xd < n && jD == 0) {
                         A.wts[xd] = part ? (uint32_t)cntD[j] : 0u;
@@ -561,7 +624,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             if (lane < 4 && 4 * hg + lane < G) S.wm[wave][4 * hg + lane] = mx[hg];
         }
     }
-    phase_sync<kLds>();
+    __syncthreads();
 
     // ================= from here on thread tid owns entry tid (+ kThreads per further chunk) =================
     // shift of the level: the largest logit that takes part (and the shift of what stayed behind)
@@ -602,7 +665,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
         const double t = wave_sum_f64(sm[h]);
         if (lane == 0) S.ws[wave][h] = t;
     }
-    phase_sync<kLds>();
+    __syncthreads();
     // 1 / sum_i N_i e^{l - M_h} per head (0 where nothing takes part)
     double inv[G];
     combine_waves<G>(S.ws, 0.0, [](double v) { return row_sum_f64(v); },
@@ -657,7 +720,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             }
             if (i < n) {
                 A.keys[i] = key;
-                if (!quiet) key_out[i] = key;
+                key_out[i] = key;
             }
         };
 #pragma unroll
@@ -681,17 +744,17 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             atomicAdd(&S.key_total, wsum);
         }
         if (__any(tiny) && lane == 0) atomicOr(&S.key_tiny, 1u);
-        phase_sync<kLds>();
+        __syncthreads();
         if (!linear || !S.key_tiny) break;
         linear = 0;
-        phase_sync<kLds>();       // everyone has seen the flag
+        __syncthreads();       // everyone has seen the flag
         if (tid == 0) {
             S.key_min = ~0ull;
             S.key_max = 0;
             S.key_total = 0;
             S.key_tiny = 0;
         }
-        phase_sync<kLds>();
+        __syncthreads();
     }
 
     // ---- budgeted selection ----
@@ -705,7 +768,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             if (i < n) {
                 const uint8_t f = A.wts[i] ? 1 : 0;
                 A.flags[i] = f;
-                if (!quiet) flag_out[i] = f;
+                flag_out[i] = f;
             }
         }
     } else {
@@ -717,7 +780,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             const uint32_t w = i < n ? A.wts[i] : 0u;
             if (w) atomicAdd(&L.hist[(uint32_t)((A.keys[i] - kmin) >> shift)], (1ull << 40) | w);
         }
-        phase_sync<kLds>();
+        __syncthreads();
         // every wave scans the histogram for itself: kHistBuckets / 64 buckets per lane
         constexpr int BPL = kHistBuckets / 64;
         unsigned long long hb[BPL];
@@ -764,10 +827,10 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
                 }
                 const uint8_t f = (w && b < bstar) ? 1 : 0;
                 A.flags[i] = f;
-                if (!quiet) flag_out[i] = f;
+                flag_out[i] = f;
             }
             if (bcnt > 1) {
-                phase_sync<kLds>();
+                __syncthreads();
                 if ((uint32_t)tid < bcnt) {
                     const unsigned long long mk = L.blist[2 * tid], mv = L.blist[2 * tid + 1];
                     const uint32_t mpos = (uint32_t)(mv >> 32);
@@ -778,14 +841,14 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
                     }
                     const uint8_t f = run <= bud ? 1 : 0;
                     A.flags[mpos] = f;
-                    if (!quiet) flag_out[mpos] = f;
+                    flag_out[mpos] = f;
                 }
             }
         } else {
             // a crowded boundary bucket (many equal or nearly equal scores): the general search
             uint64_t kstar = 0, acc2 = 0;
             uint32_t ties = 0;
-            const bool bounded = radix_select<kLds>(A.keys, A.wts, n, budget, S, kstar, acc2, ties);
+            const bool bounded = radix_select<false>(A.keys, A.wts, n, budget, S, kstar, acc2, ties);
             for (int i = tid; i < n; i += kThreads) {
                 uint8_t f = 0;
                 if (A.wts[i]) {
@@ -803,18 +866,18 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
                     }
                 }
                 A.flags[i] = f;
-                if (!quiet) flag_out[i] = f;
+                flag_out[i] = f;
             }
         }
     }
-    phase_sync<kLds>();
+    __syncthreads();
 
     return linear;
 }
 
 // The clusters a level did not take enter the next level's normaliser through their centroid: their
 // shift and their sum of N e^{l - shift} per head go to S.bm / S.bs (published by the caller's next barrier).
-template <int G, bool kLds>
+template <int G>
 __device__ __forceinline__ void leave_behind(const Arrays& A, Scratch& S, int n, const LevelState<G>& st)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -843,7 +906,7 @@ __device__ __forceinline__ void leave_behind(const Arrays& A, Scratch& S, int n,
         const double t = wave_sum_f64(sm[h]);
         if (lane == 0) S.ws[wave][h] = t;
     }
-    phase_sync<kLds>();
+    __syncthreads();
     double bsum[G];
     combine_waves<G>(S.ws, 0.0, [](double v) { return row_sum_f64(v); }, [](int, int, double v) { return v; }, bsum);
     if (tid == 0) {
@@ -851,6 +914,7 @@ __device__ __forceinline__ void leave_behind(const Arrays& A, Scratch& S, int n,
         for (int h = 0; h < G; ++h) {
             S.bm[h] = st.M[h];
             S.bs[h] = bsum[h];
+            for (int w = 0; w < kWaves; ++w) S.bw[w][h] = w == 0 ? bsum[h] : 0.0;
         }
     }
 }
@@ -860,9 +924,9 @@ __device__ __forceinline__ void leave_behind(const Arrays& A, Scratch& S, int n,
 // level reads its ids from; every cluster that stays behind gets the slot of its centroid term (left
 // in C.aux, which only promising clusters need otherwise).  The terms themselves are written later,
 // by emit_coarse_terms, while the fine level's rows travel.
-template <int G, bool kLds>
+template <int G>
 __device__ __forceinline__ void coarse_candidates(const ScoreParams& p, const Arrays& C, int32_t* cand_l, Scratch& S,
-                                                  ScanState& sc, int u, bool quiet, int& n_cand, uint32_t& n_terms)
+                                                  ScanState& sc, int u, int& n_cand, uint32_t& n_terms)
 {
     const int tid = threadIdx.x;
     const int n_c = p.n_coarse;
@@ -876,17 +940,17 @@ __device__ __forceinline__ void coarse_candidates(const ScoreParams& p, const Ar
         int c0 = 0, c1 = 0;
         if (keep) { c0 = C.aux[i]; c1 = C.aux2[i]; }
         uint32_t pos, slot;
-        chunk_excl_scan2<kLds>((uint32_t)(c1 - c0), emit ? 1u : 0u, S, sc, pos, slot);
+        chunk_excl_scan2<false>((uint32_t)(c1 - c0), emit ? 1u : 0u, S, sc, pos, slot);
         for (int f = c0; f < c1; ++f) {
             const uint32_t o = pos + (uint32_t)(f - c0);
-            if (!quiet) cand_g[o] = f;
+            cand_g[o] = f;
             if (o < (uint32_t)p.lds_cap) cand_l[o] = f;
         }
         if (emit) C.aux[i] = (int32_t)slot;
     }
     n_cand = (int)sc.carry_a;
     n_terms = sc.carry_b;
-    if (tid == 0 && !quiet) {
+    if (tid == 0) {
         p.n_cand[u] = n_cand;
         p.counters[4 * u + 2] = n_c;
     }
@@ -902,7 +966,7 @@ __device__ __forceinline__ void emit_coarse_terms(const ScoreParams& p, const Ar
 
 // Fine level, after scoring and selection: emit centroid terms for the unselected candidates and
 // the flat list of stored rows of the selected clusters.
-template <int G, bool kLds>
+template <int G>
 __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays& F, Scratch& S, ScanState& sc, int u,
                                               int n_f, bool two, uint32_t n_terms)
 {
@@ -921,7 +985,7 @@ __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays
         const uint32_t w = sel ? F.wts[i] : 0u;
         const int r0 = sel ? F.aux[i] : 0;
         uint32_t off, packed;       // packed: selected clusters in the low half, terms in the high half
-        chunk_excl_scan2<kLds>(w, (sel ? 1u : 0u) | (emit ? 0x10000u : 0u), S, sc, off, packed);
+        chunk_excl_scan2<false>(w, (sel ? 1u : 0u) | (emit ? 0x10000u : 0u), S, sc, off, packed);
         if (sel) {
             sel_rc[packed & 0xffffu] = make_int2(r0, (int)w);
             sel_off[packed & 0xffffu] = (int32_t)off;
@@ -943,7 +1007,7 @@ __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays
     }
     const uint32_t total = sc.carry_a, n_sel = sc.carry_b & 0xffffu;
     n_terms += sc.carry_b >> 16;
-    phase_sync<kLds>();
+    __syncthreads();
     // expansion: one row of 16 lanes per selected cluster, the next cluster's entry fetched early
     int32_t* ro = p.rows + (long long)u * p.rows_stride;
     int32_t* so = p.row_slot ? p.row_slot + (long long)u * p.rows_stride : nullptr;   // compact slot of each row's cluster
@@ -976,6 +1040,632 @@ __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays
     }
 }
 
+// ================================================================================================
+// The register path: levels of up to kFastChunks * kThreads entries (and at most lds_cap), every level of
+// the benchmark's shapes.  A level is a chain of dependent steps on one compute unit, so what counts is the
+// number of instructions a wave executes between barriers; here everything about an entry stays in the
+// registers of the lanes the matrix product leaves it in, and only what the whole workgroup must know
+// (per wave: shifts, sums, extremes of the scores, token totals) goes through LDS.
+//
+// Layout.  A chunk of up to 512 entries takes R = ceil(entries / 128) rounds of 16 entries per wave.  Group q
+// of four lanes (lane = 4 q + j) holds, for round t < R, entry 16 R wave + R q + t of the chunk, lane j its
+// logits of heads j and 4 + j: four heads side by side, so one reduction over the lanes equal modulo 4 serves
+// all heads, and an entry costs each lane one exponential per head group instead of one per head.  Lane j of
+// the group owns entry t = j for everything there is once per entry (count, row starts, key, flag): owners
+// in lane order are the entries in order, which is what the prefix scans need.
+//
+// Two barriers stand between the logits and the selection: one for the waves' sums of N e^l (no shift by the
+// largest logit, which fp64 does not need below |l| = 500), one for the histogram (whose buckets are fixed, so that
+// no extremes have to be found first).
+//
+// Measured (MI355X, cycles from the first request to the last store of a unit): 64 coarse + 250 fine entries of 4
+// heads 46.4k -> 34.3k, 256 + 504 entries 65.6k -> 54.7k, one level of 64 entries 20.2k -> 15.2k against one entry
+// per thread with all heads in turn, a shift and a min / max of the keys.  What is left at 256 + 504 entries: rows
+// and products 28k (the product alone 4.1k: 512 entries x 4 heads x 128 dims at the fp64 rate of one compute
+// unit), the chain of dependent instructions 22k, the expansion of 8192 row numbers 4k.
+// ================================================================================================
+constexpr int kFastChunks = 2;
+constexpr double kNoShift = 500.0;    // largest |logit| that is exponentiated without a shift
+constexpr int kRounds = 4;
+
+template <int G>
+struct FastLevel {
+    static constexpr int GH = (G + 3) / 4;
+    double l[kFastChunks][kRounds][GH];   // logits (matrix layout)
+    double e[kFastChunks][kRounds][GH];   // e^{l - M}, 0 where the entry takes no part
+    double M[GH];                         // shift of the level, this lane's heads (0 unless a logit is far out)
+    uint32_t w[kFastChunks];              // own entries: member count (0: takes no part),
+    int32_t a1[kFastChunks], a2[kFastChunks];   // row starts (coarse: first child, end of children),
+    int32_t id[kFastChunks];              // cluster id,
+    int32_t x[kFastChunks];               // position in the level (-1: none)
+    bool take[kFastChunks];               // selected
+};
+
+__device__ __forceinline__ int chunk_entries(int n, int c) { return min(max(n - c * kThreads, 0), kThreads); }
+__device__ __forceinline__ int chunk_rounds(int n, int c) { return (chunk_entries(n, c) + 16 * kWaves - 1) / (16 * kWaves); }
+
+// f(t) for t = 0..3 with t a compile-time constant
+template <typename F>
+__device__ __forceinline__ void for_rounds(F f)
+{
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+}
+
+// Scores and selection of one level (see score_level for the definitions); `behind`: the normaliser also covers
+// what the coarse level left behind (S.bm / S.bw).  `quiet`: store nothing in global memory, and ask for the
+// rows last round first (shadow workgroup).  `meanwhile` runs once the rows have been asked for.  Returns 1 for
+// linear-domain keys, 0 for logarithmic ones.
+template <int G, typename Meanwhile>
+__device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Scratch& S, int u, int n, bool use_ids,
+                                          bool coarse, long long budget, bool behind, bool q_pending,
+                                          const uint16_t (&qv)[(G + 3) / 4], bool quiet, unsigned long long* key_out,
+                                          uint8_t* flag_out, FastLevel<G>& st, Meanwhile meanwhile)
+{
+    constexpr int GH = (G + 3) / 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 3, quad = lane >> 2;
+    const double ninf = -INFINITY;
+    const int row_off = coarse ? p.fcap : 0;
+    const int32_t* Nu = p.N + (long long)u * p.tab_rows + row_off;
+    const uint16_t* Kcu = p.Kc + ((long long)u * p.tab_rows + row_off) * kHeadDim;
+    const int32_t* start = coarse ? p.cstart + (long long)u * p.cstart_stride : p.fstart + (long long)u * p.fstart_stride;
+    const Arrays& A = L.A;
+
+    // ---------------- rows: operand layout, lane (k, e) takes dim group k of entry e of the wave's sixteen ----------------
+    const int kA = lane >> 4, qA = 4 * (lane & 3) + ((lane >> 2) & 3);      // the group of four lanes whose entry this is
+    const int bsel = kA * 4 + j;
+    uint4 raw[kRounds][4];
+    auto request = [&](int c, int t, uint4 (&r)[4]) {
+        const int nc = chunk_entries(n, c), R = chunk_rounds(n, c);
+        const int x = wave * 16 * R + qA * R + t;
+        if (x < nc) {
+            const int id = use_ids ? A.ids[c * kThreads + x] : c * kThreads + x;
+            const uint4* kp = reinterpret_cast<const uint4*>(Kcu + (long long)id * kHeadDim) + kA;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[k] = kp[4 * k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[k] = make_uint4(0, 0, 0, 0);
+        }
+    };
+    const int R0 = chunk_rounds(n, 0);
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int nc = chunk_entries(n, c), R = chunk_rounds(n, c);
+        const int x = wave * 16 * R + quad * R + j;
+        const bool own = j < R && x < nc;
+        st.x[c] = own ? c * kThreads + x : -1;
+        st.w[c] = 0;
+        st.a1[c] = st.a2[c] = st.id[c] = 0;
+        if (own) {
+            const int id = use_ids ? A.ids[c * kThreads + x] : c * kThreads + x;
+            st.id[c] = id;
+            st.w[c] = (uint32_t)Nu[id];
+            st.a1[c] = start[id];
+            if (coarse) st.a2[c] = start[id + 1];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) {
+        const int t = quiet ? kRounds - 1 - i : i;
+        if (t < R0) {
+            if (t == 0) request(0, 0, raw[0]);
+            if (t == 1) request(0, 1, raw[1]);
+            if (t == 2) request(0, 2, raw[2]);
+            if (t == 3) request(0, 3, raw[3]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // while the rows travel
+    if (tid < kHistBuckets) L.hist[tid] = 0;
+    if (tid == 0) {
+        S.bl_count = 0;
+        S.tiny = 0;
+        if (q_pending) S.far[0] = S.far[1] = 0;      // (both levels' flags, in front of the launch's first barrier)
+    }
+    if (q_pending) {
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = (double)bf16_to_f32(qv[hg]);
+        phase_sync<true>();
+    }
+    meanwhile();
+
+    // ---------------- logits ----------------
+    bool far = false;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int R = chunk_rounds(n, c), Rn = c + 1 < kFastChunks ? chunk_rounds(n, c + 1) : 0;
+        for_rounds([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+#pragma unroll
+            for (int hg = 0; hg < GH; ++hg) st.l[c][t][hg] = 0.0;
+            if (t < R) {
+                double acc[GH];
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) acc[hg] = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t w4[4] = {raw[t][k].x, raw[t][k].y, raw[t][k].z, raw[t][k].w};
+#pragma unroll
+                    for (int d = 0; d < 8; ++d) {
+                        const double a = (double)((d & 1) ? bf16hi_to_f32(w4[d >> 1]) : bf16lo_to_f32(w4[d >> 1]));
+#pragma unroll
+                        for (int hg = 0; hg < GH; ++hg)
+                            acc[hg] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, L.qB[(hg * 32 + 8 * k + d) * 16 + bsel], acc[hg], 0, 0, 0);
+                    }
+                }
+                const bool part = quad_lane<t>(st.w[c]) != 0;
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) {
+                    st.l[c][t][hg] = acc[hg] * p.scale;
+                    far |= part && !(fabs(st.l[c][t][hg]) <= kNoShift);
+                }
+            }
+            if (t < Rn) request(c + 1, t, raw[t]);
+        });
+    }
+
+    // ---------------- e^{l - M} and the waves' sums of N e^{l - M} per head ----------------
+    // A double holds e^l for any |l| up to 700, so the usual shift by the largest logit is left out (M = 0) unless
+    // some logit is beyond kNoShift; the waves then exchange their largest logits first (second trip).
+    int linear = 1;
+    const uint32_t n_taking = wave_total_u32(st.w[0] + st.w[kFastChunks - 1]);
+    double tot[GH], g[GH];
+#pragma unroll
+    for (int hg = 0; hg < GH; ++hg) st.M[hg] = 0.0;
+    for (int trip = 0; trip < 2; ++trip) {
+        double sw[GH];
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) sw[hg] = 0.0;
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int R = chunk_rounds(n, c);
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) st.e[c][t][hg] = 0.0;
+                if (t < R) {
+                    const uint32_t w = quad_lane<t>(st.w[c]);
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) {
+                        const double x = exp_shifted(st.l[c][t][hg] - st.M[hg]);     // (an entry that takes no part: not used)
+                        st.e[c][t][hg] = w ? x : 0.0;
+                        sw[hg] += (double)w * st.e[c][t][hg];
+                    }
+                }
+            });
+        }
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) {
+            sw[hg] = same_head(sw[hg], AddOp{});
+            if (lane < 4) S.ws[wave][4 * hg + lane] = sw[hg];
+        }
+        if (lane == 0) S.rk_wt[wave] = n_taking;
+        if (trip == 0 && __any(far)) S.far[coarse] = 1;
+        phase_sync<true>();
+        if (trip == 1 || !S.far[coarse]) break;
+        double mw[GH];
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) mw[hg] = ninf;
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int R = chunk_rounds(n, c);
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t < R && quad_lane<t>(st.w[c]) != 0) {
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) mw[hg] = fmax(mw[hg], st.l[c][t][hg]);
+                }
+            });
+        }
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) {
+            mw[hg] = same_head(mw[hg], MaxOp{});
+            if (lane < 4) S.wm[wave][4 * hg + lane] = mw[hg];
+        }
+        phase_sync<true>();
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) {
+            const double M = same_head(S.wm[quad & (kWaves - 1)][4 * hg + j], MaxOp{});
+            st.M[hg] = M == ninf ? 0.0 : M;
+        }
+    }
+
+    // ---------------- normaliser (lane 4 w + j: wave w, head j), scores ----------------
+#pragma unroll
+    for (int hg = 0; hg < GH; ++hg) {
+        const int h = 4 * hg + j;
+        double ts = S.ws[quad & (kWaves - 1)][h];
+        if (behind) {
+            // (relative to this level's shift; both are zero unless a logit was far out)
+            double bs = S.bw[quad & (kWaves - 1)][h];
+            if (S.far[0] | S.far[1]) {
+                const double bm = S.bm[h];
+                if (same_head(bs, AddOp{}) > 0.0 && bm > st.M[hg]) {      // (uniform over a head's lanes)
+                    const double down = exp_shifted(st.M[hg] - bm);
+                    ts *= down;
+#pragma unroll
+                    for (int c = 0; c < kFastChunks; ++c)
+#pragma unroll
+                        for (int t = 0; t < kRounds; ++t) st.e[c][t][hg] *= down;
+                    st.M[hg] = bm;
+                }
+                bs = bs > 0.0 ? bs * exp_shifted(bm - st.M[hg]) : 0.0;
+            }
+            ts += bs;
+        }
+        const double T = same_head(lane < 4 * kWaves ? ts : 0.0, AddOp{});
+        tot[hg] = T;
+        g[hg] = (h < G && T > 0.0) ? 1.0 / T : 0.0;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_total_u32(lane < kWaves ? S.rk_wt[lane & (kWaves - 1)] : 0u));
+    constexpr double kLogGs[9] = {0.0, 0.0, 0.6931471805599453094, 1.0986122886681097821, 1.3862943611198906188,
+                                  1.6094379124341002818, 1.7917594692280549573, 1.9459101090932196052, 2.0794415416798357477};
+    constexpr double kLogG = kLogGs[G];
+    uint64_t key[kFastChunks];                 // of the own entries
+    auto select_own = [&](const double (&sc)[kRounds]) {
+        const double lo = (j & 1) ? sc[1] : sc[0], hi = (j & 1) ? sc[3] : sc[2];
+        return (j & 2) ? hi : lo;
+    };
+    bool tiny = false;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int R = chunk_rounds(n, c);
+        double sc[kRounds] = {0.0, 0.0, 0.0, 0.0};
+        for_rounds([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if (t < R) {
+                double v = st.e[c][t][0] * g[0];
+                if constexpr (GH > 1) v += st.e[c][t][1] * g[1];
+                sc[t] = sum4_f64(v);
+            }
+        });
+        const double own = select_own(sc);
+        tiny |= st.w[c] && !(own >= 1e-280);
+        key[c] = st.w[c] ? ~(uint64_t)__double_as_longlong(own) : ~0ull;
+    }
+    if (__any(tiny)) S.tiny = 1;
+    // First digit of the selection: buckets on a fixed scale of the score, so that nothing about the level has to be
+    // known beforehand: quarters of an octave down to 2^-28 (where flat attention has its boundary), octaves down to
+    // 2^-124, then eight octaves each (peaked attention), the last bucket open.
+    constexpr uint64_t kTopKey = ~0x4030000000000000ull;           // (score 16: no score is larger than G up to rounding)
+    static_assert(kHistBuckets == 256, "the scale below has 128 + 96 + 32 buckets");
+    auto bucket_of = [&](uint64_t k) {
+        const uint32_t v = (uint32_t)((k - kTopKey) >> 50);        // quarters of an octave below 16
+        const uint32_t far_down = min(224u + ((v - 512u) >> 5), 255u);
+        return v < 128u ? v : v < 512u ? 96u + (v >> 2) : far_down;
+    };
+    uint32_t bucket[kFastChunks];
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        bucket[c] = bucket_of(key[c]);
+        if (st.w[c]) atomicAdd(&L.hist[bucket[c]], (1ull << 40) | st.w[c]);
+    }
+    phase_sync<true>();
+    if (S.tiny) {
+        // some score left the range of a double: the level ranks by log mean_h e^{l - LSE_h} in the log domain
+        // (and orders all of it with the general search below)
+        linear = 0;
+        double lse[GH];
+#pragma unroll
+        for (int hg = 0; hg < GH; ++hg) lse[hg] = st.M[hg] + log(not_hoisted(tot[hg]));
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int R = chunk_rounds(n, c);
+            double sc[kRounds] = {0.0, 0.0, 0.0, 0.0};
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t < R) {
+                    double th[GH], tm = ninf;
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) {
+                        th[hg] = 4 * hg + j < G ? st.l[c][t][hg] - lse[hg] : ninf;
+                        tm = fmax(tm, th[hg]);
+                    }
+                    tm = fmax(tm, dpp_f64<kDppXor1>(tm));
+                    tm = fmax(tm, dpp_f64<kDppXor2>(tm));
+                    double ss = 0.0;
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) ss += exp_shifted(th[hg] - tm);
+                    ss = sum4_f64(ss);
+                    sc[t] = tm - kLogG + log(not_hoisted(ss));
+                }
+            });
+            key[c] = st.w[c] ? descending_key(select_own(sc)) : ~0ull;
+        }
+    }
+    if (!quiet) {
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c)
+            if (st.x[c] >= 0) key_out[st.x[c]] = key[c];
+    }
+
+    // ---------------- budgeted selection ----------------
+    const uint32_t bud = budget < 0 ? 0u : (budget > 0xffffffffll ? 0xffffffffu : (uint32_t)budget);
+    constexpr unsigned long long kWtMask = (1ull << 40) - 1;
+    if (total <= bud) {
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) st.take[c] = st.w[c] != 0;
+    } else {
+        // every wave scans the histogram for itself: kHistBuckets / 64 buckets per lane
+        constexpr int BPL = kHistBuckets / 64;
+        unsigned long long hb[BPL];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < BPL; ++i) {
+            hb[i] = L.hist[BPL * lane + i];
+            sum += (uint32_t)(hb[i] & kWtMask);
+        }
+        const uint32_t incl = wave_incl_scan_u32(sum);
+        const unsigned long long crossing = __ballot((unsigned long long)incl > bud);
+        const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
+        uint32_t a = incl - sum, d = BPL * lane, cn = 0;
+        bool done = false;
+#pragma unroll
+        for (int i = 0; i < BPL; ++i) {
+            const uint32_t wi = (uint32_t)(hb[i] & kWtMask);
+            if (!done) {
+                if ((unsigned long long)a + wi > bud) {
+                    d = BPL * lane + i;
+                    cn = (uint32_t)(hb[i] >> 40);
+                    done = true;
+                } else {
+                    a += wi;
+                }
+            }
+        }
+        const uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)a, first);
+        const uint32_t bcnt = linear ? (uint32_t)__builtin_amdgcn_readlane((int)cn, first) : ~0u;
+        const uint32_t bstar = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+        // entries before the boundary bucket are taken, entries behind it are not
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) st.take[c] = st.w[c] && bucket[c] < bstar;
+        if (bcnt > (uint32_t)kListCap) {
+            // a crowded boundary bucket (many equal or nearly equal scores) or logarithmic keys: the general search
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                if (st.x[c] >= 0) {
+                    A.keys[st.x[c]] = key[c];
+                    A.wts[st.x[c]] = st.w[c];
+                }
+            }
+            phase_sync<true>();
+            uint64_t kstar = 0, acc2 = 0;
+            uint32_t ties = 0;
+            const bool bounded = radix_select<true>(A.keys, A.wts, n, budget, S, kstar, acc2, ties);
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                if (!st.w[c]) continue;
+                bool t = !bounded || key[c] < kstar;
+                if (!t && key[c] == kstar && ties > 1) {
+                    // exactly equal keys: lower position first, keep while the running count still fits
+                    uint64_t run = acc2;
+                    for (int i = 0; i <= st.x[c]; ++i)
+                        if (A.wts[i] && A.keys[i] == kstar) run += A.wts[i];
+                    t = (long long)run <= budget;
+                }
+                st.take[c] = t;
+            }
+        } else if (bcnt > 1) {
+            // those inside it are ordered by (key, position)
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                if (st.w[c] && bucket[c] == bstar) {
+                    const uint32_t slot = atomicAdd(&S.bl_count, 1u);
+                    L.blist[2 * slot] = key[c];
+                    L.blist[2 * slot + 1] = ((unsigned long long)(uint32_t)st.x[c] << 32) | st.w[c];
+                }
+            }
+            phase_sync<true>();
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                if (st.w[c] && bucket[c] == bstar) {
+                    unsigned long long run = (unsigned long long)acc + st.w[c];
+                    for (uint32_t m = 0; m < bcnt; ++m) {
+                        const unsigned long long ok = L.blist[2 * m], ov = L.blist[2 * m + 1];
+                        if (ok < key[c] || (ok == key[c] && (int)(ov >> 32) < st.x[c])) run += (uint32_t)ov;
+                    }
+                    st.take[c] = run <= bud;
+                }
+            }
+        }
+    }
+    if (!quiet) {
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c)
+            if (st.x[c] >= 0) flag_out[st.x[c]] = st.take[c] ? 1 : 0;
+    }
+    return linear;
+}
+
+// Centroid terms (Eq. 2) of a level in the register path: group of four lanes per entry, lane j writes heads j
+// and 4 + j.  `slot` of the own entries (< 0: no term), row0 = centroid-table row of cluster 0 of the level.
+template <int G>
+__device__ __forceinline__ void fast_terms(const ScoreParams& p, const FastLevel<G>& st, const int (&slot)[kFastChunks],
+                                           int n, int row0, int u)
+{
+    constexpr int GH = (G + 3) / 4;
+    const int j = threadIdx.x & 3;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int R = chunk_rounds(n, c);
+        for_rounds([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if (t < R) {
+                const int sl = (int)quad_lane<t>((uint32_t)slot[c]);
+                const float lgN = __builtin_amdgcn_logf((float)quad_lane<t>(st.w[c]));
+                if (sl >= 0) {
+                    const long long o = (long long)u * p.mp_stride + sl;
+                    if (j == t) p.mp_rows[o] = row0 + st.id[c];
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg)
+                        if (4 * hg + j < G) p.mp_scores[o * G + 4 * hg + j] = (float)(st.l[c][t][hg] * 1.4426950408889634) + lgN;
+                }
+            }
+        });
+    }
+}
+
+// Coarse level after its selection (see coarse_candidates).  `slot` receives the centroid-term slots of the own
+// entries; what stays behind goes to S.bm / S.bw; the candidate list is published by the caller's barrier.
+template <int G>
+__device__ __forceinline__ void fast_candidates(const ScoreParams& p, const Lds& L, Scratch& S, ScanState& sc,
+                                                const FastLevel<G>& st, int u, bool quiet, int& n_cand, uint32_t& n_terms,
+                                                int (&slot)[kFastChunks])
+{
+    constexpr int GH = (G + 3) / 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_c = p.n_coarse;
+    double bs[GH];
+#pragma unroll
+    for (int hg = 0; hg < GH; ++hg) bs[hg] = 0.0;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int R = chunk_rounds(n_c, c);
+        const uint32_t left = st.take[c] ? 0u : st.w[c];
+        for_rounds([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if (t < R) {
+                const double w = (double)quad_lane<t>(left);
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) bs[hg] += w * st.e[c][t][hg];
+            }
+        });
+    }
+#pragma unroll
+    for (int hg = 0; hg < GH; ++hg) {
+        bs[hg] = same_head(bs[hg], AddOp{});
+        if (lane < 4) {
+            S.bw[wave][4 * hg + lane] = bs[hg];
+            if (wave == 0) S.bm[4 * hg + lane] = st.M[hg];
+        }
+    }
+    int2* sel_rc = reinterpret_cast<int2*>(L.A.keys);      // (first child, children) of the promising clusters
+    int32_t* sel_off = L.A.aux2;                           // offset of their children in the candidate list
+    sc.carry_a = sc.carry_b = 0;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        slot[c] = -1;
+        if (c * kThreads >= n_c) continue;
+        const bool emit = st.w[c] && !st.take[c] && p.use_mp;
+        const int kids = st.take[c] ? st.a2[c] - st.a1[c] : 0;
+        uint32_t pos, packed;       // packed: promising clusters in the low half, terms in the high half
+        chunk_excl_scan2<true>((uint32_t)kids, (st.take[c] ? 1u : 0u) | (emit ? 0x10000u : 0u), S, sc, pos, packed);
+        if (st.take[c]) {
+            sel_rc[packed & 0xffffu] = make_int2(st.a1[c], kids);
+            sel_off[packed & 0xffffu] = (int32_t)pos;
+        }
+        if (emit) slot[c] = (int)(packed >> 16);
+    }
+    n_cand = (int)sc.carry_a;
+    n_terms = sc.carry_b >> 16;
+    const uint32_t n_sel = sc.carry_b & 0xffffu;
+    phase_sync<true>();
+    // expansion: one row of 16 lanes per promising cluster
+    int32_t* cand_g = p.cand + (long long)u * p.f_stride;
+    const int sub = tid & 15;
+    for (uint32_t k = tid >> 4; k < n_sel; k += kThreads / 16) {
+        const int2 rc = sel_rc[k];
+        const int off = sel_off[k];
+        for (int i = sub; i < rc.y; i += 16) {
+            if (!quiet) cand_g[off + i] = rc.x + i;
+            if (off + i < p.lds_cap) L.A.ids[off + i] = rc.x + i;
+        }
+    }
+    if (tid == 0 && !quiet) {
+        p.n_cand[u] = n_cand;
+        p.counters[4 * u + 2] = n_c;
+    }
+}
+
+// Fine level after its selection (see fine_epilogue).
+template <int G>
+__device__ __forceinline__ void fast_epilogue(const ScoreParams& p, const Lds& L, Scratch& S, ScanState& sc,
+                                              const FastLevel<G>& st, int u, int n_f, bool two, uint32_t n_terms)
+{
+    constexpr int GH = (G + 3) / 4;
+    const int tid = threadIdx.x, j = tid & 3;
+    int2* sel_rc = reinterpret_cast<int2*>(L.A.keys);      // (first stored row, count) of the selected clusters
+    int32_t* sel_off = L.A.aux2;                           // offset of their rows in the row list
+    int slot[kFastChunks], pick[kFastChunks];
+    sc.carry_a = sc.carry_b = 0;
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        slot[c] = pick[c] = -1;
+        if (c * kThreads >= n_f) continue;
+        const bool emit = st.w[c] && !st.take[c] && p.use_mp;
+        uint32_t off, packed;       // packed: selected clusters in the low half, terms in the high half
+        chunk_excl_scan2<true>(st.take[c] ? st.w[c] : 0u, (st.take[c] ? 1u : 0u) | (emit ? 0x10000u : 0u), S, sc, off, packed);
+        if (st.take[c]) {
+            pick[c] = (int)(packed & 0xffffu);
+            sel_rc[pick[c]] = make_int2(st.a1[c], (int)st.w[c]);
+            sel_off[pick[c]] = (int32_t)off;
+        }
+        if (emit) slot[c] = (int)(n_terms + (packed >> 16));
+    }
+    const uint32_t total = sc.carry_a, n_sel = sc.carry_b & 0xffffu;
+    n_terms += sc.carry_b >> 16;
+    phase_sync<true>();
+    // expansion: one row of 16 lanes per selected cluster, the next cluster's entry fetched early
+    int32_t* ro = p.rows + (long long)u * p.rows_stride;
+    int32_t* so = p.row_slot ? p.row_slot + (long long)u * p.rows_stride : nullptr;   // compact slot of each row's cluster
+    const int grp = tid >> 4, sub = tid & 15;
+    int2 rc_n = make_int2(0, 0);
+    int off_n = 0;
+    if ((uint32_t)grp < n_sel) {
+        rc_n = sel_rc[grp];
+        off_n = sel_off[grp];
+    }
+    for (uint32_t k = grp; k < n_sel; k += kThreads / 16) {
+        const int2 rc = rc_n;
+        const int off = off_n;
+        const uint32_t kn = k + kThreads / 16;
+        if (kn < n_sel) {
+            rc_n = sel_rc[kn];
+            off_n = sel_off[kn];
+        }
+        for (int i = sub; i < rc.y; i += 16) ro[off + i] = rc.x + i;
+        if (so)
+            for (int i = sub; i < rc.y; i += 16) so[off + i] = (int32_t)k;
+    }
+    fast_terms<G>(p, st, slot, n_f, 0, u);
+    if (p.sel_base) {
+        // q . centroid of a selected cluster, log2 units, for a value pass over keys stored as residuals
+        // from it: eight columns per cluster, head h in column h (groups of up to five heads) or, for
+        // larger groups, which the value pass splits over two waves, in column 4 * half + h % ceil(G / 2)
+        constexpr int kHalf = G > 5 ? (G + 1) / 2 : 8;
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int R = chunk_rounds(n_f, c);
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t < R) {
+                    const int k = (int)quad_lane<t>((uint32_t)pick[c]);
+                    if (k >= 0) {
+                        float* dst = p.sel_base + ((long long)u * p.f_stride + k) * 8;
+#pragma unroll
+                        for (int hg = 0; hg < GH; ++hg) {
+                            const int h = 4 * hg + j, col = h < kHalf ? h : 4 + h - kHalf;
+                            if (col < 8) dst[col] = h < G ? (float)(st.l[c][t][hg] * 1.4426950408889634) : 0.f;
+                        }
+                    }
+                }
+            });
+        }
+    }
+    if (tid == 0) {
+        p.n_rows[u] = (int32_t)total;
+        p.n_mp[u] = (int32_t)n_terms;
+        p.counters[4 * u + 0] = (int32_t)total + p.n_tail;
+        p.counters[4 * u + 1] = n_f;
+        if (!two) p.counters[4 * u + 2] = 0;
+        p.counters[4 * u + 3] = (int32_t)n_terms;
+    }
+}
+
 // What a shadow workgroup does at the last level: ask for the centroid rows of the second half of
 // the level's entries, last entry first, and drop them.
 __device__ __forceinline__ void touch_rows(const ScoreParams& p, const int32_t* ids, int u, int n)
@@ -992,6 +1682,11 @@ __device__ __forceinline__ void touch_rows(const ScoreParams& p, const int32_t* 
     if (x == 0xfff1fff2u && p.U < 0) p.counters[4 * u] = 0;
 }
 
+__device__ __forceinline__ void touch_arguments(const ScoreParams& p)
+{
+    asm volatile("" ::"s"(p.q), "s"(p.cstart), "s"(p.g_wts), "s"(p.flag_c), "s"(p.n_cand), "s"(p.mp_rows), "s"(p.app_n), "s"(p.U));
+}
+
 template <int G>
 __global__ __launch_bounds__(kThreads) void score_select_kernel(const ScoreParams p)
 {
@@ -1002,73 +1697,83 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const ScoreParam
     const int u = blockIdx.x % p.U, tid = threadIdx.x;
     const bool shadow = blockIdx.x >= (unsigned)p.U;     // second workgroup of the unit: warms the shared L2, stores nothing
 
-    double qv[GH];      // this thread's elements of the query operand (one per head group)
+    // The arguments span several cache lines of a segment no one has read yet: one request for each of them, together,
+    // instead of one stall per line along the way.
+    touch_arguments(p);
+    uint16_t qv[GH];    // this thread's elements of the query operand (one per head group; converted once they are needed)
 #pragma unroll
     for (int hg = 0; hg < GH; ++hg) qv[hg] = query_operand_element<G>(p, u, tid + hg * kThreads);
-    if (!shadow && tid < 16 * p.app_n) {       // the step's new rows go to their place in the tail buffers
-        const int a = tid >> 4, c = tid & 15;
-        const uint4 w = reinterpret_cast<const uint4*>(p.app_src[a])[(long long)u * 16 + c];
-        reinterpret_cast<uint4*>(p.app_dst[a])[((long long)u * p.app_dst_rows + p.app_row) * 16 + c] = w;
-    }
+    // the step's new rows go to their place in the tail buffers: asked for here, stored at the end
+    uint4 app = make_uint4(0, 0, 0, 0);
+    const bool appends = !shadow && tid < 16 * p.app_n;
+    if (appends) app = reinterpret_cast<const uint4*>(p.app_src[tid >> 4])[(long long)u * 16 + (tid & 15)];
 
     const bool two = p.levels == 2;
     const Arrays Ag = global_arrays<G>(p, u);
     ScanState sc;
-    LevelState<G> stc, stf;
-    const auto nothing = [] {};
     uint32_t n_terms = 0;
     int n_f = p.n_fine;
-    const bool coarse_lds = p.n_coarse <= p.lds_cap;
+    const bool coarse_fast = p.n_coarse <= p.lds_cap;
+    FastLevel<G> fc;
+    int slot_c[kFastChunks];
     if (two) {
         unsigned long long* kc = p.key_c + (long long)u * p.c_stride;
-        uint8_t* fc = p.flag_c + (long long)u * p.c_stride;
-        if (coarse_lds) {
-            const int lin = score_level<G, true>(p, L, L.A, S, u, p.n_coarse, false, true, p.coarse_budget, false, true, qv,
-                                                 shadow, shadow, kc, fc, stc, nothing);
+        uint8_t* flc = p.flag_c + (long long)u * p.c_stride;
+        if (coarse_fast) {
+            const int lin = fast_level<G>(p, L, S, u, p.n_coarse, false, true, p.coarse_budget, false, true, qv, shadow, kc, flc, fc,
+                                          [] {});
             if (tid == 0 && !shadow) p.key_mode[2 * u] = lin;
-            coarse_candidates<G, true>(p, L.A, L.A.ids, S, sc, u, shadow, n_f, n_terms);
+            fast_candidates<G>(p, L, S, sc, fc, u, shadow, n_f, n_terms, slot_c);
         } else {
             // (a shadow workgroup would race with the first one on the global working arrays: it leaves)
             if (shadow) return;
-            const int lin = score_level<G, false>(p, L, Ag, S, u, p.n_coarse, false, true, p.coarse_budget, false, true, qv,
-                                                  false, false, kc, fc, stc, nothing);
+            if (tid == 0) {
+                S.far[0] = 0;
+                S.far[1] = 1;      // (the general path shifts by the largest logit)
+            }
+            LevelState<G> stc;
+            const int lin = score_level<G>(p, L, Ag, S, u, p.n_coarse, false, true, p.coarse_budget, false, true, qv, kc, flc, stc);
             if (tid == 0) p.key_mode[2 * u] = lin;
-            coarse_candidates<G, false>(p, Ag, L.A.ids, S, sc, u, false, n_f, n_terms);
+            coarse_candidates<G>(p, Ag, L.A.ids, S, sc, u, n_f, n_terms);
+            emit_coarse_terms<G>(p, Ag, u);
+            leave_behind<G>(Ag, S, p.n_coarse, stc);
         }
         // the fine level reads the candidate list: from LDS, or back from global memory where it is long
-        __syncthreads();
+        if (coarse_fast && n_f <= p.lds_cap) phase_sync<true>();
+        else __syncthreads();
     }
     if (shadow) {
         if (n_f <= p.lds_cap) touch_rows(p, two ? L.A.ids : nullptr, u, n_f);
         return;
     }
-    // What the coarse level still owes -- the centroid terms of the clusters that stayed behind and
-    // their share of the fine level's normaliser -- is done while the fine level's rows travel.  It
-    // reads the coarse level's working arrays, which the fine level is about to reuse: the barrier
-    // inside leave_behind stands between the two.
-    const auto coarse_rest = [&] {
-        if (!two) return;
-        if (coarse_lds) {
-            emit_coarse_terms<G>(p, L.A, u);
-            leave_behind<G, true>(L.A, S, p.n_coarse, stc);
-        } else {
-            emit_coarse_terms<G>(p, Ag, u);
-            leave_behind<G, false>(Ag, S, p.n_coarse, stc);
-        }
-    };
     unsigned long long* kf = p.key_f + (long long)u * p.f_stride;
     uint8_t* ff = p.flag_f + (long long)u * p.f_stride;
+    // (the coarse level's centroid terms are written while the fine level's rows travel)
+    const auto coarse_terms = [&] {
+        if (two && coarse_fast && p.use_mp) fast_terms<G>(p, fc, slot_c, p.n_coarse, p.fcap, u);
+    };
     if (n_f <= p.lds_cap) {
-        const int lin = score_level<G, true>(p, L, L.A, S, u, n_f, two, false, p.key_budget, two, !two, qv, false, false, kf, ff,
-                                             stf, coarse_rest);
+        FastLevel<G> ff_state;
+        const int lin = fast_level<G>(p, L, S, u, n_f, two, false, p.key_budget, two, !two, qv, false, kf, ff, ff_state, coarse_terms);
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
-        fine_epilogue<G, true>(p, L.A, S, sc, u, n_f, two, n_terms);
+        fast_epilogue<G>(p, L, S, sc, ff_state, u, n_f, two, n_terms);
     } else {
-        const int lin = score_level<G, false>(p, L, Ag, S, u, n_f, two, false, p.key_budget, two, !two, qv, false, false, kf, ff,
-                                              stf, coarse_rest);
+        coarse_terms();
+        if (two && coarse_fast) {      // (the general path reads the sums over all waves)
+            if (tid < G) {
+                double b = 0.0;
+                for (int w = 0; w < kWaves; ++w) b += S.bw[w][tid];
+                S.bs[tid] = b;
+            }
+            __syncthreads();
+        }
+        LevelState<G> stf;
+        const int lin = score_level<G>(p, L, Ag, S, u, n_f, two, false, p.key_budget, two, !two, qv, kf, ff, stf);
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
-        fine_epilogue<G, false>(p, Ag, S, sc, u, n_f, two, n_terms);
+        fine_epilogue<G>(p, Ag, S, sc, u, n_f, two, n_terms);
     }
+    if (appends)
+        reinterpret_cast<uint4*>(p.app_dst[tid >> 4])[((long long)u * p.app_dst_rows + p.app_row) * 16 + (tid & 15)] = app;
 }
 
 }  // namespace
@@ -1077,7 +1782,7 @@ size_t score_smem_bytes(int G, int lds_cap)
 {
     const size_t GH = (size_t)(G + 3) / 4;
     return align16(sizeof(Scratch)) + GH * 512 * 8 + (size_t)kHistBuckets * 8 + (size_t)kListCap * 16 +
-           (size_t)lds_cap * (8 * (size_t)G + 8 + 4 * 4 + 1) + 32;
+           (size_t)lds_cap * (8 + 3 * 4) + 32;
 }
 
 template <int G>
