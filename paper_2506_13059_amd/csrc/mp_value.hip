@@ -638,27 +638,32 @@ __global__ __launch_bounds__(256) void value_pass_kernel(const ValuePassParams p
     }
 }
 
-// One workgroup of 128 threads per (unit, head); thread d combines dimension d over the chunks in
-// chunk order (bit-reproducible).  Every thread reads the (m, l) pairs of all chunks itself (the
-// same addresses across a wave: one transaction) and works out the weights 2^(m_i - M) on its own,
-// so nothing is exchanged and nothing waited for except memory: kBatch chunks are fetched at a
-// time, all loads of a batch in flight together, with an online rescale between batches (the
-// launch picks the batch that covers all chunks in one trip to memory where it can).
-template <int kBatch>
-__global__ __launch_bounds__(128) void merge_kernel(const float* __restrict__ partials, int chunks_per_unit, int G,
-                                                    uint16_t* __restrict__ out, float* __restrict__ lse)
+// One workgroup of kSplits * 128 threads per (unit, head); thread (s, d) combines dimension d over one contiguous
+// share of the chunks in chunk order (bit-reproducible), then the first 128 threads combine the shares.  Every
+// thread reads the (m, l) pairs of its chunks itself (the same addresses across a wave: one transaction) and
+// works out the weights 2^(m_i - M) on its own; kBatch chunks are fetched at a time, all loads of a batch in
+// flight together, with an online rescale between batches.  What bounds it is the number of trips to memory in a
+// row, so the launch splits the chunks until a share is one batch (up to eight shares): 118 chunks of 8 heads x 64
+// units took 37 us with one share.
+template <int kSplits>
+__global__ __launch_bounds__(128 * kSplits) void merge_kernel(const float* __restrict__ partials, int chunks_per_unit, int G,
+                                                              uint16_t* __restrict__ out, float* __restrict__ lse)
 {
+    constexpr int kBatch = 16;
+    __shared__ float share[kSplits > 1 ? kSplits : 1][kSplits > 1 ? 130 : 1];
     const int uh = blockIdx.x;
     const int u = uh / G, h = uh - u * G;
-    const int d = threadIdx.x;
+    const int d = threadIdx.x & 127, sp = threadIdx.x >> 7;
+    const int per = (chunks_per_unit + kSplits - 1) / kSplits;
+    const int first = sp * per, end = first + per < chunks_per_unit ? first + per : chunks_per_unit;
     const float* base = partials + ((long long)u * chunks_per_unit * G + h) * kPartStride;
     const long long cs = (long long)G * kPartStride;
     float M = -INFINITY, L = 0.f, a = 0.f;
-    for (int i0 = 0; i0 < chunks_per_unit; i0 += kBatch) {
+    for (int i0 = first; i0 < end; i0 += kBatch) {
         float m[kBatch], l[kBatch], v[kBatch];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const int i = i0 + j < chunks_per_unit ? i0 + j : chunks_per_unit - 1;    // always a valid address
+            const int i = i0 + j < end ? i0 + j : end - 1;    // always a valid address
             m[j] = base[i * cs];
             l[j] = base[i * cs + 1];
             v[j] = base[i * cs + 4 + d];
@@ -666,7 +671,7 @@ __global__ __launch_bounds__(128) void merge_kernel(const float* __restrict__ pa
         float bm = -INFINITY;
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            if (i0 + j >= chunks_per_unit) m[j] = -INFINITY;
+            if (i0 + j >= end) m[j] = -INFINITY;
             bm = fmaxf(bm, m[j]);
         }
         const float Mn = fmaxf(M, bm);
@@ -683,6 +688,26 @@ __global__ __launch_bounds__(128) void merge_kernel(const float* __restrict__ pa
             }
         }
         M = Mn;
+    }
+    if constexpr (kSplits > 1) {
+        share[sp][2 + d] = a;
+        if (d == 0) {
+            share[sp][0] = M;
+            share[sp][1] = L;
+        }
+        __syncthreads();
+        if (sp > 0) return;
+        float Mt = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < kSplits; ++s) Mt = fmaxf(Mt, share[s][0]);
+        a = L = 0.f;
+#pragma unroll
+        for (int s = 0; s < kSplits; ++s) {
+            const float w = (share[s][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(share[s][0] - Mt);
+            a = fmaf(share[s][2 + d], w, a);
+            L = fmaf(share[s][1], w, L);
+        }
+        M = Mt;
     }
     const float o = (L > 0.f) ? a / L : 0.f;
     out[(long long)uh * kHeadDim + d] = f32_to_bf16_rne(o);
@@ -727,12 +752,13 @@ hipError_t launch_merge(const float* partials, int n_units, int chunks_per_unit,
 {
     const long long blocks = (long long)n_units * G;
     if (blocks <= 0) return hipSuccess;
-    if (chunks_per_unit <= 16)
-        hipLaunchKernelGGL(merge_kernel<16>, dim3((unsigned)blocks), dim3(128), 0, stream, partials, chunks_per_unit, G, out, lse);
-    else if (chunks_per_unit <= 32)
-        hipLaunchKernelGGL(merge_kernel<32>, dim3((unsigned)blocks), dim3(128), 0, stream, partials, chunks_per_unit, G, out, lse);
-    else
-        hipLaunchKernelGGL(merge_kernel<64>, dim3((unsigned)blocks), dim3(128), 0, stream, partials, chunks_per_unit, G, out, lse);
+    auto go = [&](auto kernel, int splits) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(128 * splits), 0, stream, partials, chunks_per_unit, G, out, lse);
+    };
+    if (chunks_per_unit <= 16) go(merge_kernel<1>, 1);
+    else if (chunks_per_unit <= 32) go(merge_kernel<2>, 2);
+    else if (chunks_per_unit <= 64) go(merge_kernel<4>, 4);
+    else go(merge_kernel<8>, 8);
     return hipGetLastError();
 }
 
