@@ -51,6 +51,7 @@ mp_status fail(mp_ctx* ctx, mp_status st, const char* fmt, ...)
 // Two workgroups of the value pass are resident per compute unit, 512 on the chip.
 constexpr int kResidentWgs = 512;
 
+// (vector-ALU kernel; its chunk counts are also the least workspace a dense call has to bring)
 int pick_chunk_rows(long long n_rows_per_unit, int n_units)
 {
     int cr = kChunkRowsMin;
@@ -58,7 +59,33 @@ int pick_chunk_rows(long long n_rows_per_unit, int n_units)
     return cr;
 }
 
-// Rows per workgroup for one stream of the value pass (selected keys: largest = 2048; centroid terms
+// Matrix-core kernel: workgroups per unit for a launch over all units.  One workgroup per compute unit: four waves
+// with three pieces of 4 KiB each on their way keep a compute unit's share of the memory system busy, and every
+// further workgroup only adds a prologue, an epilogue and partials to merge.  Measured (dense, us by workgroups in
+// all): 64 units x 60013 rows, 8 heads: 128: 348, 256: 292, 512: 295, 1024: 306, 4032: 330; 8 x 32768, 4 heads:
+// 128: 29.9, 256: 25.8, 512: 27.8, 1024: 37.8; 1 x 131072: 128: 21.0, 256: 20.4, 512: 26.8; selected keys, whole
+// step: 128 units x 8192: 128: 152, 256: 125, 512: 123.5, 1024: 125.8; 24 x 6250, 8 heads: 120: 56.3, 240: 49.4,
+// 480: 51.0, 792: 57.2.  More units than compute units: several rounds of workgroups, so that the last round is
+// a small part (1536 cost 1 % over 256 where both were possible).
+constexpr int kStreamWgs = 256;
+int stream_chunks_per_unit(int n_units)
+{
+    return n_units <= kStreamWgs ? kStreamWgs / n_units : std::max(1, 6 * kStreamWgs / n_units);
+}
+// Rows per chunk when n rows are cut into at most `chunks` chunks: a multiple of 64 (16 rows a wave and tile).
+int stream_chunk_rows(long long n, int chunks)
+{
+    const long long per = (n + chunks - 1) / chunks;
+    return (int)std::max<long long>(64, (per + 63) / 64 * 64);
+}
+// The matrix-core kernel moves 16 bytes at a time straight to LDS: rows have to start on such a boundary.  (Rows of
+// a caller's tensor that do not go through the vector-ALU kernel, whose loads take any alignment.)
+bool rows_aligned(const void* k, const void* v)
+{
+    return (((uintptr_t)k | (uintptr_t)v) & 15) == 0;
+}
+
+// Rows per workgroup for one stream of the vector-ALU value pass (selected keys: largest = 2048; centroid terms
 // and tail: largest = 512).  Long chunks spread the prologue and epilogue of a workgroup over more
 // bytes, but only pay off while the stream still has a workgroup for every resident slot; so: the
 // largest size that does, else the smallest (measured on cfg3: 2048 at key budget 8192 = 512
@@ -196,6 +223,7 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     ctx->max_blocks = std::max(4, c.block_w > 0 ? c.max_tokens / c.block_w + 2 : 2);
     ctx->Pcap = mp::max_stream_chunks(ctx->Ncap, ctx->U, 2048) + mp::max_stream_chunks(std::max(ctx->Tcap, 1), ctx->U, 512) +
                 mp::max_stream_chunks((int)ctx->tab_rows, ctx->U, 512);
+    ctx->Pcap = std::max(ctx->Pcap, 2 * mp::stream_chunks_per_unit(ctx->U) + 2);      // (selected keys or terms, and the tail)
 
     hipError_t e = hipGetDevice(&ctx->device);
     if (e == hipSuccess) e = mp::resolve_static_scratch();
@@ -412,6 +440,14 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     vp.scale_log2e = (float)(ctx->scale_d * 1.4426950408889634);
     const int main_max = std::min(key_budget, ctx->n_tokens);
     int ns = 0, chunk0 = 0;
+    // The matrix-core kernel takes every launch but those with 8-bit rows or a tail that does not start on 16 bytes.
+    // Its workgroups per unit are shared out over the selected keys (or, where none can be selected, the centroid
+    // terms) and the tail by their rows.
+    const bool on_matrix = ctx->cfg.kv_format == MP_KV_BF16 && rows_aligned(k_tail, v_tail);
+    const int per_unit = stream_chunks_per_unit(U);
+    const int first_max = main_max > 0 ? main_max : (use_mp ? ctx->n_fine + ctx->n_coarse : 0);
+    const int tail_rows = stream_chunk_rows((long long)first_max + n_tail, per_unit);
+    const int first_rows = stream_chunk_rows(first_max, std::max(1, per_unit - ceil_div(n_tail, tail_rows)));
     // order: centroid terms, tail, selected keys -- the longest stream goes last (see the kernel's block mapping)
     // The centroid terms ride along with the selected keys where there are any: shared out over that
     // stream's workgroups they cost each a few per cent more rows, instead of workgroups of their own -- most of
@@ -421,7 +457,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     int terms_src = -1;         // (the terms are the launch's first source: what a rider has to be)
     if (use_mp) {
         const int mp_max = ctx->n_fine + ctx->n_coarse;
-        const int cr = pick_stream_chunk_rows(mp_max, U, 512);
+        const int cr = on_matrix ? first_rows : pick_stream_chunk_rows(mp_max, U, 512);
         terms_src = ns;
         RowSource& r = vp.src[ns++];
         r.K = nullptr; r.V = ctx->Vc; r.unit_rows = ctx->tab_rows; r.rows = ctx->mp_rows; r.rows_stride = ctx->tab_rows;
@@ -429,14 +465,14 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
         r.chunk_rows = cr; r.row0 = 0; r.n_chunks = terms_ride ? 0 : ceil_div(mp_max, cr); chunk0 += r.n_chunks;
     }
     if (n_tail > 0) {
-        const int cr = pick_stream_chunk_rows(n_tail, U, 512);
+        const int cr = on_matrix ? tail_rows : pick_stream_chunk_rows(n_tail, U, 512);
         RowSource& r = vp.src[ns++];
         r.K = (const uint16_t*)k_tail; r.V = (const uint16_t*)v_tail; r.unit_rows = tail_stride ? tail_stride : n_tail; r.rows = nullptr; r.rows_stride = 0;
         r.count_dev = nullptr; r.count_max = n_tail; r.scores = nullptr; r.chunk0 = chunk0;
         r.chunk_rows = cr; r.row0 = 0; r.n_chunks = ceil_div(n_tail, cr); chunk0 += r.n_chunks;
     }
     if (main_max > 0) {
-        const int crm = pick_stream_chunk_rows(main_max, U, 2048);
+        const int crm = on_matrix ? first_rows : pick_stream_chunk_rows(main_max, U, 2048);
         RowSource& r = vp.src[ns++];
         if (ctx->cfg.kv_format == MP_KV_E4M3) {
             r.K = (const uint16_t*)ctx->Kq; r.V = (const uint16_t*)ctx->Vq; r.row_scale = ctx->kv_scale;
@@ -455,7 +491,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[1], s));
     MP_HIP(ctx, launch_score_select(sp, ctx->n_cus, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[2], s));
-    if (chunk0 > 0) MP_HIP(ctx, launch_value_pass(vp, G, s));
+    if (chunk0 > 0) MP_HIP(ctx, on_matrix ? launch_value_stream(vp, G, s) : launch_value_pass(vp, G, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[3], s));
     MP_HIP(ctx, launch_merge(ctx->partials, U, chunk0, G, (uint16_t*)out, lse, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[4], s));
@@ -726,6 +762,8 @@ size_t mp_dense_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_h
 {
     if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n < 0 || n_q_heads % n_kv_heads) return 0;
     const int U = batch * n_kv_heads, G = n_q_heads / n_kv_heads;
+    // the partials of the vector-ALU kernel's chunks (the matrix-core kernel would cut short contexts into more of
+    // them; it takes as many as fit: 8 units x 4096 rows, 4 heads: 12.8 us, 11.8 us with more room)
     const int cr = pick_chunk_rows(n, U);
     const int chunks = ceil_div(n > 0 ? n : 1, cr);
     return sizeof(float) * (size_t)U * chunks * G * kPartStride;
@@ -746,7 +784,13 @@ mp_status dense_impl(const char* who, const void* q, const void* k, const void* 
     p.q = (const uint16_t*)q;
     p.partials = partials;
     p.n_units = U;
-    const int dcr = pick_chunk_rows(n, U);
+    const bool on_matrix = rows_aligned(k, v);
+    int dcr = pick_chunk_rows(n, U);
+    if (on_matrix) {
+        // as many chunks as the kernel wants, or as the stated workspace has room for (not the one at hand: results do
+        // not depend on its size)
+        dcr = stream_chunk_rows(n, std::min(stream_chunks_per_unit(U), ceil_div(n > 0 ? n : 1, dcr)));
+    }
     p.chunks_per_unit = ceil_div(n > 0 ? n : 1, dcr);
     p.src[0].chunk_rows = dcr;
     p.src[0].row0 = 0;
@@ -758,7 +802,7 @@ mp_status dense_impl(const char* who, const void* q, const void* k, const void* 
     p.src[0].count_max = n;
     p.src[0].chunk0 = 0;
     p.src[0].n_chunks = p.chunks_per_unit;
-    hipError_t e = launch_value_pass(p, G, s);
+    hipError_t e = on_matrix ? launch_value_stream(p, G, s) : launch_value_pass(p, G, s);
     if (e == hipSuccess) e = launch_merge(p.partials, U, p.chunks_per_unit, G, (uint16_t*)out, lse, s);
     if (e != hipSuccess) return fail(nullptr, MP_EHIP, "%s: %s", who, hipGetErrorString(e));
     return MP_OK;

@@ -1,0 +1,421 @@
+// Value pass on the matrix cores, for gfx950: the counterpart of value_pass_kernel (mp_value.hip) for groups of
+// query heads whose arithmetic a vector pipe cannot do at the rate the rows arrive.
+//
+// A wave streams tiles of 16 rows.  Rows go from global memory straight to LDS (global_load_lds, 16 bytes a lane,
+// four whole rows an instruction), into a ring of two tiles per wave, so that three of the four 4 KiB pieces are on
+// their way while one is used and no registers are held for them.  Per tile:
+//   S = K Q^T      four v_mfma_f32_16x16x32_bf16 (A = 16 key rows, B = up to 16 columns of queries); lane (g, c)
+//                  receives rows 4g .. 4g+3 of column c
+//   P = 2^(S - m)  online softmax in fp32, one column (head) per lane, rescaling only when a maximum moves
+//   O += P V       eight v_mfma_f32_16x16x16_bf16 (A = P exactly as it lies in the registers, B = V read from LDS
+//                  with the transposing read)
+// The matrix cores take bf16, the probabilities are fp32: each is split exactly into three bf16 values (8 + 8 + 8
+// significant bits, by truncation), and the 16 columns of the product hold them side by side: column part * G + h.
+// Where three parts of G heads do not fit 16 columns (G > 5) the third parts take a second set of products.  The
+// sum of the parts' products is the fp32 product sum; nothing is rounded to 16 bits.
+//
+// What bounds it is the memory system: about 100 vector instructions a tile against 420 of the vector-ALU kernel (60 %
+// of a SIMD's issue slots at the dense rate with 4 heads, more than there are with 8).  Measured on the benchmark's
+// 8 GiB cache, dense, 1 / 4 / 5 / 6 / 8 heads: vector ALU 1259 / 1345 / 1367 / 1615 / 1763 us, here with the same
+// chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per compute unit (see stream_chunks_per_unit in
+// mp_api.hip) 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: 504 -> 291 us; 8 units x 32768,
+// 4 heads: 40.8 -> 26.0 us.
+#include "mp_device.h"
+#include "mp_internal.h"
+
+namespace mp {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kTile = 16;                        // rows per tile
+constexpr int kPiece = kTile * 256;              // bytes of a tile's keys (or values)
+constexpr int kRing = 4 * kPiece;                // per wave: keys and values of two tiles
+constexpr int kStrip = 64;                       // row numbers fetched at a time
+
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef const __attribute__((address_space(1))) unsigned char glb_byte;
+
+template <int kBytes, bool kOnce>
+__device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds_off)
+{
+    // (the LDS address is the same in all lanes; lane i's bytes go to it + kBytes * i)
+    auto* dst = reinterpret_cast<__attribute__((address_space(3))) uint32_t*>((uintptr_t)lds_off);
+    auto* from = (const __attribute__((address_space(1))) uint32_t*)src;
+    if constexpr (kBytes == 16 && kOnce) __builtin_amdgcn_global_load_lds(from, dst, 16, 0, 2);     // (2: non-temporal)
+    else if constexpr (kBytes == 16) __builtin_amdgcn_global_load_lds(from, dst, 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds(from, dst, 4, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Four row numbers, 16 bytes apart.
+__device__ __forceinline__ void lds_read_rows(uint32_t a, int (&r)[4])
+{
+    asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:16\n\tds_read_b32 %2, %4 offset:32\n\t"
+                 "ds_read_b32 %3, %4 offset:48\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+                 : "v"(a)
+                 : "memory");
+}
+
+template <int G>
+struct StreamState {
+    static constexpr bool kThird = 3 * G > 16;          // third parts in products of their own
+    f32x4 o[8];                                         // rows 4g+i = columns part * G + h, lane & 15 = dim of the 16
+    f32x4 o3[kThird ? 8 : 1];
+    float m, l;                                         // of this lane's column
+};
+
+// Online softmax of one tile's scores (rows 4g+i of this lane's column) and the product with its value rows.
+template <int G>
+__device__ __forceinline__ void tile_softmax(StreamState<G>& st, const float (&s)[4], float (&p)[4])
+{
+    const float mt = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    if (__any(mt > st.m)) {          // (the running maximum settles after a few tiles)
+        float mn = fmaxf(st.m, mt);
+        mn = fmaxf(mn, __shfl_xor(mn, 16, 64));
+        mn = fmaxf(mn, __shfl_xor(mn, 32, 64));
+        const float ms = mn == -INFINITY ? 0.f : mn;
+        const float a = __builtin_amdgcn_exp2f(st.m - ms);
+        st.l *= a;
+        st.m = mn;
+        const int g4 = (threadIdx.x & 48) >> 2;
+        float f[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = __shfl(a, g4 + i, 64);        // factor of column 4g+i
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                st.o[d][i] *= f[i];
+                if constexpr (StreamState<G>::kThird) st.o3[d][i] *= f[i];
+            }
+    }
+    const float ms = st.m == -INFINITY ? 0.f : st.m;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        p[i] = __builtin_amdgcn_exp2f(s[i] - ms);
+        st.l += p[i];
+    }
+}
+
+__device__ __forceinline__ s16x4 upper_halves(const float (&x)[4])
+{
+    u32x2 w;
+    w.x = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
+    w.y = __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u);
+    return __builtin_bit_cast(s16x4, w);
+}
+
+template <int G>
+__device__ __forceinline__ void tile_values(StreamState<G>& st, const float (&p)[4], uint32_t v_addr, uint32_t mask1,
+                                            uint32_t mask2)
+{
+    // this lane's part of p: p itself, what truncation to bf16 leaves, or what it leaves of that
+    float x[4], y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        x[i] = p[i] - __uint_as_float(__float_as_uint(p[i]) & mask1);
+        if constexpr (StreamState<G>::kThird) {
+            const float r = p[i] - __uint_as_float(__float_as_uint(p[i]) & 0xffff0000u);
+            y[i] = r - __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+        } else {
+            x[i] = x[i] - __uint_as_float(__float_as_uint(x[i]) & mask2);
+        }
+    }
+    const s16x4 a = upper_halves(x);
+    s16x4 v[8];
+    const uint32_t a0 = v_addr, a1 = v_addr ^ 32u, a2 = v_addr ^ 64u, a3 = v_addr ^ 96u, a4 = v_addr ^ 128u,
+                   a5 = v_addr ^ 160u, a6 = v_addr ^ 192u, a7 = v_addr ^ 224u;
+    asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %2, %10\n\t"
+                 "ds_read_b64_tr_b16 %3, %11\n\tds_read_b64_tr_b16 %4, %12\n\tds_read_b64_tr_b16 %5, %13\n\t"
+                 "ds_read_b64_tr_b16 %6, %14\n\tds_read_b64_tr_b16 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                 : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(a4), "v"(a5), "v"(a6), "v"(a7)
+                 : "memory");
+#pragma unroll
+    for (int d = 0; d < 8; ++d) st.o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, v[d], st.o[d], 0, 0, 0);
+    if constexpr (StreamState<G>::kThird) {
+        const s16x4 b = upper_halves(y);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) st.o3[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b, v[d], st.o3[d], 0, 0, 0);
+    }
+}
+
+// Rows [w0, w1) of a source through one wave.  `ring`: LDS byte offset of the wave's ring; `strips`: of its two
+// strips of row numbers.  kScored: the logits are read ready-made and only value rows are loaded.
+template <int G, bool kScored, bool kListed>
+__device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0,
+                                             int w1, uint32_t ring, uint32_t strips)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int head = c % G;                                       // (columns beyond the last part repeat a head)
+    const int part = c / G;
+    const uint32_t mask1 = part >= 1 ? 0xffff0000u : 0u, mask2 = part >= 2 ? 0xffff0000u : 0u;
+    const unsigned char* Kb = reinterpret_cast<const unsigned char*>(S.K) + (long long)u * S.unit_rows * 256;
+    const unsigned char* Vb = reinterpret_cast<const unsigned char*>(S.V) + (long long)u * S.unit_rows * 256;
+    const int32_t* rows = kListed ? S.rows + (long long)u * S.rows_stride : nullptr;
+    const float* scores = kScored ? S.scores + (long long)u * S.rows_stride * G : nullptr;
+
+    // B operand: this column's query, dims [32 ks + 8 g, +8)
+    bf16x8 q[4];
+    if constexpr (!kScored) {
+        const uint4* qp = reinterpret_cast<const uint4*>(p.q + ((long long)u * G + head) * kHeadDim);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) q[ks] = __builtin_bit_cast(bf16x8, qp[4 * ks + g]);
+    }
+    // LDS layout of a piece: row r at 256 r, its 16-byte chunk j at position j ^ r (conflict-free reads).
+    // loads: instruction i covers rows 4i .. 4i+3, lane = 16 (row - 4i) + position
+    const uint32_t chunk = (uint32_t)((c ^ g) * 16);              // ^ 64 i: byte offset of the chunk this lane loads
+    const uint32_t k_addr = ring + (uint32_t)(c * 256 + ((g ^ c) & 3) * 16 + (c >> 2) * 64);      // ^ 64 ks
+    const int vr = 4 * g + (c >> 2);
+    const uint32_t v_addr = ring + (uint32_t)(vr * 256 + ((((c & 3) >> 1) ^ vr) & 1) * 16 + (c & 1) * 8 + (vr >> 1) * 32);   // ^ 32 d
+    const int n_tiles = (w1 - w0 + kTile - 1) / kTile;
+
+    auto load_strip = [&](int s) {          // row numbers [w0 + 64 s, +64), clamped to the last row
+        if constexpr (kListed) {
+            int j = w0 + s * kStrip + lane;
+            j = j < w1 ? j : w1 - 1;
+            load_to_lds<4, false>(rows + j, strips + (uint32_t)((s & 1) * 4 * kStrip));
+        }
+    };
+    long long off[4];                        // byte offsets of the rows this lane loads for a tile
+    auto tile_rows = [&](int t) {
+        int r[4];
+        if constexpr (kListed) lds_read_rows(strips + (uint32_t)((((t >> 2) & 1) * kStrip + (t & 3) * kTile + g) * 4), r);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (!kListed) r[i] = min(w0 + t * kTile + 4 * i + g, w1 - 1);
+            off[i] = (long long)r[i] * 256 + (chunk ^ (uint32_t)(64 * i));
+        }
+    };
+    auto load_keys = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Kb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + i * 1024));
+    };
+    auto load_values = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Vb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + kPiece + i * 1024));
+    };
+
+    // In program order the loads of a wave are K0 V0 K1 V1 K2 V2 ..., four instructions a piece, and a strip of row
+    // numbers now and then.  Loads return in order, so "at most twelve outstanding" in front of a piece's use means
+    // that it has arrived (the three pieces behind it may still be under way), and that every older strip has.  A
+    // piece's slot is loaded again only after the LDS reads of the piece have returned.  Tiles past the end repeat
+    // the last row, so that the counts hold to the end.
+    load_strip(0);
+    load_strip(1);
+    if constexpr (kListed) wait_vm<0>();
+    tile_rows(0);
+    if constexpr (!kScored) load_keys(0);
+    load_values(0);
+    tile_rows(1);
+    if constexpr (!kScored) load_keys(1);
+    load_values(1);
+    for (int t = 0; t < n_tiles; ++t) {
+        const uint32_t half = (uint32_t)((t & 1) * 2 * kPiece);
+        float s[4];
+        if constexpr (kScored) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = w0 + t * kTile + 4 * g + i;
+                s[i] = j < w1 ? scores[(long long)j * G + head] : -INFINITY;
+            }
+            wait_vm<0>();
+        } else {
+            wait_vm<12>();
+            bf16x8 k[4];
+            const uint32_t a0 = k_addr + half, a1 = (k_addr ^ 64u) + half, a2 = (k_addr ^ 128u) + half, a3 = (k_addr ^ 192u) + half;
+            asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+                         "s_waitcnt lgkmcnt(0)"
+                         : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3])
+                         : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+                         : "memory");
+            tile_rows(t + 2);
+            load_keys(t + 2);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[ks], q[ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = acc[i] * p.scale_log2e;
+            if (w0 + (t + 1) * kTile > w1) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = w0 + t * kTile + 4 * g + i < w1 ? s[i] : -INFINITY;
+            }
+        }
+        float pr[4];
+        tile_softmax<G>(st, s, pr);
+        if constexpr (!kScored) wait_vm<12>();
+        tile_values<G>(st, pr, v_addr + half + kPiece, mask1, mask2);
+        if constexpr (kScored) tile_rows(t + 2);
+        load_values(t + 2);
+        // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next
+        if constexpr (kListed)
+            if ((t & 3) == 1) load_strip((t >> 2) + 2);
+    }
+    wait_vm<0>();       // (loads past the end are still landing in the ring)
+}
+
+template <int G, int kWaves>
+__global__ __launch_bounds__(64 * kWaves, 2) void value_stream_kernel(const ValuePassParams p)
+{
+    extern __shared__ __align__(256) unsigned char ring_lds[];
+    const int cidx = blockIdx.x / p.n_units;
+    const int u = blockIdx.x - cidx * p.n_units;
+    int si = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxSources; ++i)
+        if (i < p.n_sources && cidx >= p.src[i].chunk0) si = i;
+    const RowSource& S = p.src[si];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int count = S.row0 + S.count_max;
+    if (S.count_dev) {
+        const int cd = S.count_dev[u];
+        count = cd < count ? cd : count;
+    }
+    const int begin = S.row0 + (cidx - S.chunk0) * S.chunk_rows;
+    const int end = (begin + S.chunk_rows < count) ? begin + S.chunk_rows : count;
+    float* part = p.partials + ((long long)u * p.chunks_per_unit + cidx) * G * kPartStride;
+    const RowSource* T = S.guest ? &p.src[0] : nullptr;
+    int g0 = 0, g1 = 0;
+    if (T) {
+        int nt = T->count_max;
+        if (T->count_dev) {
+            const int cd = T->count_dev[u];
+            nt = cd < nt ? cd : nt;
+        }
+        const long long k = cidx - S.chunk0;
+        g0 = (int)(nt * k / S.n_chunks);
+        g1 = (int)(nt * (k + 1) / S.n_chunks);
+    }
+    if (begin >= end && g0 >= g1) {
+        if (tid < G) {
+            part[tid * kPartStride + 0] = -INFINITY;
+            part[tid * kPartStride + 1] = 0.f;
+        }
+        return;
+    }
+    StreamState<G> st;
+    st.m = -INFINITY;
+    st.l = 0.f;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        st.o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (StreamState<G>::kThird) st.o3[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
+    const uint32_t ring = lds0 + (uint32_t)(wave * kRing), strips = lds0 + (uint32_t)(kWaves * kRing + wave * 8 * kStrip);
+    const int wave_rows = ((S.chunk_rows / kWaves) + kTile - 1) / kTile * kTile;
+    const int w0 = begin + wave * wave_rows, w1 = (w0 + wave_rows < end) ? w0 + wave_rows : end;
+    if (w0 < w1) {
+        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w0, w1, ring, strips);
+        else if (S.rows) stream_tiles<G, false, true>(st, S, p, u, w0, w1, ring, strips);
+        else stream_tiles<G, false, false>(st, S, p, u, w0, w1, ring, strips);
+    }
+    if (g0 < g1) {
+        const int per = (((g1 - g0) + kWaves - 1) / kWaves + 15) & ~15;
+        const int a = g0 + wave * per, b = (a + per < g1) ? a + per : g1;
+        if (a < b) stream_tiles<G, true, true>(st, *T, p, u, a, b, ring, strips);
+    }
+    // ---- combine the waves ----
+    float l = st.l;
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    __syncthreads();                         // (every wave is done with its ring)
+    float* sm = reinterpret_cast<float*>(ring_lds);
+    float* sm_m = sm;                        // [kWaves][16]
+    float* sm_l = sm + 16 * kWaves;
+    constexpr int kCols = StreamState<G>::kThird ? 16 + 8 : 16;
+    float* sm_o = sm + 32 * kWaves;          // [kWaves][kCols][128]
+    if (lane < 16) {
+        sm_m[wave * 16 + lane] = st.m;
+        sm_l[wave * 16 + lane] = l;
+    }
+    const int g = lane >> 4, c = lane & 15;
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sm_o[(wave * kCols + 4 * g + i) * 128 + 16 * d + c] = st.o[d][i];
+            if constexpr (StreamState<G>::kThird)
+                if (g < 2) sm_o[(wave * kCols + 16 + 4 * g + i) * 128 + 16 * d + c] = st.o3[d][i];
+        }
+    __syncthreads();
+    for (int o = tid; o < G * 128; o += 64 * kWaves) {
+        const int h = o >> 7, d = o & 127;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sm_m[w * 16 + h]);
+        const float Ms = M == -INFINITY ? 0.f : M;
+        float a = 0.f, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float f = __builtin_amdgcn_exp2f(sm_m[w * 16 + h] - Ms);
+            L = fmaf(sm_l[w * 16 + h], f, L);
+            float x = sm_o[(w * kCols + h) * 128 + d];
+            x += sm_o[(w * kCols + G + h) * 128 + d];
+            x += sm_o[(w * kCols + (StreamState<G>::kThird ? 16 : 2 * G) + h) * 128 + d];
+            a = fmaf(x, f, a);
+        }
+        float* ph = part + h * kPartStride;
+        ph[4 + d] = a;
+        if (d == 0) {
+            ph[0] = M;
+            ph[1] = L;
+        }
+    }
+}
+
+template <int G, int kWaves>
+hipError_t launch_stream_w(const ValuePassParams& p, unsigned blocks, hipStream_t s)
+{
+    static bool configured = false;
+    constexpr size_t smem = kWaves * (kRing + 8 * kStrip);
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&value_stream_kernel<G, kWaves>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL((value_stream_kernel<G, kWaves>), dim3(blocks), dim3(64 * kWaves), smem, s, p);
+    return hipGetLastError();
+}
+
+// Four waves a workgroup, or eight where the launch leaves half of the compute units idle and a wave's share is a
+// long chain of tiles all the same (dense calls over short contexts, whose workspace limits the chunks: 8 units x
+// 4096 rows, 4 / 8 heads: 13.4 / 15.3 us with four waves, 12.8 / 14.7 us with eight).  Elsewhere the two are within 1 %.
+template <int G>
+hipError_t launch_stream_g(const ValuePassParams& p, hipStream_t s)
+{
+    const long long blocks = (long long)p.n_units * p.chunks_per_unit;
+    if (blocks <= 0) return hipSuccess;
+    const bool eight = blocks <= 128 && p.src[p.n_sources - 1].chunk_rows >= 512;
+    return eight ? launch_stream_w<G, 8>(p, (unsigned)blocks, s) : launch_stream_w<G, 4>(p, (unsigned)blocks, s);
+}
+
+}  // namespace
+
+hipError_t launch_value_stream(const ValuePassParams& p, int G, hipStream_t s)
+{
+    switch (G) {
+        case 1: return launch_stream_g<1>(p, s);
+        case 2: return launch_stream_g<2>(p, s);
+        case 3: return launch_stream_g<3>(p, s);
+        case 4: return launch_stream_g<4>(p, s);
+        case 5: return launch_stream_g<5>(p, s);
+        case 6: return launch_stream_g<6>(p, s);
+        case 7: return launch_stream_g<7>(p, s);
+        case 8: return launch_stream_g<8>(p, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace mp

@@ -1,4 +1,5 @@
-// Value pass and merge for gfx950.
+// Value pass on the vector ALU, and merge, for gfx950.  Launches over 8-bit rows and over rows that do not start on 16
+// bytes (a caller's tail or dense keys) come here; all others go to the matrix-core kernel (mp_stream.hip).
 //
 // The value pass is the byte mover of the decode step: it streams 256-byte key rows and value rows
 // (the keys of the selected clusters, the unclustered tail, or all keys for the dense comparison)
