@@ -22,6 +22,7 @@
 //      score is within the same margin of the best one and evaluates their distances in fp64
 //      without fused multiply-adds.
 #include <algorithm>
+#include <type_traits>
 
 #include "mp_device.h"
 #include "mp_internal.h"
@@ -32,6 +33,7 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 32;                 // centroids per tile = rows of the MFMA A operand
 constexpr int kRowBytes = 256 + 16;       // LDS row of one centroid: 128 dims, then -|c|^2/2 as three bf16 and five zeros
@@ -58,28 +60,6 @@ __device__ __forceinline__ void fold_scores(const f32x16_t (&acc)[2], int j0, fl
             best[c] = fmaxf(fmaxf(va, vb), best[c]);
         }
         btile[c] = best[c] != before ? j0 : btile[c];
-    }
-}
-
-// The nine operand fragments a lane takes from one tile: the offset slots, then dims [16 ks + 8 half, +8).
-__device__ __forceinline__ void read_fragments(const unsigned char* tile, int col, int half, bf16x8_t (&f)[9])
-{
-    const unsigned char* row = tile + col * kRowBytes;
-    f[8] = *reinterpret_cast<const bf16x8_t*>(row + 256);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) f[ks] = *reinterpret_cast<const bf16x8_t*>(row + 32 * ks + 16 * half);
-}
-
-__device__ __forceinline__ void multiply_tile(const bf16x8_t (&f)[9], const bf16x8_t (&xb)[2][8], bf16x8_t ones,
-                                              bf16x8_t ones_too, f32x16_t (&acc)[2])
-{
-    const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[8], ones, zero, 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[8], ones_too, zero, 0, 0, 0);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks], xb[0][ks], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks], xb[1][ks], acc[1], 0, 0, 0);
     }
 }
 
@@ -266,123 +246,277 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
                   amb_list + u * list_stride, amb_cnt + u * cnt_stride + b);
 }
 
-// The same stage for blocks of at most kResidentK centroids (every blockwise build with one centroid
-// per 32 tokens and blocks of 8192): all centroids of the block stay in LDS, a workgroup walks
-// several chunks of 256 points of its (block, unit), and the points of the next chunk are on their
-// way from memory while the current ones are multiplied.  No barrier after the centroids are in
-// place.  grid = (workgroups per (block, unit), nb, U), dynamic LDS = kResidentK rows.
-constexpr int kResidentK = 256;
-__global__ __launch_bounds__(256) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
-                                                              const int32_t* __restrict__ blocks,
-                                                              const uint16_t* __restrict__ C, long long c_unit_rows,
-                                                              int32_t* __restrict__ assign, long long assign_stride,
-                                                              int32_t* __restrict__ amb_list, long long list_stride,
-                                                              int32_t* __restrict__ amb_cnt, int cnt_stride)
+// The same stage for blocks of at most 512 centroids and at least 1024 points.  The block's centroids stay in LDS
+// (256-byte rows, 16-byte pieces at position piece ^ (row & 15), and -|c|^2/2 apart: it is the accumulators' initial
+// value), every wave walks chunks of 64 points held in registers as B operands, no barrier after the centroids are in
+// place.  16 x 16 products: a load instruction of the points covers 64 contiguous bytes of 16 rows, and a tile's
+// accumulators are few enough for four waves a SIMD, which hide each other's loads, LDS reads and comparisons.
+//
+// What bounds it: per tile of 16 centroids x 64 points 16 matrix instructions (16 cycles each) and 36 comparison
+// instructions (16 to place the slot, 20 for best and second best).  The two overlap across waves -- a loop
+// of 4 32x32x16 products and 32 vector instructions takes 299 ns for four waves, 219 and 236 ns apart -- so occupancy and instruction
+// count decide: with two waves a SIMD, 32 x 32 products and 79 vector instructions per 2048 scores 1330 us for 16.8 M
+// points x 256 centroids; points streamed through LDS and centroids in registers, two waves, 1390; this
+// layout with three waves 1352, with four waves 1044 us (38.6 -> 27.3 us for 262144 points).  The points alone take
+// 0.65 ms at the rate of the dense kernel; clocks fall to about 2.0 GHz under this load.
+//
+// A lane (g, c) holds rows 4g .. 4g+3 of a tile for column c of four columns groups: point 16 q + c, q < 4.  The slot of a
+// score among the sixteen tiles of a half (tile & 15, row & 3) rides in its six lowest mantissa bits, a change of less
+// than 2^-17 of its magnitude.  A partial sum is at most 1.5 max(|x|^2, |c|^2) and is rounded to nearest at most 128
+// times (2^-24 each): with the slot bits two scores are off by less than 2 (1.5 * 2^-17 + 1.5 * 2^-17) = 0.75 * 2^-14 of
+// that scale together, the margin is 2^-14.
+constexpr int kRowTile = 16;
+constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
+constexpr int kNearCap = 512;
+constexpr uint32_t kSlotMask = 63u;
+
+typedef const __attribute__((address_space(3))) bf16x8_t lds_frag;
+typedef const __attribute__((address_space(3))) f32x4_t lds_four;
+// (plain operations, no inline assembly: only the compiler knows how long a matrix result must not be read)
+__device__ __forceinline__ float with_slot(float v, uint32_t clear, uint32_t slot)
 {
-    extern __shared__ __align__(16) unsigned char ctile[];      // [kResidentK][kRowBytes]
-    __shared__ float wave_c2max[4];
+    return __uint_as_float((__float_as_uint(v) & clear) | slot);
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b)      // a = {a.low, b.low}, b = {a.high, b.high}
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows(float& a, float& b)        // the same with rows 1, 3 of a and 0, 2 of b
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// Two candidates (best, second, origin bits) of the same point become one; `bit` marks that the second one won.
+__device__ __forceinline__ void merge_pair(float& best, float& second, uint32_t& from, float best2, float second2, uint32_t from2,
+                                           uint32_t bit)
+{
+    second = fmaxf(fmaxf(second, second2), fminf(best, best2));
+    from = best2 > best ? (from2 | bit) : from;
+    best = fmaxf(best, best2);
+}
+
+template <int kW>
+__global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
+                                                                    const int32_t* __restrict__ blocks,
+                                                                    const uint16_t* __restrict__ C, long long c_unit_rows,
+                                                                    int32_t* __restrict__ assign, long long assign_stride,
+                                                                    int32_t* __restrict__ amb_list, long long list_stride,
+                                                                    int32_t* __restrict__ amb_cnt, int cnt_stride, int k_cap)
+{
+    extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
+    __shared__ float wave_c2max[kW];
+    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, handed over at the end
+    __shared__ int near_n, near_at;
     const int u = blockIdx.z, b = blockIdx.y;
     const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2];
-    const int k1 = min(blocks[4 * b + 3], k0 + kResidentK);     // (the launch guarantees the block has no more)
-    const int n_chunks = (x1 - x0 + kPtsPerWg - 1) / kPtsPerWg;
-    int chunk = blockIdx.x;
-    if (chunk >= n_chunks) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 31, half = lane >> 5;
-    const uint16_t* Xu = X + (long long)u * x_unit_rows * kHeadDim;
-
-    bf16x8_t xb[2][8], xn[2][8];
-    auto load_points = [&](int ch, bf16x8_t (&dst)[2][8]) {
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int t = x0 + ch * kPtsPerWg + wave * 64 + 32 * c + col;
-            const uint4* xp = reinterpret_cast<const uint4*>(Xu + (long long)(t < x1 ? t : x0) * kHeadDim);
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) dst[c][ks] = __builtin_bit_cast(bf16x8_t, xp[2 * ks + half]);
-        }
-    };
-    load_points(chunk, xb);
+    const int k1 = min(blocks[4 * b + 3], k0 + k_cap);            // (the launch guarantees the block has no more)
+    const int all_chunks = (x1 - x0 + 63) / 64;
+    const int per = (all_chunks + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int chunk0 = (int)blockIdx.x * per, chunk1 = min(chunk0 + per, all_chunks);
+    if (chunk0 >= chunk1) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);
+    float* c_init = reinterpret_cast<float*>(rows_lds + k_cap * 256);
 
     // ---- the block's centroids: 16 lanes per row, rows past the last centroid are zeros that can never win ----
-    const int ntiles = (k1 - k0 + kTile - 1) / kTile;
+    const int ntiles = (k1 - k0 + kRowTile - 1) / kRowTile;
     float c2max = 0.f;
     {
         const uint16_t* Cu = C + (long long)u * c_unit_rows * kHeadDim;
-        for (int e = tid; e < ntiles * kTile * 16; e += 256) {
+        for (int e = tid; e < ntiles * kRowTile * 16; e += 64 * kW) {
             const int row = e >> 4, seg = e & 15;
             const bool exists = k0 + row < k1;
             uint4 w = make_uint4(0, 0, 0, 0);
             if (exists) w = reinterpret_cast<const uint4*>(Cu + (long long)(k0 + row) * kHeadDim)[seg];
-            c2max = fmaxf(c2max, deposit_piece(ctile + row * kRowBytes, seg, w, exists));
+            *reinterpret_cast<uint4*>(rows_lds + row * 256 + ((seg ^ row) & 15) * 16) = w;
+            float s = dot2_bf16(w.x, w.x, 0.f);
+            s = dot2_bf16(w.y, w.y, s);
+            s = dot2_bf16(w.z, w.z, s);
+            s = dot2_bf16(w.w, w.w, s);
+            s = sum8(s);
+            s += dpp_f32<kDppMirror>(s);         // the other 8 lanes of the row of 16
+            c2max = fmaxf(c2max, s);
+            if (seg == 0) c_init[row] = exists ? -0.5f * s : kNoCentroid;
         }
     }
     c2max = wave_max_f32(c2max);
     if (lane == 0) wave_c2max[wave] = c2max;
+    if (tid == 0) near_n = 0;
     __syncthreads();
-    c2max = fmaxf(fmaxf(wave_c2max[0], wave_c2max[1]), fmaxf(wave_c2max[2], wave_c2max[3]));
+#pragma unroll
+    for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
 
-    const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, half == 0 ? make_uint4(0x3f803f80u, 0x00003f80u, 0u, 0u)
-                                                                  : make_uint4(0u, 0u, 0u, 0u));
-    bf16x8_t ones_too = ones;
-    asm volatile("" : "+v"(ones_too));
-    while (true) {
-        const int next = chunk + (int)gridDim.x;
-        const bool has_next = next < n_chunks;
-        if (has_next) load_points(next, xn);
-        float x2[2] = {0.f, 0.f};
-        int tpt[2];
+    int32_t* assign_u = assign + u * assign_stride;
+    int32_t* list_u = amb_list + u * list_stride;
+    int32_t* cnt_ub = amb_cnt + u * cnt_stride + b;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
+    uint32_t clear = ~kSlotMask;
+    asm volatile("" : "+v"(clear));              // (a register: the instruction takes one scalar operand, the slot)
+#pragma unroll 1
+    for (int chunk = chunk0 + wave; chunk < chunk1; chunk += kW) {
+        bf16x8_t x[4][4];                        // points 16 q + c, dims [32 ks + 8 g, +8)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            tpt[c] = x0 + chunk * kPtsPerWg + wave * 64 + 32 * c + col;
+        for (int q = 0; q < 4; ++q) {
+            const int t = min(x0 + chunk * 64 + 16 * q + c, x1 - 1);
+            const uint4* xp = reinterpret_cast<const uint4*>(Xu + (long long)t * 256) + g;
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                const uint4 w = __builtin_bit_cast(uint4, xb[c][ks]);
-                x2[c] = dot2_bf16(w.x, w.x, x2[c]);      // |x|^2 only scales the margin
-                x2[c] = dot2_bf16(w.y, w.y, x2[c]);
-                x2[c] = dot2_bf16(w.z, w.z, x2[c]);
-                x2[c] = dot2_bf16(w.w, w.w, x2[c]);
+            for (int ks = 0; ks < 4; ++ks) x[q][ks] = __builtin_bit_cast(bf16x8_t, xp[4 * ks]);
+        }
+        float best[4], second[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) best[q] = second[q] = -INFINITY;
+        // |x|^2 only scales the margin; lane = point after the reduction
+        float n2[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            n2[q] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const uint4 w = __builtin_bit_cast(uint4, x[q][ks]);
+                n2[q] = dot2_bf16(w.x, w.x, n2[q]);
+                n2[q] = dot2_bf16(w.y, w.y, n2[q]);
+                n2[q] = dot2_bf16(w.z, w.z, n2[q]);
+                n2[q] = dot2_bf16(w.w, w.w, n2[q]);
             }
         }
-        float best[2] = {-INFINITY, -INFINITY}, second[2] = {-INFINITY, -INFINITY};
-        int btile[2] = {k0, k0};
-        // The comparison of one tile's scores runs while the next tile is multiplied: two accumulator
-        // sets, and an instruction order that puts a few comparison instructions behind every pair of
-        // matrix instructions (a matrix instruction waits for its predecessor on the same accumulators
-        // anyway) and keeps one LDS read in flight.
-        auto multiply_and_fold = [&](int t, f32x16_t (&cur)[2], const f32x16_t (&prev)[2]) {
-            bf16x8_t f[9];
-            read_fragments(ctile + t * kTile * kRowBytes, col, half, f);
-            multiply_tile(f, xb, ones, ones_too, cur);
-            fold_scores(prev, k0 + (t - 1) * kTile, best, second, btile);
-            // order: fragment reads run one step ahead of the pair of matrix instructions that use them,
-            // eight comparison instructions follow every pair
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        auto one_tile = [&](const uint32_t (&fr)[4], uint32_t ci_at, auto step, uint32_t slot) {
+            constexpr int kStep = decltype(step)::value;
+            bf16x8_t f[4];
 #pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);     // two matrix instructions
-                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);     // eight vector instructions
-                if (q < 7) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // the read after next
+            for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<lds_frag*>((uintptr_t)(fr[ks] + kStep * kRowTile * 256));
+            const f32x4_t ci = *reinterpret_cast<lds_four*>((uintptr_t)(ci_at + kStep * kRowTile * 4));
+            f32x4_t acc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0], x[q][0], ci, 0, 0, 0);
+#pragma unroll
+            for (int ks = 1; ks < 4; ++ks)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks], x[q][ks], acc[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = with_slot(acc[q][i], clear, slot + 4u * kStep + i);
+                // best and second best of the running pair and four scores: five instructions
+                const float m0 = __builtin_amdgcn_fmed3f(best[q], v[0], v[1]);
+                best[q] = fmaxf(fmaxf(v[0], v[1]), best[q]);
+                const float m1 = __builtin_amdgcn_fmed3f(best[q], v[2], v[3]);
+                best[q] = fmaxf(fmaxf(v[2], v[3]), best[q]);
+                second[q] = fmaxf(fmaxf(m0, m1), second[q]);
             }
         };
-        f32x16_t acc_a[2], acc_b[2];
+        auto tiles = [&](int ta, int tb) {
+            uint32_t fr[4], ci_at = lds0 + (uint32_t)(k_cap * 256 + (ta * kRowTile + 4 * g) * 4);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                fr[ks] = lds0 + (uint32_t)(ta * kRowTile * 256 + c * 256 + ((g ^ c) & 3) * 16 + ((64 * ks) ^ ((c >> 2) * 64)));
+            uint32_t slot = 0;
+            int t = ta;
+#pragma unroll 1
+            for (; t + 4 <= tb; t += 4) {
+                one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
+                one_tile(fr, ci_at, std::integral_constant<int, 1>{}, slot);
+                one_tile(fr, ci_at, std::integral_constant<int, 2>{}, slot);
+                one_tile(fr, ci_at, std::integral_constant<int, 3>{}, slot);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) fr[ks] += 4 * kRowTile * 256;
+                ci_at += 4 * kRowTile * 4;
+                slot += 16u;
+            }
+#pragma unroll 1
+            for (; t < tb; ++t) {
+                one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) fr[ks] += kRowTile * 256;
+                ci_at += kRowTile * 4;
+                slot += 4u;
+            }
+        };
+        tiles(0, min(ntiles, kHalfTiles));
+        uint32_t from[4] = {0u, 0u, 0u, 0u};
+        if (ntiles > kHalfTiles) {
+            float first_half[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) first_half[q] = best[q];
+            tiles(kHalfTiles, ntiles);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) from[q] = best[q] != first_half[q] ? 4u : 0u;
+        }
+        const int t_first = x0 + chunk * 64;
+        // lane (g, c) ends up with point 16 g + c = lane: halves first (points q and q + 2), then rows
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            float fl = __uint_as_float(from[q]), fh = __uint_as_float(from[q + 2]);
+            swap_halves(best[q], best[q + 2]);
+            swap_halves(second[q], second[q + 2]);
+            swap_halves(n2[q], n2[q + 2]);
+            swap_halves(fl, fh);
+            from[q] = __float_as_uint(fl);
+            merge_pair(best[q], second[q], from[q], best[q + 2], second[q + 2], __float_as_uint(fh), 2u);
+            n2[q] += n2[q + 2];
+        }
         {
-            bf16x8_t f[9];
-            read_fragments(ctile, col, half, f);
-            multiply_tile(f, xb, ones, ones_too, acc_a);
+            float fl = __uint_as_float(from[0]), fh = __uint_as_float(from[1]);
+            swap_rows(best[0], best[1]);
+            swap_rows(second[0], second[1]);
+            swap_rows(n2[0], n2[1]);
+            swap_rows(fl, fh);
+            from[0] = __float_as_uint(fl);
+            merge_pair(best[0], second[0], from[0], best[1], second[1], __float_as_uint(fh), 1u);
+            n2[0] += n2[1];
         }
-        for (int t = 1; t < ntiles; t += 2) {
-            multiply_and_fold(t, acc_b, acc_a);
-            if (t + 1 < ntiles) multiply_and_fold(t + 1, acc_a, acc_b);
+        const int t = t_first + lane;
+        if (t < x1) {
+            const uint32_t slot = __float_as_uint(best[0]) & kSlotMask;
+            const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
+            assign_u[t] = k0 + tile * kRowTile + 4 * row_g + (int)(slot & 3u);
+            const float margin = kMarginScale * fmaxf(n2[0], c2max);
+            // (written so that a point without any comparable score also goes to the exact pass)
+            if (!(best[0] - second[0] > margin)) {
+                // (through LDS: a global counter's answer would have to wait for the points under way)
+                const int pos = atomicAdd(&near_n, 1);
+                if (pos < kNearCap) near_list[pos] = t;
+                else list_u[x0 + atomicAdd(cnt_ub, 1)] = t;
+            }
         }
-        if (ntiles & 1) fold_scores(acc_a, k0 + (ntiles - 1) * kTile, best, second, btile);
-        else fold_scores(acc_b, k0 + (ntiles - 1) * kTile, best, second, btile);
-        finish_points(half, best, second, btile, x2, tpt, x0, x1, c2max, assign + u * assign_stride,
-                      amb_list + u * list_stride, amb_cnt + u * cnt_stride + b);
-        if (!has_next) break;
-        for (int c = 0; c < 2; ++c)
-            for (int ks = 0; ks < 8; ++ks) xb[c][ks] = xn[c][ks];
-        chunk = next;
     }
+    __syncthreads();
+    const int n = min(near_n, kNearCap);
+    if (tid == 0 && n > 0) near_at = atomicAdd(cnt_ub, n);
+    __syncthreads();
+    for (int i = tid; i < n; i += 64 * kW) list_u[x0 + near_at + i] = near_list[i];
+}
+
+constexpr int kResidentMaxK = 512;
+constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
+template <int kW>
+hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts, int max_k,
+                           int U, const uint16_t* C, long long c_unit_rows, int32_t* assign, long long assign_stride,
+                           int32_t* amb_list, long long list_stride, int32_t* amb_cnt, int cnt_stride, hipStream_t s)
+{
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&assign_resident_kernel<kW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kResidentMaxK * 260);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    const int k_cap = (max_k + kRowTile - 1) / kRowTile * kRowTile;
+    // workgroups per (block, unit): one round of resident workgroups where they fit it, else at least four rounds, so
+    // that the last one weighs little; no fewer than one chunk a wave each
+    constexpr long long kSlots = 4096 / kW;                      // sixteen waves on each of 256 compute units
+    const long long groups = (long long)nb * U;
+    const int chunks = (max_pts + 63) / 64;
+    const long long want = groups <= kSlots ? kSlots / groups : (4 * kSlots + groups - 1) / groups;
+    const int gx = (int)std::max<long long>(1, std::min<long long>(chunks / kW, want));
+    hipLaunchKernelGGL(assign_resident_kernel<kW>, dim3(gx, nb, U), dim3(64 * kW), (size_t)k_cap * 260, s, X, x_unit_rows,
+                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, k_cap);
+    return hipGetLastError();
 }
 
 // Stage 2.  One wave per listed point, three passes over the block's centroids:
@@ -572,20 +706,14 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
     if (nb > cnt_stride || U > 65535) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     const int n_chunks = (max_pts + kPtsPerWg - 1) / kPtsPerWg;
-    if (max_k > 0 && max_k <= kResidentK && n_chunks >= 4) {
-        // enough workgroups to fill the chip, several chunks each where the blocks are long enough
-        static bool configured = false;
-        const int smem = kResidentK * kRowBytes;
-        if (!configured) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&assign_resident_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-            if (e != hipSuccess) return e;
-            configured = true;
-        }
-        const long long groups = (long long)nb * U;
-        const int gx = (int)std::min<long long>(n_chunks, std::max<long long>(4, (1024 + groups - 1) / groups));
-        hipLaunchKernelGGL(assign_resident_kernel, dim3(gx, nb, U), dim3(256), smem, s, X, x_unit_rows, blocks_dev, C,
-                           c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride);
+    if (max_k > 0 && max_k <= kResidentMaxK && max_pts >= 1024) {
+        // two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen
+        auto go = [&](auto launch) {
+            return launch(X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows, assign, assign_stride, amb_list,
+                          list_stride, amb_cnt, cnt_stride, s);
+        };
+        e = max_k <= kResidentTwiceK ? go(launch_resident<8>) : go(launch_resident<16>);
+        if (e != hipSuccess) return e;
     } else {
         hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
                            c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride);

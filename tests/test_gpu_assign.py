@@ -1,0 +1,30 @@
+"""GPU parity of the k-means assignment at the edges of the kernel that keeps a block's centroids in LDS: tiles of 16
+centroids (ragged last tile), slots of sixteen tiles (more than 256 centroids take a second half), eight or sixteen
+waves a workgroup (304 centroids and more), the limit of 512, and chunks of 64 points with a ragged end.  Assignments,
+counts and centroids are bit-identical to the oracle's."""
+import pytest
+
+from tests.test_gpu_kmeans import _run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k,n", [(1, 1024), (15, 1025), (16, 1087), (17, 1100), (255, 2113), (256, 1500), (257, 1535),
+                                 (273, 2050), (304, 1801), (305, 1801), (400, 1999), (512, 2300), (513, 1600)])
+def test_centroid_counts(k, n):
+    print(f"k={k} n={n}", flush=True)
+    ctx, _, _ = _run_case(1, 2, 2, n, max(2, k // 3), 1, k, 0, 0, 0, iters=2, seed=300 + k)
+    ctx.close()
+
+
+def test_more_near_ties_than_a_workgroup_lists_in_lds():
+    # one distinct key row: every point of every workgroup goes to the exact pass
+    ctx, _, _ = _run_case(1, 2, 1, 9000, 4, 1, 40, 0, 0, 0, iters=1, seed=21, distinct_rows=1)
+    ctx.close()
+
+
+def test_many_blocks_of_many_units():
+    # (block, unit) pairs beyond one round of workgroups are covered by the full-size test; here a handful with ragged ends
+    ctx, _, _ = _run_case(2, 4, 2, 5000, 60, 2, 150, 10, 1200, 600, iters=2, seed=22)
+    assert ctx.mp_get_sizes()["n_blocks"] == 4
+    ctx.close()
