@@ -298,6 +298,150 @@ __device__ __forceinline__ void merge_pair(float& best, float& second, uint32_t&
     best = fmaxf(best, best2);
 }
 
+// The nearest of the centroids in LDS (rows at lds0, -|c|^2/2 behind k_cap rows) for the 64 points first, first + 1, ...
+// (clamped to `last`) of Xu: lane = point.  `near`: its two best scores are closer than the margin.
+struct Nearest {
+    int j;
+    bool near;
+};
+__device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int first, int last, uint32_t lds0, int k_cap,
+                                                    int ntiles, float c2max)
+{
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    uint32_t clear = ~kSlotMask;
+    asm volatile("" : "+v"(clear));              // (a register: the instruction takes one scalar operand, the slot)
+    bf16x8_t x[4][4];                        // points 16 q + c, dims [32 ks + 8 g, +8)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int t = min(first + 16 * q + c, last);
+        const uint4* xp = reinterpret_cast<const uint4*>(Xu + (long long)t * 256) + g;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) x[q][ks] = __builtin_bit_cast(bf16x8_t, xp[4 * ks]);
+    }
+    float best[4], second[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) best[q] = second[q] = -INFINITY;
+    // |x|^2 only scales the margin; lane = point after the reduction
+    float n2[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        n2[q] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const uint4 w = __builtin_bit_cast(uint4, x[q][ks]);
+            n2[q] = dot2_bf16(w.x, w.x, n2[q]);
+            n2[q] = dot2_bf16(w.y, w.y, n2[q]);
+            n2[q] = dot2_bf16(w.z, w.z, n2[q]);
+            n2[q] = dot2_bf16(w.w, w.w, n2[q]);
+        }
+    }
+    auto one_tile = [&](const uint32_t (&fr)[4], uint32_t ci_at, auto step, uint32_t slot) {
+        constexpr int kStep = decltype(step)::value;
+        bf16x8_t f[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<lds_frag*>((uintptr_t)(fr[ks] + kStep * kRowTile * 256));
+        const f32x4_t ci = *reinterpret_cast<lds_four*>((uintptr_t)(ci_at + kStep * kRowTile * 4));
+        f32x4_t acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0], x[q][0], ci, 0, 0, 0);
+#pragma unroll
+        for (int ks = 1; ks < 4; ++ks)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks], x[q][ks], acc[q], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = with_slot(acc[q][i], clear, slot + 4u * kStep + i);
+            // best and second best of the running pair and four scores: five instructions
+            const float m0 = __builtin_amdgcn_fmed3f(best[q], v[0], v[1]);
+            best[q] = fmaxf(fmaxf(v[0], v[1]), best[q]);
+            const float m1 = __builtin_amdgcn_fmed3f(best[q], v[2], v[3]);
+            best[q] = fmaxf(fmaxf(v[2], v[3]), best[q]);
+            second[q] = fmaxf(fmaxf(m0, m1), second[q]);
+        }
+    };
+    auto tiles = [&](int ta, int tb) {
+        uint32_t fr[4], ci_at = lds0 + (uint32_t)(k_cap * 256 + (ta * kRowTile + 4 * g) * 4);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            fr[ks] = lds0 + (uint32_t)(ta * kRowTile * 256 + c * 256 + ((g ^ c) & 3) * 16 + ((64 * ks) ^ ((c >> 2) * 64)));
+        uint32_t slot = 0;
+        int t = ta;
+#pragma unroll 1
+        for (; t + 4 <= tb; t += 4) {
+            one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
+            one_tile(fr, ci_at, std::integral_constant<int, 1>{}, slot);
+            one_tile(fr, ci_at, std::integral_constant<int, 2>{}, slot);
+            one_tile(fr, ci_at, std::integral_constant<int, 3>{}, slot);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) fr[ks] += 4 * kRowTile * 256;
+            ci_at += 4 * kRowTile * 4;
+            slot += 16u;
+        }
+#pragma unroll 1
+        for (; t < tb; ++t) {
+            one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) fr[ks] += kRowTile * 256;
+            ci_at += kRowTile * 4;
+            slot += 4u;
+        }
+    };
+    tiles(0, min(ntiles, kHalfTiles));
+    uint32_t from[4] = {0u, 0u, 0u, 0u};
+    if (ntiles > kHalfTiles) {
+        float first_half[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) first_half[q] = best[q];
+        tiles(kHalfTiles, ntiles);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) from[q] = best[q] != first_half[q] ? 4u : 0u;
+    }
+    // lane (g, c) ends up with point 16 g + c = lane: halves first (points q and q + 2), then rows
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        float fl = __uint_as_float(from[q]), fh = __uint_as_float(from[q + 2]);
+        swap_halves(best[q], best[q + 2]);
+        swap_halves(second[q], second[q + 2]);
+        swap_halves(n2[q], n2[q + 2]);
+        swap_halves(fl, fh);
+        from[q] = __float_as_uint(fl);
+        merge_pair(best[q], second[q], from[q], best[q + 2], second[q + 2], __float_as_uint(fh), 2u);
+        n2[q] += n2[q + 2];
+    }
+    {
+        float fl = __uint_as_float(from[0]), fh = __uint_as_float(from[1]);
+        swap_rows(best[0], best[1]);
+        swap_rows(second[0], second[1]);
+        swap_rows(n2[0], n2[1]);
+        swap_rows(fl, fh);
+        from[0] = __float_as_uint(fl);
+        merge_pair(best[0], second[0], from[0], best[1], second[1], __float_as_uint(fh), 1u);
+        n2[0] += n2[1];
+    }
+    const uint32_t slot = __float_as_uint(best[0]) & kSlotMask;
+    const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
+    const float margin = kMarginScale * fmaxf(n2[0], c2max);
+    // (written so that a point without any comparable score also goes to the exact pass)
+    return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin)};
+}
+
+// One 16-byte piece of a centroid row (16 lanes per row) to its place in LDS; the lane with the first piece writes
+// -|c|^2/2.  Returns |c|^2.
+__device__ __forceinline__ float place_centroid(unsigned char* rows_lds, float* c_init, int row, int seg, uint4 w, bool exists)
+{
+    *reinterpret_cast<uint4*>(rows_lds + row * 256 + ((seg ^ row) & 15) * 16) = w;
+    float s = dot2_bf16(w.x, w.x, 0.f);
+    s = dot2_bf16(w.y, w.y, s);
+    s = dot2_bf16(w.z, w.z, s);
+    s = dot2_bf16(w.w, w.w, s);
+    s = sum8(s);
+    s += dpp_f32<kDppMirror>(s);         // the other 8 lanes of the row of 16
+    if (seg == 0) c_init[row] = exists ? -0.5f * s : kNoCentroid;
+    return s;
+}
+
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                                     const int32_t* __restrict__ blocks,
@@ -319,7 +463,6 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     if (chunk0 >= chunk1) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, g = lane >> 4;
     const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);
     float* c_init = reinterpret_cast<float*>(rows_lds + k_cap * 256);
 
@@ -333,15 +476,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
             const bool exists = k0 + row < k1;
             uint4 w = make_uint4(0, 0, 0, 0);
             if (exists) w = reinterpret_cast<const uint4*>(Cu + (long long)(k0 + row) * kHeadDim)[seg];
-            *reinterpret_cast<uint4*>(rows_lds + row * 256 + ((seg ^ row) & 15) * 16) = w;
-            float s = dot2_bf16(w.x, w.x, 0.f);
-            s = dot2_bf16(w.y, w.y, s);
-            s = dot2_bf16(w.z, w.z, s);
-            s = dot2_bf16(w.w, w.w, s);
-            s = sum8(s);
-            s += dpp_f32<kDppMirror>(s);         // the other 8 lanes of the row of 16
-            c2max = fmaxf(c2max, s);
-            if (seg == 0) c_init[row] = exists ? -0.5f * s : kNoCentroid;
+            c2max = fmaxf(c2max, place_centroid(rows_lds, c_init, row, seg, w, exists));
         }
     }
     c2max = wave_max_f32(c2max);
@@ -355,129 +490,13 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     int32_t* list_u = amb_list + u * list_stride;
     int32_t* cnt_ub = amb_cnt + u * cnt_stride + b;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
-    uint32_t clear = ~kSlotMask;
-    asm volatile("" : "+v"(clear));              // (a register: the instruction takes one scalar operand, the slot)
 #pragma unroll 1
     for (int chunk = chunk0 + wave; chunk < chunk1; chunk += kW) {
-        bf16x8_t x[4][4];                        // points 16 q + c, dims [32 ks + 8 g, +8)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int t = min(x0 + chunk * 64 + 16 * q + c, x1 - 1);
-            const uint4* xp = reinterpret_cast<const uint4*>(Xu + (long long)t * 256) + g;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) x[q][ks] = __builtin_bit_cast(bf16x8_t, xp[4 * ks]);
-        }
-        float best[4], second[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) best[q] = second[q] = -INFINITY;
-        // |x|^2 only scales the margin; lane = point after the reduction
-        float n2[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            n2[q] = 0.f;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const uint4 w = __builtin_bit_cast(uint4, x[q][ks]);
-                n2[q] = dot2_bf16(w.x, w.x, n2[q]);
-                n2[q] = dot2_bf16(w.y, w.y, n2[q]);
-                n2[q] = dot2_bf16(w.z, w.z, n2[q]);
-                n2[q] = dot2_bf16(w.w, w.w, n2[q]);
-            }
-        }
-        auto one_tile = [&](const uint32_t (&fr)[4], uint32_t ci_at, auto step, uint32_t slot) {
-            constexpr int kStep = decltype(step)::value;
-            bf16x8_t f[4];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<lds_frag*>((uintptr_t)(fr[ks] + kStep * kRowTile * 256));
-            const f32x4_t ci = *reinterpret_cast<lds_four*>((uintptr_t)(ci_at + kStep * kRowTile * 4));
-            f32x4_t acc[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0], x[q][0], ci, 0, 0, 0);
-#pragma unroll
-            for (int ks = 1; ks < 4; ++ks)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks], x[q][ks], acc[q], 0, 0, 0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = with_slot(acc[q][i], clear, slot + 4u * kStep + i);
-                // best and second best of the running pair and four scores: five instructions
-                const float m0 = __builtin_amdgcn_fmed3f(best[q], v[0], v[1]);
-                best[q] = fmaxf(fmaxf(v[0], v[1]), best[q]);
-                const float m1 = __builtin_amdgcn_fmed3f(best[q], v[2], v[3]);
-                best[q] = fmaxf(fmaxf(v[2], v[3]), best[q]);
-                second[q] = fmaxf(fmaxf(m0, m1), second[q]);
-            }
-        };
-        auto tiles = [&](int ta, int tb) {
-            uint32_t fr[4], ci_at = lds0 + (uint32_t)(k_cap * 256 + (ta * kRowTile + 4 * g) * 4);
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                fr[ks] = lds0 + (uint32_t)(ta * kRowTile * 256 + c * 256 + ((g ^ c) & 3) * 16 + ((64 * ks) ^ ((c >> 2) * 64)));
-            uint32_t slot = 0;
-            int t = ta;
-#pragma unroll 1
-            for (; t + 4 <= tb; t += 4) {
-                one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
-                one_tile(fr, ci_at, std::integral_constant<int, 1>{}, slot);
-                one_tile(fr, ci_at, std::integral_constant<int, 2>{}, slot);
-                one_tile(fr, ci_at, std::integral_constant<int, 3>{}, slot);
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) fr[ks] += 4 * kRowTile * 256;
-                ci_at += 4 * kRowTile * 4;
-                slot += 16u;
-            }
-#pragma unroll 1
-            for (; t < tb; ++t) {
-                one_tile(fr, ci_at, std::integral_constant<int, 0>{}, slot);
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) fr[ks] += kRowTile * 256;
-                ci_at += kRowTile * 4;
-                slot += 4u;
-            }
-        };
-        tiles(0, min(ntiles, kHalfTiles));
-        uint32_t from[4] = {0u, 0u, 0u, 0u};
-        if (ntiles > kHalfTiles) {
-            float first_half[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) first_half[q] = best[q];
-            tiles(kHalfTiles, ntiles);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) from[q] = best[q] != first_half[q] ? 4u : 0u;
-        }
-        const int t_first = x0 + chunk * 64;
-        // lane (g, c) ends up with point 16 g + c = lane: halves first (points q and q + 2), then rows
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            float fl = __uint_as_float(from[q]), fh = __uint_as_float(from[q + 2]);
-            swap_halves(best[q], best[q + 2]);
-            swap_halves(second[q], second[q + 2]);
-            swap_halves(n2[q], n2[q + 2]);
-            swap_halves(fl, fh);
-            from[q] = __float_as_uint(fl);
-            merge_pair(best[q], second[q], from[q], best[q + 2], second[q + 2], __float_as_uint(fh), 2u);
-            n2[q] += n2[q + 2];
-        }
-        {
-            float fl = __uint_as_float(from[0]), fh = __uint_as_float(from[1]);
-            swap_rows(best[0], best[1]);
-            swap_rows(second[0], second[1]);
-            swap_rows(n2[0], n2[1]);
-            swap_rows(fl, fh);
-            from[0] = __float_as_uint(fl);
-            merge_pair(best[0], second[0], from[0], best[1], second[1], __float_as_uint(fh), 1u);
-            n2[0] += n2[1];
-        }
-        const int t = t_first + lane;
+        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, k_cap, ntiles, c2max);
+        const int t = x0 + chunk * 64 + lane;
         if (t < x1) {
-            const uint32_t slot = __float_as_uint(best[0]) & kSlotMask;
-            const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
-            assign_u[t] = k0 + tile * kRowTile + 4 * row_g + (int)(slot & 3u);
-            const float margin = kMarginScale * fmaxf(n2[0], c2max);
-            // (written so that a point without any comparable score also goes to the exact pass)
-            if (!(best[0] - second[0] > margin)) {
+            assign_u[t] = k0 + r.j;
+            if (r.near) {
                 // (through LDS: a global counter's answer would have to wait for the points under way)
                 const int pos = atomicAdd(&near_n, 1);
                 if (pos < kNearCap) near_list[pos] = t;
@@ -519,6 +538,198 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------------------------
+// The coarse level of a range in one launch (Sec. 3.4): all Lloyd iterations over a block's fine centroids, the new
+// order of the fine clusters, and the rows of the centroid tables that go with it.  One workgroup per (block, unit): a
+// block has some hundred points and some tens of centroids, which fit one compute unit, and every step of an iteration is a
+// few microseconds of latency when it is a launch of its own (assignment, exact pass, member lists, means: 30 us for 32
+// (block, unit) pairs, times ten iterations).  Here an iteration is five barriers; the decisions and sums are those of the
+// separate kernels: near ties decided in fp64 as defined, members summed in ascending order in fp64, one rounding.
+// Bound by the latency of one pair's chain, a member row from memory being its longest link (hence the sixteen at once):
+// 10.4 us an iteration for 32 pairs of 256 points and 16 centroids.  A bound of two waves a SIMD does away with the spills
+// and is slower (1000 against 780 us for 2048 pairs).  Build of one 32K prompt: 1214 -> 1095 us; sixteen of 128K: 29.1 ->
+// 28.4 ms; refresh of eight 8K contexts: 970 -> 940 us.
+// ------------------------------------------------------------------------------------------------
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kLevelMaxK = 256;
+
+// |x - c|^2 in fp64 as in exact_distance, the centroid in LDS
+__device__ __forceinline__ double exact_distance_lds(const uint4* xrow, const unsigned char* rows_lds, int j)
+{
+    double s = 0.0;
+#pragma unroll 2
+    for (int i = 0; i < 16; ++i) {
+        const uint4 xw = xrow[i], cw = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((i ^ j) & 15) * 16);
+        const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w}, x4[4] = {xw.x, xw.y, xw.z, xw.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double d0 = __dsub_rn((double)bf16lo_to_f32(x4[e]), (double)bf16lo_to_f32(c4[e]));
+            const double d1 = __dsub_rn((double)bf16hi_to_f32(x4[e]), (double)bf16hi_to_f32(c4[e]));
+            s = __dadd_rn(s, __dmul_rn(d0, d0));
+            s = __dadd_rn(s, __dmul_rn(d1, d1));
+        }
+    }
+    return s;
+}
+
+template <int kW>
+__global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
+{
+    extern __shared__ __align__(256) unsigned char rows_lds[];   // [k_cap][256 bytes], [k_cap] -|c|^2/2, then:
+    float* c_init = reinterpret_cast<float*>(rows_lds + p.k_cap * 256);
+    uint16_t* asg = reinterpret_cast<uint16_t*>(c_init + p.k_cap);    // [n_cap] cluster of each point
+    uint16_t* order = asg + p.n_cap;                                  // [n_cap] points, cluster after cluster
+    uint16_t* near_pts = order + p.n_cap;                             // [n_cap]
+    __shared__ int count[kLevelMaxK], near_n;
+    __shared__ float wave_c2max[2][kW];
+    const int b = blockIdx.x, u = blockIdx.y;
+    const int x0 = p.blocks[4 * b + 0], n = p.blocks[4 * b + 1] - x0, k0 = p.blocks[4 * b + 2], k = p.blocks[4 * b + 3] - k0;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(p.X) + (long long)u * p.x_unit_rows * 256;
+    const uint32_t* Xw = reinterpret_cast<const uint32_t*>(Xu) + (long long)x0 * 64;
+    uint4* Ku = reinterpret_cast<uint4*>(p.Kc) + (long long)u * p.tab_rows * 16;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
+    const int ntiles = (k + kRowTile - 1) / kRowTile;
+    const int chunks = (n + 63) / 64;
+
+    // ---- first centroids: the stored ones of old clusters, seeds for the others ----
+    float c2max = 0.f;
+    for (int e = tid; e < ntiles * kRowTile * 16; e += 64 * kW) {
+        const int row = e >> 4, seg = e & 15, j = k0 + row;
+        uint4 w = make_uint4(0, 0, 0, 0);
+        if (row < k) {
+            if (j < p.old_end) w = Ku[(long long)(p.fcap + j) * 16 + seg];
+            else w = reinterpret_cast<const uint4*>(Xu)[(long long)((p.seed_x0 < 0 ? x0 : p.seed_x0) + p.seeds[u * p.seed_stride + j]) * 16 + seg];
+        }
+        c2max = fmaxf(c2max, place_centroid(rows_lds, c_init, row, seg, w, row < k));
+    }
+    c2max = wave_max_f32(c2max);
+    if (lane == 0) wave_c2max[0][wave] = c2max;
+
+    for (int it = 0; it < p.iters; ++it) {
+        if (tid == 0) near_n = 0;
+        __syncthreads();
+        c2max = 0.f;
+#pragma unroll
+        for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[it & 1][w]);
+        // ---- nearest centroid of every point ----
+        for (int ch = wave; ch < chunks; ch += kW) {
+            const Nearest r = nearest_of_chunk(Xu, x0 + ch * 64, x0 + n - 1, lds0, p.k_cap, ntiles, c2max);
+            const int t = ch * 64 + lane;
+            if (t < n) {
+                asg[t] = (uint16_t)min(r.j, k - 1);
+                if (r.near) near_pts[atomicAdd(&near_n, 1)] = (uint16_t)t;
+            }
+        }
+        __syncthreads();
+        // ---- near ties, one wave per point: smallest exact distance, lowest index among equals ----
+        for (int e = wave; e < near_n; e += kW) {
+            const int t = near_pts[e];
+            const uint4* xrow = reinterpret_cast<const uint4*>(Xu) + (long long)(x0 + t) * 16;
+            double bd = INFINITY;
+            int bj = 0;
+            for (int j = lane; j < k; j += 64) {
+                const double d = exact_distance_lds(xrow, rows_lds, j);
+                if (d < bd) { bd = d; bj = j; }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const double od = __shfl_xor(bd, off, 64);
+                const int oj = __shfl_xor(bj, off, 64);
+                if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
+            }
+            if (lane == 0) asg[t] = (uint16_t)bj;
+        }
+        __syncthreads();
+        // ---- member lists: one wave per cluster finds its points 64 at a time ----
+        for (int j = wave; j < k; j += kW) {
+            int m = 0;
+            for (int ch = 0; ch < chunks; ++ch) {
+                const int t = ch * 64 + lane;
+                m += __popcll(__ballot(t < n && asg[t] == j));
+            }
+            if (lane == 0) count[j] = m;
+        }
+        __syncthreads();
+        float next_c2max = 0.f;
+        for (int j = wave; j < k; j += kW) {
+            int pos = 0;                             // points of the clusters before this one
+            for (int i = lane; i < j; i += 64) pos += count[i];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) pos += __shfl_xor(pos, off, 64);
+            const int m = count[j];
+            // this wave places the cluster's points, in ascending order, and sums their rows
+            const int p0 = pos;
+            for (int ch = 0; ch < chunks; ++ch) {
+                const int t = ch * 64 + lane;
+                const unsigned long long mine = __ballot(t < n && asg[t] == j);
+                if ((mine >> lane) & 1ull) order[pos + __popcll(mine & ((1ull << lane) - 1ull))] = (uint16_t)t;
+                pos += __popcll(mine);
+            }
+            wave_lds_sync();
+            double a0 = 0.0, a1 = 0.0;
+            for (int base = 0; base < m; base += 64) {
+                const int nm = min(m - base, 64);
+                const int member = lane < nm ? order[p0 + base + lane] : 0;
+                constexpr int kBatch = 16;          // rows in flight (a cluster's time is its number of trips to memory)
+                for (int q0 = 0; q0 < nm; q0 += kBatch) {
+                    uint32_t w[kBatch];
+#pragma unroll
+                    for (int q = 0; q < kBatch; ++q) {
+                        const long long r = __builtin_amdgcn_readlane(member, (q0 + q) & 63);
+                        w[q] = (q0 + q < nm) ? Xw[r * 64 + lane] : 0u;
+                    }
+#pragma unroll
+                    for (int q = 0; q < kBatch; ++q) {
+                        if (q0 + q < nm) {
+                            a0 += (double)bf16lo_to_f32(w[q]);
+                            a1 += (double)bf16hi_to_f32(w[q]);
+                        }
+                    }
+                }
+            }
+            // new centroid (an empty cluster keeps its own), its place in LDS: dims 2 lane, 2 lane + 1
+            uint32_t* at = reinterpret_cast<uint32_t*>(rows_lds + j * 256 + (((lane >> 2) ^ j) & 15) * 16) + (lane & 3);
+            uint32_t row = *at;
+            if (m > 0) {
+                const double den = (double)m;
+                row = (uint32_t)f64_to_bf16_rne(a0 / den) | ((uint32_t)f64_to_bf16_rne(a1 / den) << 16);
+                *at = row;
+            }
+            float s = dot2_bf16(row, row, 0.f);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (lane == 0) c_init[j] = -0.5f * s;
+            next_c2max = fmaxf(next_c2max, s);
+        }
+        if (lane == 0) wave_c2max[(it + 1) & 1][wave] = next_c2max;
+    }
+    __syncthreads();
+    // ---- the new order: list position -> old fine id, old -> new id, parents, and the rows of the tables ----
+    const int at0 = x0 - p.f0;
+    for (int i = tid; i < n; i += 64 * kW) {
+        const int t = order[i];
+        p.plist[u * p.list_stride + at0 + i] = x0 + t;
+        p.newid[u * p.list_stride + x0 + t] = x0 + i;
+        p.cof[u * p.list_stride + x0 + i] = k0 + asg[t];
+    }
+    for (int e = tid; e < n * 16; e += 64 * kW) {
+        const int i = e >> 4, seg = e & 15;
+        Ku[(long long)(x0 + i) * 16 + seg] = reinterpret_cast<const uint4*>(Xu)[(long long)(x0 + order[i]) * 16 + seg];
+    }
+    for (int e = tid; e < k * 16; e += 64 * kW) {
+        const int j = e >> 4, seg = e & 15;
+        Ku[(long long)(p.fcap + k0 + j) * 16 + seg] = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((seg ^ j) & 15) * 16);
+    }
+}
+
 // Stage 2.  One wave per listed point, three passes over the block's centroids:
 //   1. fp32 scores s_j = x.c_j - |c_j|^2/2 again (8 lanes per centroid, 16 dims each, sequential
 //      fused multiply-adds: error far below the bound of stage 1), their maximum and max_j |c_j|^2;
@@ -533,13 +744,6 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
 // dispatch order and spread over the whole chip.
 constexpr int kCandCap = 64;
 constexpr int kScoreCache = 2048;     // scores of pass 1 kept in LDS for pass 2 when the block has no more centroids
-
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // |x - c|^2 in fp64, dims in index order, rounding after every operation
 __device__ __forceinline__ double exact_distance(const uint16_t* xrow /*LDS*/, const uint16_t* crow /*global*/)
@@ -696,6 +900,44 @@ __global__ __launch_bounds__(256) void assign_recheck_kernel(const uint16_t* __r
 }
 
 }  // namespace
+
+static size_t coarse_level_smem(int max_pts, int max_k)
+{
+    const size_t k_cap = (size_t)(max_k + kRowTile - 1) / kRowTile * kRowTile, n_cap = (size_t)(max_pts + 3) / 4 * 4;
+    return k_cap * 260 + n_cap * 6;
+}
+
+// (sixteen chunks of points: beyond that one workgroup per block takes longer than the separate launches)
+bool coarse_level_fits(int max_pts, int max_k)
+{
+    return max_pts >= 1 && max_pts <= 1024 && max_k >= 1 && max_k <= kLevelMaxK;
+}
+
+template <int kW>
+static hipError_t launch_coarse_waves(const CoarseLevel& p, int nb, int U, size_t smem, hipStream_t s)
+{
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&coarse_level_kernel<kW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)coarse_level_smem(1024, kLevelMaxK));
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL(coarse_level_kernel<kW>, dim3(nb, U), dim3(64 * kW), smem, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int max_k, hipStream_t s)
+{
+    if (nb <= 0 || U <= 0) return hipSuccess;
+    if (!coarse_level_fits(max_pts, max_k) || p.iters < 1) return hipErrorInvalidValue;
+    p.k_cap = (max_k + kRowTile - 1) / kRowTile * kRowTile;
+    p.n_cap = (max_pts + 3) / 4 * 4;
+    // Sixteen waves where every pair has a compute unit of its own (a pair's time is what counts then: 104 against 132 us
+    // for 32 pairs and ten iterations), else two workgroups of eight a compute unit (755 against 890 us for 2048 pairs).
+    const size_t smem = coarse_level_smem(max_pts, max_k);
+    return (long long)nb * U <= 256 ? launch_coarse_waves<16>(p, nb, U, smem, s) : launch_coarse_waves<8>(p, nb, U, smem, s);
+}
 
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,

@@ -384,7 +384,9 @@ namespace {
 // After the fine level of a range has its working centroids in km_Cf[f0,f1) and the assignment of
 // its points in km_assign (old numbering), and -- two levels -- the coarse working centroids in
 // km_Cc[c0,c1): run the coarse Lloyd iterations (coarse_iters >= 1), renumber, and finalize.
-mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, bool init_coarse_from_seeds,
+// First coarse centroids: the stored key centroids of the clusters below old_c_end, for the others the fine
+// centroids (seed_f0 < 0 ? block's first : seed_f0) + km_seed_c.
+mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int old_c_end, int seed_f0,
                               bool fine_keys_are_means, int max_kf, int max_kc, hipStream_t s)
 {
     const int U = ctx->U;
@@ -393,15 +395,32 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, boo
     const int kf = r.f1 - r.f0, kc = r.c1 - r.c0;
     const int32_t* bdev_c = ctx->blocks_dev + 8 * (size_t)ctx->max_blocks;
     const long long Fcap = ctx->Fcap, Ccap1 = std::max(ctx->Ccap, 1);
-    if (two) {
+    if (two && coarse_level_fits(max_kf, max_kc)) {
+        CoarseLevel cl{};
+        cl.X = ctx->km_Cf; cl.x_unit_rows = Fcap; cl.blocks = bdev_c; cl.f0 = r.f0; cl.iters = coarse_iters;
+        cl.old_end = old_c_end; cl.seeds = ctx->km_seed_c; cl.seed_stride = Ccap1; cl.seed_x0 = seed_f0;
+        cl.plist = ctx->km_plist; cl.newid = ctx->km_newid; cl.cof = ctx->cof; cl.list_stride = Fcap;
+        cl.Kc = ctx->Kc; cl.tab_rows = ctx->tab_rows; cl.fcap = ctx->Fcap;
+        MP_HIPC(launch_coarse_level(cl, nb, U, max_kf, max_kc, s));
+        hipLaunchKernelGGL(map_ids_kernel, dim3(blocks_for(r.n_pts, 256), U), dim3(256), 0, s, ctx->km_assign,
+                           (long long)ctx->Ncap, 0, r.n_pts, ctx->km_newid, Fcap, ctx->km_assign, (long long)ctx->Ncap, 0);
+        MP_HIPC(hipGetLastError());
+    } else if (two) {
+        // (more clusters than one workgroup takes: a launch per step)
+        if (old_c_end > r.c0) {
+            hipLaunchKernelGGL(gather1_rows_kernel, dim3(blocks_for((long long)(old_c_end - r.c0) * 16, 256), U), dim3(256), 0, s,
+                               (const uint4*)ctx->Kc, ctx->tab_rows, ctx->Fcap + r.c0, nullptr, 0, 0, old_c_end - r.c0,
+                               (uint4*)ctx->km_Cc, Ccap1, r.c0);
+            MP_HIPC(hipGetLastError());
+        }
         Problem pc{};
         pc.X = ctx->km_Cf; pc.x_unit_rows = Fcap; pc.n_points = r.f1; pc.p_first = r.f0; pc.blocks_dev = bdev_c; pc.nb = nb;
         pc.max_pts = max_kf; pc.max_k = max_kc; pc.k_total = r.c1; pc.k_first = r.c0; pc.C = ctx->km_Cc; pc.c_unit_rows = Ccap1;
         pc.assign = ctx->km_parent; pc.assign_stride = Fcap; pc.list = ctx->km_plist; pc.list_stride = Fcap;
         pc.cnt = ctx->km_cnt; pc.start = ctx->km_start; pc.cnt_stride = ctx->tab_rows;
-        if (init_coarse_from_seeds) {
-            hipLaunchKernelGGL(init_centroids_kernel, dim3(nb, U), dim3(256), 0, s, pc.X, pc.x_unit_rows, pc.blocks_dev,
-                               ctx->km_seed_c, Ccap1, pc.C, pc.c_unit_rows);
+        if (old_c_end < r.c1) {      // (an update's descriptor of its new clusters sits in the scratch slot)
+            hipLaunchKernelGGL(init_centroids_kernel, dim3(seed_f0 < 0 ? nb : 1, U), dim3(256), 0, s, pc.X, pc.x_unit_rows,
+                               seed_f0 < 0 ? pc.blocks_dev : ctx->blocks_dev + 8, ctx->km_seed_c, Ccap1, pc.C, pc.c_unit_rows);
             MP_HIPC(hipGetLastError());
         }
         for (int it = 0; it < coarse_iters; ++it) {
@@ -458,7 +477,7 @@ mp_status cluster_range(mp_ctx* ctx, const Range& r, int iters, hipStream_t s)
         const mp_status st = lloyd_iteration(ctx, pf, it == iters - 1, s);
         if (st != MP_OK) return st;
     }
-    return coarse_and_finalize(ctx, r, iters, true, iters > 0, max_kf, max_kc, s);
+    return coarse_and_finalize(ctx, r, iters, r.c0, -1, iters > 0, max_kf, max_kc, s);
 }
 
 }  // namespace
@@ -706,18 +725,7 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
         if (st != MP_OK) return st;
     }
     // ---- coarse level: stored coarse key centroids, plus seeds taken from the new fine centroids ----
-    if (two) {
-        hipLaunchKernelGGL(gather1_rows_kernel, dim3(blocks_for((long long)kc_old * 16, 256), U), dim3(256), 0, s,
-                           (const uint4*)ctx->Kc, ctx->tab_rows, ctx->Fcap + c0, nullptr, 0, 0, kc_old, (uint4*)ctx->km_Cc,
-                           Ccap1, c0);
-        MP_HIPC(hipGetLastError());
-        if (n_new_coarse > 0) {
-            hipLaunchKernelGGL(init_centroids_kernel, dim3(1, U), dim3(256), 0, s, ctx->km_Cf, Fcap, ctx->blocks_dev + 8,
-                               ctx->km_seed_c, Ccap1, ctx->km_Cc, Ccap1);
-            MP_HIPC(hipGetLastError());
-        }
-    }
-    mp_status st = coarse_and_finalize(ctx, r, std::max(1, refine_iters), false, refine_iters > 0, max_kf, max_kc, s);
+    mp_status st = coarse_and_finalize(ctx, r, std::max(1, refine_iters), lb.c1, lb.f1, refine_iters > 0, max_kf, max_kc, s);
     if (st != MP_OK) return st;
     lb.t1 = t0 + nb; lb.f1 = f1; lb.c1 = c1;
     ctx->blocks.back() = lb;

@@ -141,6 +141,33 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,
                          long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* amb_cnt,
                          int32_t* amb_cnt_next, int cnt_stride, hipStream_t s);
+// The coarse level of a range of blocks in one launch: `iters` Lloyd iterations over the fine working centroids X of each
+// block, then the fine clusters in their new order.  blocks: int32 [nb][4] = {first fine id, end, first coarse id, end}.
+struct CoarseLevel {
+    const uint16_t* X;           // bf16 [U, x_unit_rows, 128] by fine id
+    long long x_unit_rows;
+    const int32_t* blocks;
+    int f0;                      // first fine id of the range (list positions count from it)
+    int iters;
+    // first centroids: cluster j < old_end starts from its stored key centroid, any other from point
+    // (seed_x0 < 0 ? the block's first : seed_x0) + seeds[u][j]
+    int old_end;
+    const int32_t* seeds;        // [U, seed_stride]
+    long long seed_stride;
+    int seed_x0;
+    // results: plist[u][position] = old fine id, newid[u][old fine id], cof[u][new fine id] (all of list_stride), and
+    // in Kc the working centroids: fine rows in the new order, coarse rows from row fcap
+    int32_t* plist;
+    int32_t* newid;
+    int32_t* cof;
+    long long list_stride;
+    uint16_t* Kc;                // bf16 [U, tab_rows, 128]
+    long long tab_rows;
+    int fcap;
+    int k_cap, n_cap;            // (set by the launch)
+};
+bool coarse_level_fits(int max_pts, int max_k);
+hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int max_k, hipStream_t s);
 hipError_t launch_histogram(const int32_t* ids, long long ids_stride, int n, int U, int32_t* cnt,
                             long long cnt_stride, hipStream_t s);
 hipError_t launch_exclusive_scan(const int32_t* cnt, long long cnt_stride, int k, int U, int32_t* start,

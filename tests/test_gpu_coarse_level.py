@@ -1,0 +1,28 @@
+"""GPU parity of the coarse level in one launch at its edges: chunks of 64 points, tiles of 16 centroids, slots of sixteen
+tiles, its limits of 1024 points and 256 centroids a block (one more takes the launch-per-step path), sixteen waves up to
+256 (block, unit) pairs and eight beyond, and degenerate inputs.  Every result is bit-identical to the oracle's."""
+import pytest
+
+from tests.test_gpu_kmeans import _run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nf,nc", [(1, 1), (2, 1), (63, 15), (64, 16), (65, 17), (129, 64), (520, 255), (530, 256),
+                                   (530, 257), (1024, 16), (1025, 16)])
+def test_edges(nf, nc):
+    print(f"nf={nf} nc={nc}", flush=True)
+    ctx, _, _ = _run_case(1, 2, 2, nf + 300, max(2, nf // 3), 2, nf, nc, 0, 0, iters=3, seed=500 + nf + nc)
+    ctx.close()
+
+
+def test_more_pairs_than_compute_units():
+    ctx, _, _ = _run_case(9, 4, 4, 1100, 20, 2, 130, 20, 128, 64, iters=2, seed=51)
+    assert 36 * ctx.mp_get_sizes()["n_blocks"] > 256
+    ctx.close()
+
+
+@pytest.mark.parametrize("distinct", [1, 9])
+def test_every_point_a_near_tie(distinct):
+    ctx, _, _ = _run_case(1, 2, 2, 600, 4, 2, 200, 40, 0, 0, iters=3, seed=52, distinct_rows=distinct)
+    ctx.close()
