@@ -20,7 +20,7 @@
 //   2. Every other point (near-equal or equal distances) goes onto a per-block list and
 //      assign_recheck_kernel decides it exactly as defined above: it collects the centroids whose
 //      score is within the same margin of the best one and evaluates their distances in fp64
-//      without fused multiply-adds.
+//      without fused multiply-adds.  (Kernels that hold a block's centroids do this themselves.)
 #include <algorithm>
 #include <type_traits>
 
@@ -442,19 +442,130 @@ __device__ __forceinline__ float place_centroid(unsigned char* rows_lds, float* 
     return s;
 }
 
+// |x - c|^2 in fp64 as in exact_distance, the centroid in LDS
+__device__ __forceinline__ double exact_distance_lds(const uint4* xrow, const unsigned char* rows_lds, int j)
+{
+    double s = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < 16; ++i) {
+        const uint4 xw = xrow[i], cw = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((i ^ j) & 15) * 16);
+        const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w}, x4[4] = {xw.x, xw.y, xw.z, xw.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double d0 = __dsub_rn((double)bf16lo_to_f32(x4[e]), (double)bf16lo_to_f32(c4[e]));
+            const double d1 = __dsub_rn((double)bf16hi_to_f32(x4[e]), (double)bf16hi_to_f32(c4[e]));
+            s = __dadd_rn(s, __dmul_rn(d0, d0));
+            s = __dadd_rn(s, __dmul_rn(d1, d1));
+        }
+    }
+    return s;
+}
+
+// (counted anew: as the thread's index it would be kept in a register through the loop before, which has none left)
+__device__ __forceinline__ int lane_id()
+{
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+}
+
+// The near ties decided exactly, sixteen points a wave: lane (g, c) has point t of column c (the same in its four lanes)
+// and rows 4 g + i of every tile.  Scores again, their maximum, and every centroid within the margin of it is a
+// candidate, a bit in its lane's mask: the nearest centroid in exact arithmetic, and everything tied with it, is among
+// them.  Then the candidates' distances as defined, one of every lane at a time; smallest distance, equal distances ->
+// lowest index.  Returns it in all four lanes.
+// A launch of its own fetched the 64 KiB of a block's centroids for every point: 14.6 us for 32 blocks of 8192 points,
+// 140 us for 2048.  Here it adds 9 us to the first's assignment (the longest chain: four tiles' products, compared, four
+// more, then two or three distances of 2 us) and nothing measurable to the second's, whose waves fill each other's gaps.
+__device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, int k_cap,
+                                             int k, float c2max)
+{
+    const int lane = lane_id(), c = lane & 15, g = lane >> 4;
+    const int ntiles = (k + kRowTile - 1) / kRowTile;
+    const uint4* xrow = reinterpret_cast<const uint4*>(Xu + (long long)t * 256);
+    bf16x8_t x[4];
+    float n2 = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const uint4 w = xrow[4 * ks + g];
+        x[ks] = __builtin_bit_cast(bf16x8_t, w);
+        n2 = dot2_bf16(w.x, w.x, n2);
+        n2 = dot2_bf16(w.y, w.y, n2);
+        n2 = dot2_bf16(w.z, w.z, n2);
+        n2 = dot2_bf16(w.w, w.w, n2);
+    }
+    n2 += __shfl_xor(n2, 16, 64);
+    n2 += __shfl_xor(n2, 32, 64);
+    const uint32_t at = lds0 + (uint32_t)(c * 256 + ((g ^ c) & 3) * 16), turn = (uint32_t)((c >> 2) * 64);
+    auto scores = [&](int tile) {
+        f32x4_t acc = *reinterpret_cast<lds_four*>((uintptr_t)(lds0 + (uint32_t)(k_cap * 256 + (tile * kRowTile + 4 * g) * 4)));
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const bf16x8_t f = *reinterpret_cast<lds_frag*>((uintptr_t)(at + (uint32_t)(tile * kRowTile * 256) + ((uint32_t)(64 * ks) ^ turn)));
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, x[ks], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+    float best = -INFINITY;
+    for (int tile = 0; tile < ntiles; tile += 4) {
+        f32x4_t s[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = scores(min(tile + r, ntiles - 1));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) best = fmaxf(best, fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3])));
+    }
+    best = fmaxf(best, __shfl_xor(best, 16, 64));
+    best = fmaxf(best, __shfl_xor(best, 32, 64));
+    const float thr = best - kMarginScale * fmaxf(n2, c2max);
+    double bd = INFINITY;
+    int bj = 0;
+    for (int t0 = 0; t0 < ntiles; t0 += 16) {
+        unsigned long long mask = 0;
+        const int t1 = min(t0 + 16, ntiles);
+        for (int tile = t0; tile < t1; tile += 4) {
+            f32x4_t s[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[r] = scores(min(tile + r, ntiles - 1));
+            uint32_t bits = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bits |= (!(s[r][i] < thr) && (tile + r) * kRowTile + 4 * g + i < k) ? 1u << (4 * r + i) : 0u;
+            mask |= (unsigned long long)bits << (4 * (tile - t0));
+        }
+        while (__any(mask != 0)) {
+            if (mask != 0) {
+                const int e = __ffsll(mask) - 1;
+                mask &= mask - 1;
+                const int j = (t0 + (e >> 2)) * kRowTile + 4 * g + (e & 3);
+                const double d = exact_distance_lds(xrow, rows_lds, j);
+                if (d < bd) { bd = d; bj = j; }
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 16; off >>= 1) {
+        const double od = __shfl_xor(bd, off, 64);
+        const int oj = __shfl_xor(bj, off, 64);
+        if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
+    }
+    return bj;
+}
+
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                                     const int32_t* __restrict__ blocks,
                                                                     const uint16_t* __restrict__ C, long long c_unit_rows,
                                                                     int32_t* __restrict__ assign, long long assign_stride,
                                                                     int32_t* __restrict__ amb_list, long long list_stride,
-                                                                    int32_t* __restrict__ amb_cnt, int cnt_stride, int k_cap)
+                                                                    int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap)
 {
     extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
     __shared__ float wave_c2max[kW];
-    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, handed over at the end
-    __shared__ int near_n, near_at;
+    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them
+    __shared__ int near_n;
     const int u = blockIdx.z, b = blockIdx.y;
+    // (this kernel leaves the counters of the other one alone; the next assignment step finds them zero all the same)
+    if (b == 0 && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < cnt_stride; i += 64 * kW) cnt_next[u * cnt_stride + i] = 0;
     const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2];
     const int k1 = min(blocks[4 * b + 3], k0 + k_cap);            // (the launch guarantees the block has no more)
     const int all_chunks = (x1 - x0 + 63) / 64;
@@ -487,28 +598,31 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
 
     int32_t* assign_u = assign + u * assign_stride;
-    int32_t* list_u = amb_list + u * list_stride;
-    int32_t* cnt_ub = amb_cnt + u * cnt_stride + b;
+    int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
 #pragma unroll 1
     for (int chunk = chunk0 + wave; chunk < chunk1; chunk += kW) {
         const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, k_cap, ntiles, c2max);
         const int t = x0 + chunk * 64 + lane;
         if (t < x1) {
-            assign_u[t] = k0 + r.j;
             if (r.near) {
-                // (through LDS: a global counter's answer would have to wait for the points under way)
                 const int pos = atomicAdd(&near_n, 1);
                 if (pos < kNearCap) near_list[pos] = t;
-                else list_u[x0 + atomicAdd(cnt_ub, 1)] = t;
+                else more[pos] = t;
+            } else {
+                assign_u[t] = k0 + r.j;
             }
         }
     }
     __syncthreads();
-    const int n = min(near_n, kNearCap);
-    if (tid == 0 && n > 0) near_at = atomicAdd(cnt_ub, n);
-    __syncthreads();
-    for (int i = tid; i < n; i += 64 * kW) list_u[x0 + near_at + i] = near_list[i];
+    // ---- near ties: here, where the centroids are, instead of in a launch that fetches them for every point ----
+    const int n = near_n;
+    for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
+        const int e = min(e0 + (lane_id() & 15), n - 1);
+        const int t = e < kNearCap ? near_list[e] : more[e];
+        const int j = nearest_exact(Xu, t, rows_lds, lds0, k_cap, k1 - k0, c2max);
+        if (lane_id() < 16) assign_u[t] = k0 + j;
+    }
 }
 
 constexpr int kResidentMaxK = 512;
@@ -516,7 +630,7 @@ constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) byte
 template <int kW>
 hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts, int max_k,
                            int U, const uint16_t* C, long long c_unit_rows, int32_t* assign, long long assign_stride,
-                           int32_t* amb_list, long long list_stride, int32_t* amb_cnt, int cnt_stride, hipStream_t s)
+                           int32_t* amb_list, long long list_stride, int32_t* cnt_next, int cnt_stride, hipStream_t s)
 {
     static bool configured = false;
     if (!configured) {
@@ -534,7 +648,7 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
     const long long want = groups <= kSlots ? kSlots / groups : (4 * kSlots + groups - 1) / groups;
     const int gx = (int)std::max<long long>(1, std::min<long long>(chunks / kW, want));
     hipLaunchKernelGGL(assign_resident_kernel<kW>, dim3(gx, nb, U), dim3(64 * kW), (size_t)k_cap * 260, s, X, x_unit_rows,
-                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, k_cap);
+                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, cnt_next, cnt_stride, k_cap);
     return hipGetLastError();
 }
 
@@ -558,25 +672,6 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 constexpr int kLevelMaxK = 256;
-
-// |x - c|^2 in fp64 as in exact_distance, the centroid in LDS
-__device__ __forceinline__ double exact_distance_lds(const uint4* xrow, const unsigned char* rows_lds, int j)
-{
-    double s = 0.0;
-#pragma unroll 2
-    for (int i = 0; i < 16; ++i) {
-        const uint4 xw = xrow[i], cw = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((i ^ j) & 15) * 16);
-        const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w}, x4[4] = {xw.x, xw.y, xw.z, xw.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double d0 = __dsub_rn((double)bf16lo_to_f32(x4[e]), (double)bf16lo_to_f32(c4[e]));
-            const double d1 = __dsub_rn((double)bf16hi_to_f32(x4[e]), (double)bf16hi_to_f32(c4[e]));
-            s = __dadd_rn(s, __dmul_rn(d0, d0));
-            s = __dadd_rn(s, __dmul_rn(d1, d1));
-        }
-    }
-    return s;
-}
 
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
@@ -629,23 +724,11 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
             }
         }
         __syncthreads();
-        // ---- near ties, one wave per point: smallest exact distance, lowest index among equals ----
-        for (int e = wave; e < near_n; e += kW) {
-            const int t = near_pts[e];
-            const uint4* xrow = reinterpret_cast<const uint4*>(Xu) + (long long)(x0 + t) * 16;
-            double bd = INFINITY;
-            int bj = 0;
-            for (int j = lane; j < k; j += 64) {
-                const double d = exact_distance_lds(xrow, rows_lds, j);
-                if (d < bd) { bd = d; bj = j; }
-            }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const double od = __shfl_xor(bd, off, 64);
-                const int oj = __shfl_xor(bj, off, 64);
-                if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
-            }
-            if (lane == 0) asg[t] = (uint16_t)bj;
+        // ---- near ties ----
+        for (int e0 = wave * 16; e0 < near_n; e0 += kW * 16) {
+            const int t = near_pts[min(e0 + (lane & 15), near_n - 1)];
+            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, p.k_cap, k, c2max);
+            if (lane < 16) asg[t] = (uint16_t)j;
         }
         __syncthreads();
         // ---- member lists: one wave per cluster finds its points 64 at a time ----
@@ -946,21 +1029,18 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
 {
     if (nb <= 0 || max_pts <= 0 || U <= 0) return hipSuccess;
     if (nb > cnt_stride || U > 65535) return hipErrorInvalidValue;
-    hipError_t e = hipSuccess;
     const int n_chunks = (max_pts + kPtsPerWg - 1) / kPtsPerWg;
     if (max_k > 0 && max_k <= kResidentMaxK && max_pts >= 1024) {
         // two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen
         auto go = [&](auto launch) {
             return launch(X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows, assign, assign_stride, amb_list,
-                          list_stride, amb_cnt, cnt_stride, s);
+                          list_stride, amb_cnt_next, cnt_stride, s);
         };
-        e = max_k <= kResidentTwiceK ? go(launch_resident<8>) : go(launch_resident<16>);
-        if (e != hipSuccess) return e;
-    } else {
-        hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
-                           c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride);
+        return max_k <= kResidentTwiceK ? go(launch_resident<8>) : go(launch_resident<16>);
     }
-    e = hipGetLastError();
+    hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
+                       c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int z = std::min(32, (max_pts + 3) / 4);      // (deeper grids only add workgroups that find nothing to do)
     hipLaunchKernelGGL(assign_recheck_kernel, dim3(nb, U, z), dim3(256), 0, s, X, x_unit_rows,

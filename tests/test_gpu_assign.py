@@ -28,3 +28,31 @@ def test_many_blocks_of_many_units():
     ctx, _, _ = _run_case(2, 4, 2, 5000, 60, 2, 150, 10, 1200, 600, iters=2, seed=22)
     assert ctx.mp_get_sizes()["n_blocks"] == 4
     ctx.close()
+
+
+def test_kernels_in_turn_on_one_context():
+    # blocks of 600 centroids keep their near ties in a list that a second launch works off, blocks of 100 decide them
+    # at once: each finds the other's counters as it needs them, and gives what a context of its own gives
+    import torch
+    from paper_2506_13059_amd import binding as mp, inputs
+    U, n = 2, 3000
+    K, V = inputs.draw_tokens(inputs.make_modes(U, 40, "cuda", 31), n, 32, noise=0.05)
+    K, V = K.view(1, U, n, 128), V.view(1, U, n, 128)
+
+    def result(ctx, k):
+        seeds, _ = inputs.draw_seeds(U, mp.mp_plan_blocks(n, 0, 0, k, 0), 1, 33 + k)
+        ctx.mp_cluster_kv(K, V, k, 0, iters=2, init_fine=seeds)
+        got = [ctx.mp_get_assignments()[0].clone()] + [x.clone() for x in ctx.mp_get_centroids(0)]
+        torch.cuda.synchronize()
+        return got
+
+    def fresh():
+        return mp.MpContext(1, U, U, max_tokens=n, levels=1, max_fine=600, max_coarse=0, block_w=0, block_alpha=0, max_tail=0)
+
+    one = fresh()
+    for k in (600, 100, 600, 600, 100, 100, 600):
+        other = fresh()
+        for a, b in zip(result(one, k), result(other, k)):
+            assert torch.equal(a, b)
+        other.close()
+    one.close()
