@@ -660,7 +660,7 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
 // (block, unit) pairs, times ten iterations).  Here an iteration is five barriers; the decisions and sums are those of the
 // separate kernels: near ties decided in fp64 as defined, members summed in ascending order in fp64, one rounding.
 // Bound by the latency of one pair's chain, a member row from memory being its longest link (hence the sixteen at once):
-// 10.4 us an iteration for 32 pairs of 256 points and 16 centroids.  A bound of two waves a SIMD does away with the spills
+// 11.8 us an iteration for 32 pairs of 256 points and 16 centroids.  A bound of two waves a SIMD does away with the spills
 // and is slower (1000 against 780 us for 2048 pairs).  Build of one 32K prompt: 1214 -> 1095 us; sixteen of 128K: 29.1 ->
 // 28.4 ms; refresh of eight 8K contexts: 970 -> 940 us.
 // ------------------------------------------------------------------------------------------------
