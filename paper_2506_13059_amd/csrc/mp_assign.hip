@@ -672,6 +672,7 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 constexpr int kLevelMaxK = 256;
+constexpr int kLevelMaxPts = 512;
 
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
@@ -990,10 +991,11 @@ static size_t coarse_level_smem(int max_pts, int max_k)
     return k_cap * 260 + n_cap * 6;
 }
 
-// (sixteen chunks of points: beyond that one workgroup per block takes longer than the separate launches)
+// (Beyond that one workgroup per block takes longer than the separate launches, which spread a block over the chip:
+// refreshes of 64 blocks of 256 .. 1100 points average 1133 us with the line at 512 points, 1181 with it at 1024.)
 bool coarse_level_fits(int max_pts, int max_k)
 {
-    return max_pts >= 1 && max_pts <= 1024 && max_k >= 1 && max_k <= kLevelMaxK;
+    return max_pts >= 1 && max_pts <= kLevelMaxPts && max_k >= 1 && max_k <= kLevelMaxK;
 }
 
 template <int kW>
@@ -1002,7 +1004,7 @@ static hipError_t launch_coarse_waves(const CoarseLevel& p, int nb, int U, size_
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&coarse_level_kernel<kW>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)coarse_level_smem(1024, kLevelMaxK));
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)coarse_level_smem(kLevelMaxPts, kLevelMaxK));
         if (e != hipSuccess) return e;
         configured = true;
     }

@@ -1,5 +1,5 @@
 """GPU parity of the coarse level in one launch at its edges: chunks of 64 points, tiles of 16 centroids, slots of sixteen
-tiles, its limits of 1024 points and 256 centroids a block (one more takes the launch-per-step path), sixteen waves up to
+tiles, its limits of 512 points and 256 centroids a block (one more takes the launch-per-step path), sixteen waves up to
 256 (block, unit) pairs and eight beyond, and degenerate inputs.  Every result is bit-identical to the oracle's."""
 import pytest
 
@@ -8,8 +8,8 @@ from tests.test_gpu_kmeans import _run_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nf,nc", [(1, 1), (2, 1), (63, 15), (64, 16), (65, 17), (129, 64), (520, 255), (530, 256),
-                                   (530, 257), (1024, 16), (1025, 16)])
+@pytest.mark.parametrize("nf,nc", [(1, 1), (2, 1), (63, 15), (64, 16), (65, 17), (129, 64), (500, 255), (511, 256),
+                                   (510, 257), (512, 16), (513, 16), (1025, 16)])
 def test_edges(nf, nc):
     print(f"nf={nf} nc={nc}", flush=True)
     ctx, _, _ = _run_case(1, 2, 2, nf + 300, max(2, nf // 3), 2, nf, nc, 0, 0, iters=3, seed=500 + nf + nc)
