@@ -13,6 +13,8 @@
 // significant bits, by truncation), and the 16 columns of the product hold them side by side: column part * G + h.
 // Where three parts of G heads do not fit 16 columns (G > 5) the third parts take a second set of products.  The
 // sum of the parts' products is the fp32 product sum; nothing is rounded to 16 bits.
+// Infinite values come out as the products of the fp32 probabilities would have them: see part_floor, and the rows past
+// the end of a wave's share are zeros by the time their probability of zero meets them.
 //
 // What bounds it is the memory system: about 100 vector instructions a tile against 420 of the vector-ALU kernel (60 %
 // of a SIMD's issue slots at the dense rate with 4 heads, more than there are with 8).  Measured on the benchmark's
@@ -115,6 +117,20 @@ __device__ __forceinline__ s16x4 upper_halves(const float (&x)[4])
     return __builtin_bit_cast(s16x4, w);
 }
 
+// The parts of a probability above zero are at least 2^-126 (or the probability itself, if that is less): a part of zero
+// times an infinite value would be NaN.  Where a part was less, this adds at most 2^-126 of a value: less than the
+// rounding of the products for any probability above 2^-100, and nothing beside the row of the largest for the others.
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u16x4 part_floor(const float (&p)[4])
+{
+    const u16x4 tiny = {0x0080, 0x0080, 0x0080, 0x0080};        // (bf16 values of one sign compare like whole numbers)
+    return __builtin_elementwise_min(__builtin_bit_cast(u16x4, upper_halves(p)), tiny);
+}
+__device__ __forceinline__ s16x4 raised(s16x4 part, u16x4 floor)
+{
+    return __builtin_bit_cast(s16x4, __builtin_elementwise_max(__builtin_bit_cast(u16x4, part), floor));
+}
+
 template <int G>
 __device__ __forceinline__ void tile_values(StreamState<G>& st, const float (&p)[4], uint32_t v_addr, uint32_t mask1,
                                             uint32_t mask2)
@@ -131,7 +147,8 @@ __device__ __forceinline__ void tile_values(StreamState<G>& st, const float (&p)
             x[i] = x[i] - __uint_as_float(__float_as_uint(x[i]) & mask2);
         }
     }
-    const s16x4 a = upper_halves(x);
+    const u16x4 floor = part_floor(p);
+    const s16x4 a = raised(upper_halves(x), floor);
     s16x4 v[8];
     const uint32_t a0 = v_addr, a1 = v_addr ^ 32u, a2 = v_addr ^ 64u, a3 = v_addr ^ 96u, a4 = v_addr ^ 128u,
                    a5 = v_addr ^ 160u, a6 = v_addr ^ 192u, a7 = v_addr ^ 224u;
@@ -144,7 +161,7 @@ __device__ __forceinline__ void tile_values(StreamState<G>& st, const float (&p)
 #pragma unroll
     for (int d = 0; d < 8; ++d) st.o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, v[d], st.o[d], 0, 0, 0);
     if constexpr (StreamState<G>::kThird) {
-        const s16x4 b = upper_halves(y);
+        const s16x4 b = raised(upper_halves(y), floor);
 #pragma unroll
         for (int d = 0; d < 8; ++d) st.o3[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b, v[d], st.o3[d], 0, 0, 0);
     }
@@ -206,6 +223,16 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
         for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Vb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + kPiece + i * 1024));
     };
 
+    // The value rows of tile t past the end of the wave's share (repeats of its last row) are zeroed: their probability is
+    // zero, and so is then their product whatever that row holds.
+    auto clear_past_end = [&](int t, uint32_t piece) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (w0 + t * kTile + 4 * i + g >= w1)
+                *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(piece + (uint32_t)((4 * i + g) * 256 + c * 16))) = zero;
+    };
+
     // In program order the loads of a wave are K0 V0 K1 V1 K2 V2 ..., four instructions a piece, and a strip of row
     // numbers now and then.  Loads return in order, so "at most twelve outstanding" in front of a piece's use means
     // that it has arrived (the three pieces behind it may still be under way), and that every older strip has.  A
@@ -254,6 +281,7 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
         float pr[4];
         tile_softmax<G>(st, s, pr);
         if constexpr (!kScored) wait_vm<12>();
+        if (w0 + (t + 1) * kTile > w1) clear_past_end(t, ring + half + kPiece);
         tile_values<G>(st, pr, v_addr + half + kPiece, mask1, mask2);
         if constexpr (kScored) tile_rows(t + 2);
         load_values(t + 2);

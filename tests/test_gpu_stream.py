@@ -113,3 +113,50 @@ def test_results_do_not_depend_on_the_size_of_the_workspace():
     with pytest.raises(mp.MpError) as e:
         mp.mp_dense_attention(q, K, V, workspace=torch.empty(need - 1, dtype=torch.uint8, device="cuda"))
     assert e.value.status == mp.MP_EINVAL
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("n", [1, 37, 500, 2511])
+def test_infinite_values(G, n):
+    """A value row with an infinity: every probability is above zero, so the output's dimension is that infinity, NaN where
+    both signs meet or a value is NaN, and the other dimensions are what they are without it."""
+    from paper_2506_13059_amd import binding as mp
+    q, K, V = _inputs(2, 2, G, n, 900 + 10 * G + n)
+    ref, _ = _reference(q, K, V)
+    X = V.clone()
+    last, some = n - 1, n // 3
+    X[:, :, last, 5] = math.inf
+    X[:, :, some, 77] = -math.inf
+    X[:, :, some, 127] = math.nan
+    both = n > 1
+    if both:
+        X[:, :, last, 64], X[:, :, some, 64] = math.inf, -math.inf
+    print(f"G={G} n={n}", flush=True)
+    out = mp.mp_dense_attention(q, K, X).double()
+    torch.cuda.synchronize()
+    assert bool((out[..., 5] == math.inf).all()) and bool((out[..., 77] == -math.inf).all())
+    assert bool(out[..., 127].isnan().all()) and (not both or bool(out[..., 64].isnan().all()))
+    rest = [d for d in range(128) if d not in (5, 77, 127) and not (both and d == 64)]
+    err = (out - ref)[..., rest].abs()
+    assert bool((err <= 2.0 ** -8 * ref[..., rest].abs() + 2e-5 * ref.abs().max()).all())
+
+
+def test_infinite_values_of_a_decode_step():
+    from paper_2506_13059_amd import binding as mp, inputs
+    centers = inputs.make_modes(2, 40, "cuda", 9)
+    K, V = inputs.draw_tokens(centers, 1500, 10)
+    K, V = K.view(1, 2, 1500, 128).contiguous(), V.view(1, 2, 1500, 128).clone()
+    V[:, :, 60 * 7 + 11, 3] = math.inf              # (token 431: a member of cluster 11)
+    q = inputs.draw_queries(centers, 4, 1, 11, softness=0.05).view(1, 8, 128)
+    fot = torch.arange(1500, device="cuda", dtype=torch.int32).remainder(60).expand(2, -1).contiguous()
+    kt, vt = K[:, :, :70].contiguous(), V[:, :, 100:170].clone()
+    vt[:, :, 69, 9] = -math.inf
+    ctx = mp.MpContext(1, 8, 2, max_tokens=1500, levels=1, max_fine=60, max_tail=70)
+    ctx.mp_set_clustering(K, V, fot, 60)
+    for budget in (1500, 300, 0):                   # as a row, as a row or a centroid term, as a centroid term
+        out = ctx.mp_decode_attention(q, budget, 0, kt, vt)
+        torch.cuda.synchronize()
+        assert bool((out[..., 3] == math.inf).all()) and bool((out[..., 9] == -math.inf).all()), budget
+        rest = [d for d in range(128) if d not in (3, 9)]
+        assert bool(out[..., rest].isfinite().all()), budget
+    ctx.close()
