@@ -10,13 +10,10 @@
 //      v_mfma_f32_32x32x16_bf16, fp32 accumulation.  The offset -|c_j|^2/2 is part of the
 //      contraction: split exactly into three bf16 values, it sits in three extra slots of the
 //      reduction dimension against ones on the point side, so the scores leave the matrix cores
-//      complete.  Per point the kernel keeps the best and the second best score.  The products
-//      are exact and every one of the 131 accumulation steps loses at most one unit in the last
-//      place of a partial sum bounded by max(|x||c|, |c|^2/2), so each score is within
-//      2^-16 max(|x|^2, max_j |c_j|^2) of its exact value (2^-19 more for four mantissa bits that
-//      carry an index during the comparison).  A point whose two best scores are
-//      further apart than 2^-14 of that scale has a unique nearest centroid in exact arithmetic
-//      too (and by far more than fp64 rounding), which is the fp64 answer.
+//      complete.  Per point the kernel keeps the best and the second best score.  A point whose two
+//      best scores are further apart than the margin of mp_margin.h (2^-14 of max(|x|^2,
+//      max_j |c_j|^2), 1.1 times what the two can be off together) has a unique nearest centroid in
+//      exact arithmetic too (and by far more than fp64 rounding), which is the fp64 answer.
 //   2. Every other point (near-equal or equal distances) goes onto a per-block list and
 //      assign_recheck_kernel decides it exactly as defined above: it collects the centroids whose
 //      score is within the same margin of the best one and evaluates their distances in fp64
@@ -26,6 +23,7 @@
 
 #include "mp_device.h"
 #include "mp_internal.h"
+#include "mp_margin.h"
 
 namespace mp {
 
@@ -37,7 +35,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 32;                 // centroids per tile = rows of the MFMA A operand
 constexpr int kRowBytes = 256 + 16;       // LDS row of one centroid: 128 dims, then -|c|^2/2 as three bf16 and five zeros
-constexpr float kMarginScale = 1.0f / 16384.0f;  // 2^-14: 1.8 times the sum of two scores' error bounds
+constexpr uint32_t kTiledSlotMask = (1u << kTiledSlotBits) - 1u;
 constexpr float kNoCentroid = -3.0e38f;          // score of a padded row (finite: index bits are packed into scores)
 
 // Scores of 32 centroids (one LDS tile: rows of kRowBytes, -|c|^2/2 in three bf16 pieces behind the
@@ -54,8 +52,8 @@ __device__ __forceinline__ void fold_scores(const f32x16_t (&acc)[2], int j0, fl
         const float before = best[c];
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
-            const float va = __uint_as_float((__float_as_uint(acc[c][i]) & ~15u) | (uint32_t)i);
-            const float vb = __uint_as_float((__float_as_uint(acc[c][i + 1]) & ~15u) | (uint32_t)(i + 1));
+            const float va = __uint_as_float((__float_as_uint(acc[c][i]) & ~kTiledSlotMask) | (uint32_t)i);
+            const float vb = __uint_as_float((__float_as_uint(acc[c][i + 1]) & ~kTiledSlotMask) | (uint32_t)(i + 1));
             second[c] = fmaxf(second[c], __builtin_amdgcn_fmed3f(best[c], va, vb));
             best[c] = fmaxf(fmaxf(va, vb), best[c]);
         }
@@ -117,7 +115,7 @@ __device__ __forceinline__ void finish_points(int half, const float (&best)[2], 
 {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const int slot = (int)(__float_as_uint(best[c]) & 15u);
+        const int slot = (int)(__float_as_uint(best[c]) & kTiledSlotMask);
         const int bj = btile[c] + 8 * (slot >> 2) + 4 * half + (slot & 3);
         const float ob = __shfl_xor(best[c], 32, 64), os = __shfl_xor(second[c], 32, 64);
         const int oj = __shfl_xor(bj, 32, 64);
@@ -130,7 +128,7 @@ __device__ __forceinline__ void finish_points(int half, const float (&best)[2], 
         const int t = tpt[c];
         if (t < x1 && half == 0) {
             assign_u[t] = j;
-            const float margin = kMarginScale * fmaxf(xx, c2max);
+            const float margin = near_margin(fmaxf(xx, c2max));
             // (written so that a point without any comparable score also goes to the exact pass)
             if (!(bst - sec > margin)) {
                 const int pos = atomicAdd(amb_cnt_ub, 1);
@@ -262,13 +260,11 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
 //
 // A lane (g, c) holds rows 4g .. 4g+3 of a tile for column c of four columns groups: point 16 q + c, q < 4.  The slot of a
 // score among the sixteen tiles of a half (tile & 15, row & 3) rides in its six lowest mantissa bits, a change of less
-// than 2^-17 of its magnitude.  A partial sum is at most 1.5 max(|x|^2, |c|^2) and is rounded to nearest at most 128
-// times (2^-24 each): with the slot bits two scores are off by less than 2 (1.5 * 2^-17 + 1.5 * 2^-17) = 0.75 * 2^-14 of
-// that scale together, the margin is 2^-14.
+// than 2^-17 of its magnitude, which the margin covers (near_margin_of_best).
 constexpr int kRowTile = 16;
 constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
 constexpr int kNearCap = 512;
-constexpr uint32_t kSlotMask = 63u;
+constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
 
 typedef const __attribute__((address_space(3))) bf16x8_t lds_frag;
 typedef const __attribute__((address_space(3))) f32x4_t lds_four;
@@ -422,7 +418,7 @@ __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int
     }
     const uint32_t slot = __float_as_uint(best[0]) & kSlotMask;
     const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
-    const float margin = kMarginScale * fmaxf(n2[0], c2max);
+    const float margin = near_margin_of_best(fmaxf(n2[0], c2max), best[0]);
     // (written so that a point without any comparable score also goes to the exact pass)
     return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin)};
 }
@@ -514,7 +510,7 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
     }
     best = fmaxf(best, __shfl_xor(best, 16, 64));
     best = fmaxf(best, __shfl_xor(best, 32, 64));
-    const float thr = best - kMarginScale * fmaxf(n2, c2max);
+    const float thr = best - near_margin(fmaxf(n2, c2max));
     double bd = INFINITY;
     int bj = 0;
     for (int t0 = 0; t0 < ntiles; t0 += 16) {
@@ -936,7 +932,7 @@ __global__ __launch_bounds__(256) void assign_recheck_kernel(const uint16_t* __r
         }
         best = wave_max_f32(best);
         c2max = wave_max_f32(c2max);
-        const float thr = best - kMarginScale * fmaxf(x2, c2max);
+        const float thr = best - near_margin(fmaxf(x2, c2max));
         if (lane == 0) ncand[wave] = 0;
         wave_lds_sync();
         auto consider = [&](int j, float sc) {

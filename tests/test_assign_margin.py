@@ -1,0 +1,74 @@
+"""The margin below which the k-means assignment hands a point to its exact pass, against the error that it has to cover:
+the header's functions, compiled for the host, over scores that are as wrong as the model of the matrix cores allows."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_13059_amd", "csrc", "mp_margin.h")
+ULP = 2.0 ** -23
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("margin")
+    src, so = d / "m.cpp", d / "m.so"
+    src.write_text(f'''#include "{HEADER}"
+extern "C" float tiled(float m, float) {{ return mp::near_margin(m); }}
+extern "C" float resident(float m, float best) {{ return mp::near_margin_of_best(m, best); }}
+extern "C" int tiled_bits() {{ return mp::kTiledSlotBits; }}
+extern "C" int resident_bits() {{ return mp::kResidentSlotBits; }}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-o", str(so), str(src)])
+    h = ctypes.CDLL(str(so))
+    for f in (h.tiled, h.resident):
+        f.restype, f.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_float]
+    return h
+
+
+def _accumulation_error(M, steps):
+    # every partial sum is at most 1.5 M, a step loses at most one unit in its last place; half of |c|^2 (at most M): twelve
+    return (steps * 1.5 + 12 * 0.5) * ULP * M
+
+
+def _slotted(v, bits, slot):
+    w = np.asarray(v, np.float32).view(np.uint32)
+    return ((w & ~np.uint32((1 << bits) - 1)) | slot.astype(np.uint32)).view(np.float32)
+
+
+@pytest.mark.parametrize("kernel,steps", [("tiled", 131), ("resident", 128)])
+def test_every_winner_that_an_error_can_change_is_near(lib, kernel, steps):
+    margin, bits = getattr(lib, kernel), getattr(lib, kernel + "_bits")()
+    rng = np.random.default_rng(1)
+    n = 20000
+    changed = 0
+    for M in (1.0, 3.7, 1e-6, 250.0, 1e20):
+        E = _accumulation_error(M, steps)
+        true_best = M * np.concatenate([rng.uniform(-1.5, 0.5, n), np.full(n, -1.5), np.full(n, 0.5), rng.uniform(-1e-3, 1e-3, n)])
+        gap = (2.5 * E + 3 * 2.0 ** bits * ULP * M) * rng.uniform(0, 1, true_best.size) ** 6        # (many close to zero)
+        # the nearest centroid's score is as low as the model allows, another one's as high
+        low = _slotted(true_best - E, bits, np.where(true_best > 0, 0, (1 << bits) - 1))
+        high = _slotted(true_best - gap + E, bits, np.where(true_best - gap + E > 0, (1 << bits) - 1, 0))
+        wrong = high > low                                   # the other one wins the comparison
+        changed += int(wrong.sum())
+        for b, s in zip(high[wrong][::7], low[wrong][::7]):
+            # (M as the kernel has it is an fp32 sum: up to a hundred roundings too small)
+            assert not b - s > margin(M * (1 - 100 * ULP), float(b)), (M, b, s)
+    assert changed > 1000
+
+
+@pytest.mark.parametrize("kernel,steps", [("tiled", 131), ("resident", 128)])
+def test_bound(lib, kernel, steps):
+    margin, bits = getattr(lib, kernel), getattr(lib, kernel + "_bits")()
+    for M in (1.0, 1e-3, 77.0):
+        for best in np.linspace(-1.5 * M, 0.5 * M, 401):
+            need = 2 * _accumulation_error(M, steps) + 2 * 2.0 ** bits * ULP * abs(best)
+            assert margin(M * (1 - 100 * ULP), best) * (1 - 2.0 ** (bits - 23)) > need, (M, best)
+
+
+def test_candidates_of_the_exact_pass(lib):
+    # scores without index bits: whatever can be the nearest is within the margin of the best
+    for M in (1.0, 9.0):
+        assert lib.tiled(M * (1 - 100 * ULP), 0.0) > 2 * _accumulation_error(M, 131)
