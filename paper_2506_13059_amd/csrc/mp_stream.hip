@@ -22,6 +22,8 @@
 // chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per compute unit (see stream_chunks_per_unit in
 // mp_api.hip) 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: 504 -> 291 us; 8 units x 32768,
 // 4 heads: 40.8 -> 26.0 us.
+#include <type_traits>
+
 #include "mp_device.h"
 #include "mp_internal.h"
 
@@ -234,20 +236,26 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     };
 
     // In program order the loads of a wave are K0 V0 K1 V1 K2 V2 ..., four instructions a piece, and a strip of row
-    // numbers now and then.  Loads return in order, so "at most twelve outstanding" in front of a piece's use means
-    // that it has arrived (the three pieces behind it may still be under way), and that every older strip has.  A
-    // piece's slot is loaded again only after the LDS reads of the piece have returned.  Tiles past the end repeat
-    // the last row, so that the counts hold to the end.
+    // numbers now and then.  Loads return in order, so "at most as many outstanding as the pieces behind it have" (twelve,
+    // fewer at the last two tiles) in front of a piece's use means that it has arrived, and that every older strip has.  A
+    // piece's slot is loaded again only after the LDS reads of the piece have returned.  Nothing is asked for past the end:
+    // a share is often a single tile, and rows no one uses made its end wait for a second trip to memory (dense calls over
+    // up to 8192 rows of 8 units, 4 heads: 12.5-15.1 -> 11.9-13.8 us).
+    const bool single = n_tiles == 1;
     load_strip(0);
-    load_strip(1);
+    if (n_tiles > kStrip / kTile) load_strip(1);
     if constexpr (kListed) wait_vm<0>();
     tile_rows(0);
     if constexpr (!kScored) load_keys(0);
     load_values(0);
-    tile_rows(1);
-    if constexpr (!kScored) load_keys(1);
-    load_values(1);
-    for (int t = 0; t < n_tiles; ++t) {
+    if (!single) {
+        tile_rows(1);
+        if constexpr (!kScored) load_keys(1);
+        load_values(1);
+    }
+    // kAhead: how many tiles follow (two: two or more)
+    auto tile = [&](int t, auto ahead) {
+        constexpr int kAhead = decltype(ahead)::value;
         const uint32_t half = (uint32_t)((t & 1) * 2 * kPiece);
         float s[4];
         if constexpr (kScored) {
@@ -258,7 +266,7 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
             }
             wait_vm<0>();
         } else {
-            wait_vm<12>();
+            wait_vm<kAhead == 0 ? 4 : 12>();
             bf16x8 k[4];
             const uint32_t a0 = k_addr + half, a1 = (k_addr ^ 64u) + half, a2 = (k_addr ^ 128u) + half, a3 = (k_addr ^ 192u) + half;
             asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
@@ -266,30 +274,37 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
                          : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3])
                          : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
                          : "memory");
-            tile_rows(t + 2);
-            load_keys(t + 2);
+            if constexpr (kAhead == 2) {
+                tile_rows(t + 2);
+                load_keys(t + 2);
+            }
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[ks], q[ks], acc, 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[i] = acc[i] * p.scale_log2e;
-            if (w0 + (t + 1) * kTile > w1) {
+            if constexpr (kAhead == 0) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s[i] = w0 + t * kTile + 4 * g + i < w1 ? s[i] : -INFINITY;
             }
         }
         float pr[4];
         tile_softmax<G>(st, s, pr);
-        if constexpr (!kScored) wait_vm<12>();
-        if (w0 + (t + 1) * kTile > w1) clear_past_end(t, ring + half + kPiece);
+        if constexpr (!kScored) wait_vm<4 * (kAhead == 2 ? 3 : 2 * kAhead)>();
+        if constexpr (kAhead == 0) clear_past_end(t, ring + half + kPiece);
         tile_values<G>(st, pr, v_addr + half + kPiece, mask1, mask2);
-        if constexpr (kScored) tile_rows(t + 2);
-        load_values(t + 2);
-        // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next
-        if constexpr (kListed)
-            if ((t & 3) == 1) load_strip((t >> 2) + 2);
-    }
-    wait_vm<0>();       // (loads past the end are still landing in the ring)
+        if constexpr (kAhead == 2) {
+            if constexpr (kScored) tile_rows(t + 2);
+            load_values(t + 2);
+            // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next
+            if constexpr (kListed)
+                if ((t & 3) == 1 && ((t >> 2) + 2) * (kStrip / kTile) < n_tiles) load_strip((t >> 2) + 2);
+        }
+    };
+    int t = 0;
+    for (; t + 2 < n_tiles; ++t) tile(t, std::integral_constant<int, 2>{});
+    if (!single) tile(t++, std::integral_constant<int, 1>{});
+    tile(t, std::integral_constant<int, 0>{});
 }
 
 template <int G, int kWaves>
