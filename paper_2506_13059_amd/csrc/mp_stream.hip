@@ -169,8 +169,21 @@ __device__ __forceinline__ void tile_values(StreamState<G>& st, const float (&p)
     }
 }
 
+// Logits of rows 4g .. 4g+3 of a tile, stored row after row.
+template <int G>
+__device__ __forceinline__ void lds_read_scores(uint32_t a, float (&s)[4])
+{
+    asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:%5\n\tds_read_b32 %2, %4 offset:%6\n\t"
+                 "ds_read_b32 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]), "=&v"(s[3])
+                 : "v"(a), "n"(4 * G), "n"(8 * G), "n"(12 * G)
+                 : "memory");
+}
+
 // Rows [w0, w1) of a source through one wave.  `ring`: LDS byte offset of the wave's ring; `strips`: of its two
-// strips of row numbers.  kScored: the logits are read ready-made and only value rows are loaded.
+// strips of row numbers.  kScored: the logits are ready-made; they take the place of the key rows in the ring.  (Fetched
+// into registers when their tile was due, they made every tile a trip to memory of its own: one level of 4096 centroids,
+// 64 / 256 units of 4 heads, whole step: 127.5 / 226.9 -> 122.5 / 205.0 us.)
 template <int G, bool kScored, bool kListed>
 __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0,
                                              int w1, uint32_t ring, uint32_t strips)
@@ -216,9 +229,18 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
             off[i] = (long long)r[i] * 256 + (chunk ^ (uint32_t)(64 * i));
         }
     };
+    constexpr int kKeyLoads = kScored ? (kTile * G + 63) / 64 : 4;       // instructions of load_keys
     auto load_keys = [&](int t) {
+        if constexpr (kScored) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Kb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + i * 1024));
+            for (int i = 0; i < kKeyLoads; ++i) {
+                const int x = min((w0 + t * kTile) * G + 64 * i + lane, w1 * G - 1);
+                load_to_lds<4, false>(scores + x, ring + (uint32_t)((t & 1) * 2 * kPiece + i * 256));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Kb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + i * 1024));
+        }
     };
     auto load_values = [&](int t) {
 #pragma unroll
@@ -235,9 +257,9 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
                 *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(piece + (uint32_t)((4 * i + g) * 256 + c * 16))) = zero;
     };
 
-    // In program order the loads of a wave are K0 V0 K1 V1 K2 V2 ..., four instructions a piece, and a strip of row
-    // numbers now and then.  Loads return in order, so "at most as many outstanding as the pieces behind it have" (twelve,
-    // fewer at the last two tiles) in front of a piece's use means that it has arrived, and that every older strip has.  A
+    // In program order the loads of a wave are K0 V0 K1 V1 K2 V2 ..., four instructions a piece (logits in the place of keys:
+    // one or two), and a strip of row numbers now and then.  Loads return in order, so "at most as many outstanding as the
+    // pieces behind it have" in front of a piece's use means that it has arrived, and that every older strip has.  A
     // piece's slot is loaded again only after the LDS reads of the piece have returned.  Nothing is asked for past the end:
     // a share is often a single tile, and rows no one uses made its end wait for a second trip to memory (dense calls over
     // up to 8192 rows of 8 units, 4 heads: 12.5-15.1 -> 11.9-13.8 us).
@@ -246,11 +268,11 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     if (n_tiles > kStrip / kTile) load_strip(1);
     if constexpr (kListed) wait_vm<0>();
     tile_rows(0);
-    if constexpr (!kScored) load_keys(0);
+    load_keys(0);
     load_values(0);
     if (!single) {
         tile_rows(1);
-        if constexpr (!kScored) load_keys(1);
+        load_keys(1);
         load_values(1);
     }
     // kAhead: how many tiles follow (two: two or more)
@@ -258,15 +280,14 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
         constexpr int kAhead = decltype(ahead)::value;
         const uint32_t half = (uint32_t)((t & 1) * 2 * kPiece);
         float s[4];
+        wait_vm<kAhead == 0 ? 4 : 8 + kKeyLoads>();
         if constexpr (kScored) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = w0 + t * kTile + 4 * g + i;
-                s[i] = j < w1 ? scores[(long long)j * G + head] : -INFINITY;
+            lds_read_scores<G>(ring + half + (uint32_t)((4 * g * G + head) * 4), s);
+            if constexpr (kAhead == 2) {
+                tile_rows(t + 2);
+                load_keys(t + 2);
             }
-            wait_vm<0>();
         } else {
-            wait_vm<kAhead == 0 ? 4 : 12>();
             bf16x8 k[4];
             const uint32_t a0 = k_addr + half, a1 = (k_addr ^ 64u) + half, a2 = (k_addr ^ 128u) + half, a3 = (k_addr ^ 192u) + half;
             asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
@@ -283,18 +304,17 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
             for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[ks], q[ks], acc, 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[i] = acc[i] * p.scale_log2e;
-            if constexpr (kAhead == 0) {
+        }
+        if constexpr (kAhead == 0) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) s[i] = w0 + t * kTile + 4 * g + i < w1 ? s[i] : -INFINITY;
-            }
+            for (int i = 0; i < 4; ++i) s[i] = w0 + t * kTile + 4 * g + i < w1 ? s[i] : -INFINITY;
         }
         float pr[4];
         tile_softmax<G>(st, s, pr);
-        if constexpr (!kScored) wait_vm<4 * (kAhead == 2 ? 3 : 2 * kAhead)>();
+        wait_vm<kAhead == 2 ? 4 + 2 * kKeyLoads : kAhead * (4 + kKeyLoads)>();
         if constexpr (kAhead == 0) clear_past_end(t, ring + half + kPiece);
         tile_values<G>(st, pr, v_addr + half + kPiece, mask1, mask2);
         if constexpr (kAhead == 2) {
-            if constexpr (kScored) tile_rows(t + 2);
             load_values(t + 2);
             // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next
             if constexpr (kListed)
