@@ -82,6 +82,7 @@ struct Scratch {
     // level in progress, maintained with LDS atomics
     unsigned long long key_min, key_max;
     uint32_t key_total, key_tiny, bl_count;
+    uint32_t ahead[kListCap];         // register path, per entry of the boundary list: tokens of the entries before it
 };
 
 struct Arrays {
@@ -1160,7 +1161,8 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
     }
     __builtin_amdgcn_sched_barrier(0);
     // while the rows travel
-    if (tid < kHistBuckets) L.hist[tid] = 0;
+    if (tid < kHistBuckets) L.hist[tid] = S.hist[0][tid] = S.hist[1][tid] = S.hist[2][tid] = 0;
+    if (tid < kListCap) S.ahead[tid] = 0;
     if (tid == 0) {
         S.bl_count = 0;
         S.tiny = 0;
@@ -1330,24 +1332,27 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
     if (__any(tiny)) S.tiny = 1;
     // First digit of the selection: buckets on a fixed scale of the score, so that nothing about the level has to be
     // known beforehand: quarters of an octave down to 2^-28 (where flat attention has its boundary), octaves down to
-    // 2^-124, then eight octaves each (peaked attention), the last bucket open.
-    constexpr uint64_t kTopKey = ~0x4030000000000000ull;           // (score 16: no score is larger than G up to rounding)
+    // 2^-124, then eight octaves each (peaked attention), the last bucket open.  `pos`: quarter octaves below 16 (no
+    // score is larger than G up to rounding) with 50 binary places, the octaves linear inside.
+    constexpr uint64_t kTopKey = ~0x4030000000000000ull;
     static_assert(kHistBuckets == 256, "the scale below has 128 + 96 + 32 buckets");
-    auto bucket_of = [&](uint64_t k) {
-        const uint32_t v = (uint32_t)((k - kTopKey) >> 50);        // quarters of an octave below 16
+    auto bucket_of = [&](uint64_t at) {
+        const uint32_t v = (uint32_t)(at >> 50);
         const uint32_t far_down = min(224u + ((v - 512u) >> 5), 255u);
         return v < 128u ? v : v < 512u ? 96u + (v >> 2) : far_down;
     };
+    uint64_t pos[kFastChunks];
     uint32_t bucket[kFastChunks];
 #pragma unroll
     for (int c = 0; c < kFastChunks; ++c) {
-        bucket[c] = bucket_of(key[c]);
+        pos[c] = key[c] - kTopKey;
+        bucket[c] = bucket_of(pos[c]);
         if (st.w[c]) atomicAdd(&L.hist[bucket[c]], (1ull << 40) | st.w[c]);
     }
     phase_sync<true>();
+    const unsigned long long* first_digit = L.hist;
     if (S.tiny) {
         // some score left the range of a double: the level ranks by log mean_h e^{l - LSE_h} in the log domain
-        // (and orders all of it with the general search below)
         linear = 0;
         double lse[GH];
 #pragma unroll
@@ -1374,8 +1379,14 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
                     sc[t] = tm - kLogG + log(not_hoisted(ss));
                 }
             });
-            key[c] = st.w[c] ? descending_key(select_own(sc)) : ~0ull;
+            const double own = select_own(sc);
+            key[c] = st.w[c] ? descending_key(own) : ~0ull;
+            pos[c] = (uint64_t)(fmin(fmax(16.0 - own * (4.0 * 1.4426950408889634), 0.0), 16383.0) * 0x1p50);
+            bucket[c] = bucket_of(pos[c]);
+            if (st.w[c]) atomicAdd(&S.hist[0][bucket[c]], (1ull << 40) | st.w[c]);
         }
+        phase_sync<true>();
+        first_digit = S.hist[0];
     }
     if (!quiet) {
 #pragma unroll
@@ -1390,41 +1401,76 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
 #pragma unroll
         for (int c = 0; c < kFastChunks; ++c) st.take[c] = st.w[c] != 0;
     } else {
-        // every wave scans the histogram for itself: kHistBuckets / 64 buckets per lane
-        constexpr int BPL = kHistBuckets / 64;
-        unsigned long long hb[BPL];
-        uint32_t sum = 0;
+        // The bucket in which the running token count passes the budget, what lies before it and how many it holds: every
+        // wave scans the histogram for itself, kHistBuckets / 64 buckets per lane.
+        uint32_t acc = 0, bcnt = 0, bstar = 0;
+        auto find_boundary = [&](const unsigned long long* hist) {
+            constexpr int BPL = kHistBuckets / 64;
+            unsigned long long hb[BPL];
+            uint32_t sum = 0;
 #pragma unroll
-        for (int i = 0; i < BPL; ++i) {
-            hb[i] = L.hist[BPL * lane + i];
-            sum += (uint32_t)(hb[i] & kWtMask);
-        }
-        const uint32_t incl = wave_incl_scan_u32(sum);
-        const unsigned long long crossing = __ballot((unsigned long long)incl > bud);
-        const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
-        uint32_t a = incl - sum, d = BPL * lane, cn = 0;
-        bool done = false;
+            for (int i = 0; i < BPL; ++i) {
+                hb[i] = hist[BPL * lane + i];
+                sum += (uint32_t)(hb[i] & kWtMask);
+            }
+            const uint32_t incl = acc + wave_incl_scan_u32(sum);
+            const unsigned long long crossing = __ballot((unsigned long long)incl > bud);
+            const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
+            uint32_t a = incl - sum, d = BPL * lane, cn = 0;
+            bool done = false;
 #pragma unroll
-        for (int i = 0; i < BPL; ++i) {
-            const uint32_t wi = (uint32_t)(hb[i] & kWtMask);
-            if (!done) {
-                if ((unsigned long long)a + wi > bud) {
-                    d = BPL * lane + i;
-                    cn = (uint32_t)(hb[i] >> 40);
-                    done = true;
-                } else {
-                    a += wi;
+            for (int i = 0; i < BPL; ++i) {
+                const uint32_t wi = (uint32_t)(hb[i] & kWtMask);
+                if (!done) {
+                    if ((unsigned long long)a + wi > bud) {
+                        d = BPL * lane + i;
+                        cn = (uint32_t)(hb[i] >> 40);
+                        done = true;
+                    } else {
+                        a += wi;
+                    }
                 }
             }
-        }
-        const uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)a, first);
-        const uint32_t bcnt = linear ? (uint32_t)__builtin_amdgcn_readlane((int)cn, first) : ~0u;
-        const uint32_t bstar = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+            acc = (uint32_t)__builtin_amdgcn_readlane((int)a, first);
+            bcnt = (uint32_t)__builtin_amdgcn_readlane((int)cn, first);
+            bstar = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+        };
+        find_boundary(first_digit);
         // entries before the boundary bucket are taken, entries behind it are not
+        bool inside[kFastChunks];
 #pragma unroll
-        for (int c = 0; c < kFastChunks; ++c) st.take[c] = st.w[c] && bucket[c] < bstar;
+        for (int c = 0; c < kFastChunks; ++c) {
+            st.take[c] = st.w[c] && bucket[c] < bstar;
+            inside[c] = st.w[c] && bucket[c] == bstar;
+        }
+        // Flat attention puts much of a level into one bucket: up to two more digits, 256 slices of it each (the last slice
+        // of the open bucket takes the rest).  The general search divides all entries anew, digit by digit from their
+        // extremes.  Whole step of 8 units, 1024 clusters in one level, 1 / 3 / 5 heads, near and past a full bucket: 42 / 42 /
+        // 49 us with it, 29 / 30 / 36 with these digits and the list below; 2048 and 128 clusters, 4 heads, peaked scores in
+        // the log domain 44 -> 33.
+        uint64_t low = (uint64_t)(bstar < 128u ? bstar : bstar < 224u ? 4u * (bstar - 96u) : 512u + 32u * (bstar - 224u)) << 50;
+        int slice = bstar < 128u ? 50 : bstar < 224u ? 52 : 55;
+#pragma unroll 1
+        for (int digit = 1; digit <= 2 && bcnt > (uint32_t)kListCap; ++digit) {
+            slice -= 8;
+            uint32_t sub[kFastChunks];
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                const uint64_t at = (pos[c] - low) >> slice;
+                sub[c] = at < 255u ? (uint32_t)at : 255u;
+                if (inside[c]) atomicAdd(&S.hist[digit][sub[c]], (1ull << 40) | st.w[c]);
+            }
+            phase_sync<true>();
+            find_boundary(S.hist[digit]);
+#pragma unroll
+            for (int c = 0; c < kFastChunks; ++c) {
+                st.take[c] |= inside[c] && sub[c] < bstar;
+                inside[c] = inside[c] && sub[c] == bstar;
+            }
+            low += (uint64_t)bstar << slice;
+        }
         if (bcnt > (uint32_t)kListCap) {
-            // a crowded boundary bucket (many equal or nearly equal scores) or logarithmic keys: the general search
+            // a crowded slice (many equal or almost equal scores): the general search
 #pragma unroll
             for (int c = 0; c < kFastChunks; ++c) {
                 if (st.x[c] >= 0) {
@@ -1450,26 +1496,47 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
                 st.take[c] = t;
             }
         } else if (bcnt > 1) {
-            // those inside it are ordered by (key, position)
+            // Those inside it are ordered by (key, position).
+            uint32_t at[kFastChunks];
 #pragma unroll
             for (int c = 0; c < kFastChunks; ++c) {
-                if (st.w[c] && bucket[c] == bstar) {
-                    const uint32_t slot = atomicAdd(&S.bl_count, 1u);
-                    L.blist[2 * slot] = key[c];
-                    L.blist[2 * slot + 1] = ((unsigned long long)(uint32_t)st.x[c] << 32) | st.w[c];
+                at[c] = 0;
+                if (inside[c]) {
+                    at[c] = atomicAdd(&S.bl_count, 1u);
+                    L.blist[2 * at[c]] = key[c];
+                    L.blist[2 * at[c] + 1] = ((unsigned long long)(uint32_t)st.x[c] << 32) | st.w[c];
                 }
             }
             phase_sync<true>();
+            constexpr uint32_t kShare = kListCap / kWaves;
+            // tokens of the entries [first, end) of the list that come before (k, x); four at a time (their reads together)
+            auto tokens_before = [&](uint32_t first, uint32_t end, unsigned long long k, uint32_t x) {
+                uint32_t run = 0;
+#pragma unroll 1
+                for (; first < end; first += 4)
 #pragma unroll
-            for (int c = 0; c < kFastChunks; ++c) {
-                if (st.w[c] && bucket[c] == bstar) {
-                    unsigned long long run = (unsigned long long)acc + st.w[c];
-                    for (uint32_t m = 0; m < bcnt; ++m) {
+                    for (uint32_t m = first; m < first + 4; ++m) {
                         const unsigned long long ok = L.blist[2 * m], ov = L.blist[2 * m + 1];
-                        if (ok < key[c] || (ok == key[c] && (int)(ov >> 32) < st.x[c])) run += (uint32_t)ov;
+                        const bool before = ok < k || (ok == k && (uint32_t)(ov >> 32) < x);
+                        run += m < end && before ? (uint32_t)ov : 0u;
                     }
-                    st.take[c] = run <= bud;
-                }
+                return run;
+            };
+            if (bcnt <= 12u) {
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c)
+                    if (inside[c]) st.take[c] = (unsigned long long)acc + tokens_before(0, bcnt, key[c], (uint32_t)st.x[c]) + st.w[c] <= bud;
+            } else {
+                // A longer list: every entry's lane adds up an eighth of it in every wave.  (Its owner alone going through
+                // the whole list: 100 cycles an entry and chunk, 8 us at 60 entries.)
+                static_assert(kListCap == 64, "one lane per entry of the list");
+                const uint32_t first = kShare * wave, end = min(first + kShare, bcnt);
+                if (first < end && lane < bcnt)
+                    atomicAdd(&S.ahead[lane], tokens_before(first, end, L.blist[2 * lane], (uint32_t)(L.blist[2 * lane + 1] >> 32)));
+                phase_sync<true>();
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c)
+                    if (inside[c]) st.take[c] = (unsigned long long)acc + S.ahead[at[c]] + st.w[c] <= bud;
             }
         }
     }

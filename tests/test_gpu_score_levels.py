@@ -66,3 +66,16 @@ def test_all_scores_equal(nf):
     r = compare_decode(ctx, torch.zeros_like(q), K, V, n // 3, label=f"equal nf={nf}")
     assert r["exempt"] == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("nf,nc,G", [(400, 0, 1), (900, 0, 3), (1024, 0, 4), (900, 400, 5), (700, 300, 8)])
+@pytest.mark.parametrize("softness", [0.0005, 0.004, 0.02])
+def test_flat_attention(nf, nc, G, softness):
+    """Scores of a whole level within a fraction of an octave and yet all different: the boundary is found by the second
+    digit of the selection, or, where even its slices are crowded, by the general search."""
+    from tests.gpu_util import compare_decode
+    ctx, K, V, q, n = _ctx(G, nf, nc, softness, 600 + nf + G)
+    print(f"nf={nf} nc={nc} G={G} softness={softness}", flush=True)
+    for kb, cb in ((n // 16, n // 4), (n // 3, n // 2), (n - 5, n - 9)):
+        compare_decode(ctx, q, K, V, kb, cb, label=f"flat nf={nf} G={G} kb={kb}")
+    ctx.close()
