@@ -15,6 +15,7 @@
 
 #include "mp_ctx.h"
 #include "mp_internal.h"
+#include "mp_plan.h"
 
 using namespace mp;
 
@@ -438,7 +439,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     vp.partials = ctx->partials;
     vp.n_units = U;
     vp.scale_log2e = (float)(ctx->scale_d * 1.4426950408889634);
-    const int main_max = std::min(key_budget, ctx->n_tokens);
+    const int main_max = most_selected(ctx->cfg.levels, key_budget, coarse_budget, ctx->n_tokens);
     int ns = 0, chunk0 = 0;
     // The matrix-core kernel takes every launch but those with 8-bit rows or a tail that does not start on 16 bytes.
     // Its workgroups per unit are shared out over the selected keys (or, where none can be selected, the centroid
