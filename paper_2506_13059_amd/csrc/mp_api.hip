@@ -60,25 +60,6 @@ int pick_chunk_rows(long long n_rows_per_unit, int n_units)
     return cr;
 }
 
-// Matrix-core kernel: workgroups per unit for a launch over all units.  One workgroup per compute unit: four waves
-// with three pieces of 4 KiB each on their way keep a compute unit's share of the memory system busy, and every
-// further workgroup only adds a prologue, an epilogue and partials to merge.  Measured (dense, us by workgroups in
-// all): 64 units x 60013 rows, 8 heads: 128: 348, 256: 292, 512: 295, 1024: 306, 4032: 330; 8 x 32768, 4 heads:
-// 128: 29.9, 256: 25.8, 512: 27.8, 1024: 37.8; 1 x 131072: 128: 21.0, 256: 20.4, 512: 26.8; selected keys, whole
-// step: 128 units x 8192: 128: 152, 256: 125, 512: 123.5, 1024: 125.8; 24 x 6250, 8 heads: 120: 56.3, 240: 49.4,
-// 480: 51.0, 792: 57.2.  More units than compute units: several rounds of workgroups, so that the last round is
-// a small part (1536 cost 1 % over 256 where both were possible).
-constexpr int kStreamWgs = 256;
-int stream_chunks_per_unit(int n_units)
-{
-    return n_units <= kStreamWgs ? kStreamWgs / n_units : std::max(1, 6 * kStreamWgs / n_units);
-}
-// Rows per chunk when n rows are cut into at most `chunks` chunks: a multiple of 64 (16 rows a wave and tile).
-int stream_chunk_rows(long long n, int chunks)
-{
-    const long long per = (n + chunks - 1) / chunks;
-    return (int)std::max<long long>(64, (per + 63) / 64 * 64);
-}
 // The matrix-core kernel moves 16 bytes at a time straight to LDS: rows have to start on such a boundary.  (Rows of
 // a caller's tensor that do not go through the vector-ALU kernel, whose loads take any alignment.)
 bool rows_aligned(const void* k, const void* v)
@@ -445,10 +426,8 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     // Its workgroups per unit are shared out over the selected keys (or, where none can be selected, the centroid
     // terms) and the tail by their rows.
     const bool on_matrix = ctx->cfg.kv_format == MP_KV_BF16 && rows_aligned(k_tail, v_tail);
-    const int per_unit = stream_chunks_per_unit(U);
     const int first_max = main_max > 0 ? main_max : (use_mp ? ctx->n_fine + ctx->n_coarse : 0);
-    const int tail_rows = stream_chunk_rows((long long)first_max + n_tail, per_unit);
-    const int first_rows = stream_chunk_rows(first_max, std::max(1, per_unit - ceil_div(n_tail, tail_rows)));
+    const StreamPlan plan = plan_streams(U, first_max, n_tail);
     // order: centroid terms, tail, selected keys -- the longest stream goes last (see the kernel's block mapping)
     // The centroid terms ride along with the selected keys where there are any: shared out over that
     // stream's workgroups they cost each a few per cent more rows, instead of workgroups of their own -- most of
@@ -458,7 +437,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     int terms_src = -1;         // (the terms are the launch's first source: what a rider has to be)
     if (use_mp) {
         const int mp_max = ctx->n_fine + ctx->n_coarse;
-        const int cr = on_matrix ? first_rows : pick_stream_chunk_rows(mp_max, U, 512);
+        const int cr = on_matrix ? plan.first_rows : pick_stream_chunk_rows(mp_max, U, 512);
         terms_src = ns;
         RowSource& r = vp.src[ns++];
         r.K = nullptr; r.V = ctx->Vc; r.unit_rows = ctx->tab_rows; r.rows = ctx->mp_rows; r.rows_stride = ctx->tab_rows;
@@ -466,14 +445,14 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
         r.chunk_rows = cr; r.row0 = 0; r.n_chunks = terms_ride ? 0 : ceil_div(mp_max, cr); chunk0 += r.n_chunks;
     }
     if (n_tail > 0) {
-        const int cr = on_matrix ? tail_rows : pick_stream_chunk_rows(n_tail, U, 512);
+        const int cr = on_matrix ? plan.tail_rows : pick_stream_chunk_rows(n_tail, U, 512);
         RowSource& r = vp.src[ns++];
         r.K = (const uint16_t*)k_tail; r.V = (const uint16_t*)v_tail; r.unit_rows = tail_stride ? tail_stride : n_tail; r.rows = nullptr; r.rows_stride = 0;
         r.count_dev = nullptr; r.count_max = n_tail; r.scores = nullptr; r.chunk0 = chunk0;
         r.chunk_rows = cr; r.row0 = 0; r.n_chunks = ceil_div(n_tail, cr); chunk0 += r.n_chunks;
     }
     if (main_max > 0) {
-        const int crm = on_matrix ? first_rows : pick_stream_chunk_rows(main_max, U, 2048);
+        const int crm = on_matrix ? plan.first_rows : pick_stream_chunk_rows(main_max, U, 2048);
         RowSource& r = vp.src[ns++];
         if (ctx->cfg.kv_format == MP_KV_E4M3) {
             r.K = (const uint16_t*)ctx->Kq; r.V = (const uint16_t*)ctx->Vq; r.row_scale = ctx->kv_scale;

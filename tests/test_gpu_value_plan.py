@@ -31,3 +31,20 @@ def test_coarse_budget_below_the_key_budget(G, kb, cb):
         print(f"G={G} kb={kb} cb={cb} tail={tail}", flush=True)
         compare_decode(ctx, q, K, V, kb, cb, kt, vt, label=f"G={G} kb={kb} cb={cb} tail={tail}")
         ctx.close()
+
+
+@pytest.mark.parametrize("U,G", [(96, 4), (129, 3), (136, 5), (160, 8), (200, 4), (264, 3)])
+def test_unit_counts_that_do_not_divide_the_chip(U, G):
+    from paper_2506_13059_amd import binding as mp
+    from tests.gpu_util import compare_decode
+    from tests.test_gpu_stream import _check
+    for tail in (0, 130):
+        ctx, K, V, q, kt, vt = _ctx(U, G, 1400, 60, 8, 70 + U, tail)
+        print(f"U={U} G={G} tail={tail}", flush=True)
+        for kb in (500, 0):
+            compare_decode(ctx, q, K, V, kb, 700, kt, vt, units=[0, 1, U // 2, U - 2, U - 1], label=f"U={U} G={G} tail={tail} kb={kb}")
+        ctx.close()
+    lse = torch.empty(q.shape[:2], dtype=torch.float32, device="cuda")
+    out = mp.mp_dense_attention(q, K, V, lse=lse)
+    torch.cuda.synchronize()
+    _check(out, lse, q, K, V, f"dense U={U} G={G}")
