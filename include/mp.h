@@ -25,8 +25,8 @@
  *   - head_dim must be 128.  1 <= G <= 8.
  *   - Inputs are meant to be finite.  An infinite value (v, v_tail; bf16 rows) makes that dimension of the outputs that
  *     attend it with a probability above zero infinite (NaN where both signs meet, where a value is NaN, or where the
- *     probability is too small for fp32), and leaves the other dimensions alone.  Rows of a caller's tensors that do not
- *     start on 16 bytes may give NaN instead.  Queries and keys that are not finite give unspecified outputs, no error.
+ *     probability is too small for fp32), and leaves the other dimensions alone.  Queries and keys that are not finite
+ *     give unspecified outputs, no error.
  *   - A context may be used from one host thread at a time; calls on the same context that
  *     overlap on the GPU (different streams without ordering) race on its workspace.
  */

@@ -82,6 +82,13 @@ __device__ __forceinline__ void load_vrow(RowRegs& t, const uint16_t* __restrict
     }
 }
 
+// (a row past the end repeats one that may hold an infinity: its probability is zero, and so has to be its product)
+__device__ __forceinline__ void clear_vrow(RowRegs& t)
+{
+    t.vlo = make_uint4(0, 0, 0, 0);
+    t.vhi = make_uint4(0, 0, 0, 0);
+}
+
 template <int G>
 struct HeadState {
     float m[G];
@@ -379,6 +386,8 @@ __device__ __forceinline__ void stream_rows(HeadState<G>& st, const RowSource& S
             RowRegs t0, t1;
             load_vrow<kWide>(t0, Vb, ia, c);
             load_vrow<kWide>(t1, Vb, ib, c);
+            if (!va) clear_vrow(t0);
+            if (!vb) clear_vrow(t1);
             float s0[G], s1[G];
 #pragma unroll
             for (int h = 0; h < G; ++h) {
@@ -389,6 +398,7 @@ __device__ __forceinline__ void stream_rows(HeadState<G>& st, const RowSource& S
         }
     } else {
         const uint16_t* __restrict__ Kb = S.K + (long long)u * S.unit_rows * kHeadDim;
+        const uint16_t* past_end = p.q + (long long)u * gt * kHeadDim;
         uint4 qlo[G], qhi[G];
 #pragma unroll
         for (int h = 0; h < G; ++h) {
@@ -423,9 +433,13 @@ __device__ __forceinline__ void stream_rows(HeadState<G>& st, const RowSource& S
                     const long long i0 = __shfl(src_reg, slot & 63, 64);
                     const long long i1 = __shfl(src_reg, (slot + 8) & 63, 64);
                     const uint4* k0 = reinterpret_cast<const uint4*>(Kb + i0 * kHeadDim) + c;
-                    const uint4* v0 = reinterpret_cast<const uint4*>(Vb + i0 * kHeadDim) + c;
                     const uint4* k1 = reinterpret_cast<const uint4*>(Kb + i1 * kHeadDim) + c;
-                    const uint4* v1 = reinterpret_cast<const uint4*>(Vb + i1 * kHeadDim) + c;
+                    // (a row past the end has probability zero, and its values have to be finite: those of the query, which
+                    // is at hand)
+                    const uint16_t* r0 = j0 + slot < w1 ? Vb + i0 * kHeadDim : past_end;
+                    const uint16_t* r1 = j0 + slot + 8 < w1 ? Vb + i1 * kHeadDim : past_end;
+                    const uint4* v0 = reinterpret_cast<const uint4*>(r0) + c;
+                    const uint4* v1 = reinterpret_cast<const uint4*>(r1) + c;
                     issue_load16<kOnce>(b[0], k0);
                     issue_load16<kOnce>(b[1], k0 + 8);
                     issue_load16<kOnce>(b[2], v0);
