@@ -205,7 +205,7 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     ctx->max_blocks = std::max(4, c.block_w > 0 ? c.max_tokens / c.block_w + 2 : 2);
     ctx->Pcap = mp::max_stream_chunks(ctx->Ncap, ctx->U, 2048) + mp::max_stream_chunks(std::max(ctx->Tcap, 1), ctx->U, 512) +
                 mp::max_stream_chunks((int)ctx->tab_rows, ctx->U, 512);
-    ctx->Pcap = std::max(ctx->Pcap, 2 * mp::stream_chunks_per_unit(ctx->U) + 2);      // (selected keys or terms, and the tail)
+    ctx->Pcap = std::max(ctx->Pcap, mp::most_stream_chunks(ctx->U) + 1);
 
     hipError_t e = hipGetDevice(&ctx->device);
     if (e == hipSuccess) e = mp::resolve_static_scratch();
@@ -769,7 +769,7 @@ mp_status dense_impl(const char* who, const void* q, const void* k, const void* 
     if (on_matrix) {
         // as many chunks as the kernel wants, or as the stated workspace has room for (not the one at hand: results do
         // not depend on its size)
-        dcr = stream_chunk_rows(n, std::min(stream_chunks_per_unit(U), ceil_div(n > 0 ? n : 1, dcr)));
+        dcr = plan_streams(U, n, 0, ceil_div(n > 0 ? n : 1, dcr)).first_rows;
     }
     p.chunks_per_unit = ceil_div(n > 0 ? n : 1, dcr);
     p.src[0].chunk_rows = dcr;

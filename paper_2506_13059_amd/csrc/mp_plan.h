@@ -25,19 +25,16 @@ inline int most_selected(int levels, int key_budget, int coarse_budget, int n_to
 // 480: 51.0, 792: 57.2.
 //
 // Two thirds of the compute units are enough (170 workgroups reach what 256 do), a few more workgroups than compute units
-// are not (some then have two, and these are the call's time).  So: as many per unit as fit one round, if that fills two
-// thirds of it, else as many as fit two (both resident at once).  Dense, 32768 rows, 4 heads, us by workgroups per unit:
-// 86 units 2: 222, 3: 305, 5: 214; 96: 2: 243, 3: 314, 4: 252; 129: 1: 389, 2: 461, 3: 330; 144: 1: 398, 2: 465, 3: 353;
-// 160: 1: 415, 2: 486, 3: 392; 176: 1: 438, 2: 508; 192: 1: 476, 2: 509.
+// are not (some then have two, and these are the call's time).  So: as many per unit as fit one round, unless two rounds
+// (both resident at once) leave no more than three quarters of its rows to the busiest compute unit: 129 to 170 units,
+// and others where a long tail makes the shares uneven.  Dense, 32768 rows, 4 heads, us by
+// workgroups per unit: 86 units 2: 222, 3: 305, 5: 214; 96: 2: 243, 3: 314, 4: 252; 129: 1: 389, 2: 461, 3: 330; 144: 1:
+// 398, 2: 465, 3: 353; 160: 1: 415, 2: 486, 3: 392; 176: 1: 438, 2: 508; 192: 1: 476, 2: 509.
 // More units than compute units: the count (of up to six rounds) whose last round is fullest; 264 units 1: 883, 2: 756,
 // 3: 714, 5: 707; 320: 2: 793, 3: 778, 4: 816.
 constexpr int kStreamWgs = 256;
-inline int stream_chunks_per_unit(int n_units)
+inline int fullest_rounds(int n_units)
 {
-    if (n_units <= kStreamWgs) {
-        const int one = kStreamWgs / n_units;
-        return 3 * one * n_units >= 2 * kStreamWgs ? one : 2 * kStreamWgs / n_units;
-    }
     int best = 1;
     double best_fill = 0.0;
     for (int c = 1; c == 1 || (long long)c * n_units <= 6 * kStreamWgs; ++c) {
@@ -51,6 +48,12 @@ inline int stream_chunks_per_unit(int n_units)
     return best;
 }
 
+// Most chunks a unit's rows are cut into (a short stream's chunk on top: one more).
+inline int most_stream_chunks(int n_units)
+{
+    return n_units <= kStreamWgs ? 2 * kStreamWgs / n_units : fullest_rounds(n_units);
+}
+
 // Rows per chunk when n rows are cut into at most `chunks` chunks of about the same size: a multiple of 64 (16 rows a wave
 // and tile).
 inline int stream_chunk_rows(long long n, int chunks)
@@ -59,16 +62,48 @@ inline int stream_chunk_rows(long long n, int chunks)
     return (int)std::max<long long>(64, (per + 63) / 64 * 64);
 }
 
-// Rows per chunk of the selected keys (or centroid terms) and of the tail.  Chunks of both are about the same length, in
-// all one more than the count above at most: a short tail is one short chunk and takes none away from the keys.  (It took
-// one of two from units 86 to 128, and both streams had one chunk each: 96 units, 2048 keys, tail of 130, 4 heads, whole
-// step 57 us, now 42.)  Each stream's chunks are cut evenly, so that a short one's rows are spread over its four waves.
+// Rows of the longest chunk when two streams are cut into `chunks` chunks together.  A stream of up to half a chunk is one
+// chunk on top of them and takes none away from the other.
+inline int longest_chunk(long long first, long long tail, int chunks)
+{
+    const int of_first = stream_chunk_rows(first, chunks), of_tail = stream_chunk_rows(tail, chunks);
+    if (2 * tail <= of_first) return of_first;
+    if (2 * first <= of_tail) return of_tail;
+    if (chunks == 1) return std::max(of_first, of_tail);
+    const int share = (int)(chunks * first / (first + tail));
+    int best = 0;
+    for (int k = std::max(1, share); k <= std::max(1, share) + 1 && k < chunks; ++k) {
+        const int rows = std::max(stream_chunk_rows(first, k), stream_chunk_rows(tail, chunks - k));
+        if (best == 0 || rows < best) best = rows;
+    }
+    return best ? best : std::max(stream_chunk_rows(first, chunks - 1), stream_chunk_rows(tail, 1));
+}
+
+// Rows per chunk of the selected keys (or centroid terms, or a dense call's keys) and of the tail; `most` limits the chunks
+// of each.  (A short tail took one of two chunks from units 86 to 128: 96 units, 2048 keys, tail of 130, 4 heads, whole
+// step 57 us, now 42.  A third chunk of the same length for it is as bad where it is long: 96 units, 512 keys, tail of 1500,
+// 1 head 43.4 -> 38 us.)  Each stream's chunks are cut evenly, so that a short one's rows are spread over its four waves.
 struct StreamPlan {
     int first_rows, tail_rows;
 };
-inline StreamPlan plan_streams(int n_units, long long first, long long tail)
+inline StreamPlan plan_streams(int n_units, long long first, long long tail, int most = 1 << 20)
 {
-    const int rows = stream_chunk_rows(first + tail, stream_chunks_per_unit(n_units));
+    int rows = 0;
+    if (n_units > kStreamWgs) {
+        rows = longest_chunk(first, tail, std::min(most, fullest_rounds(n_units)));
+    } else {
+        long long best = 0;      // rows of the busiest compute unit
+        for (int r = 1; r <= 2; ++r) {
+            const int t = longest_chunk(first, tail, std::min(most, r * kStreamWgs / n_units));
+            // (a stream of up to half a chunk does not count)
+            const long long chunks = (2 * first > t ? (first + t - 1) / t : 0) + (2 * tail > t ? (tail + t - 1) / t : 0);
+            const long long busiest = (chunks * n_units + kStreamWgs - 1) / kStreamWgs * t;
+            if (r == 1 || 4 * busiest <= 3 * best) {
+                rows = t;
+                best = busiest;
+            }
+        }
+    }
     auto even = [&](long long n) { return stream_chunk_rows(n, (int)std::max<long long>(1, (n + rows - 1) / rows)); };
     return StreamPlan{even(first), even(tail)};
 }
