@@ -764,9 +764,10 @@ mp_status dense_impl(const char* who, const void* q, const void* k, const void* 
     p.q = (const uint16_t*)q;
     p.partials = partials;
     p.n_units = U;
-    const bool on_matrix = rows_aligned(k, v);
+    const bool short_call = short_dense_on_vector_alu(G, U, n);
+    const bool on_matrix = rows_aligned(k, v) && !short_call;
     int dcr = pick_chunk_rows(n, U);
-    if (on_matrix) {
+    if (on_matrix || short_call) {
         // as many chunks as the kernel wants, or as the stated workspace has room for (not the one at hand: results do
         // not depend on its size)
         dcr = plan_streams(U, n, 0, ceil_div(n > 0 ? n : 1, dcr)).first_rows;

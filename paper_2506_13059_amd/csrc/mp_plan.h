@@ -108,4 +108,14 @@ inline StreamPlan plan_streams(int n_units, long long first, long long tail, int
     return StreamPlan{even(first), even(tail)};
 }
 
+// Dense calls of one or two heads to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one
+// chain of latencies, and its chain is shorter: no staging in LDS, and the work of an epilogue grows with the heads.  Us
+// on the device, here / matrix cores, 1 head: 1 unit x 8192 rows 9.4 / 10.2, 8 x 2000 10.9 / 11.6, 64 x 500 11.6 / 12.4, 128 x
+// 500 13.2 / 14.1; 2 heads: 8 x 500 11.1 / 11.3, 64 x 500 12.1 / 12.7, 100 x 500 12.5 / 13.9; at 131072 rows in all the two meet
+// (64 x 2000 16.1 / 16.6, 128 x 2000 26.8 / 27.6; 32 x 8192, 1 head 28.1 / 26.4), and with three heads the matrix cores win.
+inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
+{
+    return group <= 2 && n_units * n <= 131072;
+}
+
 }  // namespace mp

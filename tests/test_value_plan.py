@@ -19,10 +19,12 @@ extern "C" void plan(int units, long long first, long long tail, int most, int* 
     out[0] = p.first_rows;
     out[1] = p.tail_rows;
 }}
+extern "C" int short_dense(int group, int units, long long n) {{ return mp::short_dense_on_vector_alu(group, units, n); }}
 extern "C" int most_selected(int levels, int kb, int cb, int n) {{ return mp::most_selected(levels, kb, cb, n); }}
 ''')
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", str(so), str(src)])
     h = ctypes.CDLL(str(so))
+    h.short_dense.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
     h.plan.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
     return h
 
@@ -90,3 +92,7 @@ def test_a_long_tail_does_not_spill_into_a_second_round(lib):
             # the long chunks fit one round, or fill more than half of the second
             assert long_ones <= 256 or long_ones > 340, (units, first, tail, a, b)
 
+
+def test_dense_calls_on_the_vector_alu(lib):
+    assert lib.short_dense(1, 1, 8192) and lib.short_dense(2, 128, 500) and lib.short_dense(2, 64, 2048)
+    assert not lib.short_dense(3, 1, 100) and not lib.short_dense(1, 64, 2049) and not lib.short_dense(2, 128, 1 << 40)
