@@ -56,3 +56,10 @@ def test_kernels_in_turn_on_one_context():
             assert torch.equal(a, b)
         other.close()
     one.close()
+
+
+@pytest.mark.parametrize("k,n,distinct", [(300, 3000, 1), (512, 3000, 3), (512, 1100, 40)])
+def test_few_points_to_a_workgroup(k, n, distinct):
+    # one unit: every workgroup has a chunk or two, the exact decisions of its points are shared by waves without points
+    ctx, _, _ = _run_case(1, 1, 1, n, 4, 1, k, 0, 0, 0, iters=2, seed=24 + distinct, distinct_rows=distinct)
+    ctx.close()
