@@ -24,6 +24,7 @@
 #include "mp_device.h"
 #include "mp_internal.h"
 #include "mp_margin.h"
+#include "mp_plan.h"
 
 namespace mp {
 
@@ -670,9 +671,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kLevelMaxK = 256;
-constexpr int kLevelMaxPts = 512;
-
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
 {
@@ -990,13 +988,6 @@ static size_t coarse_level_smem(int max_pts, int max_k)
     return k_cap * 260 + n_cap * 6;
 }
 
-// (Beyond that one workgroup per block takes longer than the separate launches, which spread a block over the chip:
-// refreshes of 64 blocks of 256 .. 1100 points average 1133 us with the line at 512 points, 1181 with it at 1024.)
-bool coarse_level_fits(int max_pts, int max_k)
-{
-    return max_pts >= 1 && max_pts <= kLevelMaxPts && max_k >= 1 && max_k <= kLevelMaxK;
-}
-
 template <int kW>
 static hipError_t launch_coarse_waves(const CoarseLevel& p, int nb, int U, size_t smem, hipStream_t s)
 {
@@ -1014,7 +1005,7 @@ static hipError_t launch_coarse_waves(const CoarseLevel& p, int nb, int U, size_
 hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int max_k, hipStream_t s)
 {
     if (nb <= 0 || U <= 0) return hipSuccess;
-    if (!coarse_level_fits(max_pts, max_k) || p.iters < 1) return hipErrorInvalidValue;
+    if (max_pts < 1 || max_pts > kLevelMaxPts || max_k < 1 || max_k > kLevelMaxK || p.iters < 1) return hipErrorInvalidValue;
     p.k_cap = (max_k + kRowTile - 1) / kRowTile * kRowTile;
     p.n_cap = (max_pts + 3) / 4 * 4;
     // Sixteen waves where every pair has a compute unit of its own (a pair's time is what counts then: 104 against 132 us

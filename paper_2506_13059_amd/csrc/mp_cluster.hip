@@ -17,6 +17,7 @@
 #include "mp_ctx.h"
 #include "mp_device.h"
 #include "mp_internal.h"
+#include "mp_plan.h"
 
 namespace mp {
 
@@ -395,7 +396,7 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
     const int kf = r.f1 - r.f0, kc = r.c1 - r.c0;
     const int32_t* bdev_c = ctx->blocks_dev + 8 * (size_t)ctx->max_blocks;
     const long long Fcap = ctx->Fcap, Ccap1 = std::max(ctx->Ccap, 1);
-    if (two && coarse_level_fits(max_kf, max_kc)) {
+    if (two && coarse_level_fits((long long)nb * U, max_kf, max_kc)) {
         CoarseLevel cl{};
         cl.X = ctx->km_Cf; cl.x_unit_rows = Fcap; cl.blocks = bdev_c; cl.f0 = r.f0; cl.iters = coarse_iters;
         cl.old_end = old_c_end; cl.seeds = ctx->km_seed_c; cl.seed_stride = Ccap1; cl.seed_x0 = seed_f0;
@@ -406,7 +407,7 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
                            (long long)ctx->Ncap, 0, r.n_pts, ctx->km_newid, Fcap, ctx->km_assign, (long long)ctx->Ncap, 0);
         MP_HIPC(hipGetLastError());
     } else if (two) {
-        // (more clusters than one workgroup takes: a launch per step)
+        // (more clusters than one workgroup does in less time: a launch per step)
         if (old_c_end > r.c0) {
             hipLaunchKernelGGL(gather1_rows_kernel, dim3(blocks_for((long long)(old_c_end - r.c0) * 16, 256), U), dim3(256), 0, s,
                                (const uint4*)ctx->Kc, ctx->tab_rows, ctx->Fcap + r.c0, nullptr, 0, 0, old_c_end - r.c0,

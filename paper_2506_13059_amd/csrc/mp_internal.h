@@ -166,7 +166,6 @@ struct CoarseLevel {
     int fcap;
     int k_cap, n_cap;            // (set by the launch)
 };
-bool coarse_level_fits(int max_pts, int max_k);
 hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int max_k, hipStream_t s);
 hipError_t launch_histogram(const int32_t* ids, long long ids_stride, int n, int U, int32_t* cnt,
                             long long cnt_stride, hipStream_t s);

@@ -1,5 +1,4 @@
-// Sizes that the value pass's launch is planned with: plain host functions of the call's sizes, so that they can be checked
-// without a GPU.
+// How launches are planned: plain host functions of the call's sizes, so that they can be checked without a GPU.
 #pragma once
 
 #include <algorithm>
@@ -116,6 +115,26 @@ inline StreamPlan plan_streams(int n_units, long long first, long long tail, int
 inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
 {
     return group <= 2 && n_units * n <= 131072;
+}
+
+// Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one
+// workgroup per pair, or in a launch per step.  The workgroup's time grows with its clusters (each is one wave's walk over
+// all points and a trip to memory, sixteen or eight waves) and points, that of the steps with their number and, beyond one
+// round of workgroups, the pairs.  Whole build of ten iterations, one launch / steps, us:
+//   1 pair     256 points x 32: 552 / 627,   x 64: 576 / 572,   x 256: 864 / 472;   512 x 32: 789 / 818, x 64: 865 / 732
+//   64 pairs   160 points x 64: 595 / 612,   x 96: 620 / 603;   256 x 48: 761 / 851, x 64: 804 / 831, x 96: 814 / 795;
+//              512 x 48: 1328 / 1408,        x 64: 1437 / 1392, x 256: 1754 / 1295
+//   256 pairs  256 points x 96: 1352 / 1437, x 256: 1577 / 1586; 512 x 48: 2499 / 2682, x 128: 2683 / 2658
+//   1024 pairs 256 points x 64: 5035 / 5092, x 128: 5462 / 5428; 512 x 48: 8509 / 8640, x 64: 8983 / 8688
+// More than 512 points always take the steps (refreshes of 64 blocks of 256 .. 1100 points average 1133 us with the line
+// at 512 points, 1181 with it at 1024).
+constexpr int kLevelMaxPts = 512;
+constexpr int kLevelMaxK = 101;          // (the most the lines below admit, with no more clusters than points)
+inline bool coarse_level_fits(long long pairs, int max_pts, int max_k)
+{
+    if (max_pts < 1 || max_k < 1 || max_pts > kLevelMaxPts || max_k > kLevelMaxK) return false;
+    if (max_k < 64 || max_pts * max_k <= 10240) return true;
+    return max_pts <= 256 && max_k <= (pairs >= 192 ? 96 : pairs >= 32 ? 64 : 0);
 }
 
 }  // namespace mp

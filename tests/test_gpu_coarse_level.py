@@ -1,6 +1,7 @@
-"""GPU parity of the coarse level in one launch at its edges: chunks of 64 points, tiles of 16 centroids, slots of sixteen
-tiles, its limits of 512 points and 256 centroids a block (one more takes the launch-per-step path), sixteen waves up to
-256 (block, unit) pairs and eight beyond, and degenerate inputs.  Every result is bit-identical to the oracle's."""
+"""GPU parity of the coarse level in one launch at its edges: chunks of 64 points, tiles of 16 centroids, its limits (512
+points, 63 centroids, or more of them over few points; one more takes the launch-per-step path, which the larger cases
+are for), sixteen waves up to 256 (block, unit) pairs and eight beyond, and degenerate inputs.  Every result is
+bit-identical to the oracle's."""
 import pytest
 
 from tests.test_gpu_kmeans import _run_case
@@ -13,6 +14,19 @@ pytestmark = pytest.mark.gpu
 def test_edges(nf, nc):
     print(f"nf={nf} nc={nc}", flush=True)
     ctx, _, _ = _run_case(1, 2, 2, nf + 300, max(2, nf // 3), 2, nf, nc, 0, 0, iters=3, seed=500 + nf + nc)
+    ctx.close()
+
+
+@pytest.mark.parametrize("nf,nc", [(512, 63), (512, 64), (160, 64), (161, 64), (101, 101), (102, 102), (255, 40)])
+def test_limits(nf, nc):
+    print(f"nf={nf} nc={nc}", flush=True)
+    ctx, _, _ = _run_case(1, 2, 2, nf + 300, max(2, nf // 3), 2, nf, nc, 0, 0, iters=3, seed=700 + nf + nc)
+    ctx.close()
+
+
+def test_limits_of_many_pairs():
+    # 32 pairs take up to 64 centroids over 256 points
+    ctx, _, _ = _run_case(8, 4, 4, 700, 90, 2, 250, 64, 0, 0, iters=2, seed=53)
     ctx.close()
 
 

@@ -1,4 +1,4 @@
-"""How the value pass's launch is planned: the header's functions, compiled for the host."""
+"""How launches are planned: the header's functions, compiled for the host."""
 import ctypes
 import os
 import subprocess
@@ -20,10 +20,12 @@ extern "C" void plan(int units, long long first, long long tail, int most, int* 
     out[1] = p.tail_rows;
 }}
 extern "C" int short_dense(int group, int units, long long n) {{ return mp::short_dense_on_vector_alu(group, units, n); }}
+extern "C" int coarse_level(long long pairs, int pts, int k) {{ return mp::coarse_level_fits(pairs, pts, k); }}
 extern "C" int most_selected(int levels, int kb, int cb, int n) {{ return mp::most_selected(levels, kb, cb, n); }}
 ''')
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", str(so), str(src)])
     h = ctypes.CDLL(str(so))
+    h.coarse_level.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     h.short_dense.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
     h.plan.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
     return h
@@ -96,3 +98,14 @@ def test_a_long_tail_does_not_spill_into_a_second_round(lib):
 def test_dense_calls_on_the_vector_alu(lib):
     assert lib.short_dense(1, 1, 8192) and lib.short_dense(2, 128, 500) and lib.short_dense(2, 64, 2048)
     assert not lib.short_dense(3, 1, 100) and not lib.short_dense(1, 64, 2049) and not lib.short_dense(2, 128, 1 << 40)
+
+
+def test_coarse_level_in_one_launch_only_where_it_is_the_faster_way(lib):
+    # (pairs, points, clusters): measured on both sides of every line
+    for case in ((1, 512, 32), (64, 256, 48), (64, 160, 64), (1, 64, 64), (64, 256, 64), (256, 256, 96), (1024, 512, 48), (1, 1, 1)):
+        assert lib.coarse_level(*case), case
+    for case in ((1, 256, 64), (1, 512, 64), (1, 256, 256), (64, 160, 96), (64, 512, 64), (1024, 512, 64), (256, 512, 128), (1, 513, 16),
+                 (64, 256, 96), (1, 0, 0)):
+        assert not lib.coarse_level(*case), case
+    # the kernel's arrays are made for this many
+    assert max(k for k in range(1, 513) for pts in (k, 256, 512) if pts >= k and lib.coarse_level(1 << 20, pts, k)) == 101
