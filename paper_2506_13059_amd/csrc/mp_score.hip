@@ -22,9 +22,9 @@
 // in the linear domain (same order as its logarithm, the rank key the getters report).  Selection =
 // "take clusters in descending score order (ties: lower id) while the running token count stays
 // within the budget, stop at the first that does not fit"; token counts are positive, so this is a
-// threshold on (score, id): one 256-bucket histogram over the leading bits of the score and a direct
-// comparison among the entries of the boundary bucket (a most-significant-digit radix search takes
-// over where that bucket is crowded).
+// threshold on (score, id): a 256-bucket histogram over the leading bits of the score and a direct
+// comparison among the entries of the boundary bucket (where that bucket is crowded the register path
+// divides it by up to two more digits; a most-significant-digit radix search takes over behind both).
 //
 // A level of at most lds_cap entries takes the register path (fast_level): its per-entry values live in
 // registers, the candidate list and the compact list of selected clusters in LDS, and its barriers wait for LDS
@@ -405,7 +405,6 @@ __device__ __forceinline__ double same_head(double x, Op op)
     return across_rows<32>(x, op);
 }
 struct MaxOp { __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); } };
-struct MinOp { __device__ __forceinline__ double operator()(double a, double b) const { return fmin(a, b); } };
 struct AddOp { __device__ __forceinline__ double operator()(double a, double b) const { return a + b; } };
 // Sum over the wave; every lane receives it.
 __device__ __forceinline__ uint32_t wave_total_u32(uint32_t v)
@@ -420,25 +419,11 @@ __device__ __forceinline__ uint32_t wave_total_u32(uint32_t v)
     exchange_u32<32>(v, a, b);
     return a + b;
 }
-// Combination over aligned groups of 8 lanes.
-template <typename Op>
-__device__ __forceinline__ double eight_lanes(double x, Op op)
-{
-    x = op(x, dpp_f64<kDppXor1>(x));
-    x = op(x, dpp_f64<kDppXor2>(x));
-    return op(x, dpp_f64<kDppHalfMirror>(x));
-}
 // The value lane t of each group of four holds.
 template <int t>
 __device__ __forceinline__ uint32_t quad_lane(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, t * 0x55, 0xf, 0xf, true);
-}
-__device__ __forceinline__ double uniform_f64(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll)), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 // Largest value over the 16 lanes of a wave that own the same head (lanes equal modulo 4).
 __device__ __forceinline__ double max_same_head(double x) { return same_head(x, MaxOp{}); }
@@ -490,16 +475,90 @@ __device__ __forceinline__ void emit_term(const ScoreParams& p, const Arrays& A,
     for (int h = 0; h < G; ++h) p.mp_scores[o * G + h] = (float)(A.lg[h * A.lg_stride + i] * 1.4426950408889634) + lgN;
 }
 
+// The bucket of a histogram (entry count << 40 | token count each) in which the running token count, `before` to start
+// with, passes the budget; what lies before that bucket and how many entries it holds.  Every wave scans the histogram
+// for itself, kHistBuckets / 64 buckets per lane.
+struct Boundary {
+    uint32_t before, entries, bucket;
+};
+__device__ __forceinline__ Boundary find_boundary(const unsigned long long* hist, uint32_t before, uint32_t budget)
+{
+    constexpr unsigned long long kWtMask = (1ull << 40) - 1;
+    constexpr int BPL = kHistBuckets / 64;
+    const int lane = threadIdx.x & 63;
+    unsigned long long hb[BPL];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < BPL; ++i) {
+        hb[i] = hist[BPL * lane + i];
+        sum += (uint32_t)(hb[i] & kWtMask);
+    }
+    const uint32_t incl = before + wave_incl_scan_u32(sum);
+    const unsigned long long crossing = __ballot((unsigned long long)incl > budget);
+    const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
+    uint32_t a = incl - sum, d = BPL * lane, cn = 0;
+    bool done = false;
+#pragma unroll
+    for (int i = 0; i < BPL; ++i) {
+        const uint32_t wi = (uint32_t)(hb[i] & kWtMask);
+        if (!done) {
+            if ((unsigned long long)a + wi > budget) {
+                d = BPL * lane + i;
+                cn = (uint32_t)(hb[i] >> 40);
+                done = true;
+            } else {
+                a += wi;
+            }
+        }
+    }
+    return Boundary{(uint32_t)__builtin_amdgcn_readlane((int)a, first), (uint32_t)__builtin_amdgcn_readlane((int)cn, first),
+                    (uint32_t)__builtin_amdgcn_readlane((int)d, first)};
+}
+
+// The flat list of stored rows of the selected clusters, from (first stored row, count) and offset of each: one row of 16
+// lanes per cluster, the next cluster's entry fetched early.
+__device__ __forceinline__ void expand_rows(const ScoreParams& p, int u, const int2* sel_rc, const int32_t* sel_off, uint32_t n_sel)
+{
+    const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;
+    int32_t* ro = p.rows + (long long)u * p.rows_stride;
+    int32_t* so = p.row_slot ? p.row_slot + (long long)u * p.rows_stride : nullptr;   // compact slot of each row's cluster
+    int2 rc_n = make_int2(0, 0);
+    int off_n = 0;
+    if ((uint32_t)grp < n_sel) {
+        rc_n = sel_rc[grp];
+        off_n = sel_off[grp];
+    }
+    for (uint32_t k = grp; k < n_sel; k += kThreads / 16) {
+        const int2 rc = rc_n;
+        const int off = off_n;
+        const uint32_t kn = k + kThreads / 16;
+        if (kn < n_sel) {
+            rc_n = sel_rc[kn];
+            off_n = sel_off[kn];
+        }
+        for (int i = sub; i < rc.y; i += 16) ro[off + i] = rc.x + i;
+        if (so)
+            for (int i = sub; i < rc.y; i += 16) so[off + i] = (int32_t)k;
+    }
+}
+__device__ __forceinline__ void write_counters(const ScoreParams& p, int u, uint32_t total, uint32_t n_terms, int n_f, bool two)
+{
+    if (threadIdx.x != 0) return;
+    p.n_rows[u] = (int32_t)total;
+    p.n_mp[u] = (int32_t)n_terms;
+    p.counters[4 * u + 0] = (int32_t)total + p.n_tail;
+    p.counters[4 * u + 1] = n_f;
+    if (!two) p.counters[4 * u + 2] = 0;
+    p.counters[4 * u + 3] = (int32_t)n_terms;
+}
+
 // One level: logits, Eq. 1 normaliser, scores, budgeted selection.
 // Entry x stands for cluster id (use_ids ? A.ids[x] : x).  `with_behind`: the normaliser also covers
-// the coarse clusters that stayed behind (S.bm / S.bs).  `meanwhile` runs (in every thread) once the
-// level's centroid rows have been asked for: work of the previous level that the requests did not
-// have to wait for.  `q_pending`: the
-// query operand still has to go to LDS (first level of the launch; qv = this thread's element).
-// `quiet`: store nothing in global memory (shadow workgroup); `reverse`: ask for the rows last round
-// first.  On return A holds logits, keys, member counts (0 = takes no part), row starts and flags,
-// all published by a barrier.  Returns 1 if the keys are linear-domain scores, 0 if they are
-// logarithmic rank keys (the rare case of scores below the range of a double).
+// the coarse clusters that stayed behind (S.bm / S.bs).  `q_pending`: the query operand still has to go
+// to LDS (first level of the launch; qv = this thread's element).  On return A holds logits, keys,
+// member counts (0 = takes no part), row starts and flags, all published by a barrier.  Returns 1 if
+// the keys are linear-domain scores, 0 if they are logarithmic rank keys (the rare case of scores
+// below the range of a double).
 // What a level keeps of its own entries after the selection: the shift per head, and for the first
 // kKeep chunks of kThreads entries the member count and e^{l - shift} of this thread's entry.
 template <int G>
@@ -762,7 +821,6 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
     const uint64_t kmin = S.key_min, kmax = S.key_max;
     const uint32_t total = S.key_total;
     const uint32_t bud = budget < 0 ? 0u : (budget > 0xffffffffll ? 0xffffffffu : (uint32_t)budget);
-    constexpr unsigned long long kWtMask = (1ull << 40) - 1;
     if (total <= bud) {
         for (int c = 0; c < chunks; ++c) {
             const int i = tid + c * kThreads;
@@ -782,36 +840,8 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
             if (w) atomicAdd(&L.hist[(uint32_t)((A.keys[i] - kmin) >> shift)], (1ull << 40) | w);
         }
         __syncthreads();
-        // every wave scans the histogram for itself: kHistBuckets / 64 buckets per lane
-        constexpr int BPL = kHistBuckets / 64;
-        unsigned long long hb[BPL];
-        uint32_t sum = 0;
-#pragma unroll
-        for (int j = 0; j < BPL; ++j) {
-            hb[j] = L.hist[BPL * lane + j];
-            sum += (uint32_t)(hb[j] & kWtMask);
-        }
-        const uint32_t incl = wave_incl_scan_u32(sum);
-        const unsigned long long crossing = __ballot((unsigned long long)incl > bud);
-        const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
-        uint32_t a = incl - sum, d = BPL * lane, cn = 0;
-        bool done = false;
-#pragma unroll
-        for (int j = 0; j < BPL; ++j) {
-            const uint32_t wj = (uint32_t)(hb[j] & kWtMask);
-            if (!done) {
-                if ((unsigned long long)a + wj > bud) {
-                    d = BPL * lane + j;
-                    cn = (uint32_t)(hb[j] >> 40);
-                    done = true;
-                } else {
-                    a += wj;
-                }
-            }
-        }
-        const uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)a, first);
-        const uint32_t bcnt = (uint32_t)__builtin_amdgcn_readlane((int)cn, first);
-        const uint32_t bstar = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+        const Boundary at = find_boundary(L.hist, 0, bud);
+        const uint32_t acc = at.before, bcnt = at.entries, bstar = at.bucket;
         if (bcnt <= (uint32_t)kListCap) {
             // entries before the boundary bucket are taken, entries behind it are not; those inside it
             // (often one: the first that does not fit) queue up to be ordered by (key, position)
@@ -1009,36 +1039,8 @@ __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays
     const uint32_t total = sc.carry_a, n_sel = sc.carry_b & 0xffffu;
     n_terms += sc.carry_b >> 16;
     __syncthreads();
-    // expansion: one row of 16 lanes per selected cluster, the next cluster's entry fetched early
-    int32_t* ro = p.rows + (long long)u * p.rows_stride;
-    int32_t* so = p.row_slot ? p.row_slot + (long long)u * p.rows_stride : nullptr;   // compact slot of each row's cluster
-    const int grp = tid >> 4, sub = tid & 15;
-    int2 rc_n = make_int2(0, 0);
-    int off_n = 0;
-    if ((uint32_t)grp < n_sel) {
-        rc_n = sel_rc[grp];
-        off_n = sel_off[grp];
-    }
-    for (uint32_t k = grp; k < n_sel; k += kThreads / 16) {
-        const int2 rc = rc_n;
-        const int off = off_n;
-        const uint32_t kn = k + kThreads / 16;
-        if (kn < n_sel) {
-            rc_n = sel_rc[kn];
-            off_n = sel_off[kn];
-        }
-        for (int j = sub; j < rc.y; j += 16) ro[off + j] = rc.x + j;
-        if (so)
-            for (int j = sub; j < rc.y; j += 16) so[off + j] = (int32_t)k;
-    }
-    if (tid == 0) {
-        p.n_rows[u] = (int32_t)total;
-        p.n_mp[u] = (int32_t)n_terms;
-        p.counters[4 * u + 0] = (int32_t)total + p.n_tail;
-        p.counters[4 * u + 1] = n_f;
-        if (!two) p.counters[4 * u + 2] = 0;
-        p.counters[4 * u + 3] = (int32_t)n_terms;
-    }
+    expand_rows(p, u, sel_rc, sel_off, n_sel);
+    write_counters(p, u, total, n_terms, n_f, two);
 }
 
 // ================================================================================================
@@ -1396,46 +1398,12 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
 
     // ---------------- budgeted selection ----------------
     const uint32_t bud = budget < 0 ? 0u : (budget > 0xffffffffll ? 0xffffffffu : (uint32_t)budget);
-    constexpr unsigned long long kWtMask = (1ull << 40) - 1;
     if (total <= bud) {
 #pragma unroll
         for (int c = 0; c < kFastChunks; ++c) st.take[c] = st.w[c] != 0;
     } else {
-        // The bucket in which the running token count passes the budget, what lies before it and how many it holds: every
-        // wave scans the histogram for itself, kHistBuckets / 64 buckets per lane.
-        uint32_t acc = 0, bcnt = 0, bstar = 0;
-        auto find_boundary = [&](const unsigned long long* hist) {
-            constexpr int BPL = kHistBuckets / 64;
-            unsigned long long hb[BPL];
-            uint32_t sum = 0;
-#pragma unroll
-            for (int i = 0; i < BPL; ++i) {
-                hb[i] = hist[BPL * lane + i];
-                sum += (uint32_t)(hb[i] & kWtMask);
-            }
-            const uint32_t incl = acc + wave_incl_scan_u32(sum);
-            const unsigned long long crossing = __ballot((unsigned long long)incl > bud);
-            const int first = crossing ? __ffsll((long long)crossing) - 1 : 63;
-            uint32_t a = incl - sum, d = BPL * lane, cn = 0;
-            bool done = false;
-#pragma unroll
-            for (int i = 0; i < BPL; ++i) {
-                const uint32_t wi = (uint32_t)(hb[i] & kWtMask);
-                if (!done) {
-                    if ((unsigned long long)a + wi > bud) {
-                        d = BPL * lane + i;
-                        cn = (uint32_t)(hb[i] >> 40);
-                        done = true;
-                    } else {
-                        a += wi;
-                    }
-                }
-            }
-            acc = (uint32_t)__builtin_amdgcn_readlane((int)a, first);
-            bcnt = (uint32_t)__builtin_amdgcn_readlane((int)cn, first);
-            bstar = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
-        };
-        find_boundary(first_digit);
+        const Boundary first_cut = find_boundary(first_digit, 0, bud);
+        uint32_t acc = first_cut.before, bcnt = first_cut.entries, bstar = first_cut.bucket;
         // entries before the boundary bucket are taken, entries behind it are not
         bool inside[kFastChunks];
 #pragma unroll
@@ -1461,7 +1429,10 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
                 if (inside[c]) atomicAdd(&S.hist[digit][sub[c]], (1ull << 40) | st.w[c]);
             }
             phase_sync<true>();
-            find_boundary(S.hist[digit]);
+            const Boundary cut = find_boundary(S.hist[digit], acc, bud);
+            acc = cut.before;
+            bcnt = cut.entries;
+            bstar = cut.bucket;
 #pragma unroll
             for (int c = 0; c < kFastChunks; ++c) {
                 st.take[c] |= inside[c] && sub[c] < bstar;
@@ -1676,28 +1647,7 @@ __device__ __forceinline__ void fast_epilogue(const ScoreParams& p, const Lds& L
     const uint32_t total = sc.carry_a, n_sel = sc.carry_b & 0xffffu;
     n_terms += sc.carry_b >> 16;
     phase_sync<true>();
-    // expansion: one row of 16 lanes per selected cluster, the next cluster's entry fetched early
-    int32_t* ro = p.rows + (long long)u * p.rows_stride;
-    int32_t* so = p.row_slot ? p.row_slot + (long long)u * p.rows_stride : nullptr;   // compact slot of each row's cluster
-    const int grp = tid >> 4, sub = tid & 15;
-    int2 rc_n = make_int2(0, 0);
-    int off_n = 0;
-    if ((uint32_t)grp < n_sel) {
-        rc_n = sel_rc[grp];
-        off_n = sel_off[grp];
-    }
-    for (uint32_t k = grp; k < n_sel; k += kThreads / 16) {
-        const int2 rc = rc_n;
-        const int off = off_n;
-        const uint32_t kn = k + kThreads / 16;
-        if (kn < n_sel) {
-            rc_n = sel_rc[kn];
-            off_n = sel_off[kn];
-        }
-        for (int i = sub; i < rc.y; i += 16) ro[off + i] = rc.x + i;
-        if (so)
-            for (int i = sub; i < rc.y; i += 16) so[off + i] = (int32_t)k;
-    }
+    expand_rows(p, u, sel_rc, sel_off, n_sel);
     fast_terms<G>(p, st, slot, n_f, 0, u);
     if (p.sel_base) {
         // q . centroid of a selected cluster, log2 units, for a value pass over keys stored as residuals
@@ -1723,14 +1673,7 @@ __device__ __forceinline__ void fast_epilogue(const ScoreParams& p, const Lds& L
             });
         }
     }
-    if (tid == 0) {
-        p.n_rows[u] = (int32_t)total;
-        p.n_mp[u] = (int32_t)n_terms;
-        p.counters[4 * u + 0] = (int32_t)total + p.n_tail;
-        p.counters[4 * u + 1] = n_f;
-        if (!two) p.counters[4 * u + 2] = 0;
-        p.counters[4 * u + 3] = (int32_t)n_terms;
-    }
+    write_counters(p, u, total, n_terms, n_f, two);
 }
 
 // What a shadow workgroup does at the last level: ask for the centroid rows of the second half of

@@ -43,7 +43,6 @@ constexpr int kRing = 4 * kPiece;                // per wave: keys and values of
 constexpr int kStrip = 64;                       // row numbers fetched at a time
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef const __attribute__((address_space(1))) unsigned char glb_byte;
 
 template <int kBytes, bool kOnce>
 __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds_off)
