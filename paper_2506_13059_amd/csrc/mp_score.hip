@@ -1411,62 +1411,7 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
             st.take[c] = st.w[c] && bucket[c] < bstar;
             inside[c] = st.w[c] && bucket[c] == bstar;
         }
-        // Flat attention puts much of a level into one bucket: up to two more digits, 256 slices of it each (the last slice
-        // of the open bucket takes the rest).  The general search divides all entries anew, digit by digit from their
-        // extremes.  Whole step of 8 units, 1024 clusters in one level, 1 / 3 / 5 heads, near and past a full bucket: 42 / 42 /
-        // 49 us with it, 29 / 30 / 36 with these digits and the list below; 2048 and 128 clusters, 4 heads, peaked scores in
-        // the log domain 44 -> 33.
-        uint64_t low = (uint64_t)(bstar < 128u ? bstar : bstar < 224u ? 4u * (bstar - 96u) : 512u + 32u * (bstar - 224u)) << 50;
-        int slice = bstar < 128u ? 50 : bstar < 224u ? 52 : 55;
-#pragma unroll 1
-        for (int digit = 1; digit <= 2 && bcnt > (uint32_t)kListCap; ++digit) {
-            slice -= 8;
-            uint32_t sub[kFastChunks];
-#pragma unroll
-            for (int c = 0; c < kFastChunks; ++c) {
-                const uint64_t at = (pos[c] - low) >> slice;
-                sub[c] = at < 255u ? (uint32_t)at : 255u;
-                if (inside[c]) atomicAdd(&S.hist[digit][sub[c]], (1ull << 40) | st.w[c]);
-            }
-            phase_sync<true>();
-            const Boundary cut = find_boundary(S.hist[digit], acc, bud);
-            acc = cut.before;
-            bcnt = cut.entries;
-            bstar = cut.bucket;
-#pragma unroll
-            for (int c = 0; c < kFastChunks; ++c) {
-                st.take[c] |= inside[c] && sub[c] < bstar;
-                inside[c] = inside[c] && sub[c] == bstar;
-            }
-            low += (uint64_t)bstar << slice;
-        }
-        if (bcnt > (uint32_t)kListCap) {
-            // a crowded slice (many equal or almost equal scores): the general search
-#pragma unroll
-            for (int c = 0; c < kFastChunks; ++c) {
-                if (st.x[c] >= 0) {
-                    A.keys[st.x[c]] = key[c];
-                    A.wts[st.x[c]] = st.w[c];
-                }
-            }
-            phase_sync<true>();
-            uint64_t kstar = 0, acc2 = 0;
-            uint32_t ties = 0;
-            const bool bounded = radix_select<true>(A.keys, A.wts, n, budget, S, kstar, acc2, ties);
-#pragma unroll
-            for (int c = 0; c < kFastChunks; ++c) {
-                if (!st.w[c]) continue;
-                bool t = !bounded || key[c] < kstar;
-                if (!t && key[c] == kstar && ties > 1) {
-                    // exactly equal keys: lower position first, keep while the running count still fits
-                    uint64_t run = acc2;
-                    for (int i = 0; i <= st.x[c]; ++i)
-                        if (A.wts[i] && A.keys[i] == kstar) run += A.wts[i];
-                    t = (long long)run <= budget;
-                }
-                st.take[c] = t;
-            }
-        } else if (bcnt > 1) {
+        auto order_inside = [&](auto direct) {
             // Those inside it are ordered by (key, position).
             uint32_t at[kFastChunks];
 #pragma unroll
@@ -1493,7 +1438,7 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
                     }
                 return run;
             };
-            if (bcnt <= 12u) {
+            if constexpr (decltype(direct)::value) {
 #pragma unroll
                 for (int c = 0; c < kFastChunks; ++c)
                     if (inside[c]) st.take[c] = (unsigned long long)acc + tokens_before(0, bcnt, key[c], (uint32_t)st.x[c]) + st.w[c] <= bud;
@@ -1508,6 +1453,71 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
 #pragma unroll
                 for (int c = 0; c < kFastChunks; ++c)
                     if (inside[c]) st.take[c] = (unsigned long long)acc + S.ahead[at[c]] + st.w[c] <= bud;
+            }
+        };
+        if (bcnt <= 12u) {
+            if (bcnt > 1) order_inside(std::true_type{});
+        } else {
+            // (All that is rare stands in this one block: every jump over code that has not run yet costs the common path
+            // about 0.2 us.  With the digits, the general search and the longer list in blocks of their own the launch took
+            // 17.8 instead of 17.2 us at 64 + 250 clusters, 15.8 instead of 15.2 in a generation step.)
+            // Flat attention puts much of a level into one bucket: up to two more digits, 256 slices of it each (the last slice
+            // of the open bucket takes the rest).  The general search divides all entries anew, digit by digit from their
+            // extremes.  Whole step of 8 units, 1024 clusters in one level, 1 / 3 / 5 heads, near and past a full bucket: 42 / 42 /
+            // 49 us with it, 29 / 30 / 36 with these digits and the list below; 2048 and 128 clusters, 4 heads, peaked scores in
+            // the log domain 44 -> 33.
+            uint64_t low = (uint64_t)(bstar < 128u ? bstar : bstar < 224u ? 4u * (bstar - 96u) : 512u + 32u * (bstar - 224u)) << 50;
+            int slice = bstar < 128u ? 50 : bstar < 224u ? 52 : 55;
+#pragma unroll 1
+            for (int digit = 1; digit <= 2 && bcnt > (uint32_t)kListCap; ++digit) {
+                slice -= 8;
+                uint32_t sub[kFastChunks];
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c) {
+                    const uint64_t at = (pos[c] - low) >> slice;
+                    sub[c] = at < 255u ? (uint32_t)at : 255u;
+                    if (inside[c]) atomicAdd(&S.hist[digit][sub[c]], (1ull << 40) | st.w[c]);
+                }
+                phase_sync<true>();
+                const Boundary cut = find_boundary(S.hist[digit], acc, bud);
+                acc = cut.before;
+                bcnt = cut.entries;
+                bstar = cut.bucket;
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c) {
+                    st.take[c] |= inside[c] && sub[c] < bstar;
+                    inside[c] = inside[c] && sub[c] == bstar;
+                }
+                low += (uint64_t)bstar << slice;
+            }
+            if (bcnt > (uint32_t)kListCap) {
+                // a crowded slice (many equal or almost equal scores): the general search
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c) {
+                    if (st.x[c] >= 0) {
+                        A.keys[st.x[c]] = key[c];
+                        A.wts[st.x[c]] = st.w[c];
+                    }
+                }
+                phase_sync<true>();
+                uint64_t kstar = 0, acc2 = 0;
+                uint32_t ties = 0;
+                const bool bounded = radix_select<true>(A.keys, A.wts, n, budget, S, kstar, acc2, ties);
+#pragma unroll
+                for (int c = 0; c < kFastChunks; ++c) {
+                    if (!st.w[c]) continue;
+                    bool t = !bounded || key[c] < kstar;
+                    if (!t && key[c] == kstar && ties > 1) {
+                        // exactly equal keys: lower position first, keep while the running count still fits
+                        uint64_t run = acc2;
+                        for (int i = 0; i <= st.x[c]; ++i)
+                            if (A.wts[i] && A.keys[i] == kstar) run += A.wts[i];
+                        t = (long long)run <= budget;
+                    }
+                    st.take[c] = t;
+                }
+            } else if (bcnt > 1) {
+                order_inside(std::false_type{});
             }
         }
     }
