@@ -256,8 +256,9 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
 // of 4 32x32x16 products and 32 vector instructions takes 299 ns for four waves, 219 and 236 ns apart -- so occupancy and instruction
 // count decide: with two waves a SIMD, 32 x 32 products and 79 vector instructions per 2048 scores 1330 us for 16.8 M
 // points x 256 centroids; points streamed through LDS and centroids in registers, two waves, 1390; this
-// layout with three waves 1352, with four waves 1044 us (38.6 -> 27.3 us for 262144 points).  The points alone take
-// 0.65 ms at the rate of the dense kernel; clocks fall to about 2.0 GHz under this load.
+// layout with three waves 1352, with four waves 1044 us (38.6 -> 27.3 us for 262144 points); these figures are without
+// the near ties, with them a launch takes 1142 to 1183 us and 36.3 us (nearest_exact).  The points alone take 0.65 ms at
+// the rate of the dense kernel; clocks fall to about 2.0 GHz under this load.
 //
 // A lane (g, c) holds rows 4g .. 4g+3 of a tile for column c of four columns groups: point 16 q + c, q < 4.  The slot of a
 // score among the sixteen tiles of a half (tile & 15, row & 3) rides in its six lowest mantissa bits, a change of less
@@ -471,7 +472,8 @@ __device__ __forceinline__ int lane_id()
 // lowest index.  Returns it in all four lanes.
 // A launch of its own fetched the 64 KiB of a block's centroids for every point: 14.6 us for 32 blocks of 8192 points,
 // 140 us for 2048.  Here it adds 9 us to the first's assignment (the longest chain: four tiles' products, compared, four
-// more, then two or three distances of 2 us) and nothing measurable to the second's, whose waves fill each other's gaps.
+// more, then two or three distances of 2 us) and about 100 to 140 to the second's (1044 us without near ties, 1142 to 1183
+// with them).
 __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, int k_cap,
                                              int k, float c2max)
 {
@@ -1009,7 +1011,7 @@ hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int ma
     p.k_cap = (max_k + kRowTile - 1) / kRowTile * kRowTile;
     p.n_cap = (max_pts + 3) / 4 * 4;
     // Sixteen waves where every pair has a compute unit of its own (a pair's time is what counts then: 104 against 132 us
-    // for 32 pairs and ten iterations), else two workgroups of eight a compute unit (755 against 890 us for 2048 pairs).
+    // for 32 pairs and ten iterations where the line was drawn, 110 to 118 us in the build of a 32K prompt), else two workgroups of eight a compute unit (755 against 890 us for 2048 pairs).
     const size_t smem = coarse_level_smem(max_pts, max_k);
     return (long long)nb * U <= 256 ? launch_coarse_waves<16>(p, nb, U, smem, s) : launch_coarse_waves<8>(p, nb, U, smem, s);
 }

@@ -19,9 +19,9 @@
 // What bounds it is the memory system: about 100 vector instructions a tile against 420 of the vector-ALU kernel (60 %
 // of a SIMD's issue slots at the dense rate with 4 heads, more than there are with 8).  Measured on the benchmark's
 // 8 GiB cache, dense, 1 / 4 / 5 / 6 / 8 heads: vector ALU 1259 / 1345 / 1367 / 1615 / 1763 us, here with the same
-// chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per compute unit (see stream_chunks_per_unit in
-// mp_api.hip) 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: 504 -> 291 us; 8 units x 32768,
-// 4 heads: 40.8 -> 26.0 us.
+// chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per compute unit (see plan_streams in mp_plan.h)
+// 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: the call 505 -> 301 to 306 us, 294 of them
+// this kernel; 8 units x 32768, 4 heads: 40.8 -> 26.0 us.
 #include <type_traits>
 
 #include "mp_device.h"

@@ -1,5 +1,6 @@
-// Value pass on the vector ALU, and merge, for gfx950.  Launches over 8-bit rows and over rows that do not start on 16
-// bytes (a caller's tail or dense keys) come here; all others go to the matrix-core kernel (mp_stream.hip).
+// Value pass on the vector ALU, and merge, for gfx950.  Launches over 8-bit rows, over rows that do not start on 16
+// bytes (a caller's tail or dense keys) and dense calls of one or two heads to a unit over few rows
+// (short_dense_on_vector_alu in mp_plan.h) come here; all others go to the matrix-core kernel (mp_stream.hip).
 //
 // The value pass is the byte mover of the decode step: it streams 256-byte key rows and value rows
 // (the keys of the selected clusters, the unclustered tail, or all keys for the dense comparison)
