@@ -30,6 +30,16 @@ def test_many_blocks_of_many_units():
     ctx.close()
 
 
+@pytest.mark.parametrize("nf", [1130, 1140, 920])
+def test_blocks_on_both_sides_of_a_limit(nf):
+    """The largest block of a launch decides its kernel: 508 / 513 / 414 centroids in the first block, 622 / 627 / 506 in the
+    last, so that one, both or none is beyond 512; the coarse level's points are the same counts."""
+    print(f"nf={nf}", flush=True)
+    ctx, _, _ = _run_case(1, 4, 2, 4548, 200, 2, nf, 40, 2048, 1024, iters=2, seed=400 + nf)
+    assert ctx.mp_get_sizes()["n_blocks"] == 2
+    ctx.close()
+
+
 def test_kernels_in_turn_on_one_context():
     # blocks of 600 centroids keep their near ties in a list that a second launch works off, blocks of 100 decide them
     # at once: each finds the other's counters as it needs them, and gives what a context of its own gives
