@@ -216,11 +216,12 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     else { A(Kp, U * N * D); A(Vp, U * N * D); }
     A(perm, U * N); A(fot, U * N);
     A(fstart, U * (F + 1)); A(cof, U * F); A(cstart, U * (Cc + 1));
-    if (c.levels == 2) { A(sumK, U * F * D); A(sumV, U * F * D); }
+    A(sumK, U * F * D);
+    if (c.levels == 2) A(sumV, U * F * D);
     A(Kc, U * T * D); A(Vc, U * T * D); A(Ncl, U * T);
     A(Kfb, U * (size_t)ctx->FBcap * D); A(Vfb, U * (size_t)ctx->FBcap * D);
     if (c.lookup_keys) A(Kfs, U * (size_t)ctx->FBcap * D);
-    A(km_assign, U * N); A(km_list, U * N); A(km_cnt, U * T); A(km_start, U * (T + 2));
+    A(km_assign, U * N); A(km_assign2, U * N); A(km_marks, U * (size_t)mp::marks_of(ctx->Ncap, ctx->max_blocks)); A(km_range, U * F); A(km_list, U * N); A(km_cnt, U * T); A(km_start, U * (T + 2));
     A(km_Cf, U * F * D); A(km_Cc, U * Cc * D); A(km_parent, U * F); A(km_plist, U * F); A(km_newid, U * F);
     A(km_seed_f, U * F); A(km_seed_c, U * Cc); A(blocks_dev, 3 * (size_t)ctx->max_blocks * 4);
     A(km_amb, 2 * U * (size_t)ctx->max_blocks);

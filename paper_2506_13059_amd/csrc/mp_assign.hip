@@ -112,8 +112,9 @@ __device__ __forceinline__ float deposit_piece(unsigned char* tile_row, int seg,
 __device__ __forceinline__ void finish_points(int half, const float (&best)[2], const float (&second)[2],
                                               const int (&btile)[2], const float (&x2)[2], const int (&tpt)[2], int x0,
                                               int x1, float c2max, int32_t* assign_u, int32_t* amb_list_u,
-                                              int32_t* amb_cnt_ub)
+                                              int32_t* amb_cnt_ub, const int32_t* old_u, unsigned long long* mark)
 {
+    unsigned long long marked = 0;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int slot = (int)(__float_as_uint(best[c]) & kTiledSlotMask);
@@ -127,16 +128,21 @@ __device__ __forceinline__ void finish_points(int half, const float (&best)[2], 
         const float bst = fmaxf(best[c], ob);
         const float xx = x2[c] + ox;
         const int t = tpt[c];
+        bool moved = false;
         if (t < x1 && half == 0) {
             assign_u[t] = j;
             const float margin = near_margin(fmaxf(xx, c2max));
             // (written so that a point without any comparable score also goes to the exact pass)
-            if (!(bst - sec > margin)) {
+            const bool near = !(bst - sec > margin);
+            if (near) {
                 const int pos = atomicAdd(amb_cnt_ub, 1);
                 amb_list_u[x0 + pos] = t;
             }
+            moved = near || (mark && old_u[t] != j);
         }
+        marked |= __ballot(moved) << (32 * c);               // (the lower half has a bit of each of its 32 points)
     }
+    if (mark && (threadIdx.x & 63) == 0) *mark = marked;
 }
 
 // grid = (ceil(max points per block / 256), nb, U); 256 threads = 4 waves of 64 points (two MFMA
@@ -151,7 +157,7 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
                                                           const uint16_t* __restrict__ C, long long c_unit_rows,
                                                           int32_t* __restrict__ assign, long long assign_stride,
                                                           int32_t* __restrict__ amb_list, long long list_stride,
-                                                          int32_t* __restrict__ amb_cnt, int cnt_stride)
+                                                          int32_t* __restrict__ amb_cnt, int cnt_stride, const MoveMarks mv)
 {
     __shared__ __align__(16) unsigned char tile[2][kTile * kRowBytes];
     __shared__ float wave_c2max[4];
@@ -241,8 +247,10 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
     if (lane == 0) wave_c2max[wave] = c2max;
     __syncthreads();
     c2max = fmaxf(fmaxf(wave_c2max[0], wave_c2max[1]), fmaxf(wave_c2max[2], wave_c2max[3]));
+    const int chunk = (p0 - x0) / 64 + wave;
     finish_points(half, best, second, btile, x2, tpt, x0, x1, c2max, assign + u * assign_stride,
-                  amb_list + u * list_stride, amb_cnt + u * cnt_stride + b);
+                  amb_list + u * list_stride, amb_cnt + u * cnt_stride + b, mv.old_ids + u * assign_stride,
+                  mv.marks && 64 * chunk < x1 - x0 ? mv.marks + u * mv.stride + first_mark(x0, b) + chunk : nullptr);
 }
 
 // The same stage for blocks of at most 512 centroids and at least 1024 points.  The block's centroids stay in LDS
@@ -555,7 +563,8 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
                                                                     const uint16_t* __restrict__ C, long long c_unit_rows,
                                                                     int32_t* __restrict__ assign, long long assign_stride,
                                                                     int32_t* __restrict__ amb_list, long long list_stride,
-                                                                    int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap)
+                                                                    int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap,
+                                                                    const MoveMarks mv)
 {
     extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
     __shared__ float wave_c2max[kW];
@@ -597,12 +606,20 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
 
     int32_t* assign_u = assign + u * assign_stride;
+    const int32_t* old_u = mv.old_ids + u * assign_stride;
+    unsigned long long* marks = mv.marks + u * mv.stride + first_mark(x0, b);
     int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
 #pragma unroll 1
     for (int chunk = chunk0 + wave; chunk < chunk1; chunk += kW) {
-        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, k_cap, ntiles, c2max);
         const int t = x0 + chunk * 64 + lane;
+        int old = 0;
+        if (mv.marks) old = old_u[min(t, x1 - 1)];
+        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, k_cap, ntiles, c2max);
+        if (mv.marks) {
+            const unsigned long long marked = __ballot(t < x1 && (r.near || old != k0 + r.j));
+            if (lane == 0) marks[chunk] = marked;
+        }
         if (t < x1) {
             if (r.near) {
                 const int pos = atomicAdd(&near_n, 1);
@@ -629,7 +646,8 @@ constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) byte
 template <int kW>
 hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts, int max_k,
                            int U, const uint16_t* C, long long c_unit_rows, int32_t* assign, long long assign_stride,
-                           int32_t* amb_list, long long list_stride, int32_t* cnt_next, int cnt_stride, hipStream_t s)
+                           int32_t* amb_list, long long list_stride, int32_t* cnt_next, int cnt_stride, const MoveMarks& mv,
+                           hipStream_t s)
 {
     static bool configured = false;
     if (!configured) {
@@ -650,7 +668,7 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
     const long long want = groups <= kSlots ? kSlots / groups : (4 * kSlots + groups - 1) / groups;
     const int gx = (int)std::max<long long>(1, std::min<long long>(chunks, want));
     hipLaunchKernelGGL(assign_resident_kernel<kW>, dim3(gx, nb, U), dim3(64 * kW), (size_t)k_cap * 260, s, X, x_unit_rows,
-                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, cnt_next, cnt_stride, k_cap);
+                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, cnt_next, cnt_stride, k_cap, mv);
     return hipGetLastError();
 }
 
@@ -666,13 +684,6 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
 // and is slower (1000 against 780 us for 2048 pairs).  Build of one 32K prompt: 1214 -> 1095 us; sixteen of 128K: 29.1 ->
 // 28.4 ms; refresh of eight 8K contexts: 970 -> 940 us.
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
 {
@@ -1019,7 +1030,7 @@ hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int ma
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,
                          long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* amb_cnt,
-                         int32_t* amb_cnt_next, int cnt_stride, hipStream_t s)
+                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, hipStream_t s)
 {
     if (nb <= 0 || max_pts <= 0 || U <= 0) return hipSuccess;
     if (nb > cnt_stride || U > 65535) return hipErrorInvalidValue;
@@ -1028,12 +1039,12 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
         // two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen
         auto go = [&](auto launch) {
             return launch(X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows, assign, assign_stride, amb_list,
-                          list_stride, amb_cnt_next, cnt_stride, s);
+                          list_stride, amb_cnt_next, cnt_stride, mv, s);
         };
         return max_k <= kResidentTwiceK ? go(launch_resident<8>) : go(launch_resident<16>);
     }
     hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
-                       c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride);
+                       c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, mv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int z = std::min(32, (max_pts + 3) / 4);      // (deeper grids only add workgroups that find nothing to do)

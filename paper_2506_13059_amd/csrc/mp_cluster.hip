@@ -216,8 +216,11 @@ struct Problem {
     long long cnt_stride;
     int k_first;                  // first cluster id of the blocks
     int p_first;                  // first point index of the blocks
-    double* sum_out;              // optional [U, sum_unit_rows, 128]: the fp64 member sums behind the new centroids
+    // Fine level (null at the coarse one): what the iterations after the first update instead of summing afresh.
+    double* sums;                 // [U, sum_unit_rows, 128] fp64 member sums behind C; the coarse tables are built from them too
     long long sum_unit_rows;
+    uint32_t* range;              // [U, sum_unit_rows] exponents of the points, by cluster of the first iteration
+    int32_t* other_assign;        // a second array like assign
 };
 
 // The counter array of the near-tie lists to use now (which = 0) and the one to leave zeroed for the next step (1).
@@ -226,12 +229,12 @@ inline int32_t* amb_counters(mp_ctx* ctx, int which)
     return ctx->km_amb + (size_t)((ctx->amb_turn ^ which) & 1) * ctx->U * ctx->max_blocks;
 }
 
-mp_status launch_assign(mp_ctx* ctx, const Problem& pr, hipStream_t s)
+mp_status launch_assign(mp_ctx* ctx, const Problem& pr, const MoveMarks& mv, hipStream_t s)
 {
     // the member-list array is free during the assignment step and holds the points of the exact pass
     MP_HIPC(mp::launch_assign(pr.X, pr.x_unit_rows, pr.blocks_dev, pr.nb, pr.max_pts, pr.max_k, ctx->U, pr.C, pr.c_unit_rows,
                               pr.assign, pr.assign_stride, pr.list, pr.list_stride, amb_counters(ctx, 0), amb_counters(ctx, 1),
-                              ctx->max_blocks, s));
+                              ctx->max_blocks, mv, s));
     ctx->amb_turn ^= 1;
     return MP_OK;
 }
@@ -245,18 +248,33 @@ mp_status build_lists(mp_ctx* ctx, const Problem& pr, hipStream_t s)
     return MP_OK;
 }
 
-// One Lloyd iteration: assign, member lists, centroid <- bf16(mean of members); empty keeps.
-// keep_sums: also store the member sums (pr.sum_out), which the coarse tables are built from when this was
-// the last iteration.
-mp_status lloyd_iteration(mp_ctx* ctx, const Problem& pr, bool keep_sums, hipStream_t s)
+// Lloyd iterations: assign, centroid <- bf16(mean of members); empty keeps.  The first one builds member lists and sums the
+// members; with pr.sums the later ones move the sums by the points that changed cluster (a launch less, and the few
+// per cent of the points that move instead of all).  The last assignment ends in pr.assign.
+mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, hipStream_t s)
 {
-    mp_status st = launch_assign(ctx, pr, s);
-    if (st != MP_OK) return st;
-    st = build_lists(ctx, pr, s);
-    if (st != MP_OK) return st;
-    MP_HIPC(launch_cluster_means(pr.X, pr.x_unit_rows, pr.list, pr.list_stride, pr.start, pr.cnt_stride + 1,
-                                 pr.k_first, pr.k_total, ctx->U, pr.C, pr.c_unit_rows, 0, pr.C, pr.c_unit_rows,
-                                 nullptr, 0, 0, keep_sums ? pr.sum_out : nullptr, pr.sum_unit_rows, s));
+    Problem now = pr;
+    for (int it = 0; it < iters; ++it) {
+        const int32_t* before = now.assign;
+        if (pr.sums) now.assign = (iters - 1 - it) % 2 ? pr.other_assign : pr.assign;
+        if (pr.sums && it > 0) {
+            const MoveMarks marks{before, ctx->km_marks, marks_of(ctx->Ncap, ctx->max_blocks)};
+            MP_TRY(launch_assign(ctx, now, marks, s));
+            MoveMeans mv{};
+            mv.X = pr.X; mv.x_unit_rows = pr.x_unit_rows; mv.blocks = pr.blocks_dev;
+            mv.old_ids = before; mv.new_ids = now.assign; mv.ids_stride = pr.assign_stride;
+            mv.marks = marks.marks; mv.marks_stride = marks.stride;
+            mv.C = pr.C; mv.c_unit_rows = pr.c_unit_rows; mv.count = pr.cnt; mv.count_stride = pr.cnt_stride;
+            mv.sum = pr.sums; mv.sum_unit_rows = pr.sum_unit_rows; mv.range = pr.range; mv.range_stride = pr.sum_unit_rows;
+            MP_HIPC(launch_move_means(mv, pr.nb, pr.max_k, ctx->U, s));
+            continue;
+        }
+        MP_TRY(launch_assign(ctx, now, MoveMarks{}, s));
+        MP_TRY(build_lists(ctx, now, s));
+        MP_HIPC(launch_cluster_means(pr.X, pr.x_unit_rows, pr.list, pr.list_stride, pr.start, pr.cnt_stride + 1,
+                                     pr.k_first, pr.k_total, ctx->U, pr.C, pr.c_unit_rows, 0, pr.C, pr.c_unit_rows,
+                                     pr.sums ? pr.cnt : nullptr, pr.cnt_stride, 0, pr.sums, pr.sum_unit_rows, pr.range, s));
+    }
     return MP_OK;
 }
 
@@ -361,9 +379,10 @@ mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void
     if (!fine_keys_are_means)
         MP_HIPC(launch_cluster_means((const uint16_t*)Xk, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
                                      ctx->Kc, tab, 0, key_fallback ? ctx->Kc : nullptr, tab, nullptr, 0, 0,
-                                     two ? ctx->sumK : nullptr, ctx->Fcap, s));
+                                     two ? ctx->sumK : nullptr, ctx->Fcap, nullptr, s));
     MP_HIPC(launch_cluster_means((const uint16_t*)Xv, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
-                                 ctx->Vc, tab, 0, nullptr, 0, ctx->Ncl, tab, 0, two ? ctx->sumV : nullptr, ctx->Fcap, s));
+                                 ctx->Vc, tab, 0, nullptr, 0, ctx->Ncl, tab, 0, two ? ctx->sumV : nullptr, ctx->Fcap,
+                                 nullptr, s));
     if (bytes)   // (8-bit keys are residuals from the fine key centroids, which are final only now)
         MP_HIPC(launch_gather_quantize_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, ids, ids_stride, ctx->Kc, tab, n_pts, U,
                                             ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, s));
@@ -424,10 +443,7 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
                                seed_f0 < 0 ? pc.blocks_dev : ctx->blocks_dev + 8, ctx->km_seed_c, Ccap1, pc.C, pc.c_unit_rows);
             MP_HIPC(hipGetLastError());
         }
-        for (int it = 0; it < coarse_iters; ++it) {
-            const mp_status st = lloyd_iteration(ctx, pc, false, s);
-            if (st != MP_OK) return st;
-        }
+        MP_TRY(lloyd_iterations(ctx, pc, coarse_iters, s));
         // km_plist[0..kf) = fine ids of the range grouped by coarse cluster (ascending inside): new order
         hipLaunchKernelGGL(invert_perm_kernel, dim3(blocks_for(kf, 256), U), dim3(256), 0, s, ctx->km_plist, Fcap, 0, kf,
                            r.f0, ctx->km_newid, Fcap);
@@ -473,11 +489,8 @@ mp_status cluster_range(mp_ctx* ctx, const Range& r, int iters, hipStream_t s)
     hipLaunchKernelGGL(init_centroids_kernel, dim3(nb, U), dim3(256), 0, s, pf.X, pf.x_unit_rows, pf.blocks_dev,
                        ctx->km_seed_f, (long long)ctx->Fcap, pf.C, pf.c_unit_rows);
     MP_HIPC(hipGetLastError());
-    pf.sum_out = ctx->sumK; pf.sum_unit_rows = ctx->Fcap;
-    for (int it = 0; it < iters; ++it) {
-        const mp_status st = lloyd_iteration(ctx, pf, it == iters - 1, s);
-        if (st != MP_OK) return st;
-    }
+    pf.sums = ctx->sumK; pf.sum_unit_rows = ctx->Fcap; pf.range = ctx->km_range; pf.other_assign = ctx->km_assign2;
+    MP_TRY(lloyd_iterations(ctx, pf, iters, s));
     return coarse_and_finalize(ctx, r, iters, r.c0, -1, iters > 0, max_kf, max_kc, s);
 }
 
@@ -707,7 +720,7 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     // ---- one-shot assignment of the appended tokens + running mean of the touched centroids ----
     MP_HIPC(mp::launch_assign(ctx->Kfb, (long long)ctx->FBcap, ctx->blocks_dev, 1, n_new, 0, U, ctx->km_Cf, Fcap,
                               ctx->km_assign, Ncap, ctx->km_list, Ncap, amb_counters(ctx, 0), amb_counters(ctx, 1),
-                              ctx->max_blocks, s));
+                              ctx->max_blocks, MoveMarks{}, s));
     ctx->amb_turn ^= 1;
     MP_HIPC(hipMemcpy2DAsync(ctx->km_assign, (size_t)Ncap * 4, ctx->fot + t0, (size_t)Ncap * 4, (size_t)nb_old * 4, U,
                              hipMemcpyDeviceToDevice, s));
@@ -720,11 +733,8 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     pf.max_pts = nb; pf.max_k = kf; pf.k_total = f1; pf.k_first = f0; pf.C = ctx->km_Cf; pf.c_unit_rows = Fcap;
     pf.assign = ctx->km_assign; pf.assign_stride = Ncap; pf.list = ctx->km_list; pf.list_stride = Ncap;
     pf.cnt = ctx->km_cnt; pf.start = ctx->km_start; pf.cnt_stride = ctx->tab_rows;
-    pf.sum_out = ctx->sumK; pf.sum_unit_rows = ctx->Fcap;
-    for (int it = 0; it < refine_iters; ++it) {
-        const mp_status st = lloyd_iteration(ctx, pf, it == refine_iters - 1, s);
-        if (st != MP_OK) return st;
-    }
+    pf.sums = ctx->sumK; pf.sum_unit_rows = ctx->Fcap; pf.range = ctx->km_range; pf.other_assign = ctx->km_assign2;
+    MP_TRY(lloyd_iterations(ctx, pf, refine_iters, s));
     // ---- coarse level: stored coarse key centroids, plus seeds taken from the new fine centroids ----
     mp_status st = coarse_and_finalize(ctx, r, std::max(1, refine_iters), lb.c1, lb.f1, refine_iters > 0, max_kf, max_kc, s);
     if (st != MP_OK) return st;

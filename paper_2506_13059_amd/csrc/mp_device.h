@@ -66,6 +66,20 @@ __device__ __forceinline__ uint16_t f64_to_bf16_rne(double v)
     return (uint16_t)((sign | mag) >> 16);
 }
 
+// bf16 of the quotient a / den (a whole number above 0, inv = 1 / den in fp64), as f64_to_bf16_rne(a / den) has it, without
+// the division (some twenty instructions) wherever that cannot matter.  a * inv is within three units of the last place of the
+// rounded quotient, and both round to the same bf16 value unless a number half way between two of them (the lower 45 bits
+// of the mantissa: a one and zeros) or the end of the normal range is that near.
+__device__ __forceinline__ uint16_t quotient_to_bf16(double a, double den, double inv)
+{
+    double q = a * inv;
+    const uint64_t b = (uint64_t)__double_as_longlong(q);
+    const uint32_t low = (uint32_t)b, e = (uint32_t)(b >> 52) & 0x7ffu;
+    const bool half_way = (((uint32_t)(b >> 32) & 0x1fffu) == 0x1000u && low < 16u) || (((uint32_t)(b >> 32) & 0x1fffu) == 0xfffu && low > 0xfffffff0u);
+    if (half_way || e - 900u > 245u) q = a / den;            // (exponents 2^-123 .. 2^122 are the ordinary case)
+    return f64_to_bf16_rne(q);
+}
+
 // a.x*b.x + a.y*b.y + c on packed bf16 pairs (v_dot2c_f32_bf16)
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c)
 {
@@ -96,6 +110,14 @@ __device__ __forceinline__ double exp_shifted(double x)
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
     return ldexp(p, (int)kf);
+}
+
+// What the lanes of a wave have written to LDS is there for the others (no barrier between waves).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // ---- DPP cross-lane moves inside a row of 16 lanes ----------------------------------------------

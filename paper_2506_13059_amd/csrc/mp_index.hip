@@ -349,6 +349,8 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
 // One wave per cluster of [k0, k): fp64 sum of the member rows in list order, mean rounded once to bf16.
 // Lane l owns dims 2l and 2l+1.  Empty cluster: `fallback` row if given (else zeros).
 // mean_out row index = out_row0 + cluster id.  count_out optional.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <bool kRange>
 __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                            const int32_t* __restrict__ list, long long list_stride,
                                                            const int32_t* __restrict__ start, long long start_stride,
@@ -357,7 +359,8 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
                                                            const uint16_t* __restrict__ fallback,
                                                            long long fb_unit_rows, int32_t* __restrict__ count_out,
                                                            long long count_stride, int count_off,
-                                                           double* __restrict__ sum_out, long long sum_unit_rows)
+                                                           double* __restrict__ sum_out, long long sum_unit_rows,
+                                                           uint32_t* __restrict__ range_out)
 {
     const int u = blockIdx.y;
     const int f = k0 + blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -367,6 +370,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     const uint32_t* Xu = reinterpret_cast<const uint32_t*>(X + (long long)u * x_unit_rows * kHeadDim);
     const int32_t* lp = list ? list + u * list_stride : nullptr;
     double a0 = 0.0, a1 = 0.0;
+    u16x2 largest = {0, 0}, smallest = {0xffff, 0xffff};     // magnitudes, and nonzero magnitudes less one
     // 64 member indices at a time (one per lane), then their rows kBatch at a time: the row numbers
     // reach every lane through a lane broadcast, so that kBatch row loads are in flight at once while
     // the additions keep the members' order (a wave's time is the number of trips to memory it makes:
@@ -388,9 +392,24 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
                 if (m + q < nm) {
                     a0 += (double)bf16lo_to_f32(w[q]);
                     a1 += (double)bf16hi_to_f32(w[q]);
+                    if constexpr (kRange) {
+                        const u16x2 size = __builtin_bit_cast(u16x2, w[q] & 0x7fff7fffu);
+                        largest = __builtin_elementwise_max(largest, size);
+                        smallest = __builtin_elementwise_min(smallest, (u16x2)(size - (unsigned short)1));     // (zero: the largest number)
+                    }
                 }
             }
         }
+    }
+    if constexpr (kRange) {
+        int hi = max((int)largest.x, (int)largest.y) >> 7, lo = min((int)smallest.x, (int)smallest.y);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            hi = max(hi, __shfl_xor(hi, off, 64));
+            lo = min(lo, __shfl_xor(lo, off, 64));
+        }
+        lo = min(max((lo + 1) >> 7, 1), 255);
+        if (lane == 0) range_out[u * sum_unit_rows + f] = (uint32_t)hi << 16 | (uint32_t)lo;
     }
     const int n = s1 - s0;
     uint32_t outw;
@@ -641,13 +660,16 @@ hipError_t launch_cluster_means(const uint16_t* X, long long x_unit_rows, const 
                                 const int32_t* start, long long start_stride, int k0, int k, int U,
                                 uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
                                 long long fb_unit_rows, int32_t* count_out, long long count_stride, int count_off,
-                                double* sum_out, long long sum_unit_rows, hipStream_t s)
+                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, hipStream_t s)
 {
     if (k <= k0) return hipSuccess;
-    hipLaunchKernelGGL(cluster_mean_kernel, dim3((k - k0 + 3) / 4, U), dim3(256), 0, s, X, x_unit_rows, list,
-                       list_stride, start, start_stride, k0, k, mean_out, out_unit_rows, out_row0, fallback,
-                       fb_unit_rows, count_out, count_stride, count_off, sum_out, sum_unit_rows);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((k - k0 + 3) / 4, U), dim3(256), 0, s, X, x_unit_rows, list, list_stride, start,
+                           start_stride, k0, k, mean_out, out_unit_rows, out_row0, fallback, fb_unit_rows, count_out,
+                           count_stride, count_off, sum_out, sum_unit_rows, range_out);
+        return hipGetLastError();
+    };
+    return range_out ? go(cluster_mean_kernel<true>) : go(cluster_mean_kernel<false>);
 }
 
 hipError_t launch_coarse_from_children(const double* sums, long long sum_unit_rows, const int32_t* map, long long map_stride,

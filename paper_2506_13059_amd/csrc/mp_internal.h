@@ -127,6 +127,15 @@ struct ScoreParams {
 hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, hipStream_t stream);
 size_t score_smem_bytes(int G, int cap);
 
+// Later assignment steps of a Lloyd sequence mark the points that may have changed cluster: bit i of marks[u][first_mark(x0,
+// b) + c] stands for point x0 + 64 c + i of block b.  Every word of a block is written; no array: nothing is marked.
+struct MoveMarks {
+    const int32_t* old_ids;        // [U, assign_stride] the assignment before
+    unsigned long long* marks;     // [U, stride]
+    long long stride;
+};
+constexpr int first_mark(int x0, int b) { return (x0 >> 6) + b; }
+inline long long marks_of(long long points, int blocks) { return (points >> 6) + blocks + 1; }
 // ------------------------------------------------------------------------------------------------
 // Index construction helpers (member lists, gathers, per-cluster means)
 // ------------------------------------------------------------------------------------------------
@@ -140,7 +149,7 @@ size_t score_smem_bytes(int G, int cap);
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,
                          long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* amb_cnt,
-                         int32_t* amb_cnt_next, int cnt_stride, hipStream_t s);
+                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, hipStream_t s);
 // The coarse level of a range of blocks in one launch: `iters` Lloyd iterations over the fine working centroids X of each
 // block, then the fine clusters in their new order.  blocks: int32 [nb][4] = {first fine id, end, first coarse id, end}.
 struct CoarseLevel {
@@ -193,12 +202,35 @@ hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long 
                                        const uint16_t* Kc, long long kc_unit_rows, int n, int U, void* dstK, void* dstV,
                                        float* scales, long long dst_unit_rows, int dst_row0, hipStream_t s);
 // mean_out row (out_row0 + id) = bf16(fp64 sum of the member rows in list order / count); sum_out (optional)
-// receives the fp64 sums themselves, row = id.
+// receives the fp64 sums themselves, row = id; range_out (optional) [U, sum_unit_rows] the exponent fields of a cluster's
+// largest magnitude (<< 16) and smallest nonzero one (subnormals count as 1; 255 where there is none).
 hipError_t launch_cluster_means(const uint16_t* X, long long x_unit_rows, const int32_t* list, long long list_stride,
                                 const int32_t* start, long long start_stride, int k0, int k, int U,
                                 uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
                                 long long fb_unit_rows, int32_t* count_out, long long count_stride, int count_off,
-                                double* sum_out, long long sum_unit_rows, hipStream_t s);
+                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, hipStream_t s);
+// Later Lloyd iterations: sums, counts and centroids of the clusters whose members differ between old_ids and new_ids.
+// `range` is what launch_cluster_means left for the same points.
+struct MoveMeans {
+    const uint16_t* X;             // points
+    long long x_unit_rows;
+    const int32_t* blocks;         // [nb][4]: x0, x1, k0, k1
+    const int32_t* old_ids;        // [U, ids_stride] cluster of each point behind sum, count and C
+    const int32_t* new_ids;
+    long long ids_stride;
+    const unsigned long long* marks;   // [U, marks_stride] of the points whose two ids may differ
+    long long marks_stride;
+    uint16_t* C;                   // [U, c_unit_rows, 128], row = cluster id
+    long long c_unit_rows;
+    int32_t* count;                // [U, count_stride]
+    long long count_stride;
+    double* sum;                   // [U, sum_unit_rows, 128]
+    long long sum_unit_rows;
+    const uint32_t* range;         // [U, range_stride]
+    long long range_stride;
+    int per;                       // clusters of a workgroup (set by the launch)
+};
+hipError_t launch_move_means(MoveMeans p, int nb, int max_k, int U, hipStream_t s);
 // Coarse clusters [c0, c1) from their children: sums [U, sum_unit_rows, 128] fp64 member sums of the fine clusters
 // (row = map ? map[f - map_f0] : f), cstart = first child of each coarse cluster, fine_count[f] members.
 hipError_t launch_coarse_from_children(const double* sums, long long sum_unit_rows, const int32_t* map, long long map_stride,

@@ -1,0 +1,289 @@
+// Centroid update of k-means after the first Lloyd iteration (Sec. 3.1: centroid = mean of the members): the member sums
+// of the iteration before, moved by the points that changed cluster.
+//
+// From the second iteration on few points move -- of 16.8 M keys in blocks of 8192 with 256 centroids 20, 8, 5, 2.5, 1.3
+// per cent in iterations 2 to 6, half a per cent in the tenth -- while summing afresh reads every key and sorts every
+// point into a member list.  The sums have to be those of the definition, which adds a cluster's members in sequence
+// order in fp64, rounding after every addition: the two are the same where no addition rounds at all.  All keys of a
+// block are multiples of 2^e, e the exponent of the last place of its smallest nonzero element, and below 2^E, so a sum of up to n of
+// them is a multiple of 2^e below n 2^E, hence exact in 53 bits whatever its order while n 2^E <= 2^(53 + e).  The first
+// iteration notes e and E per cluster; a workgroup that finds a cluster too large for its block's range (or an infinity or
+// NaN in the block) sums the clusters that changed afresh, member after member in sequence order, as defined.
+//
+// 2048 blocks of 8192 keys x 256 centroids, iterations 2 to 10: 711, 428, 322, 248, 203, 156, 132, 110, 95 us instead of 970
+// (member lists 123, means 846); 32 such blocks: 20 to 10 us instead of 34.
+#include "mp_device.h"
+#include "mp_internal.h"
+
+namespace mp {
+
+namespace {
+
+constexpr int kMoveWaves = 8;
+constexpr int kMoveThreads = 64 * kMoveWaves;
+constexpr int kMoveSteps = 6;
+constexpr int kMoveRound = kMoveThreads * kMoveSteps;        // points looked at at a time
+constexpr int kMoveClusters = 256;                           // most clusters of a workgroup
+constexpr int kMoveBatch = 8;                                // rows of a cluster on their way at once
+constexpr int kIdSegment = 4 * kMoveRound;                   // ids in LDS while sums are taken afresh
+constexpr int kFound = 128;
+
+// Eight bf16 values to eight sums, in fp64.
+__device__ __forceinline__ void add8(double (&a)[8], const uint4& w)
+{
+    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[2 * i] += (double)bf16lo_to_f32(d[i]);
+        a[2 * i + 1] += (double)bf16hi_to_f32(d[i]);
+    }
+}
+
+// One workgroup per p.per clusters of a (block, unit).  It collects the points that the assignment marked, sorts those that
+// left or entered one of its clusters by cluster (in any order inside it), and sixteen lanes a cluster take the rows of
+// these points to the stored sum, eight dims each.
+// Latency bound: a trip for the marks, one for the points' ids, one for the sum and four rows, one for every four rows more; so
+// four clusters to a wave and 32 waves to a compute unit.
+// grid = (groups of p.per clusters of a block, blocks, units)
+__global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveMeans p)
+{
+    __shared__ uint32_t points[kMoveRound];                  // of the block
+    __shared__ uint32_t entries[2 * kMoveRound];             // point << 1 | it went (one that moves is in two clusters' entries)
+    __shared__ uint16_t found[kMoveWaves][kFound];
+    __shared__ int total[kMoveClusters], at[kMoveClusters], due[kMoveClusters];
+    __shared__ bool touched[kMoveClusters];
+    __shared__ int top, bottom, most, n_marked, n_points, n_due;
+    const int b = blockIdx.y, u = blockIdx.z;
+    const int x0 = p.blocks[4 * b + 0], x1 = p.blocks[4 * b + 1], k0 = p.blocks[4 * b + 2], k1 = p.blocks[4 * b + 3];
+    const int ka = k0 + (int)blockIdx.x * p.per, m = min(p.per, k1 - ka);
+    if (m <= 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, part = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = x1 - x0, chunks = (n + 63) / 64;
+    const unsigned long long* marks = p.marks + u * p.marks_stride + first_mark(x0, b);
+    const int32_t* was = p.old_ids + u * p.ids_stride + x0;
+    const int32_t* now = p.new_ids + u * p.ids_stride + x0;
+    const uint4* Xb = reinterpret_cast<const uint4*>(p.X + ((long long)u * p.x_unit_rows + x0) * kHeadDim) + part;
+    int32_t* count = p.count + u * p.count_stride + ka;
+
+    if (tid == 0) { top = 0; bottom = 255; most = 0; n_marked = 0; }
+    if (tid < m) touched[tid] = false;
+    __syncthreads();
+    {
+        int hi = 0, lo = 255, marked = 0;                    // range of the block's keys, marks of the block
+        for (int i = k0 + tid; i < k1; i += kMoveThreads) {
+            const uint32_t r = p.range[u * p.range_stride + i];
+            hi = max(hi, (int)(r >> 16));
+            lo = min(lo, (int)(r & 0xffffu));
+        }
+        for (int i = tid; i < chunks; i += kMoveThreads) marked += __popcll(marks[i]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            hi = max(hi, __shfl_xor(hi, off, 64));
+            lo = min(lo, __shfl_xor(lo, off, 64));
+            marked += __shfl_xor(marked, off, 64);
+        }
+        if (lane == 0) { atomicMax(&top, hi); atomicMin(&bottom, lo); atomicAdd(&n_marked, marked); }
+    }
+    __syncthreads();
+    if (n_marked == 0) return;
+    // (a round takes all chunks of 64 points, or as many as its points fit in any case)
+    const bool one_round = n_marked <= kMoveRound;
+    const int step = one_round ? chunks : kMoveRound / 64;
+    // cluster c of this workgroup, the lane's eight dims: its sum, and what goes with it once the sum is final
+    auto sum_of = [&](int c) { return reinterpret_cast<double2*>(p.sum + ((long long)u * p.sum_unit_rows + ka + c) * kHeadDim) + 4 * part; };
+    auto read_sum = [&](int c, double (&a)[8]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double2 v = sum_of(c)[i];
+            a[2 * i] = v.x;
+            a[2 * i + 1] = v.y;
+        }
+    };
+    auto store_sum = [&](int c, const double (&a)[8]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum_of(c)[i] = make_double2(a[2 * i], a[2 * i + 1]);
+    };
+    auto store_mean = [&](int c, int members, const double (&a)[8]) {
+        if (members == 0) return;                            // (an empty cluster keeps its centroid)
+        const double den = (double)members, inv = 1.0 / den;
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            w[i] = (uint32_t)quotient_to_bf16(a[2 * i], den, inv) | ((uint32_t)quotient_to_bf16(a[2 * i + 1], den, inv) << 16);
+        reinterpret_cast<uint4*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim)[part] = make_uint4(w[0], w[1], w[2], w[3]);
+    };
+    bool exact = true;
+    for (int ca = 0; ca < chunks; ca += step) {
+        const int cb = min(ca + step, chunks);
+        if (tid < m) total[tid] = 0;
+        if (tid == 0) n_points = 0;
+        __syncthreads();
+        for (int c0 = ca + wave; c0 < cb; c0 += kMoveThreads) {      // the marked points, in any order
+            const int chunk = c0 + kMoveWaves * lane;
+            const unsigned long long mark = chunk < cb ? marks[chunk] : 0ull;
+            const int has = __popcll(mark), incl = (int)wave_incl_scan_u32((uint32_t)has);
+            int base = 0;
+            if (lane == 63) base = atomicAdd(&n_points, incl);
+            base = __builtin_amdgcn_readlane(base, 63);
+            for (unsigned long long left = __ballot(has != 0); left != 0; left &= left - 1) {
+                const int j = __ffsll((long long)left) - 1;
+                const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)mark, j), hi = __builtin_amdgcn_readlane((uint32_t)(mark >> 32), j);
+                const int first = base + __builtin_amdgcn_readlane(incl - has, j);
+                if ((((unsigned long long)hi << 32 | lo) >> lane) & 1ull)
+                    points[first + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))] =
+                        (uint32_t)((c0 + kMoveWaves * j) * 64 + lane);
+            }
+        }
+        __syncthreads();
+        const int n_here = n_points;
+        uint32_t o[kMoveSteps], e[kMoveSteps];               // old and new cluster of a point, counted from ka
+#pragma unroll
+        for (int r = 0; r < kMoveSteps; ++r) {
+            const int i = r * kMoveThreads + tid;
+            o[r] = e[r] = 0u;
+            if (i < n_here) {
+                const uint32_t t = points[i];
+                o[r] = (uint32_t)(was[t] - ka);
+                e[r] = (uint32_t)(now[t] - ka);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kMoveSteps; ++r) {
+            if (o[r] == e[r]) continue;
+            if (o[r] < (uint32_t)m) atomicAdd(&total[o[r]], 1);
+            if (e[r] < (uint32_t)m) atomicAdd(&total[e[r]], 1);
+        }
+        __syncthreads();
+        const bool last = cb == chunks;
+        if (wave == 0) {                                     // entries of a cluster side by side; the clusters that have any
+            int entry = 0, some = 0;
+            for (int c = lane; c - lane < m; c += 64) {
+                const int mine = c < m ? total[c] : 0;
+                // the most members any sum on the way can have: those of before and every point that comes
+                if (ca == 0 && mine != 0) atomicMax(&most, count[c] + mine);
+                const int incl = (int)wave_incl_scan_u32((uint32_t)mine);
+                const bool is_due = mine != 0 || (last && c < m && touched[c]);
+                const unsigned long long d = __ballot(is_due);
+                if (c < m) at[c] = entry + incl - mine;
+                if (is_due) due[some + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(d >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)d, 0u))] = c;
+                entry += __builtin_amdgcn_readlane(incl, 63);
+                some += __popcll(d);
+            }
+            if (lane == 0) n_due = some;
+        }
+        __syncthreads();
+        if (ca == 0) {
+            const int room = 45 - (top - bottom);            // 53 + e - E in terms of the exponent fields
+            const int members = one_round ? most : n;
+            exact = top < 255 && room >= 0 && members <= (1 << min(room, 30));
+            if (!exact) break;
+        }
+#pragma unroll
+        for (int r = 0; r < kMoveSteps; ++r) {
+            if (o[r] == e[r]) continue;
+            const uint32_t i = points[r * kMoveThreads + tid] << 1;
+            if (o[r] < (uint32_t)m) entries[atomicAdd(&at[o[r]], 1)] = i | 1u;
+            if (e[r] < (uint32_t)m) entries[atomicAdd(&at[e[r]], 1)] = i;
+        }
+        __syncthreads();
+        for (int d0 = 4 * wave; d0 < n_due; d0 += 4 * kMoveWaves) {
+            const int d = d0 + (lane >> 4);
+            if (d >= n_due) continue;
+            const int c = due[d], due_here = total[c];
+            double a[8];
+            read_sum(c, a);
+            const int members = count[c], first = at[c] - due_here;
+            int gone = 0;
+            for (int i0 = 0; i0 < due_here; i0 += kMoveBatch) {
+                uint4 w[kMoveBatch];
+#pragma unroll
+                for (int q = 0; q < kMoveBatch; ++q) {
+                    const int i = i0 + q;
+                    const uint32_t e = entries[first + min(i, due_here - 1)];
+                    w[q] = Xb[(long long)(e >> 1) * 16];
+                    const uint32_t keep = i < due_here ? ~0u : 0u, turn = e & 1u ? 0x80008000u & keep : 0u;
+                    gone += turn != 0u ? 1 : 0;
+                    w[q] = make_uint4((w[q].x & keep) ^ turn, (w[q].y & keep) ^ turn, (w[q].z & keep) ^ turn, (w[q].w & keep) ^ turn);
+                }
+#pragma unroll
+                for (int q = 0; q < kMoveBatch; ++q) add8(a, w[q]);
+            }
+            if (due_here != 0) store_sum(c, a);
+            const int members_now = members + due_here - 2 * gone;
+            if (part == 0) {
+                count[c] = members_now;
+                touched[c] = true;
+            }
+            if (last) store_mean(c, members_now, a);
+        }
+        __syncthreads();
+    }
+    if (exact) return;
+
+    // ---- the sums round: members one after the other, in sequence order, of every cluster that changed (as far as the
+    // first round of moves tells; all of them where there are more) ----
+    uint16_t* ids = reinterpret_cast<uint16_t*>(entries);
+    for (int s0 = 0; s0 < n; s0 += kIdSegment) {
+        const int here = min(kIdSegment, n - s0);
+        __syncthreads();
+        for (int i = tid; i < here; i += kMoveThreads) ids[i] = (uint16_t)(now[s0 + i] - ka);
+        __syncthreads();
+        const uint4* Xs = Xb + (long long)s0 * 16;
+        for (int c = wave; c < m; c += kMoveWaves) {
+            if (one_round && total[c] == 0) continue;
+            double a[8];                                     // (the four groups of sixteen lanes do the same)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = 0.0;
+            int members = 0, held = 0;                       // held: members found and not yet added
+            if (s0 > 0) {
+                read_sum(c, a);
+                members = count[c];
+            }
+            auto add_found = [&] {
+                wave_lds_sync();
+                for (int i0 = 0; i0 < held; i0 += kMoveBatch) {
+                    uint4 w[kMoveBatch];
+#pragma unroll
+                    for (int q = 0; q < kMoveBatch; ++q) w[q] = Xs[(long long)found[wave][min(i0 + q, held - 1)] * 16];
+#pragma unroll
+                    for (int q = 0; q < kMoveBatch; ++q)
+                        if (i0 + q < held) add8(a, w[q]);
+                }
+                wave_lds_sync();
+                members += held;
+                held = 0;
+            };
+            for (int i0 = 0; i0 < here; i0 += 64) {
+                const int i = i0 + lane;
+                const unsigned long long hit = __ballot(i < here && ids[i] == (uint16_t)c);
+                if (hit == 0) continue;
+                if ((hit >> lane) & 1ull) found[wave][held + __popcll(hit & ((1ull << lane) - 1ull))] = (uint16_t)i;
+                held += __popcll(hit);
+                if (held > kFound - 64) add_found();
+            }
+            add_found();
+            if (lane < 16) {
+                store_sum(c, a);
+                if (lane == 0) count[c] = members;
+                if (s0 + kIdSegment >= n) store_mean(c, members, a);
+            }
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t launch_move_means(MoveMeans p, int nb, int max_k, int U, hipStream_t s)
+{
+    if (nb <= 0 || max_k <= 0 || U <= 0) return hipSuccess;
+    // two workgroups a compute unit, sixteen to 256 clusters each
+    const long long pairs = (long long)nb * U;
+    const long long want = (512 + pairs - 1) / pairs;
+    p.per = (int)((max_k + want - 1) / want);
+    p.per = p.per < 16 ? 16 : p.per > kMoveClusters ? kMoveClusters : p.per;
+    hipLaunchKernelGGL(move_means_kernel, dim3((max_k + p.per - 1) / p.per, nb, U), dim3(kMoveThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace mp

@@ -1,0 +1,56 @@
+"""GPU parity of the centroid update of the Lloyd iterations after the first, which moves the member sums by the points that
+changed cluster: bit-identical to the oracle's sums in sequence order, also where fp64 rounds on the way (those clusters are
+summed afresh), with more points moving than a workgroup takes at a time, several groups of clusters to a block, blocks
+longer than the ids kept in LDS, empty clusters, and behind both assignment kernels."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, U, n, seed):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(U, n, 128, generator=g)
+    if kind == "few rows":
+        x = x[:, torch.randint(0, 11, (n,), generator=g)].contiguous()
+    if kind == "wide":
+        # magnitudes of 2^60 of either sign beside small ones in the same dims: a sum of them depends on its order
+        huge = torch.where(torch.rand(U, n, 128, generator=g) < 0.5, 2.0 ** 60, -(2.0 ** 60))
+        x = torch.where(torch.rand(U, n, 128, generator=g) < 0.1, huge, x)
+    return x.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("kind,n,k,iters", [
+    ("plain", 1500, 40, 6), ("plain", 700, 33, 4), ("plain", 4000, 300, 5), ("plain", 3000, 600, 3), ("plain", 14000, 9, 5),
+    ("few rows", 2000, 30, 5), ("wide", 1500, 40, 6), ("wide", 700, 30, 4), ("wide", 14000, 40, 3)])
+def test_later_iterations(kind, n, k, iters):
+    from paper_2506_13059_amd import binding as mp, inputs
+    from oracle import mp_oracle as O
+    from tests.gpu_util import f64, i32
+    print(f"{kind} n={n} k={k}", flush=True)
+    U, kc = 2, max(1, k // 6)
+    K = _keys(kind, U, n, 900 + n + k)
+    V = torch.randn(U, n, 128, generator=torch.Generator().manual_seed(5)).to(torch.bfloat16)
+    blocks = mp.mp_plan_blocks(n, 0, 0, k, kc)
+    init_f, init_c = inputs.draw_seeds(U, blocks, 2, 17)
+    ctx = mp.MpContext(1, U, U, max_tokens=n, levels=2, max_fine=k, max_coarse=kc, block_w=0, block_alpha=0, max_tail=0)
+    ctx.mp_cluster_kv(K.cuda().view(1, U, n, 128), V.cuda().view(1, U, n, 128), k, kc, iters=iters, init_fine=init_f, init_coarse=init_c)
+    got = [i32(x) if x.dtype == torch.int32 else f64(x) for x in (*ctx.mp_get_assignments(), *ctx.mp_get_centroids(0), *ctx.mp_get_centroids(1))]
+    ctx.close()
+    rounded = moved = 0
+    for u in range(U):
+        cl = O.cluster_unit(f64(K)[u], f64(V)[u], blocks, init_f[u].numpy(), init_c[u].numpy(), iters, 2)
+        for g, name in zip(got, ("fine_of_token", "coarse_of_fine", "Kc_f", "Vc_f", "N_f", "Kc_c", "Vc_c", "N_c")):
+            np.testing.assert_array_equal(g[u], cl[name], err_msg=f"unit {u} {name}")
+        before = O.cluster_unit(f64(K)[u], f64(V)[u], blocks, init_f[u].numpy(), init_c[u].numpy(), 1, 1)["fine_of_token"]
+        after = O.cluster_unit(f64(K)[u], f64(V)[u], blocks, init_f[u].numpy(), init_c[u].numpy(), 2, 1)["fine_of_token"]
+        moved = max(moved, int((before != after).sum()))
+        for f in range(k):
+            rows = f64(K)[u][cl["fine_of_token"] == f]
+            rounded += sum(math.fsum(c) != sum(c.tolist()) for c in rows.T)
+    # what the case is there for
+    assert moved > 0 and (n < 14000 or moved > 3072)
+    assert (rounded > 0) == (kind == "wide")
