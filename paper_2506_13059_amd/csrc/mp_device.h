@@ -120,6 +120,23 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Lanes of `valid` whose id equals this lane's (meaningless in the other lanes); ids of up to 3 `thirds` bits.
+__device__ __forceinline__ unsigned long long lanes_with_id(int id, bool valid, int thirds)
+{
+    const unsigned long long v = __ballot(valid);
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    for (int i = 0; i < thirds; ++i) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int bit = __builtin_amdgcn_sbfe(id, 3 * i + e, 1);            // 0 or -1
+            const unsigned long long m = __ballot(bit != 0);
+            lo &= ~((uint32_t)m ^ (uint32_t)bit);
+            hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
+        }
+    }
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 // ---- DPP cross-lane moves inside a row of 16 lanes ----------------------------------------------
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f32(float v)

@@ -109,23 +109,6 @@ __global__ __launch_bounds__(256) void member_list_kernel(const int32_t* __restr
 constexpr int kListWaves = 16;
 constexpr int kListSteps = 16;
 
-// Lanes of `valid` whose id equals this lane's (meaningless in the other lanes); ids of up to 3 `thirds` bits.
-__device__ __forceinline__ unsigned long long lanes_with_id(int id, bool valid, int thirds)
-{
-    const unsigned long long v = __ballot(valid);
-    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-    for (int i = 0; i < thirds; ++i) {
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            const int bit = __builtin_amdgcn_sbfe(id, 3 * i + e, 1);            // 0 or -1
-            const unsigned long long m = __ballot(bit != 0);
-            lo &= ~((uint32_t)m ^ (uint32_t)bit);
-            hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
-        }
-    }
-    return ((unsigned long long)hi << 32) | lo;
-}
-
 __global__ __launch_bounds__(1024) void block_lists_kernel(const int32_t* __restrict__ ids, long long ids_stride,
                                                            const int32_t* __restrict__ blocks /*[nb][4]: x0,x1,k0,k1*/,
                                                            int p_first, int waves, int32_t* __restrict__ start,

@@ -25,8 +25,7 @@ constexpr int kMoveSteps = 6;
 constexpr int kMoveRound = kMoveThreads * kMoveSteps;        // points looked at at a time
 constexpr int kMoveClusters = 256;                           // most clusters of a workgroup
 constexpr int kMoveBatch = 8;                                // rows of a cluster on their way at once
-constexpr int kIdSegment = 4 * kMoveRound;                   // ids in LDS while sums are taken afresh
-constexpr int kFound = 128;
+constexpr int kListSegment = 4 * kMoveRound;                 // points listed at a time while sums are taken afresh
 
 // Eight bf16 values to eight sums, in fp64.
 __device__ __forceinline__ void add8(double (&a)[8], const uint4& w)
@@ -49,7 +48,6 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
 {
     __shared__ uint32_t points[kMoveRound];                  // of the block
     __shared__ uint32_t entries[2 * kMoveRound];             // point << 1 | it went (one that moves is in two clusters' entries)
-    __shared__ uint16_t found[kMoveWaves][kFound];
     __shared__ int total[kMoveClusters], at[kMoveClusters], due[kMoveClusters];
     __shared__ bool touched[kMoveClusters];
     __shared__ int top, bottom, most, n_marked, n_points, n_due;
@@ -222,52 +220,96 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     if (exact) return;
 
     // ---- the sums round: members one after the other, in sequence order, of every cluster that changed (as far as the
-    // first round of moves tells; all of them where there are more) ----
-    uint16_t* ids = reinterpret_cast<uint16_t*>(entries);
-    for (int s0 = 0; s0 < n; s0 += kIdSegment) {
-        const int here = min(kIdSegment, n - s0);
+    // first round of moves tells; all of them where there are more).  A stable sort of a segment's points by cluster, each
+    // wave an eighth of them (as in block_lists_kernel), then the same sixteen lanes a cluster. ----
+    static_assert(kListSegment <= 65536 && kListSegment * 2 <= (int)sizeof(entries) && kMoveWaves * kMoveClusters * 4 <= (int)sizeof(points), "");
+    uint16_t* list = reinterpret_cast<uint16_t*>(entries);
+    int* place = reinterpret_cast<int*>(points);             // [kMoveWaves][m]
+    const int thirds = m > 1 ? (32 - __clz(m - 1) + 2) / 3 : 0;
+    for (int s0 = 0; s0 < n; s0 += kListSegment) {
+        const int here = min(kListSegment, n - s0);
+        const int per_wave = (here + kMoveThreads - 1) / kMoveThreads * 64, t0 = s0 + min(wave * per_wave, here), t1 = s0 + min((wave + 1) * per_wave, here);
+        int* mine = place + wave * m;
         __syncthreads();
-        for (int i = tid; i < here; i += kMoveThreads) ids[i] = (uint16_t)(now[s0 + i] - ka);
+        for (int i = tid; i < kMoveWaves * m; i += kMoveThreads) place[i] = 0;
+        if (s0 == 0 && !one_round)
+            for (int c = tid; c < m; c += kMoveThreads) due[c] = c;
+        __syncthreads();
+        auto walk = [&](bool write) {
+            constexpr int kAhead = 8;                        // ids on their way at once
+            for (int tb = t0; tb < t1; tb += 64 * kAhead) {
+                int id[kAhead];
+#pragma unroll
+                for (int r = 0; r < kAhead; ++r) {
+                    const int t = tb + 64 * r + lane;
+                    id[r] = t < t1 ? now[t] - ka : -1;
+                }
+#pragma unroll
+                for (int r = 0; r < kAhead; ++r) {
+                    const bool valid = (unsigned)id[r] < (unsigned)m;
+                    const unsigned long long same = lanes_with_id(id[r], valid, thirds);
+                    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+                    if (valid) {
+                        const int first = mine[id[r]];
+                        if (write) list[first + rank] = (uint16_t)(tb + 64 * r + lane - s0);
+                        if (rank == 0) mine[id[r]] = first + __popcll(same);
+                    }
+                }
+            }
+        };
+        walk(false);
+        __syncthreads();
+        for (int c = tid; c < m; c += kMoveThreads) {
+            int all = 0;
+            for (int w = 0; w < kMoveWaves; ++w) all += place[w * m + c];
+            at[c] = all;
+        }
+        __syncthreads();
+        if (wave == 0) {                                     // at: members in this segment -> first place
+            int first = 0;
+            for (int c = lane; c - lane < m; c += 64) {
+                const int all = c < m ? at[c] : 0, incl = (int)wave_incl_scan_u32((uint32_t)all);
+                if (c < m) at[c] = first + incl - all;
+                first += __builtin_amdgcn_readlane(incl, 63);
+            }
+        }
+        __syncthreads();
+        for (int c = tid; c < m; c += kMoveThreads) {
+            int next = at[c];
+            for (int w = 0; w < kMoveWaves; ++w) {
+                const int some = place[w * m + c];
+                place[w * m + c] = next;
+                next += some;
+            }
+        }
+        __syncthreads();
+        walk(true);
         __syncthreads();
         const uint4* Xs = Xb + (long long)s0 * 16;
-        for (int c = wave; c < m; c += kMoveWaves) {
-            if (one_round && total[c] == 0) continue;
-            double a[8];                                     // (the four groups of sixteen lanes do the same)
+        const int n_sums = one_round ? n_due : m;
+        for (int d0 = 4 * wave; d0 < n_sums; d0 += 4 * kMoveWaves) {
+            const int d = d0 + (lane >> 4);
+            if (d >= n_sums) continue;
+            const int c = due[d], first = at[c], end = place[(kMoveWaves - 1) * m + c];
+            double a[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) a[i] = 0.0;
-            int members = 0, held = 0;                       // held: members found and not yet added
+            int members = end - first;
             if (s0 > 0) {
                 read_sum(c, a);
-                members = count[c];
+                members += count[c];
             }
-            auto add_found = [&] {
-                wave_lds_sync();
-                for (int i0 = 0; i0 < held; i0 += kMoveBatch) {
-                    uint4 w[kMoveBatch];
+            for (int i0 = first; i0 < end; i0 += kMoveBatch) {
+                uint4 w[kMoveBatch];
 #pragma unroll
-                    for (int q = 0; q < kMoveBatch; ++q) w[q] = Xs[(long long)found[wave][min(i0 + q, held - 1)] * 16];
+                for (int q = 0; q < kMoveBatch; ++q) w[q] = Xs[(long long)list[min(i0 + q, end - 1)] * 16];
 #pragma unroll
-                    for (int q = 0; q < kMoveBatch; ++q)
-                        if (i0 + q < held) add8(a, w[q]);
-                }
-                wave_lds_sync();
-                members += held;
-                held = 0;
-            };
-            for (int i0 = 0; i0 < here; i0 += 64) {
-                const int i = i0 + lane;
-                const unsigned long long hit = __ballot(i < here && ids[i] == (uint16_t)c);
-                if (hit == 0) continue;
-                if ((hit >> lane) & 1ull) found[wave][held + __popcll(hit & ((1ull << lane) - 1ull))] = (uint16_t)i;
-                held += __popcll(hit);
-                if (held > kFound - 64) add_found();
+                for (int q = 0; q < kMoveBatch; ++q)
+                    if (i0 + q < end) add8(a, w[q]);
             }
-            add_found();
-            if (lane < 16) {
-                store_sum(c, a);
-                if (lane == 0) count[c] = members;
-                if (s0 + kIdSegment >= n) store_mean(c, members, a);
-            }
+            store_sum(c, a);
+            if (part == 0) count[c] = members;
+            if (s0 + kListSegment >= n) store_mean(c, members, a);
         }
     }
 }
