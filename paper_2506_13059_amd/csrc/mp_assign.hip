@@ -106,6 +106,19 @@ __device__ __forceinline__ float deposit_piece(unsigned char* tile_row, int seg,
     return s;
 }
 
+// The chunks [first, end) of 64 points of a block that has not changed since the last step: the same ids, no marks.
+__device__ __forceinline__ bool unchanged(const MoveMarks& mv, int u, int b, int cnt_stride)
+{
+    return mv.marks && mv.moved_before && mv.moved_before[u * cnt_stride + b] == 0;
+}
+__device__ __forceinline__ void keep_chunks(const MoveMarks& mv, int u, int b, int x0, int x1, int first, int end, int32_t* assign,
+                                            long long assign_stride)
+{
+    for (int t = x0 + 64 * first + (int)threadIdx.x; t < min(x0 + 64 * end, x1); t += (int)blockDim.x)
+        assign[u * assign_stride + t] = mv.old_ids[u * assign_stride + t];
+    for (int c = first + (int)threadIdx.x; c < end; c += (int)blockDim.x) mv.marks[u * mv.stride + first_mark(x0, b) + c] = 0;
+}
+
 // The two halves of a wave hold the other accumulator rows of the same points: combine them, write
 // the stage-1 assignment, and list the point for the exact pass unless its two best scores are
 // further apart than the margin.
@@ -165,6 +178,11 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
     const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2], k1 = blocks[4 * b + 3];
     const int p0 = x0 + (int)blockIdx.x * kPtsPerWg;
     if (p0 >= x1) return;
+    if (mv.marks && blockIdx.x == 0 && threadIdx.x == 0) mv.moved_now[u * cnt_stride + b] = 0;
+    if (unchanged(mv, u, b, cnt_stride)) {
+        keep_chunks(mv, u, b, x0, x1, (p0 - x0) / 64, min((p0 - x0 + kPtsPerWg) / 64, (x1 - x0 + 63) / 64), assign, assign_stride);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
 
@@ -580,6 +598,11 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     const int per = (all_chunks + (int)gridDim.x - 1) / (int)gridDim.x;
     const int chunk0 = (int)blockIdx.x * per, chunk1 = min(chunk0 + per, all_chunks);
     if (chunk0 >= chunk1) return;
+    if (mv.marks && blockIdx.x == 0 && threadIdx.x == 0) mv.moved_now[u * cnt_stride + b] = 0;
+    if (unchanged(mv, u, b, cnt_stride)) {
+        keep_chunks(mv, u, b, x0, x1, chunk0, chunk1, assign, assign_stride);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);

@@ -258,12 +258,14 @@ mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, hipStream_
         const int32_t* before = now.assign;
         if (pr.sums) now.assign = (iters - 1 - it) % 2 ? pr.other_assign : pr.assign;
         if (pr.sums && it > 0) {
-            const MoveMarks marks{before, ctx->km_marks, marks_of(ctx->Ncap, ctx->max_blocks)};
+            auto moved = [&](int i) { return ctx->km_moved + (size_t)(i & 1) * ctx->U * ctx->max_blocks; };
+            const MoveMarks marks{before, ctx->km_marks, marks_of(ctx->Ncap, ctx->max_blocks), it > 1 ? moved(it - 1) : nullptr, moved(it)};
             MP_TRY(launch_assign(ctx, now, marks, s));
             MoveMeans mv{};
             mv.X = pr.X; mv.x_unit_rows = pr.x_unit_rows; mv.blocks = pr.blocks_dev;
             mv.old_ids = before; mv.new_ids = now.assign; mv.ids_stride = pr.assign_stride;
             mv.marks = marks.marks; mv.marks_stride = marks.stride;
+            mv.moved = marks.moved_now; mv.moved_stride = ctx->max_blocks;
             mv.C = pr.C; mv.c_unit_rows = pr.c_unit_rows; mv.count = pr.cnt; mv.count_stride = pr.cnt_stride;
             mv.sum = pr.sums; mv.sum_unit_rows = pr.sum_unit_rows; mv.range = pr.range; mv.range_stride = pr.sum_unit_rows;
             MP_HIPC(launch_move_means(mv, pr.nb, pr.max_k, ctx->U, s));

@@ -133,6 +133,9 @@ struct MoveMarks {
     const int32_t* old_ids;        // [U, assign_stride] the assignment before
     unsigned long long* marks;     // [U, stride]
     long long stride;
+    const int32_t* moved_before;   // [U, cnt_stride]: did the step before move a point of block b?  If none, its centroids are as they
+                                   // were, and so is the assignment.  (no array: they may have changed in any case)
+    int32_t* moved_now;            // the same of this step, cleared here and set by launch_move_means
 };
 constexpr int first_mark(int x0, int b) { return (x0 >> 6) + b; }
 inline long long marks_of(long long points, int blocks) { return (points >> 6) + blocks + 1; }
@@ -220,6 +223,8 @@ struct MoveMeans {
     long long ids_stride;
     const unsigned long long* marks;   // [U, marks_stride] of the points whose two ids may differ
     long long marks_stride;
+    int32_t* moved;                // [U, moved_stride]: set for blocks of which a point moved
+    int moved_stride;
     uint16_t* C;                   // [U, c_unit_rows, 128], row = cluster id
     long long c_unit_rows;
     int32_t* count;                // [U, count_stride]

@@ -10,6 +10,9 @@
 // iteration notes e and E per cluster; a workgroup that finds a cluster too large for its block's range (or an infinity or
 // NaN in the block) sums the clusters that changed afresh, member after member in sequence order, as defined.
 //
+// A block of which no point moved has the centroids it had, so the next step keeps its assignment without looking at a key
+// (refresh of eight 8K contexts 804 -> 744 us).
+//
 // 2048 blocks of 8192 keys x 256 centroids, iterations 2 to 10: 711, 428, 322, 248, 203, 156, 132, 110, 95 us instead of 970
 // (member lists 123, means 846); 32 such blocks: 20 to 10 us instead of 34.
 #include "mp_device.h"
@@ -171,6 +174,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             if (lane == 0) n_due = some;
         }
         __syncthreads();
+        if (tid == 0 && n_due > 0) p.moved[u * p.moved_stride + b] = 1;
         if (ca == 0) {
             const int room = 45 - (top - bottom);            // 53 + e - E in terms of the exponent fields
             const int members = one_round ? most : n;
