@@ -510,16 +510,17 @@ mp_status mp_local_buffer_init(mp_ctx* ctx, int32_t window, const void* k_sink, 
         return fail(ctx, MP_ECAPACITY, "mp_local_buffer_init: n_sink + 2 * window = %lld > max_tail %d", (long long)n_sink + 2ll * window, ctx->Tcap);
     hipStream_t s = (hipStream_t)stream;
     const size_t row = kHeadDimHost * sizeof(uint16_t), pitch = (size_t)ctx->Tcap * row;
+    CopyBatch cb;
     if (n_sink > 0) {
-        MP_HIP(ctx, hipMemcpy2DAsync(ctx->Kt, pitch, k_sink, n_sink * row, n_sink * row, ctx->U, hipMemcpyDeviceToDevice, s));
-        MP_HIP(ctx, hipMemcpy2DAsync(ctx->Vt, pitch, v_sink, n_sink * row, n_sink * row, ctx->U, hipMemcpyDeviceToDevice, s));
+        cb.add(ctx->Kt, pitch, k_sink, n_sink * row, n_sink * row);
+        cb.add(ctx->Vt, pitch, v_sink, n_sink * row, n_sink * row);
     }
     if (n_recent > 0) {
-        MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Kt + n_sink * row, pitch, k_recent, n_recent * row, n_recent * row, ctx->U, hipMemcpyDeviceToDevice, s));
-        MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Vt + n_sink * row, pitch, v_recent, n_recent * row, n_recent * row, ctx->U, hipMemcpyDeviceToDevice, s));
-        if (k_recent_lookup)
-            MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Ktl + n_sink * row, pitch, k_recent_lookup, n_recent * row, n_recent * row, ctx->U, hipMemcpyDeviceToDevice, s));
+        cb.add((char*)ctx->Kt + n_sink * row, pitch, k_recent, n_recent * row, n_recent * row);
+        cb.add((char*)ctx->Vt + n_sink * row, pitch, v_recent, n_recent * row, n_recent * row);
+        if (k_recent_lookup) cb.add((char*)ctx->Ktl + n_sink * row, pitch, k_recent_lookup, n_recent * row, n_recent * row);
     }
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     ctx->lb_window = window;
     ctx->lb_sink = n_sink;
     ctx->lb_recent = n_recent;
@@ -547,18 +548,18 @@ mp_status refresh_local_buffer(mp_ctx* ctx, int32_t n_new_fine, int32_t n_new_co
     if (ctx->cfg.levels == 2 && (n_new_coarse < 0 || n_new_coarse > n_new_fine))
         return fail(ctx, MP_EINVAL, "mp_decode_step: n_new_coarse must be in [0, n_new_fine]");
     const size_t row = kHeadDimHost * sizeof(uint16_t), pitch = (size_t)ctx->Tcap * row;
-    MP_HIP(ctx, hipMemcpy2DAsync(ctx->Kts, L * row, (char*)ctx->Kt + ns * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    MP_HIP(ctx, hipMemcpy2DAsync(ctx->Vts, L * row, (char*)ctx->Vt + ns * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
     const bool lookup = ctx->cfg.lookup_keys != 0;
-    if (lookup)
-        MP_HIP(ctx, hipMemcpy2DAsync(ctx->Ktls, L * row, (char*)ctx->Ktl + ns * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    cb.add(ctx->Kts, L * row, (char*)ctx->Kt + ns * row, pitch, L * row);
+    cb.add(ctx->Vts, L * row, (char*)ctx->Vt + ns * row, pitch, L * row);
+    if (lookup) cb.add(ctx->Ktls, L * row, (char*)ctx->Ktl + ns * row, pitch, L * row);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     const mp_status st = update_clusters_impl(ctx, ctx->Kts, lookup ? ctx->Ktls : nullptr, ctx->Vts, L, n_new_fine,
                                               ctx->cfg.levels == 2 ? n_new_coarse : 0, refine_iters, split_iters, seed, seeds, s);
     if (st != MP_OK) return st;
-    if (lookup)
-        MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Ktl + ns * row, pitch, (char*)ctx->Ktl + (ns + L) * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Kt + ns * row, pitch, (char*)ctx->Kt + (ns + L) * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    MP_HIP(ctx, hipMemcpy2DAsync((char*)ctx->Vt + ns * row, pitch, (char*)ctx->Vt + (ns + L) * row, pitch, L * row, ctx->U, hipMemcpyDeviceToDevice, s));
+    for (uint16_t* t : {ctx->Kt, ctx->Vt, lookup ? ctx->Ktl : nullptr})
+        if (t) cb.add((char*)t + ns * row, pitch, (char*)t + (ns + L) * row, pitch, L * row);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     ctx->lb_recent = L;
     return MP_OK;
 }
@@ -643,12 +644,10 @@ mp_status mp_get_assignments(mp_ctx* ctx, int32_t* fine_of_token, int32_t* coars
     if (!ctx) return fail(nullptr, MP_EINVAL, "mp_get_assignments: null context");
     if (!ctx->has_index) return fail(ctx, MP_ESTATE, "mp_get_assignments: no index yet");
     hipStream_t s = (hipStream_t)stream;
-    if (fine_of_token)
-        MP_HIP(ctx, hipMemcpy2DAsync(fine_of_token, (size_t)ctx->n_tokens * 4, ctx->fot, (size_t)ctx->Ncap * 4,
-                                     (size_t)ctx->n_tokens * 4, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (coarse_of_fine && ctx->cfg.levels == 2)
-        MP_HIP(ctx, hipMemcpy2DAsync(coarse_of_fine, (size_t)ctx->n_fine * 4, ctx->cof, (size_t)ctx->Fcap * 4,
-                                     (size_t)ctx->n_fine * 4, ctx->U, hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    if (fine_of_token) cb.add(fine_of_token, (size_t)ctx->n_tokens * 4, ctx->fot, (size_t)ctx->Ncap * 4, (size_t)ctx->n_tokens * 4);
+    if (coarse_of_fine && ctx->cfg.levels == 2) cb.add(coarse_of_fine, (size_t)ctx->n_fine * 4, ctx->cof, (size_t)ctx->Fcap * 4, (size_t)ctx->n_fine * 4);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     return MP_OK;
 }
 
@@ -661,15 +660,11 @@ mp_status mp_get_centroids(mp_ctx* ctx, int32_t level, void* kc, void* vc, int32
     const int n = level == 0 ? ctx->n_fine : ctx->n_coarse;
     const size_t off = level == 0 ? 0 : (size_t)ctx->Fcap;
     const size_t row = kHeadDimHost * 2;
-    if (kc)
-        MP_HIP(ctx, hipMemcpy2DAsync(kc, n * row, (const char*)ctx->Kc + off * row, (size_t)ctx->tab_rows * row, n * row, ctx->U,
-                                     hipMemcpyDeviceToDevice, s));
-    if (vc)
-        MP_HIP(ctx, hipMemcpy2DAsync(vc, n * row, (const char*)ctx->Vc + off * row, (size_t)ctx->tab_rows * row, n * row, ctx->U,
-                                     hipMemcpyDeviceToDevice, s));
-    if (n_members)
-        MP_HIP(ctx, hipMemcpy2DAsync(n_members, (size_t)n * 4, ctx->Ncl + off, (size_t)ctx->tab_rows * 4, (size_t)n * 4, ctx->U,
-                                     hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    if (kc) cb.add(kc, n * row, (const char*)ctx->Kc + off * row, (size_t)ctx->tab_rows * row, n * row);
+    if (vc) cb.add(vc, n * row, (const char*)ctx->Vc + off * row, (size_t)ctx->tab_rows * row, n * row);
+    if (n_members) cb.add(n_members, (size_t)n * 4, ctx->Ncl + off, (size_t)ctx->tab_rows * 4, (size_t)n * 4);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     return MP_OK;
 }
 
@@ -708,15 +703,12 @@ mp_status mp_get_layout(mp_ctx* ctx, void* k_perm, void* v_perm, int32_t* perm, 
         return fail(ctx, MP_EINVAL, "mp_get_layout: this context stores 8-bit rows (use mp_get_kv_codes)");
     hipStream_t s = (hipStream_t)stream;
     const size_t row = kHeadDimHost * 2, n = ctx->n_tokens;
-    if (k_perm)
-        MP_HIP(ctx, hipMemcpy2DAsync(k_perm, n * row, ctx->Kp, (size_t)ctx->Ncap * row, n * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (v_perm)
-        MP_HIP(ctx, hipMemcpy2DAsync(v_perm, n * row, ctx->Vp, (size_t)ctx->Ncap * row, n * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (perm)
-        MP_HIP(ctx, hipMemcpy2DAsync(perm, n * 4, ctx->perm, (size_t)ctx->Ncap * 4, n * 4, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (fine_start)
-        MP_HIP(ctx, hipMemcpy2DAsync(fine_start, (size_t)(ctx->n_fine + 1) * 4, ctx->fstart, (size_t)(ctx->Fcap + 1) * 4,
-                                     (size_t)(ctx->n_fine + 1) * 4, ctx->U, hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    if (k_perm) cb.add(k_perm, n * row, ctx->Kp, (size_t)ctx->Ncap * row, n * row);
+    if (v_perm) cb.add(v_perm, n * row, ctx->Vp, (size_t)ctx->Ncap * row, n * row);
+    if (perm) cb.add(perm, n * 4, ctx->perm, (size_t)ctx->Ncap * 4, n * 4);
+    if (fine_start) cb.add(fine_start, (size_t)(ctx->n_fine + 1) * 4, ctx->fstart, (size_t)(ctx->Fcap + 1) * 4, (size_t)(ctx->n_fine + 1) * 4);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     return MP_OK;
 }
 
@@ -727,12 +719,11 @@ mp_status mp_get_kv_codes(mp_ctx* ctx, void* k_codes, void* v_codes, float* scal
     if (!ctx->has_index) return fail(ctx, MP_ESTATE, "mp_get_kv_codes: no index yet");
     hipStream_t s = (hipStream_t)stream;
     const size_t row = kHeadDimHost, n = ctx->n_tokens;
-    if (k_codes)
-        MP_HIP(ctx, hipMemcpy2DAsync(k_codes, n * row, ctx->Kq, (size_t)ctx->Ncap * row, n * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (v_codes)
-        MP_HIP(ctx, hipMemcpy2DAsync(v_codes, n * row, ctx->Vq, (size_t)ctx->Ncap * row, n * row, ctx->U, hipMemcpyDeviceToDevice, s));
-    if (scales)
-        MP_HIP(ctx, hipMemcpy2DAsync(scales, n * 8, ctx->kv_scale, (size_t)ctx->Ncap * 8, n * 8, ctx->U, hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    if (k_codes) cb.add(k_codes, n * row, ctx->Kq, (size_t)ctx->Ncap * row, n * row);
+    if (v_codes) cb.add(v_codes, n * row, ctx->Vq, (size_t)ctx->Ncap * row, n * row);
+    if (scales) cb.add(scales, n * 8, ctx->kv_scale, (size_t)ctx->Ncap * 8, n * 8);
+    MP_HIP(ctx, cb.launch(ctx->U, s));
     return MP_OK;
 }
 

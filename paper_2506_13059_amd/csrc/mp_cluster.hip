@@ -334,6 +334,7 @@ struct Range {
     int n_pts;
     std::vector<BlockPlan> blocks;  // t0/t1 = LOCAL point ranges; f*/c* = global cluster ids
     int f0, f1, c0, c1;
+    SequenceCopy seq{};             // where the stored keys and values of the last block are kept in sequence order
 };
 
 void upload_descs(const Range& r, int max_blocks, std::vector<int32_t>& bd, int& max_pts, int& max_kf, int& max_kc)
@@ -361,23 +362,25 @@ void upload_descs(const Range& r, int max_blocks, std::vector<int32_t>& bd, int&
 // member sums behind them, at the fine ids of before the renumbering when sum_map (new id - f0 -> old id) is given.
 mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void* Xv, long long x_unit_rows, int pt0,
                          int n_pts, const int32_t* ids, long long ids_stride, int f0, int f1, int c0, int c1, int nb,
-                         int max_kf, bool key_fallback, bool fine_keys_are_means, const int32_t* sum_map, hipStream_t s)
+                         int max_kf, bool key_fallback, bool fine_keys_are_means, const int32_t* sum_map, const SequenceCopy& seq,
+                         hipStream_t s)
 {
     const int U = ctx->U;
     const long long Ncap = ctx->Ncap, tab = ctx->tab_rows;
     const int32_t* bdev = ctx->blocks_dev + 4 * (size_t)ctx->max_blocks;
-    if (ids != ctx->fot + pt0)
-        MP_HIPC(hipMemcpy2DAsync(ctx->fot + pt0, (size_t)Ncap * 4, ids, (size_t)ids_stride * 4, (size_t)n_pts * 4, U,
-                                 hipMemcpyDeviceToDevice, s));
     MP_HIPC(launch_block_lists(ids, ids_stride, bdev, nb, max_kf, 0, U, ctx->km_start, tab + 1, ctx->km_list, Ncap, s));
-    MP_HIPC(launch_offset_lists(ctx->km_start, tab + 1, f0, f1, ctx->km_list, Ncap, n_pts, pt0, U, ctx->fstart,
-                                ctx->Fcap + 1, ctx->perm, Ncap, s));
+    const bool two = ctx->cfg.levels == 2;
+    StoredOrder so{};
+    so.start = ctx->km_start; so.start_stride = tab + 1; so.list = ctx->km_list; so.ids = ids != ctx->fot + pt0 ? ids : nullptr;
+    so.ids_stride = ids_stride; so.cof = two ? ctx->cof : nullptr; so.f0 = f0; so.f1 = f1; so.c0 = c0; so.c1 = c1;
+    so.n_pts = n_pts; so.pt0 = pt0; so.fcap = ctx->Fcap; so.ccap = ctx->Ccap; so.ncap = Ncap;
+    so.fstart = ctx->fstart; so.perm = ctx->perm; so.fot = ctx->fot; so.cstart = ctx->cstart;
+    MP_HIPC(launch_stored_order(so, U, s));
     const bool bytes = ctx->cfg.kv_format == MP_KV_E4M3;
     if (!bytes)
-        MP_HIPC(launch_gather_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, n_pts, U, ctx->Kp, ctx->Vp, Ncap, pt0, s));
+        MP_HIPC(launch_gather_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, n_pts, U, ctx->Kp, ctx->Vp, Ncap, pt0, seq, s));
     // (after a Lloyd iteration the working centroids already sitting in ctx->Kc ARE the member means of the
     // final assignment -- same members, same order of summation, same rounding: nothing to recompute)
-    const bool two = ctx->cfg.levels == 2;
     if (!fine_keys_are_means)
         MP_HIPC(launch_cluster_means((const uint16_t*)Xk, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
                                      ctx->Kc, tab, 0, key_fallback ? ctx->Kc : nullptr, tab, nullptr, 0, 0,
@@ -387,16 +390,14 @@ mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void
                                  nullptr, s));
     if (bytes)   // (8-bit keys are residuals from the fine key centroids, which are final only now)
         MP_HIPC(launch_gather_quantize_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, ids, ids_stride, ctx->Kc, tab, n_pts, U,
-                                            ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, s));
+                                            ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, seq, s));
     if (two) {
         // the coarse tables: sums of the children's sums, in ascending fine id (no further pass over the rows)
-        MP_HIPC(launch_coarse_start(ctx->cof, ctx->Fcap, f0, f1, c0, c1, U, ctx->cstart, ctx->Ccap + 1, s));
-        const uint16_t* kfb = key_fallback ? ctx->Kc + (long long)ctx->Fcap * kHeadDim : nullptr;
-        const int32_t* kmap = fine_keys_are_means ? sum_map : nullptr;
-        MP_HIPC(launch_coarse_from_children(ctx->sumK, ctx->Fcap, kmap, ctx->Fcap, f0, ctx->cstart, ctx->Ccap + 1, ctx->Ncl, tab,
-                                            c0, c1, U, ctx->Kc, tab, ctx->Fcap, kfb, tab, nullptr, 0, s));
-        MP_HIPC(launch_coarse_from_children(ctx->sumV, ctx->Fcap, nullptr, 0, f0, ctx->cstart, ctx->Ccap + 1, ctx->Ncl, tab,
-                                            c0, c1, U, ctx->Vc, tab, ctx->Fcap, nullptr, 0, ctx->Ncl, ctx->Fcap, s));
+        CoarseTables ct{};
+        ct.sumK = ctx->sumK; ct.sumV = ctx->sumV; ct.key_map = fine_keys_are_means ? sum_map : nullptr; ct.f0 = f0;
+        ct.cstart = ctx->cstart; ct.cstart_stride = ctx->Ccap + 1; ct.counts = ctx->Ncl; ct.c0 = c0; ct.c1 = c1;
+        ct.Kc = ctx->Kc; ct.Vc = ctx->Vc; ct.key_fallback = key_fallback ? ctx->Kc : nullptr; ct.fcap = ctx->Fcap; ct.tab_rows = tab;
+        MP_HIPC(launch_coarse_from_children(ct, U, s));
     }
     return MP_OK;
 }
@@ -470,7 +471,24 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
         MP_HIPC(hipGetLastError());
     }
     return finalize_range(ctx, r.Xk, r.Xs, r.Xv, r.x_unit_rows, r.pt0, r.n_pts, ctx->km_assign, ctx->Ncap, r.f0, r.f1, r.c0,
-                          r.c1, nb, max_kf, true, fine_keys_are_means, two ? ctx->km_plist : nullptr, s);
+                          r.c1, nb, max_kf, true, fine_keys_are_means, two ? ctx->km_plist : nullptr, r.seq, s);
+}
+
+// The n tokens of the last block (from t0) in sequence order, as the gather leaves them: keys and values, or with lookup keys
+// (which the clusters are formed on) the stored keys and values.  Nothing where the block exceeds the update workspace.
+SequenceCopy sequence_copy(mp_ctx* ctx, int t0, int n, bool lookup)
+{
+    if (n > ctx->FBcap) return SequenceCopy{};
+    return SequenceCopy{lookup ? ctx->Kfs : ctx->Kfb, ctx->Vfb, ctx->FBcap, t0};
+}
+mp_status keep_lookup_keys(mp_ctx* ctx, const void* k_lookup, int n_tokens, int t0, int n, hipStream_t s)
+{
+    if (!k_lookup || n > ctx->FBcap) return MP_OK;
+    const size_t row = kHeadDim * sizeof(uint16_t);
+    CopyBatch cb;
+    cb.add(ctx->Kfb, (size_t)ctx->FBcap * row, (const char*)k_lookup + (size_t)t0 * row, (size_t)n_tokens * row, (size_t)n * row);
+    MP_HIPC(cb.launch(ctx->U, s));
+    return MP_OK;
 }
 
 // Fresh clustering of a range: seeds are on the device (km_seed_f / km_seed_c at the range's ids).
@@ -537,22 +555,13 @@ mp_status cluster_kv_impl(mp_ctx* ctx, const void* k, const void* k_lookup, cons
     r.Xk = (const uint16_t*)(k_lookup ? k_lookup : k); r.Xs = (const uint16_t*)k; r.Xv = (const uint16_t*)v;
     r.x_unit_rows = n_tokens; r.pt0 = 0; r.n_pts = n_tokens;
     r.blocks = blocks; r.f0 = 0; r.f1 = n_fine; r.c0 = 0; r.c1 = n_coarse;
-    const mp_status st = cluster_range(ctx, r, iters, s);
-    if (st != MP_OK) return st;
-
-    // keep the last block in sequence order for the online update
+    // the last block is kept in sequence order for the online update
     const BlockPlan& lb = blocks.back();
     const int nlast = lb.t1 - lb.t0;
-    if (nlast <= ctx->FBcap) {
-        const size_t row = kHeadDim * sizeof(uint16_t);
-        MP_HIPC(hipMemcpy2DAsync(ctx->Kfb, (size_t)ctx->FBcap * row, (const char*)r.Xk + (size_t)lb.t0 * row,
-                                 (size_t)n_tokens * row, (size_t)nlast * row, U, hipMemcpyDeviceToDevice, s));
-        if (k_lookup)
-            MP_HIPC(hipMemcpy2DAsync(ctx->Kfs, (size_t)ctx->FBcap * row, (const char*)k + (size_t)lb.t0 * row,
-                                     (size_t)n_tokens * row, (size_t)nlast * row, U, hipMemcpyDeviceToDevice, s));
-        MP_HIPC(hipMemcpy2DAsync(ctx->Vfb, (size_t)ctx->FBcap * row, (const char*)v + (size_t)lb.t0 * row,
-                                 (size_t)n_tokens * row, (size_t)nlast * row, U, hipMemcpyDeviceToDevice, s));
-    }
+    r.seq = sequence_copy(ctx, lb.t0, nlast, k_lookup != nullptr);
+    const mp_status st = cluster_range(ctx, r, iters, s);
+    if (st != MP_OK) return st;
+    MP_TRY(keep_lookup_keys(ctx, k_lookup, n_tokens, lb.t0, nlast, s));
     ctx->n_tokens = n_tokens;
     ctx->n_fine = n_fine;
     ctx->n_coarse = two ? n_coarse : 0;
@@ -569,11 +578,10 @@ mp_status set_clustering_impl(mp_ctx* ctx, const void* k, const void* k_lookup, 
     MP_TRY(stage_open(ctx));
     const int U = ctx->U;
     const bool two = ctx->cfg.levels == 2;
-    MP_HIPC(hipMemcpy2DAsync(ctx->fot, (size_t)ctx->Ncap * 4, fine_of_token, (size_t)n_tokens * 4, (size_t)n_tokens * 4, U,
-                             hipMemcpyDeviceToDevice, s));
-    if (two)
-        MP_HIPC(hipMemcpy2DAsync(ctx->cof, (size_t)ctx->Fcap * 4, coarse_of_fine, (size_t)n_fine * 4, (size_t)n_fine * 4, U,
-                                 hipMemcpyDeviceToDevice, s));
+    CopyBatch cb;
+    cb.add(ctx->fot, (size_t)ctx->Ncap * 4, fine_of_token, (size_t)n_tokens * 4, (size_t)n_tokens * 4);
+    if (two) cb.add(ctx->cof, (size_t)ctx->Fcap * 4, coarse_of_fine, (size_t)n_fine * 4, (size_t)n_fine * 4);
+    MP_HIPC(cb.launch(U, s));
     Range r;
     r.blocks.assign(1, BlockPlan{0, n_tokens, 0, n_fine, 0, n_coarse});
     int max_pts, max_kf, max_kc;
@@ -583,18 +591,9 @@ mp_status set_clustering_impl(mp_ctx* ctx, const void* k, const void* k_lookup, 
     MP_TRY(flush_uploads(ctx, s));
     const void* xk = k_lookup ? k_lookup : k;
     const mp_status st = finalize_range(ctx, xk, k, v, n_tokens, 0, n_tokens, ctx->fot, ctx->Ncap, 0, n_fine, 0, n_coarse, 1,
-                                        max_kf, false, false, nullptr, s);
+                                        max_kf, false, false, nullptr, sequence_copy(ctx, 0, n_tokens, k_lookup != nullptr), s);
     if (st != MP_OK) return st;
-    if (n_tokens <= ctx->FBcap) {
-        const size_t row = kHeadDim * sizeof(uint16_t);
-        MP_HIPC(hipMemcpy2DAsync(ctx->Kfb, (size_t)ctx->FBcap * row, xk, (size_t)n_tokens * row, (size_t)n_tokens * row, U,
-                                 hipMemcpyDeviceToDevice, s));
-        if (k_lookup)
-            MP_HIPC(hipMemcpy2DAsync(ctx->Kfs, (size_t)ctx->FBcap * row, k, (size_t)n_tokens * row, (size_t)n_tokens * row, U,
-                                     hipMemcpyDeviceToDevice, s));
-        MP_HIPC(hipMemcpy2DAsync(ctx->Vfb, (size_t)ctx->FBcap * row, v, (size_t)n_tokens * row, (size_t)n_tokens * row, U,
-                                 hipMemcpyDeviceToDevice, s));
-    }
+    MP_TRY(keep_lookup_keys(ctx, k_lookup, n_tokens, 0, n_tokens, s));
     ctx->n_tokens = n_tokens;
     ctx->n_fine = n_fine;
     ctx->n_coarse = two ? n_coarse : 0;
@@ -676,15 +675,18 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     const size_t row = kHeadDim * sizeof(uint16_t);
     const long long Fcap = ctx->Fcap, Ccap1 = std::max(ctx->Ccap, 1), Ncap = ctx->Ncap;
 
-    // ---- append the new tokens to the sequence-ordered copy of the last block ----
-    MP_HIPC(hipMemcpy2DAsync((char*)ctx->Kfb + (size_t)nb_old * row, (size_t)ctx->FBcap * row,
-                             k_new_lookup ? k_new_lookup : k_new, (size_t)n_new * row, (size_t)n_new * row, U,
-                             hipMemcpyDeviceToDevice, s));
-    if (k_new_lookup)
-        MP_HIPC(hipMemcpy2DAsync((char*)ctx->Kfs + (size_t)nb_old * row, (size_t)ctx->FBcap * row, k_new, (size_t)n_new * row,
-                                 (size_t)n_new * row, U, hipMemcpyDeviceToDevice, s));
-    MP_HIPC(hipMemcpy2DAsync((char*)ctx->Vfb + (size_t)nb_old * row, (size_t)ctx->FBcap * row, v_new, (size_t)n_new * row,
-                             (size_t)n_new * row, U, hipMemcpyDeviceToDevice, s));
+    // ---- the new tokens go behind the sequence-ordered copy of the last block; working fine centroids: the stored key
+    // centroids (the new seeds follow); the block's ids ----
+    {
+        CopyBatch cb;
+        const size_t behind = (size_t)nb_old * row, pitch = (size_t)ctx->FBcap * row, width = (size_t)n_new * row;
+        cb.add((char*)ctx->Kfb + behind, pitch, k_new_lookup ? k_new_lookup : k_new, width, width);
+        if (k_new_lookup) cb.add((char*)ctx->Kfs + behind, pitch, k_new, width, width);
+        cb.add((char*)ctx->Vfb + behind, pitch, v_new, width, width);
+        cb.add(ctx->km_Cf + (size_t)f0 * kHeadDim, Fcap * row, ctx->Kc + (size_t)f0 * kHeadDim, ctx->tab_rows * row, (size_t)kf_old * row);
+        cb.add(ctx->km_assign, (size_t)Ncap * 4, ctx->fot + t0, (size_t)Ncap * 4, (size_t)nb_old * 4);
+        MP_HIPC(cb.launch(U, s));
+    }
     // seeds of the new clusters, at their global ids
     if (n_new_fine > 0)
         MP_TRY(upload_2d(ctx, ctx->km_seed_f + lb.f1, (size_t)Fcap * 4, seeds + off[0], (size_t)total * 4,
@@ -710,10 +712,6 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     MP_TRY(upload(ctx, ctx->blocks_dev, sd.data(), sd.size() * sizeof(int32_t), s));
     MP_TRY(flush_uploads(ctx, s));
 
-    // ---- working fine centroids: the stored key centroids, then the new seeds ----
-    hipLaunchKernelGGL(gather1_rows_kernel, dim3(blocks_for((long long)kf_old * 16, 256), U), dim3(256), 0, s,
-                       (const uint4*)ctx->Kc, ctx->tab_rows, f0, nullptr, 0, 0, kf_old, (uint4*)ctx->km_Cf, Fcap, f0);
-    MP_HIPC(hipGetLastError());
     if (n_new_fine > 0) {
         hipLaunchKernelGGL(init_centroids_kernel, dim3(1, U), dim3(256), 0, s, ctx->Kfb, (long long)ctx->FBcap,
                            ctx->blocks_dev + 4, ctx->km_seed_f, Fcap, ctx->km_Cf, Fcap);
@@ -724,8 +722,6 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
                               ctx->km_assign, Ncap, ctx->km_list, Ncap, amb_counters(ctx, 0), amb_counters(ctx, 1),
                               ctx->max_blocks, MoveMarks{}, s));
     ctx->amb_turn ^= 1;
-    MP_HIPC(hipMemcpy2DAsync(ctx->km_assign, (size_t)Ncap * 4, ctx->fot + t0, (size_t)Ncap * 4, (size_t)nb_old * 4, U,
-                             hipMemcpyDeviceToDevice, s));
     hipLaunchKernelGGL(running_mean_kernel, dim3((kf + 3) / 4, U), dim3(256), 0, s, ctx->Kfb, (long long)ctx->FBcap,
                        nb_old, nb, ctx->km_assign, Ncap, f0, f1, lb.f1, ctx->Ncl, ctx->tab_rows, ctx->km_Cf, Fcap);
     MP_HIPC(hipGetLastError());
@@ -762,15 +758,12 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
         if (st != MP_OK) return st;
         // the remaining tokens become the new last block: move them to the front of the sequence-ordered
         // copies, W rows at a time (a piece never overlaps its destination, W rows further down)
-        uint16_t* bufs[3] = {ctx->Kfb, ctx->Vfb, k_new_lookup ? ctx->Kfs : nullptr};
-        for (uint16_t* b : bufs) {
-            if (!b) continue;
-            for (int done = 0; done < nb - W; done += W) {
-                const int rows_now = std::min(W, nb - W - done);
-                MP_HIPC(hipMemcpy2DAsync((char*)b + (size_t)done * row, (size_t)ctx->FBcap * row,
-                                         (const char*)b + (size_t)(W + done) * row, (size_t)ctx->FBcap * row,
-                                         (size_t)rows_now * row, U, hipMemcpyDeviceToDevice, s));
-            }
+        for (int done = 0; done < nb - W; done += W) {
+            CopyBatch cb;
+            const size_t pitch = (size_t)ctx->FBcap * row, width = (size_t)std::min(W, nb - W - done) * row;
+            for (uint16_t* b : {ctx->Kfb, ctx->Vfb, k_new_lookup ? ctx->Kfs : nullptr})
+                if (b) cb.add((char*)b + (size_t)done * row, pitch, (const char*)b + (size_t)(W + done) * row, pitch, width);
+            MP_HIPC(cb.launch(U, s));
         }
         ctx->blocks.back() = BlockPlan{t0, t0 + W, f0, f0 + cnts[2], c0, c0 + cnts[4]};
         ctx->blocks.push_back(BlockPlan{t0 + W, t0 + nb, f0 + cnts[2], f1, c0 + cnts[4], c1});

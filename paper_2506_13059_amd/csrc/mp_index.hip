@@ -4,6 +4,7 @@
 //
 // Member sums run over the members in sequence order, one wave per cluster, in fp64: the result
 // does not depend on the launch shape and repeats bit for bit.
+#include <algorithm>
 #include <type_traits>
 
 #include "mp_device.h"
@@ -12,82 +13,6 @@
 namespace mp {
 
 namespace {
-
-// cnt[u][id[u][t]] += 1
-__global__ void histogram_kernel(const int32_t* __restrict__ ids, long long ids_stride, int n,
-                                 int32_t* __restrict__ cnt, long long cnt_stride)
-{
-    const int u = blockIdx.y;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) atomicAdd(cnt + u * cnt_stride + ids[u * ids_stride + t], 1);
-}
-
-// start[u][0..k] = exclusive prefix sum of cnt[u][0..k), one workgroup of 1024 threads per unit.
-__global__ __launch_bounds__(1024) void exclusive_scan_kernel(const int32_t* __restrict__ cnt, long long cnt_stride,
-                                                              int k, int32_t* __restrict__ start,
-                                                              long long start_stride)
-{
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry_s;
-    const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) carry_s = 0;
-    __syncthreads();
-    for (int base = 0; base < k; base += 1024) {
-        const int i = base + tid;
-        const uint32_t v = (i < k) ? (uint32_t)cnt[u * cnt_stride + i] : 0u;
-        const uint32_t incl = wave_incl_scan_u32(v);
-        if (lane == 63) wsum[wave] = incl;
-        __syncthreads();
-        uint32_t woff = 0;
-        for (int w = 0; w < wave; ++w) woff += wsum[w];
-        const uint32_t carry = carry_s;
-        if (i < k) start[u * start_stride + i] = (int32_t)(carry + woff + incl - v);
-        __syncthreads();
-        if (tid == 1023) carry_s = carry + woff + incl;
-        __syncthreads();
-    }
-    if (tid == 0) start[u * start_stride + k] = (int32_t)carry_s;
-}
-
-// Member lists: list[u][start[id] + rank] = point index, points of a cluster in ascending order.
-// One thread per cluster walks the ids of its block (staged through LDS, every lane reads the same
-// word, which LDS serves as a broadcast) and appends its own members.
-// grid = (ceil(max clusters per block / 256), n_blocks, U)
-constexpr int kListTile = 4096;
-__global__ __launch_bounds__(256) void member_list_kernel(const int32_t* __restrict__ ids, long long ids_stride,
-                                                          const int32_t* __restrict__ blocks /*[nb][4]: x0,x1,k0,k1*/,
-                                                          const int32_t* __restrict__ start, long long start_stride,
-                                                          int32_t* __restrict__ list, long long list_stride)
-{
-    __shared__ int32_t tile[kListTile];
-    const int u = blockIdx.z, b = blockIdx.y;
-    const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2], k1 = blocks[4 * b + 3];
-    const int kbase = k0 + blockIdx.x * 256;
-    if (kbase >= k1) return;
-    const int my = kbase + threadIdx.x;
-    const bool live = my < k1;
-    int wr = live ? start[u * start_stride + my] : 0;
-    const int32_t* idp = ids + u * ids_stride;
-    int32_t* lp = list + u * list_stride;
-    for (int t0 = x0; t0 < x1; t0 += kListTile) {
-        const int nt = (x1 - t0 < kListTile) ? x1 - t0 : kListTile;
-        __syncthreads();
-        for (int i = threadIdx.x; i < nt; i += 256) tile[i] = idp[t0 + i];
-        __syncthreads();
-        if (live) {
-            int i = 0;
-            for (; i + 4 <= nt; i += 4) {
-                const int4 v = *reinterpret_cast<const int4*>(&tile[i]);
-                if (v.x == my) lp[wr++] = t0 + i;
-                if (v.y == my) lp[wr++] = t0 + i + 1;
-                if (v.z == my) lp[wr++] = t0 + i + 2;
-                if (v.w == my) lp[wr++] = t0 + i + 3;
-            }
-            for (; i < nt; ++i)
-                if (tile[i] == my) lp[wr++] = t0 + i;
-        }
-    }
-}
 
 // Member lists and their offsets for every block of a unit in one launch: a stable counting sort of
 // the block's points by cluster id.  One workgroup of 16 waves per (block, unit); `waves` of them
@@ -242,11 +167,20 @@ __global__ __launch_bounds__(1024) void block_lists_kernel(const int32_t* __rest
     }
 }
 
+// Where the gather leaves rows s >= t0 of its sources once more, in sequence order: row s - t0 of K and V (each optional).
+__device__ __forceinline__ void keep_in_sequence(const SequenceCopy& q, int u, long long s, int c, const uint4& k, const uint4& v)
+{
+    if (s < q.t0) return;
+    const long long at = ((long long)u * q.unit_rows + s - q.t0) * 16 + c;
+    if (q.K) store_once(reinterpret_cast<uint4*>(q.K) + at, k);
+    if (q.V) store_once(reinterpret_cast<uint4*>(q.V) + at, v);
+}
+
 // dst[u][p] = src[u][list[u][p]] for 256-byte rows; one thread moves 16 bytes.
 __global__ void gather_rows_kernel(const uint4* __restrict__ srcK, const uint4* __restrict__ srcV,
                                    long long src_unit_rows, const int32_t* __restrict__ list, long long list_stride,
                                    int n, uint4* __restrict__ dstK, uint4* __restrict__ dstV, long long dst_unit_rows,
-                                   int dst_row0)
+                                   int dst_row0, const SequenceCopy seq)
 {
     const int u = blockIdx.y;
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -255,8 +189,10 @@ __global__ void gather_rows_kernel(const uint4* __restrict__ srcK, const uint4* 
     if (p >= n) return;
     const long long s = list[u * list_stride + p];
     // (a pure stream: every line is read once and written once)
-    store_once(&dstK[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], load_once(&srcK[((long long)u * src_unit_rows + s) * 16 + c]));
-    store_once(&dstV[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], load_once(&srcV[((long long)u * src_unit_rows + s) * 16 + c]));
+    const uint4 k = load_once(&srcK[((long long)u * src_unit_rows + s) * 16 + c]), v = load_once(&srcV[((long long)u * src_unit_rows + s) * 16 + c]);
+    store_once(&dstK[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], k);
+    store_once(&dstV[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], v);
+    keep_in_sequence(seq, u, s, c, k, v);
 }
 
 // The same gather into 8-bit storage.  A value row becomes 128 e4m3 codes (OCP format: bias 7,
@@ -302,7 +238,8 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
                                             long long list_stride, const int32_t* __restrict__ ids, long long ids_stride,
                                             const uint4* __restrict__ Kc, long long kc_unit_rows, int n,
                                             uint2* __restrict__ dstK, uint2* __restrict__ dstV,
-                                            float2* __restrict__ scales, long long dst_unit_rows, int dst_row0)
+                                            float2* __restrict__ scales, long long dst_unit_rows, int dst_row0,
+                                            const SequenceCopy seq)
 {
     const int u = blockIdx.y;
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -311,9 +248,11 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
     if (p >= n) return;   // (all sixteen threads of a row leave together)
     const long long s = list[u * list_stride + p];
     const long long f = ids[u * ids_stride + s];
-    F8 k = widen8(srcK[((long long)u * src_unit_rows + s) * 16 + c]);
+    const uint4 kw = srcK[((long long)u * src_unit_rows + s) * 16 + c], vw = srcV[((long long)u * src_unit_rows + s) * 16 + c];
+    keep_in_sequence(seq, u, s, c, kw, vw);
+    F8 k = widen8(kw);
     const F8 cen = widen8(Kc[((long long)u * kc_unit_rows + f) * 16 + c]);
-    const F8 v = widen8(srcV[((long long)u * src_unit_rows + s) * 16 + c]);
+    const F8 v = widen8(vw);
 #pragma unroll
     for (int i = 0; i < 8; ++i) k.v[i] -= cen.v[i];
     float ka = absmax8(k), va = absmax8(v);
@@ -409,29 +348,24 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     if (sum_out) reinterpret_cast<double2*>(sum_out + ((long long)u * sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a0, a1);
 }
 
-// Stored tables of the coarse clusters [c0, c1) from those of their fine clusters (Sec. 3.4: a coarse
+// Stored tables of the coarse clusters [c0, c1), keys (z = 0) and values, from those of their fine clusters (Sec. 3.4: a coarse
 // centroid is the mean of all rows below it): one wave per coarse cluster adds its children's fp64 member
 // sums in ascending fine id, starting from zero, divides by the children's member count and rounds once
-// to bf16.  The sum of fine cluster f is row (map ? map[f - map_f0] : f) of `sums` (sums taken before a
-// renumbering sit at the old ids).  Empty cluster: `fallback` row if given (else zeros).  Lane l owns
+// to bf16.  The key sum of fine cluster f is row (key_map ? key_map[f - f0] : f) of sumK (sums taken before a
+// renumbering sit at the old ids).  Empty cluster: `key_fallback` row if given (else zeros).  Lane l owns
 // dims 2l and 2l+1, as in cluster_mean_kernel.
-__global__ __launch_bounds__(256) void coarse_from_children_kernel(const double* __restrict__ sums, long long sum_unit_rows,
-                                                                   const int32_t* __restrict__ map, long long map_stride,
-                                                                   int map_f0, const int32_t* __restrict__ cstart,
-                                                                   long long cstart_stride,
-                                                                   const int32_t* __restrict__ fine_count,
-                                                                   long long count_stride, int c0, int c1,
-                                                                   uint16_t* __restrict__ mean_out, long long out_unit_rows,
-                                                                   int out_row0, const uint16_t* __restrict__ fallback,
-                                                                   long long fb_unit_rows, int32_t* __restrict__ count_out,
-                                                                   int count_off)
+__global__ __launch_bounds__(256) void coarse_from_children_kernel(const CoarseTables p)
 {
     const int u = blockIdx.y;
-    const int c = c0 + blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int c = p.c0 + blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (c >= c1) return;
-    const int f_begin = cstart[u * cstart_stride + c], f_end = cstart[u * cstart_stride + c + 1];
-    const double2* Su = reinterpret_cast<const double2*>(sums + (long long)u * sum_unit_rows * kHeadDim);
+    if (c >= p.c1) return;
+    const bool keys = blockIdx.z == 0;
+    const int32_t* map = keys ? p.key_map : nullptr;
+    const uint16_t* fallback = keys ? p.key_fallback : nullptr;
+    const int f_begin = p.cstart[u * p.cstart_stride + c], f_end = p.cstart[u * p.cstart_stride + c + 1];
+    const double2* Su = reinterpret_cast<const double2*>((keys ? p.sumK : p.sumV) + (long long)u * p.fcap * kHeadDim);
+    int32_t* counts = p.counts + u * p.tab_rows;
     double a0 = 0.0, a1 = 0.0;
     long long n = 0;
     for (int base = f_begin; base < f_end; base += 8) {      // eight children's rows in flight, added in order
@@ -443,9 +377,9 @@ __global__ __launch_bounds__(256) void coarse_from_children_kernel(const double*
             w[q] = make_double2(0.0, 0.0);
             cnt[q] = 0;
             if (f < f_end) {
-                const long long src = map ? map[u * map_stride + (f - map_f0)] : f;
+                const long long src = map ? map[u * (long long)p.fcap + (f - p.f0)] : f;
                 w[q] = Su[src * 64 + lane];
-                cnt[q] = fine_count[u * count_stride + f];
+                cnt[q] = counts[f];
             }
         }
 #pragma unroll
@@ -462,51 +396,50 @@ __global__ __launch_bounds__(256) void coarse_from_children_kernel(const double*
         const double inv = (double)n;
         outw = (uint32_t)f64_to_bf16_rne(a0 / inv) | ((uint32_t)f64_to_bf16_rne(a1 / inv) << 16);
     } else if (fallback) {
-        outw = reinterpret_cast<const uint32_t*>(fallback + ((long long)u * fb_unit_rows + c) * kHeadDim)[lane];
+        outw = reinterpret_cast<const uint32_t*>(fallback + ((long long)u * p.tab_rows + p.fcap + c) * kHeadDim)[lane];
     } else {
         outw = 0u;
     }
-    reinterpret_cast<uint32_t*>(mean_out + ((long long)u * out_unit_rows + out_row0 + c) * kHeadDim)[lane] = outw;
-    if (count_out && lane == 0) count_out[u * count_stride + count_off + c] = (int32_t)n;
+    reinterpret_cast<uint32_t*>((keys ? p.Kc : p.Vc) + ((long long)u * p.tab_rows + p.fcap + c) * kHeadDim)[lane] = outw;
+    if (!keys && lane == 0) counts[p.fcap + c] = (int32_t)n;
 }
 
-// For the fine range [f0, f1) whose coarse ids lie in [c0, c1) and are non-decreasing in the fine id:
-// cstart[u][c] = first fine id of the range whose coarse id is >= c, for c in [c0, c1]; cstart[c1] = f1.
-__global__ void coarse_start_kernel(const int32_t* __restrict__ cof, long long cof_stride, int f0, int f1, int c0,
-                                    int c1, int32_t* __restrict__ cstart, long long cstart_stride)
-{
-    const int u = blockIdx.y;
-    const int f = f0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (f > f1) return;
-    const int cur = (f < f1) ? cof[u * cof_stride + f] : c1;
-    const int prev = (f > f0) ? cof[u * cof_stride + f - 1] : c0 - 1;
-    for (int c = prev + 1; c <= cur; ++c) cstart[u * cstart_stride + c] = f;
-}
-
-// Stored-order tables from member lists built on local point indices:
-// fstart[u][f] = pt0 + start[u][f] for f in [f0, f1];  perm[u][pt0 + p] = pt0 + list[u][p] for p < n_pts.
-__global__ void offset_lists_kernel(const int32_t* __restrict__ start, long long start_stride, int f0, int f1,
-                                    const int32_t* __restrict__ list, long long list_stride, int n_pts, int pt0,
-                                    int32_t* __restrict__ fstart, long long fstart_stride, int32_t* __restrict__ perm,
-                                    long long perm_stride)
+// Stored-order tables from member lists built on local point indices, for the fine range [f0, f1) and n_pts points:
+// fstart[u][f] = pt0 + start[u][f] for f in [f0, f1];  perm[u][pt0 + p] = pt0 + list[u][p] and fot[u][pt0 + p] = ids[u][p] for
+// p < n_pts;  two levels, the coarse ids of the range in [c0, c1) and non-decreasing: cstart[u][c] = first fine id whose coarse
+// id is >= c, for c in [c0, c1], cstart[c1] = f1.
+__global__ void stored_order_kernel(const StoredOrder p)
 {
     const int u = blockIdx.y;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_pts) perm[u * perm_stride + pt0 + i] = pt0 + list[u * list_stride + i];
-    if (i <= f1 - f0) fstart[u * fstart_stride + f0 + i] = pt0 + start[u * start_stride + f0 + i];
+    if (i < p.n_pts) {
+        p.perm[u * p.ncap + p.pt0 + i] = p.pt0 + p.list[u * p.ncap + i];
+        if (p.ids) p.fot[u * p.ncap + p.pt0 + i] = p.ids[u * p.ids_stride + i];
+    }
+    if (i > p.f1 - p.f0) return;
+    const int f = p.f0 + i;
+    p.fstart[u * (long long)(p.fcap + 1) + f] = p.pt0 + p.start[u * p.start_stride + f];
+    if (!p.cof) return;
+    const int32_t* cof = p.cof + u * (long long)p.fcap;
+    const int cur = f < p.f1 ? cof[f] : p.c1, prev = f > p.f0 ? cof[f - 1] : p.c0 - 1;
+    for (int c = prev + 1; c <= cur; ++c) p.cstart[u * (long long)(p.ccap + 1) + c] = f;
 }
 
-// fot[u][list[p]] = f for p in [start[f], start[f+1])  (inverse of the member lists)
-__global__ void ids_from_lists_kernel(const int32_t* __restrict__ list, long long list_stride,
-                                      const int32_t* __restrict__ start, long long start_stride, int k,
-                                      int32_t* __restrict__ ids, long long ids_stride)
+// Rows of several arrays moved in one launch: see CopyBatch.  grid = (pieces of a row, rows, parts)
+template <typename T>
+__device__ __forceinline__ void copy_row(const CopyBatch::Part& p, unsigned row)
 {
-    const int u = blockIdx.y;
-    const int f = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (f >= k) return;
-    const int s0 = start[u * start_stride + f], s1 = start[u * start_stride + f + 1];
-    for (int p = s0 + lane; p < s1; p += 64) ids[u * ids_stride + list[u * list_stride + p]] = f;
+    const T* src = reinterpret_cast<const T*>(static_cast<const char*>(p.src) + row * p.spitch);
+    T* dst = reinterpret_cast<T*>(static_cast<char*>(p.dst) + row * p.dpitch);
+    const unsigned long long n = p.width / sizeof(T);
+    for (unsigned long long i = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * blockDim.x) dst[i] = src[i];
+}
+__global__ __launch_bounds__(256) void copy_batch_kernel(const CopyBatch b)
+{
+    const CopyBatch::Part& p = b.part[blockIdx.z];
+    if (p.unit == 16) copy_row<uint4>(p, blockIdx.y);
+    else if (p.unit == 4) copy_row<uint32_t>(p, blockIdx.y);
+    else copy_row<uint8_t>(p, blockIdx.y);
 }
 
 // Dense per-cluster views of the last decode call's selection, from the per-candidate arrays:
@@ -565,32 +498,6 @@ hipError_t launch_scatter_selection(const int32_t* cand, long long cand_stride, 
 }
 
 // ---- host launchers ----------------------------------------------------------------------------
-hipError_t launch_histogram(const int32_t* ids, long long ids_stride, int n, int U, int32_t* cnt,
-                            long long cnt_stride, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(histogram_kernel, dim3((n + 255) / 256, U), dim3(256), 0, s, ids, ids_stride, n, cnt,
-                       cnt_stride);
-    return hipGetLastError();
-}
-
-hipError_t launch_exclusive_scan(const int32_t* cnt, long long cnt_stride, int k, int U, int32_t* start,
-                                 long long start_stride, hipStream_t s)
-{
-    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(U), dim3(1024), 0, s, cnt, cnt_stride, k, start, start_stride);
-    return hipGetLastError();
-}
-
-hipError_t launch_member_lists(const int32_t* ids, long long ids_stride, const int32_t* blocks_dev, int nb,
-                               int max_k_per_block, int U, const int32_t* start, long long start_stride,
-                               int32_t* list, long long list_stride, hipStream_t s)
-{
-    if (nb <= 0 || max_k_per_block <= 0) return hipSuccess;
-    hipLaunchKernelGGL(member_list_kernel, dim3((max_k_per_block + 255) / 256, nb, U), dim3(256), 0, s, ids,
-                       ids_stride, blocks_dev, start, start_stride, list, list_stride);
-    return hipGetLastError();
-}
-
 hipError_t launch_block_lists(const int32_t* ids, long long ids_stride, const int32_t* blocks_dev, int nb,
                               int max_k_per_block, int p_first, int U, int32_t* start, long long start_stride,
                               int32_t* list, long long list_stride, hipStream_t s)
@@ -615,27 +522,27 @@ hipError_t launch_block_lists(const int32_t* ids, long long ids_stride, const in
 
 hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                               long long list_stride, int n, int U, void* dstK, void* dstV, long long dst_unit_rows,
-                              int dst_row0, hipStream_t s)
+                              int dst_row0, const SequenceCopy& seq, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     const long long threads = (long long)n * 16;
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((threads + 255) / 256), U), dim3(256), 0, s,
                        (const uint4*)srcK, (const uint4*)srcV, src_unit_rows, list, list_stride, n, (uint4*)dstK,
-                       (uint4*)dstV, dst_unit_rows, dst_row0);
+                       (uint4*)dstV, dst_unit_rows, dst_row0, seq);
     return hipGetLastError();
 }
 
 hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                                        long long list_stride, const int32_t* ids, long long ids_stride,
                                        const uint16_t* Kc, long long kc_unit_rows, int n, int U, void* dstK, void* dstV,
-                                       float* scales, long long dst_unit_rows, int dst_row0, hipStream_t s)
+                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     const long long threads = (long long)n * 16;
     hipLaunchKernelGGL(gather_quantize_rows_kernel, dim3((unsigned)((threads + 255) / 256), U), dim3(256), 0, s,
                        (const uint4*)srcK, (const uint4*)srcV, src_unit_rows, list, list_stride, ids, ids_stride,
                        (const uint4*)Kc, kc_unit_rows, n, (uint2*)dstK, (uint2*)dstV, (float2*)scales, dst_unit_rows,
-                       dst_row0);
+                       dst_row0, seq);
     return hipGetLastError();
 }
 
@@ -655,44 +562,36 @@ hipError_t launch_cluster_means(const uint16_t* X, long long x_unit_rows, const 
     return range_out ? go(cluster_mean_kernel<true>) : go(cluster_mean_kernel<false>);
 }
 
-hipError_t launch_coarse_from_children(const double* sums, long long sum_unit_rows, const int32_t* map, long long map_stride,
-                                       int map_f0, const int32_t* cstart, long long cstart_stride,
-                                       const int32_t* fine_count, long long count_stride, int c0, int c1, int U,
-                                       uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
-                                       long long fb_unit_rows, int32_t* count_out, int count_off, hipStream_t s)
+hipError_t launch_coarse_from_children(const CoarseTables& p, int U, hipStream_t s)
 {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(coarse_from_children_kernel, dim3((c1 - c0 + 3) / 4, U), dim3(256), 0, s, sums, sum_unit_rows, map,
-                       map_stride, map_f0, cstart, cstart_stride, fine_count, count_stride, c0, c1, mean_out, out_unit_rows,
-                       out_row0, fallback, fb_unit_rows, count_out, count_off);
+    if (p.c1 <= p.c0) return hipSuccess;
+    hipLaunchKernelGGL(coarse_from_children_kernel, dim3((p.c1 - p.c0 + 3) / 4, U, 2), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_start(const int32_t* cof, long long cof_stride, int f0, int f1, int c0, int c1, int U,
-                               int32_t* cstart, long long cstart_stride, hipStream_t s)
+hipError_t launch_stored_order(const StoredOrder& p, int U, hipStream_t s)
 {
-    hipLaunchKernelGGL(coarse_start_kernel, dim3((f1 - f0 + 1 + 255) / 256, U), dim3(256), 0, s, cof, cof_stride, f0,
-                       f1, c0, c1, cstart, cstart_stride);
+    const int n = p.n_pts > p.f1 - p.f0 + 1 ? p.n_pts : p.f1 - p.f0 + 1;
+    hipLaunchKernelGGL(stored_order_kernel, dim3((n + 255) / 256, U), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_offset_lists(const int32_t* start, long long start_stride, int f0, int f1, const int32_t* list,
-                               long long list_stride, int n_pts, int pt0, int U, int32_t* fstart,
-                               long long fstart_stride, int32_t* perm, long long perm_stride, hipStream_t s)
+void CopyBatch::add(void* dst, size_t dpitch, const void* src, size_t spitch, size_t width)
 {
-    const int n = n_pts > f1 - f0 + 1 ? n_pts : f1 - f0 + 1;
-    hipLaunchKernelGGL(offset_lists_kernel, dim3((n + 255) / 256, U), dim3(256), 0, s, start, start_stride, f0, f1,
-                       list, list_stride, n_pts, pt0, fstart, fstart_stride, perm, perm_stride);
-    return hipGetLastError();
+    if (width == 0) return;
+    const size_t all = (uintptr_t)dst | dpitch | (uintptr_t)src | spitch | width;
+    part[n++] = Part{src, dst, (long long)spitch, (long long)dpitch, width, all % 16 == 0 ? 16u : all % 4 == 0 ? 4u : 1u};
 }
 
-hipError_t launch_ids_from_lists(const int32_t* list, long long list_stride, const int32_t* start,
-                                 long long start_stride, int k, int U, int32_t* ids, long long ids_stride,
-                                 hipStream_t s)
+hipError_t CopyBatch::launch(int rows, hipStream_t s)
 {
-    if (k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(ids_from_lists_kernel, dim3((k + 3) / 4, U), dim3(256), 0, s, list, list_stride, start,
-                       start_stride, k, ids, ids_stride);
+    if (n == 0 || rows == 0) return hipSuccess;
+    unsigned long long most = 1;
+    for (int i = 0; i < n; ++i) most = std::max<unsigned long long>(most, part[i].width / part[i].unit);
+    // (up to four pieces a thread: enough workgroups to fill the chip in any case that takes longer than a launch)
+    const unsigned gx = (unsigned)std::min<unsigned long long>((most + 1023) / 1024, 4096);
+    hipLaunchKernelGGL(copy_batch_kernel, dim3(gx, rows, n), dim3(256), 0, s, *this);
+    n = 0;
     return hipGetLastError();
 }
 

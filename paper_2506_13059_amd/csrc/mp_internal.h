@@ -179,23 +179,22 @@ struct CoarseLevel {
     int k_cap, n_cap;            // (set by the launch)
 };
 hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int max_k, hipStream_t s);
-hipError_t launch_histogram(const int32_t* ids, long long ids_stride, int n, int U, int32_t* cnt,
-                            long long cnt_stride, hipStream_t s);
-hipError_t launch_exclusive_scan(const int32_t* cnt, long long cnt_stride, int k, int U, int32_t* start,
-                                 long long start_stride, hipStream_t s);
 // Member lists of all blocks in one launch (stable counting sort by cluster id):
 // start[u][id] = first list position of cluster id, counted from point p_first; the entry after the
 // last block's last cluster receives the end position; list[u][position] = point index.
 hipError_t launch_block_lists(const int32_t* ids, long long ids_stride, const int32_t* blocks_dev, int nb,
                               int max_k_per_block, int p_first, int U, int32_t* start, long long start_stride,
                               int32_t* list, long long list_stride, hipStream_t s);
-// blocks_dev: int32 [nb][4] = {first point, end point, first cluster, end cluster}
-hipError_t launch_member_lists(const int32_t* ids, long long ids_stride, const int32_t* blocks_dev, int nb,
-                               int max_k_per_block, int U, const int32_t* start, long long start_stride,
-                               int32_t* list, long long list_stride, hipStream_t s);
+// The rows t0 and up of a gather's sources once more, in sequence order (arrays of unit_rows rows a unit; null: not wanted).
+struct SequenceCopy {
+    void *K, *V;
+    long long unit_rows;
+    int t0;
+};
+
 hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                               long long list_stride, int n, int U, void* dstK, void* dstV, long long dst_unit_rows,
-                              int dst_row0, hipStream_t s);
+                              int dst_row0, const SequenceCopy& seq, hipStream_t s);
 // The same into 8-bit storage: dstK / dstV receive 128 e4m3 codes per row, scales [U, dst_unit_rows, 2] the
 // rows' fp32 scales {key, value} (scale = max|x| / 448, 1 for a zero row; code = round-to-nearest-even(x / scale)).
 // For a value row x is the row; for a key row x = fp32(key) - fp32(Kc[ids[point]]), the residual from the key
@@ -203,7 +202,7 @@ hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_
 hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                                        long long list_stride, const int32_t* ids, long long ids_stride,
                                        const uint16_t* Kc, long long kc_unit_rows, int n, int U, void* dstK, void* dstV,
-                                       float* scales, long long dst_unit_rows, int dst_row0, hipStream_t s);
+                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq, hipStream_t s);
 // mean_out row (out_row0 + id) = bf16(fp64 sum of the member rows in list order / count); sum_out (optional)
 // receives the fp64 sums themselves, row = id; range_out (optional) [U, sum_unit_rows] the exponent fields of a cluster's
 // largest magnitude (<< 16) and smallest nonzero one (subnormals count as 1; 255 where there is none).
@@ -236,21 +235,50 @@ struct MoveMeans {
     int per;                       // clusters of a workgroup (set by the launch)
 };
 hipError_t launch_move_means(MoveMeans p, int nb, int max_k, int U, hipStream_t s);
-// Coarse clusters [c0, c1) from their children: sums [U, sum_unit_rows, 128] fp64 member sums of the fine clusters
-// (row = map ? map[f - map_f0] : f), cstart = first child of each coarse cluster, fine_count[f] members.
-hipError_t launch_coarse_from_children(const double* sums, long long sum_unit_rows, const int32_t* map, long long map_stride,
-                                       int map_f0, const int32_t* cstart, long long cstart_stride,
-                                       const int32_t* fine_count, long long count_stride, int c0, int c1, int U,
-                                       uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
-                                       long long fb_unit_rows, int32_t* count_out, int count_off, hipStream_t s);
-hipError_t launch_coarse_start(const int32_t* cof, long long cof_stride, int f0, int f1, int c0, int c1, int U,
-                               int32_t* cstart, long long cstart_stride, hipStream_t s);
-hipError_t launch_offset_lists(const int32_t* start, long long start_stride, int f0, int f1, const int32_t* list,
-                               long long list_stride, int n_pts, int pt0, int U, int32_t* fstart,
-                               long long fstart_stride, int32_t* perm, long long perm_stride, hipStream_t s);
-hipError_t launch_ids_from_lists(const int32_t* list, long long list_stride, const int32_t* start,
-                                 long long start_stride, int k, int U, int32_t* ids, long long ids_stride,
-                                 hipStream_t s);
+// Coarse clusters [c0, c1) from their children: sumK, sumV [U, fcap, 128] fp64 member sums of the fine clusters (key sums at
+// row key_map ? key_map[f - f0] : f), cstart = first child of each coarse cluster, counts [U, tab_rows] members of the fine
+// clusters; writes rows fcap + c of Kc, Vc [U, tab_rows, 128] and of counts.
+struct CoarseTables {
+    const double *sumK, *sumV;
+    const int32_t* key_map;        // [U, fcap]
+    int f0;
+    const int32_t* cstart;
+    long long cstart_stride;
+    int32_t* counts;
+    int c0, c1;
+    uint16_t *Kc, *Vc;
+    const uint16_t* key_fallback;  // Kc, or null
+    int fcap;
+    long long tab_rows;
+};
+hipError_t launch_coarse_from_children(const CoarseTables& p, int U, hipStream_t s);
+struct StoredOrder {
+    const int32_t* start;          // [U, start_stride] first list position of a cluster
+    long long start_stride;
+    const int32_t* list;           // [U, ncap]
+    const int32_t* ids;            // [U, ids_stride], or null: fot is in place already
+    long long ids_stride;
+    const int32_t* cof;            // [U, fcap], or null: one level
+    int f0, f1, c0, c1, n_pts, pt0, fcap, ccap;
+    long long ncap;
+    int32_t *fstart, *perm, *fot, *cstart;
+};
+hipError_t launch_stored_order(const StoredOrder& p, int U, hipStream_t s);
+// Device-to-device copies of `rows` rows each, several in one launch (a copy of its own is 5 us whatever its size).
+struct CopyBatch {
+    struct Part {
+        const void* src;
+        void* dst;
+        long long spitch, dpitch;
+        unsigned long long width;
+        unsigned unit;             // bytes moved at a time: what pointers, pitches and width are multiples of
+    };
+    static constexpr int kParts = 8;
+    Part part[kParts];
+    int n = 0;
+    void add(void* dst, size_t dpitch, const void* src, size_t spitch, size_t width);
+    hipError_t launch(int rows, hipStream_t s);
+};
 // Views of the last scoring launch, by cluster id.  keys [U, pos_stride] by position; key_mode[2*u + level]
 // says what they are: 0 = order-preserving image of the rank key r = log mean_h e^{l - LSE_h}; 1 = complement
 // of the bit pattern of sum_h e^{l - LSE_h} (then r = log(sum) - log G).  r_out receives r (NaN: took no part).
