@@ -423,10 +423,11 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     vp.scale_log2e = (float)(ctx->scale_d * 1.4426950408889634);
     const int main_max = most_selected(ctx->cfg.levels, key_budget, coarse_budget, ctx->n_tokens);
     int ns = 0, chunk0 = 0;
-    // The matrix-core kernel takes every launch but those with 8-bit rows or a tail that does not start on 16 bytes.
+    // The matrix-core kernels take every launch but those with a tail that does not start on 16 bytes, and 8-bit rows of one
+    // head to a unit.
     // Its workgroups per unit are shared out over the selected keys (or, where none can be selected, the centroid
     // terms) and the tail by their rows.
-    const bool on_matrix = ctx->cfg.kv_format == MP_KV_BF16 && rows_aligned(k_tail, v_tail);
+    const bool bytes = ctx->cfg.kv_format == MP_KV_E4M3, on_matrix = rows_aligned(k_tail, v_tail) && !(bytes && bytes_on_vector_alu(G));
     const int first_max = main_max > 0 ? main_max : (use_mp ? ctx->n_fine + ctx->n_coarse : 0);
     const StreamPlan plan = plan_streams(U, first_max, n_tail);
     // order: centroid terms, tail, selected keys -- the longest stream goes last (see the kernel's block mapping)
@@ -455,7 +456,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     if (main_max > 0) {
         const int crm = on_matrix ? plan.first_rows : pick_stream_chunk_rows(main_max, U, 2048);
         RowSource& r = vp.src[ns++];
-        if (ctx->cfg.kv_format == MP_KV_E4M3) {
+        if (bytes) {
             r.K = (const uint16_t*)ctx->Kq; r.V = (const uint16_t*)ctx->Vq; r.row_scale = ctx->kv_scale;
             r.row_slot = ctx->row_slot; r.slot_base = ctx->sel_base; r.base_stride = ctx->Fcap;
         }
@@ -472,7 +473,8 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[1], s));
     MP_HIP(ctx, launch_score_select(sp, ctx->n_cus, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[2], s));
-    if (chunk0 > 0) MP_HIP(ctx, on_matrix ? launch_value_stream(vp, G, s) : launch_value_pass(vp, G, s));
+    if (chunk0 > 0)
+        MP_HIP(ctx, !on_matrix ? launch_value_pass(vp, G, s) : bytes && main_max > 0 ? launch_value_stream8(vp, G, s) : launch_value_stream(vp, G, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[3], s));
     MP_HIP(ctx, launch_merge(ctx->partials, U, chunk0, G, (uint16_t*)out, lse, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[4], s));

@@ -53,6 +53,8 @@ struct ValuePassParams {
 hipError_t launch_value_pass(const ValuePassParams& p, int G, hipStream_t stream);
 // The same launch on the matrix cores: bf16 rows that start on 16 bytes, chunk_rows a multiple of 64.
 hipError_t launch_value_stream(const ValuePassParams& p, int G, hipStream_t stream);
+// ... of which one source's rows are listed 8-bit rows.
+hipError_t launch_value_stream8(const ValuePassParams& p, int G, hipStream_t stream);
 
 // Merge of the partials of a unit into the output: out bf16 [U*G, 128], lse fp32 [U*G] (optional).
 hipError_t launch_merge(const float* partials, int n_units, int chunks_per_unit, int G, uint16_t* out,

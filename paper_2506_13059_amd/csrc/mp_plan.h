@@ -117,6 +117,12 @@ inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
     return group <= 2 && n_units * n <= 131072;
 }
 
+// Selected keys stored as 8-bit rows, one query head to a unit: the vector-ALU kernel.  A row's sixteen columns of the matrix
+// product would hold three parts of one head; the conversions are for all sixteen.  Whole step, us, here / matrix cores, 1 head:
+// 32 units x 4096 keys 30.5 / 32.1, 64 x 4096 36.5 / 37.8, 128 x 4096 51.0 / 51.1; 2 heads: 8 x 4096 28.1 / 27.8, 32 x 4096 34.1 /
+// 34.7, 128 x 8192 87.5 / 85.6; 4 heads: 128 x 4096 65.4 / 53.4; 8 heads: 64 x 4096 65.7 / 45.0.
+inline bool bytes_on_vector_alu(int group) { return group == 1; }
+
 // Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one
 // workgroup per pair, or in a launch per step.  The workgroup's time grows with its clusters (each is one wave's walk over
 // all points and a trip to memory, sixteen or eight waves) and points, that of the steps with their number and, beyond one

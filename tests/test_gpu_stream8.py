@@ -1,0 +1,67 @@
+"""GPU parity of the matrix-core value pass over 8-bit rows at the edges of its tiles (32 rows), strips (64 row numbers) and
+waves, for every split of the probabilities and both column layouts of the logit shares, and of the vector-ALU kernel that
+one head to a unit and a tail without 16-byte alignment keep using."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(G, n, tail, seed, clusters=7):
+    from paper_2506_13059_amd import binding as mp
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, K, V, kt, vt = (torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+                       for s in ((1, 2 * G, 128), (1, 2, n, 128), (1, 2, n, 128), (1, 2, tail, 128), (1, 2, tail, 128)))
+    k = min(clusters, n)
+    fot = (torch.arange(n, device="cuda", dtype=torch.int32) * 5 % k).expand(2, -1).contiguous()
+    ctx = mp.MpContext(1, 2 * G, 2, max_tokens=n, levels=1, max_fine=k, max_tail=max(tail, 1), kv_format=mp.MP_KV_E4M3)
+    ctx.mp_set_clustering(K, V, fot, k)
+    return ctx, q, K, V, kt, vt
+
+
+def _reference(ctx, q, K, V, kt, vt):
+    from tests.test_gpu_fp8 import _dequantised
+    Kd, Vd = _dequantised(ctx, K, V)
+    out = []
+    for u in range(2):
+        k, v = torch.cat([Kd[u], kt[0, u].double().cpu()]), torch.cat([Vd[u], vt[0, u].double().cpu()])
+        l = q.view(2, -1, 128)[u].double().cpu() @ k.T / math.sqrt(128)
+        out.append(torch.softmax(l, 1) @ v)
+    return torch.stack(out).view(q.shape)
+
+
+def _check(got, ref, label):
+    # one rounding to bf16 (2^-8 of the value at most), fp32 sums before it
+    err = (got.double().cpu() - ref).abs()
+    bound = 2.0 ** -8 * ref.abs() + 2e-5 * ref.abs().max()
+    assert bool((err <= bound).all()), (label, float((err - bound).max()))
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 127, 128, 161, 255, 257, 700, 1025, 9000])
+def test_tile_edges(n):
+    for G, tail in ((2, 0), (4, 17), (5, 0), (6, 33), (8, 0)):
+        print(f"n={n} G={G}", flush=True)
+        ctx, q, K, V, kt, vt = _context(G, n, tail, 40 + n + G)
+        out = ctx.mp_decode_attention(q, n, 0, kt if tail else None, vt if tail else None)
+        _check(out, _reference(ctx, q, K, V, kt, vt), f"n={n} G={G}")
+        ctx.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 7])
+def test_both_kernels(G):
+    # a tail off 16 bytes sends the whole launch to the vector ALU; part of the clusters stays behind as centroid terms
+    print(f"G={G}", flush=True)
+    ctx, q, K, V, kt, vt = _context(G, 1500, 70, 60 + G, clusters=60)
+
+    def shifted(x, by):
+        flat = torch.empty(x.numel() + by, dtype=x.dtype, device="cuda")[by:]
+        flat.copy_(x.reshape(-1))
+        return flat.view(x.shape)
+    a = ctx.mp_decode_attention(q, 400, 0, kt, vt)
+    b = ctx.mp_decode_attention(q, 400, 0, shifted(kt, 4), shifted(vt, 2))
+    torch.cuda.synchronize()
+    # the same fp32 sums in another order: at most one step of the bf16 output (2^-7 of the value) apart
+    assert bool(((a.double() - b.double()).abs() <= 2.0 ** -7 * a.double().abs() + 1e-5).all())
+    ctx.close()
