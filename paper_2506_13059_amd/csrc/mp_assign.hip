@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
 // than 2^-17 of its magnitude, which the margin covers (near_margin_of_best).
 constexpr int kRowTile = 16;
 constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
-constexpr int kNearCap = 512;
+constexpr int kNearCap = 256;                    // (a multiple of sixteen)
 constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
 
 typedef const __attribute__((address_space(3))) bf16x8_t lds_frag;
@@ -327,6 +327,7 @@ __device__ __forceinline__ void merge_pair(float& best, float& second, uint32_t&
 struct Nearest {
     int j;
     bool near;
+    float best;      // the best score (its lowest bits carry the slot)
 };
 __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int first, int last, uint32_t lds0, int k_cap,
                                                     int ntiles, float c2max)
@@ -448,7 +449,7 @@ __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int
     const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
     const float margin = near_margin_of_best(fmaxf(n2[0], c2max), best[0]);
     // (written so that a point without any comparable score also goes to the exact pass)
-    return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin)};
+    return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin), best[0]};
 }
 
 // One 16-byte piece of a centroid row (16 lanes per row) to its place in LDS; the lane with the first piece writes
@@ -500,8 +501,9 @@ __device__ __forceinline__ int lane_id()
 // 140 us for 2048.  Here it adds 9 us to the first's assignment (the longest chain: four tiles' products, compared, four
 // more, then two or three distances of 2 us) and about 100 to 140 to the second's (1044 us without near ties, 1142 to 1183
 // with them).
+// known: `best` is what nearest_of_chunk found, at most 2^-17 of its size off, and need not be looked for again.
 __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, int k_cap,
-                                             int k, float c2max)
+                                             int k, float c2max, bool known, float best)
 {
     const int lane = lane_id(), c = lane & 15, g = lane >> 4;
     const int ntiles = (k + kRowTile - 1) / kRowTile;
@@ -529,17 +531,19 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
         }
         return acc;
     };
-    float best = -INFINITY;
-    for (int tile = 0; tile < ntiles; tile += 4) {
-        f32x4_t s[4];
+    if (!known) {
+        best = -INFINITY;
+        for (int tile = 0; tile < ntiles; tile += 4) {
+            f32x4_t s[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[r] = scores(min(tile + r, ntiles - 1));
+            for (int r = 0; r < 4; ++r) s[r] = scores(min(tile + r, ntiles - 1));
 #pragma unroll
-        for (int r = 0; r < 4; ++r) best = fmaxf(best, fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3])));
+            for (int r = 0; r < 4; ++r) best = fmaxf(best, fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3])));
+        }
+        best = fmaxf(best, __shfl_xor(best, 16, 64));
+        best = fmaxf(best, __shfl_xor(best, 32, 64));
     }
-    best = fmaxf(best, __shfl_xor(best, 16, 64));
-    best = fmaxf(best, __shfl_xor(best, 32, 64));
-    const float thr = best - near_margin(fmaxf(n2, c2max));
+    const float thr = best - near_margin(fmaxf(n2, c2max)) - fabsf(best) * (1.0f / 65536.0f);
     double bd = INFINITY;
     int bj = 0;
     for (int t0 = 0; t0 < ntiles; t0 += 16) {
@@ -586,7 +590,8 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
 {
     extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
     __shared__ float wave_c2max[kW];
-    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them
+    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them,
+    __shared__ float near_best[kNearCap];                         // and their best scores
     __shared__ int near_n;
     const int u = blockIdx.z, b = blockIdx.y;
     // (this kernel leaves the counters of the other one alone; the next assignment step finds them zero all the same)
@@ -646,8 +651,12 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
         if (t < x1) {
             if (r.near) {
                 const int pos = atomicAdd(&near_n, 1);
-                if (pos < kNearCap) near_list[pos] = t;
-                else more[pos] = t;
+                if (pos < kNearCap) {
+                    near_list[pos] = t;
+                    near_best[pos] = r.best;
+                } else {
+                    more[pos] = t;
+                }
             } else {
                 assign_u[t] = k0 + r.j;
             }
@@ -659,7 +668,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
         const int e = min(e0 + (lane_id() & 15), n - 1);
         const int t = e < kNearCap ? near_list[e] : more[e];
-        const int j = nearest_exact(Xu, t, rows_lds, lds0, k_cap, k1 - k0, c2max);
+        const int j = nearest_exact(Xu, t, rows_lds, lds0, k_cap, k1 - k0, c2max, e0 < kNearCap, e < kNearCap ? near_best[e] : 0.f);
         if (lane_id() < 16) assign_u[t] = k0 + j;
     }
 }
@@ -700,7 +709,8 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
 // order of the fine clusters, and the rows of the centroid tables that go with it.  One workgroup per (block, unit): a
 // block has some hundred points and some tens of centroids, which fit one compute unit, and every step of an iteration is a
 // few microseconds of latency when it is a launch of its own (assignment, exact pass, member lists, means: 30 us for 32
-// (block, unit) pairs, times ten iterations).  Here an iteration is five barriers; the decisions and sums are those of the
+// (block, unit) pairs, times ten iterations).  Here an iteration is five barriers, and the
+// first that moves no point ends them (the rest would repeat it); the decisions and sums are those of the
 // separate kernels: near ties decided in fp64 as defined, members summed in ascending order in fp64, one rounding.
 // Bound by the latency of one pair's chain, a member row from memory being its longest link (hence the sixteen at once):
 // 11.8 us an iteration for 32 pairs of 256 points and 16 centroids.  A bound of two waves a SIMD does away with the spills
@@ -715,7 +725,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
     uint16_t* asg = reinterpret_cast<uint16_t*>(c_init + p.k_cap);    // [n_cap] cluster of each point
     uint16_t* order = asg + p.n_cap;                                  // [n_cap] points, cluster after cluster
     uint16_t* near_pts = order + p.n_cap;                             // [n_cap]
-    __shared__ int count[kLevelMaxK], near_n;
+    __shared__ int count[kLevelMaxK], near_n, moved;
     __shared__ float wave_c2max[2][kW];
     const int b = blockIdx.x, u = blockIdx.y;
     const int x0 = p.blocks[4 * b + 0], n = p.blocks[4 * b + 1] - x0, k0 = p.blocks[4 * b + 2], k = p.blocks[4 * b + 3] - k0;
@@ -743,7 +753,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
     if (lane == 0) wave_c2max[0][wave] = c2max;
 
     for (int it = 0; it < p.iters; ++it) {
-        if (tid == 0) near_n = 0;
+        if (tid == 0) near_n = moved = 0;
         __syncthreads();
         c2max = 0.f;
 #pragma unroll
@@ -753,18 +763,27 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
             const Nearest r = nearest_of_chunk(Xu, x0 + ch * 64, x0 + n - 1, lds0, p.k_cap, ntiles, c2max);
             const int t = ch * 64 + lane;
             if (t < n) {
-                asg[t] = (uint16_t)min(r.j, k - 1);
-                if (r.near) near_pts[atomicAdd(&near_n, 1)] = (uint16_t)t;
+                const uint16_t j = (uint16_t)min(r.j, k - 1);
+                if (r.near) {
+                    near_pts[atomicAdd(&near_n, 1)] = (uint16_t)t;
+                } else if (it == 0 || asg[t] != j) {
+                    asg[t] = j;
+                    moved = 1;
+                }
             }
         }
         __syncthreads();
         // ---- near ties ----
         for (int e0 = wave * 16; e0 < near_n; e0 += kW * 16) {
             const int t = near_pts[min(e0 + (lane & 15), near_n - 1)];
-            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, p.k_cap, k, c2max);
-            if (lane < 16) asg[t] = (uint16_t)j;
+            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, p.k_cap, k, c2max, false, 0.f);
+            if (lane < 16 && (it == 0 || asg[t] != j)) {
+                asg[t] = (uint16_t)j;
+                moved = 1;
+            }
         }
         __syncthreads();
+        if (moved == 0) break;        // the same assignment as before: the same centroids, and so in every iteration after it
         // ---- member lists: one wave per cluster finds its points 64 at a time ----
         for (int j = wave; j < k; j += kW) {
             int m = 0;

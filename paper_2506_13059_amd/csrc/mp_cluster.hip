@@ -23,7 +23,7 @@ namespace mp {
 
 namespace {
 
-// C[u][k] = X[u][x0(block of k) + seed[u][k]]   grid = (nb, U)
+// C[u][k] = X[u][x0(block of k) + seed[u][k]]   grid = (nb, U, sixteens of clusters)
 __global__ __launch_bounds__(256) void init_centroids_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                              const int32_t* __restrict__ blocks,
                                                              const int32_t* __restrict__ seeds, long long seed_stride,
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void init_centroids_kernel(const uint16_t* __r
     const int b = blockIdx.x, u = blockIdx.y;
     const int x0 = blocks[4 * b + 0], k0 = blocks[4 * b + 2], k1 = blocks[4 * b + 3];
     const int lane16 = threadIdx.x & 15;
-    for (int k = k0 + (threadIdx.x >> 4); k < k1; k += 16) {
+    for (int k = k0 + (int)blockIdx.z * 16 + (threadIdx.x >> 4); k < k1; k += 16 * gridDim.z) {
         const long long src = x0 + seeds[u * seed_stride + k];
         reinterpret_cast<uint4*>(C + ((long long)u * c_unit_rows + k) * kHeadDim)[lane16] =
             reinterpret_cast<const uint4*>(X + ((long long)u * x_unit_rows + src) * kHeadDim)[lane16];
@@ -442,7 +442,7 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
         pc.assign = ctx->km_parent; pc.assign_stride = Fcap; pc.list = ctx->km_plist; pc.list_stride = Fcap;
         pc.cnt = ctx->km_cnt; pc.start = ctx->km_start; pc.cnt_stride = ctx->tab_rows;
         if (old_c_end < r.c1) {      // (an update's descriptor of its new clusters sits in the scratch slot)
-            hipLaunchKernelGGL(init_centroids_kernel, dim3(seed_f0 < 0 ? nb : 1, U), dim3(256), 0, s, pc.X, pc.x_unit_rows,
+            hipLaunchKernelGGL(init_centroids_kernel, dim3(seed_f0 < 0 ? nb : 1, U, blocks_for(max_kc, 16)), dim3(256), 0, s, pc.X, pc.x_unit_rows,
                                seed_f0 < 0 ? pc.blocks_dev : ctx->blocks_dev + 8, ctx->km_seed_c, Ccap1, pc.C, pc.c_unit_rows);
             MP_HIPC(hipGetLastError());
         }
@@ -506,7 +506,7 @@ mp_status cluster_range(mp_ctx* ctx, const Range& r, int iters, hipStream_t s)
     pf.max_pts = max_pts; pf.max_k = max_kf; pf.k_total = r.f1; pf.k_first = r.f0; pf.C = ctx->km_Cf; pf.c_unit_rows = ctx->Fcap;
     pf.assign = ctx->km_assign; pf.assign_stride = ctx->Ncap; pf.list = ctx->km_list; pf.list_stride = ctx->Ncap;
     pf.cnt = ctx->km_cnt; pf.start = ctx->km_start; pf.cnt_stride = ctx->tab_rows;
-    hipLaunchKernelGGL(init_centroids_kernel, dim3(nb, U), dim3(256), 0, s, pf.X, pf.x_unit_rows, pf.blocks_dev,
+    hipLaunchKernelGGL(init_centroids_kernel, dim3(nb, U, blocks_for(max_kf, 16)), dim3(256), 0, s, pf.X, pf.x_unit_rows, pf.blocks_dev,
                        ctx->km_seed_f, (long long)ctx->Fcap, pf.C, pf.c_unit_rows);
     MP_HIPC(hipGetLastError());
     pf.sums = ctx->sumK; pf.sum_unit_rows = ctx->Fcap; pf.range = ctx->km_range; pf.other_assign = ctx->km_assign2;
@@ -713,7 +713,7 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     MP_TRY(flush_uploads(ctx, s));
 
     if (n_new_fine > 0) {
-        hipLaunchKernelGGL(init_centroids_kernel, dim3(1, U), dim3(256), 0, s, ctx->Kfb, (long long)ctx->FBcap,
+        hipLaunchKernelGGL(init_centroids_kernel, dim3(1, U, blocks_for(n_new_fine, 16)), dim3(256), 0, s, ctx->Kfb, (long long)ctx->FBcap,
                            ctx->blocks_dev + 4, ctx->km_seed_f, Fcap, ctx->km_Cf, Fcap);
         MP_HIPC(hipGetLastError());
     }
