@@ -33,10 +33,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void value_stream_kernel(const Valu
 {
     extern __shared__ __align__(256) unsigned char ring_lds[];
     const int tid = threadIdx.x, wave = tid >> 6;
-    const StreamShare w = stream_share<kWaves>(p);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
+    const uint32_t ring = lds0 + (uint32_t)(wave * kRing), strips = lds0 + (uint32_t)(kWaves * kRing + wave * kStripBytes);
+    const uint32_t guest_strip = strips + 8 * kStrip;
+    touch_arguments(p);
+    const StreamShare w = stream_share<kWaves>(p, [&](const RowSource& S, int u, int first) { fetch_strip(S.rows, S, u, first, strips); });
     const RowSource& S = p.src[w.source];
     const int u = w.u;
     float* part = p.partials + ((long long)u * p.chunks_per_unit + w.chunk) * G * kPartStride;
+    if (w.w0 >= w.w1) nothing_on_its_way();  // (what was asked for early is in place before its space is used or given back)
     if (w.begin >= w.end && w.g0 >= w.g1) {
         if (tid < G) {
             part[tid * kPartStride + 0] = -INFINITY;
@@ -46,14 +51,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void value_stream_kernel(const Valu
     }
     StreamState<G> st;
     clear_state(st);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
-    const uint32_t ring = lds0 + (uint32_t)(wave * kRing), strips = lds0 + (uint32_t)(kWaves * kRing + wave * 8 * kStrip);
+    auto guest = [&] { if (w.a < w.b) fetch_strip(p.src[0].rows, p.src[0], u, w.a, guest_strip); };
     if (w.w0 < w.w1) {
-        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips);
-        else if (S.rows) stream_tiles<G, false, true>(st, S, p, u, w.w0, w.w1, ring, strips);
-        else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips);
+        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+        else if (S.rows) stream_tiles<G, false, true>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+        else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+    } else {
+        guest();
     }
-    if (w.a < w.b) stream_tiles<G, true, true>(st, p.src[0], p, u, w.a, w.b, ring, strips);
+    if (w.a < w.b) {
+        take_guest_strip(guest_strip, strips);
+        stream_tiles<G, true, true>(st, p.src[0], p, u, w.a, w.b, ring, strips, [] {});
+    }
     combine_waves<G, kWaves>(st, reinterpret_cast<float*>(ring_lds), part);
 }
 
@@ -61,7 +70,7 @@ template <int G, int kWaves>
 hipError_t launch_stream_w(const ValuePassParams& p, unsigned blocks, hipStream_t s)
 {
     static bool configured = false;
-    constexpr size_t smem = kWaves * (kRing + 8 * kStrip);
+    constexpr size_t smem = kWaves * (kRing + kStripBytes);
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&value_stream_kernel<G, kWaves>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);

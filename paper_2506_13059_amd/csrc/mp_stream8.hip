@@ -25,8 +25,8 @@ constexpr int kShares = kTile8 * 32;             // ... logit shares: columns 0 
 constexpr int kScales = kTile8 * 8;              // ... {key scale, value scale}
 constexpr int kSlot8 = 2 * kCodes + kShares + kScales;
 constexpr int kRing8 = 2 * kSlot8;               // per wave
-constexpr int kStrips8 = 16 * kStrip;            // two strips of row numbers, two of cluster slots
-static_assert(kRing8 >= kRing && kStrips8 >= 8 * kStrip, "the other sources of a launch use the same space");
+constexpr int kStrips8 = 20 * kStrip;            // two strips of row numbers, two of cluster slots, the guest source's first
+static_assert(kRing8 >= kRing && kStrips8 >= kStripBytes, "the other sources of a launch use the same space");
 static_assert(4 * (kRing8 + kStrips8) <= 80 * 1024, "two workgroups a compute unit");
 
 __device__ __forceinline__ bf16x8 widen_codes(u32x2 w)
@@ -84,9 +84,9 @@ __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p
 }
 
 // Listed 8-bit rows [w0, w1) through one wave (the counterpart of stream_tiles, whose comments on the pipeline hold here).
-template <int G>
+template <int G, typename Started>
 __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0, int w1,
-                                              uint32_t ring, uint32_t strips)
+                                              uint32_t ring, uint32_t strips, Started started)
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
     const int head = c % G, part = c / G;                         // (columns beyond the last part repeat a head)
@@ -131,6 +131,13 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
                      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(scale_row), "=&v"(slot)
                      : "v"(a0), "v"(a1), "v"(a2)
                      : "memory");
+        if (t == n_tiles - 1) {              // (past the share's end a strip holds anything: the tile's first row instead)
+            const int row0 = __builtin_amdgcn_readfirstlane(r[0]), slot0 = __builtin_amdgcn_readfirstlane(slot), left = w1 - w0 - t * kTile8;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = 8 * i + lr < left ? r[i] : row0;
+            scale_row = (lane >> 1) < left ? scale_row : row0;
+            slot = (lane & 31) < left ? slot : slot0;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) off[i] = (long long)r[i] * 128 + (((lane & 7) ^ ((8 * i + lr) >> 1)) & 7) * 16;
     };
@@ -149,12 +156,12 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
 
     // K0 V0 K1 V1 K2 V2 ..., six instructions (codes, shares, scales) and four, two for a strip now and then.
     const bool single = n_tiles == 1;
-    load_strip(0);
-    if (n_tiles > kStrip / kTile8) load_strip(1);
     wait_vm<0>();
     tile_rows(0);
+    if (n_tiles > kStrip / kTile8) load_strip(1);
     load_keys(0);
     load_values(0);
+    started();
     if (!single) {
         tile_rows(1);
         load_keys(1);
@@ -234,10 +241,18 @@ __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassPa
     constexpr int kWaves = 4;
     extern __shared__ __align__(256) unsigned char ring_lds[];
     const int tid = threadIdx.x, wave = tid >> 6;
-    const StreamShare w = stream_share<kWaves>(p);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
+    const uint32_t ring = lds0 + (uint32_t)(wave * kRing8), strips = lds0 + (uint32_t)(kWaves * kRing8 + wave * kStrips8);
+    const uint32_t guest_strip = strips + 16 * kStrip;
+    touch_arguments(p);
+    const StreamShare w = stream_share<kWaves>(p, [&](const RowSource& S, int u, int first) {
+        fetch_strip(S.rows, S, u, first, strips);
+        if (S.row_slot) fetch_strip(S.row_slot, S, u, first, strips + 8 * kStrip);
+    });
     const RowSource& S = p.src[w.source];
     const int u = w.u;
     float* part = p.partials + ((long long)u * p.chunks_per_unit + w.chunk) * G * kPartStride;
+    if (w.w0 >= w.w1) nothing_on_its_way();  // (what was asked for early is in place before its space is used or given back)
     if (w.begin >= w.end && w.g0 >= w.g1) {
         if (tid < G) {
             part[tid * kPartStride + 0] = -INFINITY;
@@ -247,14 +262,18 @@ __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassPa
     }
     StreamState<G> st;
     clear_state(st);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
-    const uint32_t ring = lds0 + (uint32_t)(wave * kRing8), strips = lds0 + (uint32_t)(kWaves * kRing8 + wave * kStrips8);
+    auto guest = [&] { if (w.a < w.b) fetch_strip(p.src[0].rows, p.src[0], u, w.a, guest_strip); };
     if (w.w0 < w.w1) {
-        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips);
-        else if (S.row_scale) stream_tiles8<G>(st, S, p, u, w.w0, w.w1, ring, strips);
-        else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips);
+        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+        else if (S.row_scale) stream_tiles8<G>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+        else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+    } else {
+        guest();
     }
-    if (w.a < w.b) stream_tiles<G, true, true>(st, p.src[0], p, u, w.a, w.b, ring, strips);
+    if (w.a < w.b) {
+        take_guest_strip(guest_strip, strips);
+        stream_tiles<G, true, true>(st, p.src[0], p, u, w.a, w.b, ring, strips, [] {});
+    }
     combine_waves<G, kWaves>(st, reinterpret_cast<float*>(ring_lds), part);
 }
 

@@ -20,6 +20,7 @@ constexpr int kTile = 16;                        // rows per tile
 constexpr int kPiece = kTile * 256;              // bytes of a tile's keys (or values)
 constexpr int kRing = 4 * kPiece;                // per wave: keys and values of two tiles
 constexpr int kStrip = 64;                       // row numbers fetched at a time
+constexpr int kStripBytes = 12 * kStrip;         // per wave: two strips, and the first one of the launch's guest source
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
@@ -37,6 +38,11 @@ template <int N>
 __device__ __forceinline__ void wait_vm()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// A wave without rows waits for its early loads.
+__device__ __forceinline__ void nothing_on_its_way()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
 }
 // Four row numbers, 16 bytes apart.
 __device__ __forceinline__ void lds_read_rows(uint32_t a, int (&r)[4])
@@ -164,9 +170,11 @@ __device__ __forceinline__ void lds_read_scores(uint32_t a, float (&s)[4])
 // strips of row numbers.  kScored: the logits are ready-made; they take the place of the key rows in the ring.  (Fetched
 // into registers when their tile was due, they made every tile a trip to memory of its own: one level of 4096 centroids,
 // 64 / 256 units of 4 heads, whole step: 127.5 / 226.9 -> 122.5 / 205.0 us.)
-template <int G, bool kScored, bool kListed>
+// The first strip is on its way or there already (early_strip, take_guest_strip); `started` runs once it is in place, and
+// may ask for one more strip.
+template <int G, bool kScored, bool kListed, typename Started>
 __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0,
-                                             int w1, uint32_t ring, uint32_t strips)
+                                             int w1, uint32_t ring, uint32_t strips, Started started)
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
     const int head = c % G;                                       // (columns beyond the last part repeat a head)
@@ -203,6 +211,12 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     auto tile_rows = [&](int t) {
         int r[4];
         if constexpr (kListed) lds_read_rows(strips + (uint32_t)((((t >> 2) & 1) * kStrip + (t & 3) * kTile + g) * 4), r);
+        if constexpr (kListed)
+            if (t == n_tiles - 1) {          // (past the share's end a strip holds anything: the tile's first row instead)
+                const int first = __builtin_amdgcn_readfirstlane(r[0]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[i] = w0 + t * kTile + 4 * i + g < w1 ? r[i] : first;
+            }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (!kListed) r[i] = min(w0 + t * kTile + 4 * i + g, w1 - 1);
@@ -244,12 +258,12 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     // a share is often a single tile, and rows no one uses made its end wait for a second trip to memory (dense calls over
     // up to 8192 rows of 8 units, 4 heads: 12.5-15.1 -> 11.9-13.8 us).
     const bool single = n_tiles == 1;
-    load_strip(0);
-    if (n_tiles > kStrip / kTile) load_strip(1);
     if constexpr (kListed) wait_vm<0>();
     tile_rows(0);
+    if (n_tiles > kStrip / kTile) load_strip(1);
     load_keys(0);
     load_values(0);
+    started();
     if (!single) {
         tile_rows(1);
         load_keys(1);
@@ -307,13 +321,25 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     tile(t, std::integral_constant<int, 0>{});
 }
 
+// The arguments span eight cache lines of a segment no one has read yet: one request for each of them, together.
+__device__ __forceinline__ void touch_arguments(const ValuePassParams& p)
+{
+    static_assert(sizeof(ValuePassParams) <= 512 && sizeof(RowSource) == 120, "");
+    asm volatile("" ::"s"(p.q), "s"(p.src[0].scores), "s"(p.src[0].guest), "s"(p.src[1].count_dev), "s"(p.src[1].guest),
+                 "s"(p.src[2].count_max), "s"(p.src[2].guest), "s"(p.src[3].scores));
+}
+
 // What a workgroup works on: its unit, chunk and source, the rows [begin, end) of the chunk and [w0, w1) of this wave, and of
 // the guest source (src[0], which rides along) the rows [g0, g1) and [a, b).
 struct StreamShare {
     int u, chunk, source, begin, end, w0, w1, g0, g1, a, b;
 };
-template <int kWaves>
-__device__ __forceinline__ StreamShare stream_share(const ValuePassParams& p)
+// A launch over a short selection is a chain of trips to memory: arguments, counts, row numbers, rows, and the guest's row
+// numbers and rows.  Each step is asked for as early as it can be (one level of 64 clusters, 1 unit: step 16.9 -> 16.4 us; 8 units x
+// 4096 keys 28.6 -> 27.8; 32 units x 4096, 5 heads 42.0 -> 41.1).  The wave's first row numbers do not wait for the count: `early(source, unit, first position)` asks for them, and what lies past the end
+// is never used as an address.
+template <int kWaves, typename Early>
+__device__ __forceinline__ StreamShare stream_share(const ValuePassParams& p, Early early)
 {
     StreamShare r;
     r.chunk = blockIdx.x / p.n_units;
@@ -323,33 +349,50 @@ __device__ __forceinline__ StreamShare stream_share(const ValuePassParams& p)
     for (int i = 1; i < kMaxSources; ++i)
         if (i < p.n_sources && r.chunk >= p.src[i].chunk0) r.source = i;
     const RowSource& S = p.src[r.source];
+    const RowSource& T = p.src[0];
     const int wave = threadIdx.x >> 6;
-    int count = S.row0 + S.count_max;
-    if (S.count_dev) {
-        const int cd = S.count_dev[u];
-        count = cd < count ? cd : count;
-    }
     r.begin = S.row0 + (r.chunk - S.chunk0) * S.chunk_rows;
+    const int wave_rows = ((S.chunk_rows / kWaves) + kTile - 1) / kTile * kTile;
+    r.w0 = r.begin + wave * wave_rows;
+    // (the source's fields in one trip, the counts in one more)
+    asm volatile("" ::"s"(S.rows), "s"(S.rows_stride), "s"(S.count_dev), "s"(S.count_max), "s"(S.scores), "s"(S.n_chunks), "s"(S.guest),
+                 "s"(T.count_dev), "s"(T.count_max), "s"(S.K), "s"(S.V), "s"(S.unit_rows));
+    typedef const __attribute__((address_space(4))) int32_t constant_int;
+    int counted = 0, guests = 0;
+    if (S.count_dev) counted = ((constant_int*)S.count_dev)[u];
+    if (S.guest && T.count_dev) guests = ((constant_int*)T.count_dev)[u];
+    if (S.rows) early(S, u, r.w0);
+    int count = S.row0 + S.count_max;
+    if (S.count_dev) count = counted < count ? counted : count;
     r.end = (r.begin + S.chunk_rows < count) ? r.begin + S.chunk_rows : count;
     r.g0 = r.g1 = 0;
     if (S.guest) {
-        const RowSource& T = p.src[0];
         int nt = T.count_max;
-        if (T.count_dev) {
-            const int cd = T.count_dev[u];
-            nt = cd < nt ? cd : nt;
-        }
+        if (T.count_dev) nt = guests < nt ? guests : nt;
         const long long k = r.chunk - S.chunk0;
         r.g0 = (int)(nt * k / S.n_chunks);
         r.g1 = (int)(nt * (k + 1) / S.n_chunks);
     }
-    const int wave_rows = ((S.chunk_rows / kWaves) + kTile - 1) / kTile * kTile;
-    r.w0 = r.begin + wave * wave_rows;
     r.w1 = (r.w0 + wave_rows < r.end) ? r.w0 + wave_rows : r.end;
     const int per = (((r.g1 - r.g0) + kWaves - 1) / kWaves + 15) & ~15;
     r.a = r.g0 + wave * per;
     r.b = (r.a + per < r.g1) ? r.a + per : r.g1;
     return r;
+}
+// The row numbers of 64 list positions from `first` to LDS, inside the unit's list.
+__device__ __forceinline__ void fetch_strip(const int32_t* list, const RowSource& S, int u, int first, uint32_t to)
+{
+    const long long j = min((long long)first + (threadIdx.x & 63), S.rows_stride - 1);
+    load_to_lds<4, false>(list + (long long)u * S.rows_stride + j, to);
+}
+// The guest source's first strip, fetched beside the main source's rows, takes the place of the first strip.
+__device__ __forceinline__ void take_guest_strip(uint32_t from, uint32_t strips)
+{
+    wait_vm<0>();
+    const uint32_t at = (threadIdx.x & 63) * 4;
+    int row;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)\n\tds_write_b32 %2, %0\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(row) : "v"(from + at), "v"(strips + at) : "memory");
 }
 template <int G>
 __device__ __forceinline__ void clear_state(StreamState<G>& st)
