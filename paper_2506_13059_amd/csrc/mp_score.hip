@@ -365,12 +365,19 @@ __device__ __forceinline__ Arrays global_arrays(const ScoreParams& p, int u)
 // x = (hg * 32 + 8c + r) * 16 + 4k + j, is dimension 32c + 8k + r of head 4 hg + j.
 // After the product lane (i, b, j) owns the logit of entry 4b + i and head j.
 // ------------------------------------------------------------------------------------------------
+// Thread x carries element x of every head group, as bf16 until it is needed: loaded without a branch (a head past the last
+// reads the last one's and counts as zero later), so that nothing waits for it before the rows have been asked for.
 template <int G>
-__device__ __forceinline__ uint16_t query_operand_element(const ScoreParams& p, int u, int x)
+__device__ __forceinline__ uint16_t query_operand_element(const uint16_t* q, int u, int hg, int x)
 {
-    const int hg = x >> 9, s = (x >> 4) & 31, k = (x >> 2) & 3, j = x & 3;
-    const int h = 4 * hg + j, d = 32 * (s >> 3) + 8 * k + (s & 7);
-    return h < G ? p.q[((long long)u * G + h) * kHeadDim + d] : (uint16_t)0;
+    const int s = x >> 4, k = (x >> 2) & 3, h = min(4 * hg + (x & 3), G - 1), d = 32 * (s >> 3) + 8 * k + (s & 7);
+    return q[((long long)u * G + h) * kHeadDim + d];
+}
+
+template <int G>
+__device__ __forceinline__ double query_operand(uint16_t v, int hg, int x)
+{
+    return 4 * hg + (x & 3) < G ? (double)bf16_to_f32(v) : 0.0;
 }
 
 constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
@@ -632,7 +639,7 @@ __device__ __forceinline__ int score_level(const ScoreParams& p, const Lds& L, c
         }
         if (q_pending) {
 #pragma unroll
-            for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = (double)bf16_to_f32(qv[hg]);
+            for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = query_operand<G>(qv[hg], hg, tid);
             phase_sync<true>();
         }
 
@@ -1071,6 +1078,13 @@ constexpr int kFastChunks = 2;
 constexpr double kNoShift = 500.0;    // largest |logit| that is exponentiated without a shift
 constexpr int kRounds = 4;
 
+// One unit's rows, counts and row starts of one level.
+struct LevelTables {
+    const uint16_t* rows;
+    const int32_t* N;
+    const int32_t* start;
+};
+
 template <int G>
 struct FastLevel {
     static constexpr int GH = (G + 3) / 4;
@@ -1102,19 +1116,14 @@ __device__ __forceinline__ void for_rounds(F f)
 // rows last round first (shadow workgroup).  `meanwhile` runs once the rows have been asked for.  Returns 1 for
 // linear-domain keys, 0 for logarithmic ones.
 template <int G, typename Meanwhile>
-__device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Scratch& S, int u, int n, bool use_ids,
-                                          bool coarse, long long budget, bool behind, bool q_pending,
-                                          const uint16_t (&qv)[(G + 3) / 4], bool quiet, unsigned long long* key_out,
-                                          uint8_t* flag_out, FastLevel<G>& st, Meanwhile meanwhile)
+__device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Scratch& S, const LevelTables& T, int n, int u, bool use_ids,
+                                          bool coarse, bool behind, bool q_pending, const uint16_t (&qv)[(G + 3) / 4], bool quiet,
+                                          FastLevel<G>& st, Meanwhile meanwhile)
 {
     constexpr int GH = (G + 3) / 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 3, quad = lane >> 2;
     const double ninf = -INFINITY;
-    const int row_off = coarse ? p.fcap : 0;
-    const int32_t* Nu = p.N + (long long)u * p.tab_rows + row_off;
-    const uint16_t* Kcu = p.Kc + ((long long)u * p.tab_rows + row_off) * kHeadDim;
-    const int32_t* start = coarse ? p.cstart + (long long)u * p.cstart_stride : p.fstart + (long long)u * p.fstart_stride;
     const Arrays& A = L.A;
 
     // ---------------- rows: operand layout, lane (k, e) takes dim group k of entry e of the wave's sixteen ----------------
@@ -1126,7 +1135,7 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
         const int x = wave * 16 * R + qA * R + t;
         if (x < nc) {
             const int id = use_ids ? A.ids[c * kThreads + x] : c * kThreads + x;
-            const uint4* kp = reinterpret_cast<const uint4*>(Kcu + (long long)id * kHeadDim) + kA;
+            const uint4* kp = reinterpret_cast<const uint4*>(T.rows + (long long)id * kHeadDim) + kA;
 #pragma unroll
             for (int k = 0; k < 4; ++k) r[k] = kp[4 * k];
         } else {
@@ -1146,9 +1155,9 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
         if (own) {
             const int id = use_ids ? A.ids[c * kThreads + x] : c * kThreads + x;
             st.id[c] = id;
-            st.w[c] = (uint32_t)Nu[id];
-            st.a1[c] = start[id];
-            if (coarse) st.a2[c] = start[id + 1];
+            st.w[c] = (uint32_t)T.N[id];
+            st.a1[c] = T.start[id];
+            if (coarse) st.a2[c] = T.start[id + 1];
         }
     }
 #pragma unroll
@@ -1163,6 +1172,7 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
     }
     __builtin_amdgcn_sched_barrier(0);
     // while the rows travel
+    meanwhile();
     if (tid < kHistBuckets) L.hist[tid] = S.hist[0][tid] = S.hist[1][tid] = S.hist[2][tid] = 0;
     if (tid < kListCap) S.ahead[tid] = 0;
     if (tid == 0) {
@@ -1172,10 +1182,13 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
     }
     if (q_pending) {
 #pragma unroll
-        for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = (double)bf16_to_f32(qv[hg]);
+        for (int hg = 0; hg < GH; ++hg) L.qB[tid + hg * kThreads] = query_operand<G>(qv[hg], hg, tid);
         phase_sync<true>();
     }
-    meanwhile();
+
+    const long long budget = coarse ? p.coarse_budget : p.key_budget;
+    unsigned long long* key_out = coarse ? p.key_c + (long long)u * p.c_stride : p.key_f + (long long)u * p.f_stride;
+    uint8_t* flag_out = coarse ? p.flag_c + (long long)u * p.c_stride : p.flag_f + (long long)u * p.f_stride;
 
     // ---------------- logits ----------------
     bool far = false;
@@ -1702,51 +1715,57 @@ __device__ __forceinline__ void touch_rows(const ScoreParams& p, const int32_t* 
     if (x == 0xfff1fff2u && p.U < 0) p.counters[4 * u] = 0;
 }
 
-__device__ __forceinline__ void touch_arguments(const ScoreParams& p)
-{
-    asm volatile("" ::"s"(p.q), "s"(p.cstart), "s"(p.g_wts), "s"(p.flag_c), "s"(p.n_cand), "s"(p.mp_rows), "s"(p.app_n), "s"(p.U));
-}
-
+// What the first level's requests need, as scalars: they are in registers when a wave starts (see the build flags), while the
+// other arguments span several cache lines of a segment no one has read yet.  So the query and the first level's rows are
+// asked for at once, and the rest of the arguments, one request for each line, while those travel.  Together with a query
+// that nothing waits for in front of the rows: one level of 64 clusters, 1 unit: step 15.8 -> 15.6 us; 8 units x 4096 keys
+// 27.6 -> 27.2; 32 units x 4096, 5 heads 41.1 -> 39.7; 24 units, 8 heads 48.0 -> 47.2.
+// first_row: first row of the level in the unit's tables, 0 where there is no coarse level.
 template <int G>
-__global__ __launch_bounds__(kThreads) void score_select_kernel(const ScoreParams p)
+__global__ __launch_bounds__(kThreads) void score_select_kernel(const uint16_t* q, const uint16_t* Kc, const int32_t* N,
+                                                                const int32_t* first_start, int U, int tab_rows, int first_row,
+                                                                int n_first, int first_stride, int lds_cap, const ScoreParams p)
 {
     constexpr int GH = (G + 3) / 4;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Scratch& S = *reinterpret_cast<Scratch*>(smem_raw);
-    const Lds L = carve_lds<G>(smem_raw + align16(sizeof(Scratch)), p.lds_cap);
-    const int u = blockIdx.x % p.U, tid = threadIdx.x;
-    const bool shadow = blockIdx.x >= (unsigned)p.U;     // second workgroup of the unit: warms the shared L2, stores nothing
+    const Lds L = carve_lds<G>(smem_raw + align16(sizeof(Scratch)), lds_cap);
+    const int u = blockIdx.x % U, tid = threadIdx.x;
+    const bool shadow = blockIdx.x >= (unsigned)U;     // second workgroup of the unit: warms the shared L2, stores nothing
+    const long long tables = (long long)u * tab_rows + first_row;
+    const LevelTables first{Kc + tables * kHeadDim, N + tables, first_start + (long long)u * first_stride};
 
-    // The arguments span several cache lines of a segment no one has read yet: one request for each of them, together,
-    // instead of one stall per line along the way.
-    touch_arguments(p);
     uint16_t qv[GH];    // this thread's elements of the query operand (one per head group; converted once they are needed)
 #pragma unroll
-    for (int hg = 0; hg < GH; ++hg) qv[hg] = query_operand_element<G>(p, u, tid + hg * kThreads);
+    for (int hg = 0; hg < GH; ++hg) qv[hg] = query_operand_element<G>(q, u, hg, tid);
     // the step's new rows go to their place in the tail buffers: asked for here, stored at the end
     uint4 app = make_uint4(0, 0, 0, 0);
-    const bool appends = !shadow && tid < 16 * p.app_n;
-    if (appends) app = reinterpret_cast<const uint4*>(p.app_src[tid >> 4])[(long long)u * 16 + (tid & 15)];
+    bool appends = false;
+    const auto arguments = [&] {
+        asm volatile("" ::"s"(p.q), "s"(p.cstart), "s"(p.g_wts), "s"(p.flag_c), "s"(p.n_cand), "s"(p.mp_rows), "s"(p.app_n), "s"(p.U));
+        appends = !shadow && tid < 16 * p.app_n;
+        if (appends) app = reinterpret_cast<const uint4*>(p.app_src[tid >> 4])[(long long)u * 16 + (tid & 15)];
+    };
 
-    const bool two = p.levels == 2;
-    const Arrays Ag = global_arrays<G>(p, u);
+    const bool two = first_row != 0;
     ScanState sc;
     uint32_t n_terms = 0;
-    int n_f = p.n_fine;
-    const bool coarse_fast = p.n_coarse <= p.lds_cap;
+    int n_f = n_first;
+    const bool coarse_fast = n_first <= lds_cap;
     FastLevel<G> fc;
     int slot_c[kFastChunks];
     if (two) {
-        unsigned long long* kc = p.key_c + (long long)u * p.c_stride;
-        uint8_t* flc = p.flag_c + (long long)u * p.c_stride;
         if (coarse_fast) {
-            const int lin = fast_level<G>(p, L, S, u, p.n_coarse, false, true, p.coarse_budget, false, true, qv, shadow, kc, flc, fc,
-                                          [] {});
+            const int lin = fast_level<G>(p, L, S, first, n_first, u, false, true, false, true, qv, shadow, fc, arguments);
             if (tid == 0 && !shadow) p.key_mode[2 * u] = lin;
             fast_candidates<G>(p, L, S, sc, fc, u, shadow, n_f, n_terms, slot_c);
         } else {
             // (a shadow workgroup would race with the first one on the global working arrays: it leaves)
             if (shadow) return;
+            arguments();
+            const Arrays Ag = global_arrays<G>(p, u);
+            unsigned long long* kc = p.key_c + (long long)u * p.c_stride;
+            uint8_t* flc = p.flag_c + (long long)u * p.c_stride;
             if (tid == 0) {
                 S.far[0] = 0;
                 S.far[1] = 1;      // (the general path shifts by the largest logit)
@@ -1759,22 +1778,26 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const ScoreParam
             leave_behind<G>(Ag, S, p.n_coarse, stc);
         }
         // the fine level reads the candidate list: from LDS, or back from global memory where it is long
-        if (coarse_fast && n_f <= p.lds_cap) phase_sync<true>();
+        if (coarse_fast && n_f <= lds_cap) phase_sync<true>();
         else __syncthreads();
     }
     if (shadow) {
-        if (n_f <= p.lds_cap) touch_rows(p, two ? L.A.ids : nullptr, u, n_f);
+        if (n_f <= lds_cap) touch_rows(p, two ? L.A.ids : nullptr, u, n_f);
         return;
     }
-    unsigned long long* kf = p.key_f + (long long)u * p.f_stride;
-    uint8_t* ff = p.flag_f + (long long)u * p.f_stride;
     // (the coarse level's centroid terms are written while the fine level's rows travel)
     const auto coarse_terms = [&] {
+        if (!two) arguments();
         if (two && coarse_fast && p.use_mp) fast_terms<G>(p, fc, slot_c, p.n_coarse, p.fcap, u);
     };
-    if (n_f <= p.lds_cap) {
+    if (n_f <= lds_cap) {
         FastLevel<G> ff_state;
-        const int lin = fast_level<G>(p, L, S, u, n_f, two, false, p.key_budget, two, !two, qv, false, kf, ff, ff_state, coarse_terms);
+        LevelTables fine = first;
+        if (two) {
+            const long long t = (long long)u * tab_rows;
+            fine = LevelTables{Kc + t * kHeadDim, N + t, p.fstart + (long long)u * p.fstart_stride};
+        }
+        const int lin = fast_level<G>(p, L, S, fine, n_f, u, two, false, two, !two, qv, false, ff_state, coarse_terms);
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
         fast_epilogue<G>(p, L, S, sc, ff_state, u, n_f, two, n_terms);
     } else {
@@ -1787,6 +1810,9 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const ScoreParam
             }
             __syncthreads();
         }
+        const Arrays Ag = global_arrays<G>(p, u);
+        unsigned long long* kf = p.key_f + (long long)u * p.f_stride;
+        uint8_t* ff = p.flag_f + (long long)u * p.f_stride;
         LevelState<G> stf;
         const int lin = score_level<G>(p, L, Ag, S, u, n_f, two, false, p.key_budget, two, !two, qv, kf, ff, stf);
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
@@ -1816,7 +1842,10 @@ static hipError_t launch_score_g(const ScoreParams& p, int copies, hipStream_t s
         if (e != hipSuccess) return e;
         configured = smem;
     }
-    hipLaunchKernelGGL((score_select_kernel<G>), dim3(p.U * copies), dim3(kThreads), smem, s, p);
+    const bool two = p.levels == 2;
+    hipLaunchKernelGGL((score_select_kernel<G>), dim3(p.U * copies), dim3(kThreads), smem, s, p.q, p.Kc, p.N,
+                       two ? p.cstart : p.fstart, p.U, (int)p.tab_rows, two ? p.fcap : 0, two ? p.n_coarse : p.n_fine,
+                       (int)(two ? p.cstart_stride : p.fstart_stride), p.lds_cap, p);
     return hipGetLastError();
 }
 
