@@ -14,7 +14,8 @@
 // (refresh of eight 8K contexts 804 -> 744 us).
 //
 // 2048 blocks of 8192 keys x 256 centroids, iterations 2 to 10: 711, 428, 322, 248, 203, 156, 132, 110, 95 us instead of 970
-// (member lists 123, means 846); 32 such blocks: 20 to 10 us instead of 34.
+// (member lists 123, means 846); 32 such blocks: 20 to 10 us instead of 34, 12.1 on average (12.6 while marks, ranges and
+// counts were asked for one after the other).
 #include "mp_device.h"
 #include "mp_internal.h"
 
@@ -55,7 +56,10 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     __shared__ bool touched[kMoveClusters];
     __shared__ int top, bottom, most, n_marked, n_points, n_due;
     const int b = blockIdx.y, u = blockIdx.z;
-    const int x0 = p.blocks[4 * b + 0], x1 = p.blocks[4 * b + 1], k0 = p.blocks[4 * b + 2], k1 = p.blocks[4 * b + 3];
+    asm volatile("" ::"s"(p.blocks), "s"(p.marks), "s"(p.sum), "s"(p.per));      // (the arguments' lines in one trip)
+    typedef const __attribute__((address_space(4))) int32_t constant_int;
+    const constant_int* block = (constant_int*)p.blocks + 4 * b;
+    const int x0 = block[0], x1 = block[1], k0 = block[2], k1 = block[3];
     const int ka = k0 + (int)blockIdx.x * p.per, m = min(p.per, k1 - ka);
     if (m <= 0) return;
     const int tid = threadIdx.x, lane = tid & 63, part = lane & 15;
@@ -67,17 +71,23 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     const uint4* Xb = reinterpret_cast<const uint4*>(p.X + ((long long)u * p.x_unit_rows + x0) * kHeadDim) + part;
     int32_t* count = p.count + u * p.count_stride + ka;
 
+    // the first of what every thread looks at, in one trip: the range of a cluster's keys, 64 points' marks, a cluster's members
+    const int chunk0 = wave + kMoveWaves * lane;
+    const uint32_t range0 = k0 + tid < k1 ? p.range[u * p.range_stride + k0 + tid] : 255u;
+    const unsigned long long marks0 = chunk0 < chunks ? marks[chunk0] : 0ull;
+    const int count0 = tid < m ? count[tid] : 0;
     if (tid == 0) { top = 0; bottom = 255; most = 0; n_marked = 0; }
     if (tid < m) touched[tid] = false;
     __syncthreads();
     {
-        int hi = 0, lo = 255, marked = 0;                    // range of the block's keys, marks of the block
-        for (int i = k0 + tid; i < k1; i += kMoveThreads) {
+        // range of the block's keys, marks of the block
+        int hi = (int)(range0 >> 16), lo = (int)(range0 & 0xffffu), marked = __popcll(marks0);
+        for (int i = k0 + tid + kMoveThreads; i < k1; i += kMoveThreads) {
             const uint32_t r = p.range[u * p.range_stride + i];
             hi = max(hi, (int)(r >> 16));
             lo = min(lo, (int)(r & 0xffffu));
         }
-        for (int i = tid; i < chunks; i += kMoveThreads) marked += __popcll(marks[i]);
+        for (int i = chunk0 + kMoveThreads; i < chunks; i += kMoveThreads) marked += __popcll(marks[i]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             hi = max(hi, __shfl_xor(hi, off, 64));
@@ -122,7 +132,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
         __syncthreads();
         for (int c0 = ca + wave; c0 < cb; c0 += kMoveThreads) {      // the marked points, in any order
             const int chunk = c0 + kMoveWaves * lane;
-            const unsigned long long mark = chunk < cb ? marks[chunk] : 0ull;
+            const unsigned long long mark = chunk >= cb ? 0ull : chunk == chunk0 ? marks0 : marks[chunk];
             const int has = __popcll(mark), incl = (int)wave_incl_scan_u32((uint32_t)has);
             int base = 0;
             if (lane == 63) base = atomicAdd(&n_points, incl);
@@ -137,17 +147,23 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             }
         }
         __syncthreads();
-        const int n_here = n_points;
+        const int n_here = __builtin_amdgcn_readfirstlane(n_points);
         uint32_t o[kMoveSteps], e[kMoveSteps];               // old and new cluster of a point, counted from ka
+        // (a lane past the last point reads the first point of the block: under a lane mask each step waits for the one before)
 #pragma unroll
         for (int r = 0; r < kMoveSteps; ++r) {
             const int i = r * kMoveThreads + tid;
             o[r] = e[r] = 0u;
-            if (i < n_here) {
-                const uint32_t t = points[i];
-                o[r] = (uint32_t)(was[t] - ka);
-                e[r] = (uint32_t)(now[t] - ka);
+            if (r * kMoveThreads < n_here) {
+                const uint32_t t = i < n_here ? points[i] : 0u;
+                o[r] = (uint32_t)was[t];
+                e[r] = (uint32_t)now[t];
             }
+        }
+#pragma unroll
+        for (int r = 0; r < kMoveSteps; ++r) {
+            o[r] -= (uint32_t)ka;
+            e[r] = r * kMoveThreads + tid < n_here ? e[r] - (uint32_t)ka : o[r];
         }
 #pragma unroll
         for (int r = 0; r < kMoveSteps; ++r) {
@@ -156,13 +172,13 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             if (e[r] < (uint32_t)m) atomicAdd(&total[e[r]], 1);
         }
         __syncthreads();
+        // the most members any sum on the way can have: those of before and every point that comes
+        if (ca == 0 && tid < m && total[tid] != 0) atomicMax(&most, count0 + total[tid]);
         const bool last = cb == chunks;
         if (wave == 0) {                                     // entries of a cluster side by side; the clusters that have any
             int entry = 0, some = 0;
             for (int c = lane; c - lane < m; c += 64) {
                 const int mine = c < m ? total[c] : 0;
-                // the most members any sum on the way can have: those of before and every point that comes
-                if (ca == 0 && mine != 0) atomicMax(&most, count[c] + mine);
                 const int incl = (int)wave_incl_scan_u32((uint32_t)mine);
                 const bool is_due = mine != 0 || (last && c < m && touched[c]);
                 const unsigned long long d = __ballot(is_due);
