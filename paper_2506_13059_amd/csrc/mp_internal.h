@@ -224,7 +224,7 @@ struct MoveMeans {
     long long ids_stride;
     const unsigned long long* marks;   // [U, marks_stride] of the points whose two ids may differ
     long long marks_stride;
-    int32_t* moved;                // [U, moved_stride]: set for blocks of which a point moved
+    int32_t* moved;                // [U, moved_stride]: set for blocks of which a point moved, or may have
     int moved_stride;
     uint16_t* C;                   // [U, c_unit_rows, 128], row = cluster id
     long long c_unit_rows;

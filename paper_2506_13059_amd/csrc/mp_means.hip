@@ -195,7 +195,11 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             const int room = 45 - (top - bottom);            // 53 + e - E in terms of the exponent fields
             const int members = one_round ? most : n;
             exact = top < 255 && room >= 0 && members <= (1 << min(room, 30));
-            if (!exact) break;
+            if (!exact) {
+                // (the points of later rounds are not looked at: one of them may have moved)
+                if (!one_round && tid == 0) p.moved[u * p.moved_stride + b] = 1;
+                break;
+            }
         }
 #pragma unroll
         for (int r = 0; r < kMoveSteps; ++r) {

@@ -54,3 +54,49 @@ def test_later_iterations(kind, n, k, iters):
     # what the case is there for
     assert moved > 0 and (n < 14000 or moved > 3072)
     assert (rounded > 0) == (kind == "wide")
+
+
+def _quiet_start(U, n, seed):
+    """The first 3300 keys copies of a few rows, far apart; then keys without clusters; one key large and one element tiny, so that
+    every point is a near tie, in all iterations, and no sum is exact in any order."""
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(U, n, 128, generator=g)
+    x[:, :3300] = 40.0 * torch.randn(U, 8, 128, generator=g)[:, torch.arange(3300) % 8]
+    x[:, 3299] = 30000.0 * torch.sign(torch.randn(U, 128, generator=g))
+    x[:, 3300, 5] = 2.0 ** -24
+    return x.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("n,k,iters,refine", [(8192, 32, 6, 0), (12000, 40, 5, 0), (13000, 300, 5, 0), (8192, 600, 4, 0),
+                                              (8192, 32, 1, 4), (12500, 40, 1, 3)])
+def test_only_later_points_move(n, k, iters, refine):
+    # (with refine: the last 1500 keys are appended by an update)
+    from paper_2506_13059_amd import binding as mp
+    from oracle import mp_oracle as O
+    from tests.gpu_util import f64, i32
+    print(f"n={n} k={k} refine={refine}", flush=True)
+    U, n0 = 2, n - (1500 if refine else 0)
+    K = _quiet_start(U, n, n + k)
+    V = torch.randn(U, n, 128, generator=torch.Generator().manual_seed(6)).to(torch.bfloat16)
+    rng = np.random.default_rng(3)
+    seeds = np.stack([np.concatenate([np.arange(8), [3299], 3300 + rng.choice(n0 - 3300, k - 9, replace=False)]) for _ in range(U)]).astype(np.int32)
+    new_seeds = np.stack([rng.choice(1500, 2, replace=False) for _ in range(U)]).astype(np.int32)
+    ctx = mp.MpContext(1, U, U, max_tokens=n, levels=1, max_fine=k + 2, max_coarse=0, block_w=0, block_alpha=0, max_tail=0)
+    part = lambda x, a, b: x[:, a:b].contiguous().cuda().view(1, U, b - a, 128)
+    ctx.mp_cluster_kv(part(K, 0, n0), part(V, 0, n0), k, 0, iters=iters, init_fine=torch.tensor(seeds))
+    if refine:
+        ctx.mp_update_clusters(part(K, n0, n), part(V, n0, n), 2, 0, refine_iters=refine, split_iters=1, seeds=torch.tensor(new_seeds))
+    got = [i32(x) if x.dtype == torch.int32 else f64(x) for x in (ctx.mp_get_assignments()[0], *ctx.mp_get_centroids(0))]
+    ctx.close()
+    blocks = mp.mp_plan_blocks(n0, 0, 0, k, 0)
+    for u in range(U):
+        def after(i):
+            cl = O.cluster_unit(f64(K)[u, :n0], f64(V)[u, :n0], blocks, seeds[u], None, iters if refine else i, 1)
+            return O.update_unit(cl, f64(K)[u, n0:], f64(V)[u, n0:], 2, 0, new_seeds[u], i, 0, 0) if refine else cl
+        steps = [after(i) for i in range(1, (refine or iters) + 1)]
+        ids = [s["fine_of_token"] for s in steps]
+        # what the case is there for: the first points are at rest, later ones move in every iteration
+        assert all((a[:3072] == b[:3072]).all() and (a != b).any() for a, b in zip(ids, ids[1:]))
+        assert (ids[1] != ids[-1]).any()
+        for g, name in zip(got, ("fine_of_token", "Kc_f", "Vc_f", "N_f")):
+            np.testing.assert_array_equal(g[u], steps[-1][name], err_msg=f"unit {u} {name}")
