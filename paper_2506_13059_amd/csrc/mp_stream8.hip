@@ -36,18 +36,35 @@ __device__ __forceinline__ bf16x8 widen_codes(u32x2 w)
     return bf16x8{v[0].x, v[0].y, v[1].x, v[1].y, v[2].x, v[2].y, v[3].x, v[3].y};
 }
 
-// The same part of eight probabilities (times their rows' scales) as tile_values takes of four, and their product with the rows.
+// The weights of the rows' codes are probabilities times value scales, of any magnitude, and the lowest bit of a bf16 part is
+// 2^-133 at best.  So from a scale below kSmallScale on a wave takes its weights, and the sums it has, kRaise times up, which
+// leaves every part its bits down to the smallest values; a scale from kLargeScale on ends that (below it a sum of 2^24 rows
+// taken up stays finite).  Other scales cost a comparison a tile.
+constexpr float kSmallScale = 0x1p-80f, kLargeScale = 0x1p30f, kRaise = 0x1p64f;
+enum class Weights { ordinary, raised, large };
+template <int G>
+__device__ __forceinline__ void scale_sums(StreamState<G>& st, float by)
+{
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            st.o[d][i] *= by;
+            if constexpr (StreamState<G>::kThird) st.o3[d][i] *= by;
+        }
+}
+
+// The same part of eight weights as tile_values takes of four probabilities, and their product with the rows.  Codes are finite, so
+// a part of zero needs no floor.
 template <int G>
 __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p)[8], uint32_t v_addr, uint32_t mask1, uint32_t mask2)
 {
     float x[2][4], y[2][4];
-    u16x4 floor[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        float ph[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float v = ph[i] = p[4 * h + i];
+            const float v = p[4 * h + i];
             x[h][i] = v - __uint_as_float(__float_as_uint(v) & mask1);
             if constexpr (StreamState<G>::kThird) {
                 const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
@@ -56,10 +73,9 @@ __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p
                 x[h][i] = x[h][i] - __uint_as_float(__float_as_uint(x[h][i]) & mask2);
             }
         }
-        floor[h] = part_floor(ph);
     }
     auto operand = [&](const float (&z)[2][4]) {
-        const u32x2 lo = __builtin_bit_cast(u32x2, raised(upper_halves(z[0]), floor[0])), hi = __builtin_bit_cast(u32x2, raised(upper_halves(z[1]), floor[1]));
+        const u32x2 lo = __builtin_bit_cast(u32x2, upper_halves(z[0])), hi = __builtin_bit_cast(u32x2, upper_halves(z[1]));
         return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
     };
     const bf16x8 a = operand(x);
@@ -84,6 +100,7 @@ __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p
 }
 
 // Listed 8-bit rows [w0, w1) through one wave (the counterpart of stream_tiles, whose comments on the pipeline hold here).
+// The wave's sums are still zero.
 template <int G, typename Started>
 __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0, int w1,
                                               uint32_t ring, uint32_t strips, Started started)
@@ -113,6 +130,7 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
     const int col = head < kHalf ? head : 4 + head - kHalf;
     const uint32_t share_addr = ring + 2 * kCodes + (uint32_t)((col >> 2) * (kShares / 2) + (col & 3) * 4 + 4 * g * 16);
     const uint32_t scale_addr = ring + 2 * kCodes + kShares + (uint32_t)(4 * g * 8);
+    const uint32_t vs_addr = ring + 2 * kCodes + kShares + (uint32_t)((lane & 31) * 8 + 4);
     const int n_tiles = (w1 - w0 + kTile8 - 1) / kTile8;
 
     auto load_strip = [&](int s) {           // row numbers and slots [w0 + 64 s, +64), clamped to the last row
@@ -168,27 +186,28 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
         load_values(1);
         if (n_tiles > 2 * (kStrip / kTile8)) load_strip(2);      // (the first strip's numbers have all been read)
     }
+    Weights weights = Weights::ordinary;     // (the same in all lanes)
     auto tile = [&](int t, auto ahead) {
         constexpr int kAhead = decltype(ahead)::value;            // how many tiles follow (two: two or more)
         const uint32_t half = (uint32_t)((t & 1) * kSlot8);
         wait_vm<kAhead == 0 ? 4 : 8 + kKeyLoads>();
         u32x2 k[2][4];
         u32x4 sc[4];
-        float share[8];
+        float share[8], row_vs;                  // row_vs: the value scale of row lane & 31
         {
             const uint32_t a0 = k_addr + half, a1 = (k_addr ^ 32u) + half, a2 = (k_addr ^ 64u) + half, a3 = (k_addr ^ 96u) + half;
-            asm volatile("ds_read_b64 %0, %20\n\tds_read_b64 %1, %21\n\tds_read_b64 %2, %22\n\tds_read_b64 %3, %23\n\t"
-                         "ds_read_b64 %4, %20 offset:2048\n\tds_read_b64 %5, %21 offset:2048\n\tds_read_b64 %6, %22 offset:2048\n\t"
-                         "ds_read_b64 %7, %23 offset:2048\n\t"
-                         "ds_read_b128 %8, %24\n\tds_read_b128 %9, %24 offset:16\n\tds_read_b128 %10, %24 offset:128\n\t"
-                         "ds_read_b128 %11, %24 offset:144\n\t"
-                         "ds_read_b32 %12, %25\n\tds_read_b32 %13, %25 offset:16\n\tds_read_b32 %14, %25 offset:32\n\t"
-                         "ds_read_b32 %15, %25 offset:48\n\tds_read_b32 %16, %25 offset:256\n\tds_read_b32 %17, %25 offset:272\n\t"
-                         "ds_read_b32 %18, %25 offset:288\n\tds_read_b32 %19, %25 offset:304\n\ts_waitcnt lgkmcnt(0)"
+            asm volatile("ds_read_b64 %0, %21\n\tds_read_b64 %1, %22\n\tds_read_b64 %2, %23\n\tds_read_b64 %3, %24\n\t"
+                         "ds_read_b64 %4, %21 offset:2048\n\tds_read_b64 %5, %22 offset:2048\n\tds_read_b64 %6, %23 offset:2048\n\t"
+                         "ds_read_b64 %7, %24 offset:2048\n\t"
+                         "ds_read_b128 %8, %25\n\tds_read_b128 %9, %25 offset:16\n\tds_read_b128 %10, %25 offset:128\n\t"
+                         "ds_read_b128 %11, %25 offset:144\n\t"
+                         "ds_read_b32 %12, %26\n\tds_read_b32 %13, %26 offset:16\n\tds_read_b32 %14, %26 offset:32\n\t"
+                         "ds_read_b32 %15, %26 offset:48\n\tds_read_b32 %16, %26 offset:256\n\tds_read_b32 %17, %26 offset:272\n\t"
+                         "ds_read_b32 %18, %26 offset:288\n\tds_read_b32 %19, %26 offset:304\n\tds_read_b32 %20, %27\n\ts_waitcnt lgkmcnt(0)"
                          : "=&v"(k[0][0]), "=&v"(k[0][1]), "=&v"(k[0][2]), "=&v"(k[0][3]), "=&v"(k[1][0]), "=&v"(k[1][1]), "=&v"(k[1][2]),
                            "=&v"(k[1][3]), "=&v"(sc[0]), "=&v"(sc[1]), "=&v"(sc[2]), "=&v"(sc[3]), "=&v"(share[0]), "=&v"(share[1]),
-                           "=&v"(share[2]), "=&v"(share[3]), "=&v"(share[4]), "=&v"(share[5]), "=&v"(share[6]), "=&v"(share[7])
-                         : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(scale_addr + half), "v"(share_addr + half)
+                           "=&v"(share[2]), "=&v"(share[3]), "=&v"(share[4]), "=&v"(share[5]), "=&v"(share[6]), "=&v"(share[7]), "=&v"(row_vs)
+                         : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(scale_addr + half), "v"(share_addr + half), "v"(vs_addr + half)
                          : "memory");
         }
         if constexpr (kAhead == 2) {
@@ -214,6 +233,15 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
         }
         float pr[8];
         tile_softmax<G>(st, s, pr);
+        if (__builtin_expect(__any(!(row_vs >= kSmallScale && row_vs < kLargeScale)) && weights != Weights::large, 0)) {
+            const Weights now = __any(row_vs >= kLargeScale) ? Weights::large : Weights::raised;
+            if (now != weights) scale_sums(st, now == Weights::raised ? kRaise : weights == Weights::raised ? 1.f / kRaise : 1.f);
+            weights = now;
+        }
+        if (__builtin_expect(weights == Weights::raised, 0)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vs[i] *= kRaise;
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) pr[i] *= vs[i];
         if constexpr (kAhead == 0) {         // (the rows past the end repeat the last one: nothing of them, whatever their scale)
@@ -232,6 +260,7 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
     for (; t + 2 < n_tiles; ++t) tile(t, std::integral_constant<int, 2>{});
     if (!single) tile(t++, std::integral_constant<int, 1>{});
     tile(t, std::integral_constant<int, 0>{});
+    if (weights == Weights::raised) scale_sums(st, 1.f / kRaise);
 }
 
 // As value_stream_kernel; the selected keys are 8-bit rows, the centroid terms and the tail bf16 rows.

@@ -9,11 +9,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def _context(G, n, tail, seed, clusters=7):
+def _context(G, n, tail, seed, clusters=7, values=lambda v: v):
     from paper_2506_13059_amd import binding as mp
     g = torch.Generator(device="cuda").manual_seed(seed)
     q, K, V, kt, vt = (torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
                        for s in ((1, 2 * G, 128), (1, 2, n, 128), (1, 2, n, 128), (1, 2, tail, 128), (1, 2, tail, 128)))
+    V, vt = values(V), values(vt)
     k = min(clusters, n)
     fot = (torch.arange(n, device="cuda", dtype=torch.int32) * 5 % k).expand(2, -1).contiguous()
     ctx = mp.MpContext(1, 2 * G, 2, max_tokens=n, levels=1, max_fine=k, max_tail=max(tail, 1), kv_format=mp.MP_KV_E4M3)
@@ -35,7 +36,7 @@ def _reference(ctx, q, K, V, kt, vt):
 def _check(got, ref, label):
     # one rounding to bf16 (2^-8 of the value at most), fp32 sums before it
     err = (got.double().cpu() - ref).abs()
-    bound = 2.0 ** -8 * ref.abs() + 2e-5 * ref.abs().max()
+    bound = 2.0 ** -8 * ref.abs() + 2e-5 * ref.abs().max() + 2.0 ** -134        # (the last: subnormal bf16)
     assert bool((err <= bound).all()), (label, float((err - bound).max()))
 
 
@@ -49,19 +50,37 @@ def test_tile_edges(n):
         ctx.close()
 
 
+def _shifted(x, by):
+    flat = torch.empty(x.numel() + by, dtype=x.dtype, device="cuda")[by:]
+    flat.copy_(x.reshape(-1))
+    return flat.view(x.shape)
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 7])
 def test_both_kernels(G):
     # a tail off 16 bytes sends the whole launch to the vector ALU; part of the clusters stays behind as centroid terms
     print(f"G={G}", flush=True)
     ctx, q, K, V, kt, vt = _context(G, 1500, 70, 60 + G, clusters=60)
-
-    def shifted(x, by):
-        flat = torch.empty(x.numel() + by, dtype=x.dtype, device="cuda")[by:]
-        flat.copy_(x.reshape(-1))
-        return flat.view(x.shape)
     a = ctx.mp_decode_attention(q, 400, 0, kt, vt)
-    b = ctx.mp_decode_attention(q, 400, 0, shifted(kt, 4), shifted(vt, 2))
+    b = ctx.mp_decode_attention(q, 400, 0, _shifted(kt, 4), _shifted(vt, 2))
     torch.cuda.synchronize()
     # the same fp32 sums in another order: at most one step of the bf16 output (2^-7 of the value) apart
     assert bool(((a.double() - b.double()).abs() <= 2.0 ** -7 * a.double().abs() + 1e-5).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("size", [1e-30, 1e-33, 1e-37, 1e15, 1e36, "one large row"])
+def test_values_of_any_magnitude(size):
+    # (fp32 has the bits of every product that shows in the output; the value scales reach down to 2^-132 and up to 2^116)
+    def values(v):
+        if size == "one large row":
+            x = v.float() * 1e-30
+            x[:, :, x.shape[2] // 2] = 1e13 * v.float()[:, :, 0]
+            return x.to(torch.bfloat16)
+        return (v.float() * size).to(torch.bfloat16)
+    for G, n in ((2, 700), (5, 161), (8, 700)):
+        print(f"size={size} G={G}", flush=True)
+        ctx, q, K, V, kt, vt = _context(G, n, 17, 80 + G, values=values)
+        out = ctx.mp_decode_attention(q, n, 0, kt, vt)
+        _check(out, _reference(ctx, q, K, V, kt, vt), f"size={size} G={G}")
+        ctx.close()
