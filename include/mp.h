@@ -85,7 +85,8 @@ typedef struct {
  *             logit.  The centroid tables, the unclustered tail and every input stay bf16, and
  *             the centroids are means of the original rows, so the index is identical to the
  *             MP_KV_BF16 one.  Not available together with lookup_keys (MP_EINVAL: there the
- *             centroids are those of the lookup keys, not of the stored keys). */
+ *             centroids are those of the lookup keys, not of the stored keys).  A value row with an
+ *             infinity has an infinite scale: no dimension of an output that attends it is finite. */
 #define MP_KV_BF16 0
 #define MP_KV_E4M3 1
 

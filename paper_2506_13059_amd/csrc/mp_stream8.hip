@@ -39,7 +39,7 @@ __device__ __forceinline__ bf16x8 widen_codes(u32x2 w)
 // The weights of the rows' codes are probabilities times value scales, of any magnitude, and the lowest bit of a bf16 part is
 // 2^-133 at best.  So from a scale below kSmallScale on a wave takes its weights, and the sums it has, kRaise times up, which
 // leaves every part its bits down to the smallest values; a scale from kLargeScale on ends that (below it a sum of 2^24 rows
-// taken up stays finite).  Other scales cost a comparison a tile.
+// taken up stays finite) and may be infinite.  Other scales cost a comparison a tile.
 constexpr float kSmallScale = 0x1p-80f, kLargeScale = 0x1p30f, kRaise = 0x1p64f;
 enum class Weights { ordinary, raised, large };
 template <int G>
@@ -55,9 +55,9 @@ __device__ __forceinline__ void scale_sums(StreamState<G>& st, float by)
 }
 
 // The same part of eight weights as tile_values takes of four probabilities, and their product with the rows.  Codes are finite, so
-// a part of zero needs no floor.
+// a part of zero needs no floor; an infinite weight (`large`: there may be one) is its own part, every time.
 template <int G>
-__device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p)[8], uint32_t v_addr, uint32_t mask1, uint32_t mask2)
+__device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p)[8], bool large, uint32_t v_addr, uint32_t mask1, uint32_t mask2)
 {
     float x[2][4], y[2][4];
 #pragma unroll
@@ -72,6 +72,14 @@ __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p
             } else {
                 x[h][i] = x[h][i] - __uint_as_float(__float_as_uint(x[h][i]) & mask2);
             }
+        }
+    }
+    if (__builtin_expect(large, 0)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (p[i] != INFINITY) continue;
+            x[i >> 2][i & 3] = INFINITY;
+            if constexpr (StreamState<G>::kThird) y[i >> 2][i & 3] = INFINITY;
         }
     }
     auto operand = [&](const float (&z)[2][4]) {
@@ -249,7 +257,7 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
             for (int i = 0; i < 8; ++i) pr[i] = w0 + t * kTile8 + 16 * (i >> 2) + 4 * g + (i & 3) < w1 ? pr[i] : 0.f;
         }
         wait_vm<kAhead == 2 ? 4 + 2 * kKeyLoads : kAhead * (4 + kKeyLoads)>();
-        tile_values8<G>(st, pr, v_addr + half, mask1, mask2);
+        tile_values8<G>(st, pr, weights == Weights::large, v_addr + half, mask1, mask2);
         if constexpr (kAhead == 2) {
             load_values(t + 2);
             // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next

@@ -84,3 +84,20 @@ def test_values_of_any_magnitude(size):
         out = ctx.mp_decode_attention(q, n, 0, kt, vt)
         _check(out, _reference(ctx, q, K, V, kt, vt), f"size={size} G={G}")
         ctx.close()
+
+
+@pytest.mark.parametrize("G", [2, 4, 8])
+def test_infinite_value(G):
+    # a row with an infinity has an infinite scale, which leaves no dim of its unit's outputs finite, whichever kernel runs
+    def values(v):
+        v[0, 0, v.shape[2] // 3, 9] = float("inf")
+        return v
+    print(f"G={G}", flush=True)
+    ctx, q, K, V, kt, vt = _context(G, 700, 17, 90 + G, values=lambda v: values(v) if v.shape[2] == 700 else v)
+    a = ctx.mp_decode_attention(q, 700, 0, kt, vt).view(2, G, 128)
+    b = ctx.mp_decode_attention(q, 700, 0, _shifted(kt, 4), _shifted(vt, 2)).view(2, G, 128)
+    torch.cuda.synchronize()
+    assert not bool(torch.isfinite(a[0]).any()) and bool(torch.isfinite(a[1]).all())
+    assert torch.equal(torch.nan_to_num(a[0], nan=7.0), torch.nan_to_num(b[0], nan=7.0))
+    assert bool(((a[1].double() - b[1].double()).abs() <= 2.0 ** -7 * a[1].double().abs() + 1e-5).all())
+    ctx.close()
