@@ -3,7 +3,7 @@
 The exact-row loops (bf16 rows and 8-bit rows) issue their loads through inline assembly and waits for them by count.
 The compiler does not know those registers are in flight, so nothing it emits may touch a
 destination register between the load and the matching wait.  This test compiles the kernel to
-gfx950 assembly and replays the instruction stream of every instantiation that uses the pipeline.
+gfx950 assembly with the library's flags and replays the instruction stream of every instantiation that uses the pipeline.
 """
 import os
 import re
@@ -11,6 +11,8 @@ import shutil
 import subprocess
 
 import pytest
+
+from paper_2506_13059_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2506_13059_amd", "csrc", "mp_value.hip")
@@ -28,9 +30,8 @@ def _regs(text):
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
 def test_no_instruction_touches_a_register_that_is_still_in_flight(tmp_path):
     asm = tmp_path / "mp_value.s"
-    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-                           "-packed-fp32-ops", "-S", "--cuda-device-only", "-o", str(asm), SRC],
-                          stderr=subprocess.DEVNULL)
+    subprocess.check_call(["hipcc", *build.FLAGS, *build.EXTRA_FLAGS.get(os.path.basename(SRC), []), "-S", "--cuda-device-only",
+                           "-o", str(asm), SRC], stderr=subprocess.DEVNULL)
     lines = asm.read_text().splitlines()
     checked = 0
     i = 0

@@ -1,12 +1,15 @@
-"""CPU-only check of the load pipeline of the matrix-core value pass over 8-bit rows: the compiled tile bodies have the loads
-and counted waits that the replay below assumes, and in the replay of waves of one to 40 tiles every piece has arrived
-before its use and every strip of row numbers is there, whole, while it is read."""
+"""CPU-only check of the load pipeline of the matrix-core value pass over 8-bit rows: the stream's start and tile bodies, compiled
+with the library's flags, have the loads and counted waits that the replay below assumes, in its order, and in the replay of
+waves of one to 40 tiles every piece has arrived before its use and every strip of row numbers is there, whole, while it is
+read."""
 import os
 import re
 import shutil
 import subprocess
 
 import pytest
+
+from paper_2506_13059_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2506_13059_amd", "csrc", "mp_stream8.hip")
@@ -49,7 +52,30 @@ def _bodies(toks):
     return out
 
 
-def _replay(n, waits):
+def _start(n, guest):
+    """Loads of a wave from the wait for its first row numbers to its first tile: (what, tokens)."""
+    out = [(("rows", 1), "yy")] if n > 2 else []
+    for t in range(min(2, n)):
+        out += [(("K", t), "xxxxxy"), (("V", t), "xxxx")]
+        if t == 0 and guest:
+            out.append((("guest",), "y"))           # (the first row numbers of the source that rides along)
+    if n > 4:
+        out.append((("rows", 2), "yy"))
+    return out
+
+
+def _check_starts(lines):
+    """The loads that the listing has between the wait for the first row numbers and the first tile are _start's."""
+    toks = _tokens(lines)
+    at = [i for i, t in enumerate(toks) if t == 0 and "".join(map(str, toks[i + 1:i + 9])).startswith("yyxxxxxy")]
+    assert len(at) == 1, at
+    found = toks[at[0] + 1:]
+    found = "".join(map(str, found[:next(i for i, t in enumerate(found) if isinstance(t, int))]))
+    # (in one piece: the branches skip what a wave does not need)
+    assert found == "".join(tok for _, tok in _start(5, True)), found
+
+
+def _replay(n, waits, guest):
     pending, slot = [], {}
 
     def load(what, count):
@@ -65,16 +91,14 @@ def _replay(n, waits):
     def wait(k):
         del pending[:max(0, len(pending) - k)]
 
-    strip(0)
-    if n > 2:
-        strip(1)
+    strip(0)                             # (asked for before the wave knew how many rows it has)
     wait(0)
-    for t in range(min(2, n)):
-        rows(t)
-        load(("K", t), KEY_LOADS)
-        load(("V", t), VALUE_LOADS)
-    if n > 4:
-        strip(2)
+    for what, toks in _start(n, guest):
+        if what[0] == "K":
+            rows(what[1])
+        if what[0] == "rows":
+            slot[what[1] & 1] = what[1]
+        load(what, len(toks))
     for t in range(n):
         ahead = min(2, n - 1 - t)
         wait(waits[ahead][0])
@@ -94,8 +118,8 @@ def _replay(n, waits):
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
 def test_every_piece_has_arrived_before_its_use(tmp_path):
     asm = tmp_path / "mp_stream8.s"
-    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-                           "-packed-fp32-ops", "-S", "--cuda-device-only", "-o", str(asm), SRC], stderr=subprocess.DEVNULL)
+    subprocess.check_call(["hipcc", *build.FLAGS, *build.EXTRA_FLAGS.get(os.path.basename(SRC), []), "-S", "--cuda-device-only",
+                           "-o", str(asm), SRC], stderr=subprocess.DEVNULL)
     lines = asm.read_text().splitlines()
     starts = [i for i, x in enumerate(lines) if re.match(r"^_ZN2mp\S*value_stream8_kernelILi\d+E\S*:", x)]
     assert len(starts) == 7
@@ -106,5 +130,7 @@ def test_every_piece_has_arrived_before_its_use(tmp_path):
         last = sorted((b for b in bodies if not b[1]), reverse=True)
         assert len(main) == 1 and main[0][1] == "xxxxxy" and len(last) == 2, bodies
         waits = {2: (main[0][0], main[0][2]), 1: (last[0][0], last[0][2]), 0: (last[1][0], last[1][2])}
+        _check_starts(lines[i:end])
         for n in range(1, 41):
-            _replay(n, waits)
+            for guest in (False, True):
+                _replay(n, waits, guest)
