@@ -39,14 +39,20 @@ def _compile(src, force):
     s = os.path.join(CSRC, src)
     o = os.path.join(OBJ, src + ".o")
     newest = max([os.path.getmtime(s)] + [os.path.getmtime(h) for h in _headers()])
-    if force or not os.path.exists(o) or os.path.getmtime(o) < newest:
-        cmd = ["hipcc", *FLAGS, *EXTRA_FLAGS.get(src, []), "-c", s, "-o", o]
+    cmd = ["hipcc", *FLAGS, *EXTRA_FLAGS.get(src, []), "-c", s, "-o", o]
+    made = o + ".flags"                  # (an object made with other flags is stale, too)
+    flags = "\n".join(cmd[1:-4])
+    if force or not os.path.exists(o) or os.path.getmtime(o) < newest or not os.path.exists(made) or open(made).read() != flags:
+        if os.path.exists(made):
+            os.remove(made)
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         out = "\n".join(l for l in r.stdout.splitlines() if "not a recognized feature" not in l)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for {src}:\n{out}")
         if out.strip():
             print(out)
+        with open(made, "w") as f:
+            f.write(flags)
     return o
 
 

@@ -96,3 +96,32 @@ def test_byte_model_reproduces_the_papers_memory_operation_column():
         step_bytes, value_pass_bytes = bench.algorithmic_bytes(counters, G=4)
         assert round(step_bytes / (2 * n * 256), 2) == want
         assert value_pass_bytes < step_bytes
+
+
+def test_objects_are_remade_when_source_or_flags_change(tmp_path, monkeypatch):
+    from paper_2506_13059_amd import build
+    made = []
+
+    def compiler(cmd, **_):
+        made.append(cmd)
+        open(cmd[-1], "w").close()
+        return type("Result", (), dict(returncode=0, stdout=""))
+    monkeypatch.setattr(build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "_headers", lambda: [])
+    monkeypatch.setattr(build.subprocess, "run", compiler)
+    (tmp_path / "a.hip").write_text("")
+    build._compile("a.hip", False)
+    build._compile("a.hip", False)
+    assert len(made) == 1
+    monkeypatch.setattr(build, "FLAGS", build.FLAGS + ["-DX"])
+    build._compile("a.hip", False)
+    build._compile("a.hip", False)
+    assert len(made) == 2
+    monkeypatch.setattr(build, "EXTRA_FLAGS", {"a.hip": ["-DY"]})
+    build._compile("a.hip", False)
+    assert len(made) == 3
+    later = os.path.getmtime(tmp_path / "a.hip.o") + 5
+    os.utime(tmp_path / "a.hip", (later, later))
+    build._compile("a.hip", False)
+    assert len(made) == 4
