@@ -28,7 +28,8 @@ constexpr int kMoveThreads = 64 * kMoveWaves;
 constexpr int kMoveSteps = 6;
 constexpr int kMoveRound = kMoveThreads * kMoveSteps;        // points looked at at a time
 constexpr int kMoveClusters = 256;                           // most clusters of a workgroup
-constexpr int kMoveBatch = 8;                                // rows of a cluster on their way at once
+constexpr int kMoveBatch = 8;                                // rows on their way to sixteen lanes at once
+constexpr int kMoveMany = 8 * kMoveBatch;                    // more entries of a cluster than this take a wave
 constexpr int kListSegment = 4 * kMoveRound;                 // points listed at a time while sums are taken afresh
 
 // Eight bf16 values to eight sums, in fp64.
@@ -44,9 +45,11 @@ __device__ __forceinline__ void add8(double (&a)[8], const uint4& w)
 
 // One workgroup per p.per clusters of a (block, unit).  It collects the points that the assignment marked, sorts those that
 // left or entered one of its clusters by cluster (in any order inside it), and sixteen lanes a cluster take the rows of
-// these points to the stored sum, eight dims each.
-// Latency bound: a trip for the marks, one for the points' ids, one for the sum and four rows, one for every four rows more; so
-// four clusters to a wave and 32 waves to a compute unit.
+// these points to the stored sum, eight dims each; all four sixteens of a wave share out a cluster of many such points.
+// Latency bound: a trip for the marks, one for the points' ids, one for the sum and eight rows, one for every eight rows more
+// (or 32); so four clusters to a wave and sixteen waves, two workgroups, to a compute unit (116 registers).  Where one cluster
+// takes most of what moves, 8192 keys of which half are zeros in 256 clusters, a build of five iterations: 2789 us with all
+// members summed in every iteration, 3480 with eight rows a trip in any case, 2100 so.
 // grid = (groups of p.per clusters of a block, blocks, units)
 __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveMeans p)
 {
@@ -54,7 +57,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     __shared__ uint32_t entries[2 * kMoveRound];             // point << 1 | it went (one that moves is in two clusters' entries)
     __shared__ int total[kMoveClusters], at[kMoveClusters], due[kMoveClusters];
     __shared__ bool touched[kMoveClusters];
-    __shared__ int top, bottom, most, n_marked, n_points, n_due;
+    __shared__ int top, bottom, most, n_marked, n_points, n_few, n_many;
     const int b = blockIdx.y, u = blockIdx.z;
     asm volatile("" ::"s"(p.blocks), "s"(p.marks), "s"(p.sum), "s"(p.per));      // (the arguments' lines in one trip)
     typedef const __attribute__((address_space(4))) int32_t constant_int;
@@ -175,22 +178,25 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
         // the most members any sum on the way can have: those of before and every point that comes
         if (ca == 0 && tid < m && total[tid] != 0) atomicMax(&most, count0 + total[tid]);
         const bool last = cb == chunks;
-        if (wave == 0) {                                     // entries of a cluster side by side; the clusters that have any
-            int entry = 0, some = 0;
+        // entries of a cluster side by side; the clusters that have any: those with few of them from the front, the others from the back
+        if (wave == 0) {
+            int entry = 0, few = 0, many = 0;
             for (int c = lane; c - lane < m; c += 64) {
                 const int mine = c < m ? total[c] : 0;
                 const int incl = (int)wave_incl_scan_u32((uint32_t)mine);
                 const bool is_due = mine != 0 || (last && c < m && touched[c]);
-                const unsigned long long d = __ballot(is_due);
+                const unsigned long long f = __ballot(is_due && mine <= kMoveMany), g = __ballot(mine > kMoveMany);
+                auto before = [](unsigned long long x) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(x >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)x, 0u)); };
                 if (c < m) at[c] = entry + incl - mine;
-                if (is_due) due[some + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(d >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)d, 0u))] = c;
+                if (is_due) due[mine <= kMoveMany ? few + before(f) : kMoveClusters - 1 - many - before(g)] = c;
                 entry += __builtin_amdgcn_readlane(incl, 63);
-                some += __popcll(d);
+                few += __popcll(f);
+                many += __popcll(g);
             }
-            if (lane == 0) n_due = some;
+            if (lane == 0) { n_few = few; n_many = many; }
         }
         __syncthreads();
-        if (tid == 0 && n_due > 0) p.moved[u * p.moved_stride + b] = 1;
+        if (tid == 0 && n_few + n_many > 0) p.moved[u * p.moved_stride + b] = 1;
         if (ca == 0) {
             const int room = 45 - (top - bottom);            // 53 + e - E in terms of the exponent fields
             const int members = one_round ? most : n;
@@ -209,35 +215,56 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             if (e[r] < (uint32_t)m) entries[atomicAdd(&at[e[r]], 1)] = i;
         }
         __syncthreads();
-        for (int d0 = 4 * wave; d0 < n_due; d0 += 4 * kMoveWaves) {
-            const int d = d0 + (lane >> 4);
-            if (d >= n_due) continue;
-            const int c = due[d], due_here = total[c];
-            double a[8];
-            read_sum(c, a);
-            const int members = count[c], first = at[c] - due_here;
+        // entries [i0, i0 + kMoveBatch) from `first`, as far as there are `all`, to the sum; returns how many of them went
+        auto take = [&](double (&a)[8], int first, int i0, int all) {
+            uint4 w[kMoveBatch];
             int gone = 0;
-            for (int i0 = 0; i0 < due_here; i0 += kMoveBatch) {
-                uint4 w[kMoveBatch];
 #pragma unroll
-                for (int q = 0; q < kMoveBatch; ++q) {
-                    const int i = i0 + q;
-                    const uint32_t e = entries[first + min(i, due_here - 1)];
-                    w[q] = Xb[(long long)(e >> 1) * 16];
-                    const uint32_t keep = i < due_here ? ~0u : 0u, turn = e & 1u ? 0x80008000u & keep : 0u;
-                    gone += turn != 0u ? 1 : 0;
-                    w[q] = make_uint4((w[q].x & keep) ^ turn, (w[q].y & keep) ^ turn, (w[q].z & keep) ^ turn, (w[q].w & keep) ^ turn);
-                }
-#pragma unroll
-                for (int q = 0; q < kMoveBatch; ++q) add8(a, w[q]);
+            for (int q = 0; q < kMoveBatch; ++q) {
+                const int i = i0 + q;
+                const uint32_t e = entries[first + min(i, all - 1)];
+                w[q] = Xb[(long long)(e >> 1) * 16];
+                const uint32_t keep = i < all ? ~0u : 0u, turn = e & 1u ? 0x80008000u & keep : 0u;
+                gone += turn != 0u ? 1 : 0;
+                w[q] = make_uint4((w[q].x & keep) ^ turn, (w[q].y & keep) ^ turn, (w[q].z & keep) ^ turn, (w[q].w & keep) ^ turn);
             }
+#pragma unroll
+            for (int q = 0; q < kMoveBatch; ++q) add8(a, w[q]);
+            return gone;
+        };
+        auto store = [&](int c, int due_here, int gone, const double (&a)[8]) {
             if (due_here != 0) store_sum(c, a);
-            const int members_now = members + due_here - 2 * gone;
+            const int members_now = count[c] + due_here - 2 * gone;
             if (part == 0) {
                 count[c] = members_now;
                 touched[c] = true;
             }
             if (last) store_mean(c, members_now, a);
+        };
+        // a cluster of many entries: every sixteen lanes of a wave take a quarter of them
+        for (int d = wave; d < n_many; d += kMoveWaves) {
+            const int c = due[kMoveClusters - 1 - d], due_here = total[c], first = at[c] - due_here;
+            double a[8] = {};
+            if (lane < 16) read_sum(c, a);
+            int gone = 0;
+            for (int i0 = kMoveBatch * (lane >> 4); i0 < due_here; i0 += 4 * kMoveBatch) gone += take(a, first, i0, due_here);
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) a[i] += __shfl_xor(a[i], off, 64);
+                gone += __shfl_xor(gone, off, 64);
+            }
+            if (lane < 16) store(c, due_here, gone, a);
+        }
+        for (int d0 = 4 * wave; d0 < n_few; d0 += 4 * kMoveWaves) {
+            const int d = d0 + (lane >> 4);
+            if (d >= n_few) continue;
+            const int c = due[d], due_here = total[c], first = at[c] - due_here;
+            double a[8];
+            read_sum(c, a);
+            int gone = 0;
+            for (int i0 = 0; i0 < due_here; i0 += kMoveBatch) gone += take(a, first, i0, due_here);
+            store(c, due_here, gone, a);
         }
         __syncthreads();
     }
@@ -256,8 +283,6 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
         int* mine = place + wave * m;
         __syncthreads();
         for (int i = tid; i < kMoveWaves * m; i += kMoveThreads) place[i] = 0;
-        if (s0 == 0 && !one_round)
-            for (int c = tid; c < m; c += kMoveThreads) due[c] = c;
         __syncthreads();
         auto walk = [&](bool write) {
             constexpr int kAhead = 8;                        // ids on their way at once
@@ -310,11 +335,12 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
         walk(true);
         __syncthreads();
         const uint4* Xs = Xb + (long long)s0 * 16;
-        const int n_sums = one_round ? n_due : m;
+        const int n_sums = one_round ? n_few + n_many : m;
         for (int d0 = 4 * wave; d0 < n_sums; d0 += 4 * kMoveWaves) {
             const int d = d0 + (lane >> 4);
             if (d >= n_sums) continue;
-            const int c = due[d], first = at[c], end = place[(kMoveWaves - 1) * m + c];
+            const int c = !one_round ? d : d < n_few ? due[d] : due[kMoveClusters - 1 - (d - n_few)];
+            const int first = at[c], end = place[(kMoveWaves - 1) * m + c];
             double a[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) a[i] = 0.0;
