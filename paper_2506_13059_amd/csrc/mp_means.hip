@@ -30,7 +30,8 @@ constexpr int kMoveRound = kMoveThreads * kMoveSteps;        // points looked at
 constexpr int kMoveClusters = 256;                           // most clusters of a workgroup
 constexpr int kMoveBatch = 8;                                // rows on their way to sixteen lanes at once
 constexpr int kMoveMany = 8 * kMoveBatch;                    // more entries of a cluster than this take a wave
-constexpr int kListSegment = 4 * kMoveRound;                 // points listed at a time while sums are taken afresh
+constexpr int kListRoom = 4 * kMoveRound;                    // members listed at a time while sums are taken afresh
+constexpr int kListReach = 65536;                            // ... of this many points of the block
 
 // Eight bf16 values to eight sums, in fp64.
 __device__ __forceinline__ void add8(double (&a)[8], const uint4& w)
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     __shared__ uint32_t entries[2 * kMoveRound];             // point << 1 | it went (one that moves is in two clusters' entries)
     __shared__ int total[kMoveClusters], at[kMoveClusters], due[kMoveClusters];
     __shared__ bool touched[kMoveClusters];
-    __shared__ int top, bottom, most, n_marked, n_points, n_few, n_many;
+    __shared__ int top, bottom, most, n_marked, n_points, n_few, n_many, held;
     const int b = blockIdx.y, u = blockIdx.z;
     asm volatile("" ::"s"(p.blocks), "s"(p.marks), "s"(p.sum), "s"(p.per));      // (the arguments' lines in one trip)
     typedef const __attribute__((address_space(4))) int32_t constant_int;
@@ -272,41 +273,41 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
 
     // ---- the sums round: members one after the other, in sequence order, of every cluster that changed (as far as the
     // first round of moves tells; all of them where there are more).  A stable sort of a segment's points by cluster, each
-    // wave an eighth of them (as in block_lists_kernel), then the same sixteen lanes a cluster. ----
-    static_assert(kListSegment <= 65536 && kListSegment * 2 <= (int)sizeof(entries) && kMoveWaves * kMoveClusters * 4 <= (int)sizeof(points), "");
+    // wave an eighth of them (as in block_lists_kernel), then a wave a cluster, 32 rows at a time.  Keys of which a tenth is
+    // 1e-12 times the others, builds with lists and sums of all members in every iteration -> here: 32 blocks of 8192 keys, ten
+    // iterations 1350 -> 1219 us, 512 blocks 7164 -> 6865; 64 blocks of 2000 keys, five iterations 433 -> 399. ----
+    static_assert(kListRoom * 2 <= (int)sizeof(entries) && kMoveWaves * kMoveClusters * 4 <= (int)sizeof(points), "");
     uint16_t* list = reinterpret_cast<uint16_t*>(entries);
     int* place = reinterpret_cast<int*>(points);             // [kMoveWaves][m]
     const int thirds = m > 1 ? (32 - __clz(m - 1) + 2) / 3 : 0;
-    for (int s0 = 0; s0 < n; s0 += kListSegment) {
-        const int here = min(kListSegment, n - s0);
+    // (the members its clusters had and every point that may have come: with few clusters of a long block they fit the list)
+    if (tid == 0) held = n_marked;
+    __syncthreads();
+    if (tid < m) atomicAdd(&held, count0);
+    __syncthreads();
+    const int segment = held <= kListRoom ? kListReach : kListRoom;
+    for (int s0 = 0; s0 < n; s0 += segment) {
+        const int here = min(segment, n - s0);
         const int per_wave = (here + kMoveThreads - 1) / kMoveThreads * 64, t0 = s0 + min(wave * per_wave, here), t1 = s0 + min((wave + 1) * per_wave, here);
         int* mine = place + wave * m;
         __syncthreads();
         for (int i = tid; i < kMoveWaves * m; i += kMoveThreads) place[i] = 0;
         __syncthreads();
-        auto walk = [&](bool write) {
-            constexpr int kAhead = 8;                        // ids on their way at once
+        // the wave's points in order, 64 at a time: their clusters, counted from ka
+        auto walk = [&](auto use) {
+            constexpr int kAhead = 16;                       // ids on their way at once
             for (int tb = t0; tb < t1; tb += 64 * kAhead) {
                 int id[kAhead];
 #pragma unroll
-                for (int r = 0; r < kAhead; ++r) {
-                    const int t = tb + 64 * r + lane;
-                    id[r] = t < t1 ? now[t] - ka : -1;
-                }
+                for (int r = 0; r < kAhead; ++r) id[r] = now[min(tb + 64 * r + lane, t1 - 1)] - ka;
 #pragma unroll
                 for (int r = 0; r < kAhead; ++r) {
-                    const bool valid = (unsigned)id[r] < (unsigned)m;
-                    const unsigned long long same = lanes_with_id(id[r], valid, thirds);
-                    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-                    if (valid) {
-                        const int first = mine[id[r]];
-                        if (write) list[first + rank] = (uint16_t)(tb + 64 * r + lane - s0);
-                        if (rank == 0) mine[id[r]] = first + __popcll(same);
-                    }
+                    const int t = tb + 64 * r + lane;
+                    use(t - s0, id[r], t < t1 && (unsigned)id[r] < (unsigned)m);
                 }
             }
         };
-        walk(false);
+        walk([&](int, int id, bool valid) { if (valid) atomicAdd(&mine[id], 1); });
         __syncthreads();
         for (int c = tid; c < m; c += kMoveThreads) {
             int all = 0;
@@ -332,34 +333,52 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             }
         }
         __syncthreads();
-        walk(true);
+        walk([&](int t, int id, bool valid) {
+            if (!__any(valid)) return;
+            const unsigned long long same = lanes_with_id(id, valid, thirds);
+            const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            if (valid) {
+                const int first = mine[id];
+                list[first + rank] = (uint16_t)t;
+                if (rank == 0) mine[id] = first + __popcll(same);
+            }
+        });
         __syncthreads();
-        const uint4* Xs = Xb + (long long)s0 * 16;
+        const uint32_t* Xs = reinterpret_cast<const uint32_t*>(Xb - part) + (long long)s0 * (kHeadDim / 2) + lane;
         const int n_sums = one_round ? n_few + n_many : m;
-        for (int d0 = 4 * wave; d0 < n_sums; d0 += 4 * kMoveWaves) {
-            const int d = d0 + (lane >> 4);
-            if (d >= n_sums) continue;
+        for (int d = wave; d < n_sums; d += kMoveWaves) {    // (a lane has two dims, as in cluster_mean_kernel)
             const int c = !one_round ? d : d < n_few ? due[d] : due[kMoveClusters - 1 - (d - n_few)];
             const int first = at[c], end = place[(kMoveWaves - 1) * m + c];
-            double a[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = 0.0;
+            double2* sum = reinterpret_cast<double2*>(p.sum + ((long long)u * p.sum_unit_rows + ka + c) * kHeadDim) + lane;
+            double2 a = make_double2(0.0, 0.0);
             int members = end - first;
             if (s0 > 0) {
-                read_sum(c, a);
+                a = *sum;
                 members += count[c];
             }
-            for (int i0 = first; i0 < end; i0 += kMoveBatch) {
-                uint4 w[kMoveBatch];
+            for (int base = first; base < end; base += 64) {
+                const int here_now = min(end - base, 64), member = lane < here_now ? list[base + lane] : 0;
+                constexpr int kBatch = 32;
+                for (int q0 = 0; q0 < here_now; q0 += kBatch) {
+                    uint32_t w[kBatch];
 #pragma unroll
-                for (int q = 0; q < kMoveBatch; ++q) w[q] = Xs[(long long)list[min(i0 + q, end - 1)] * 16];
+                    for (int q = 0; q < kBatch; ++q) w[q] = Xs[(long long)__builtin_amdgcn_readlane(member, min(q0 + q, here_now - 1)) * (kHeadDim / 2)];
 #pragma unroll
-                for (int q = 0; q < kMoveBatch; ++q)
-                    if (i0 + q < end) add8(a, w[q]);
+                    for (int q = 0; q < kBatch; ++q) {
+                        if (q0 + q < here_now) {
+                            a.x += (double)bf16lo_to_f32(w[q]);
+                            a.y += (double)bf16hi_to_f32(w[q]);
+                        }
+                    }
+                }
             }
-            store_sum(c, a);
-            if (part == 0) count[c] = members;
-            if (s0 + kListSegment >= n) store_mean(c, members, a);
+            *sum = a;
+            if (lane == 0) count[c] = members;
+            if (s0 + segment >= n && members > 0) {     // (an empty cluster keeps its centroid)
+                const double den = (double)members, inv = 1.0 / den;
+                reinterpret_cast<uint32_t*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim)[lane] =
+                    (uint32_t)quotient_to_bf16(a.x, den, inv) | ((uint32_t)quotient_to_bf16(a.y, den, inv) << 16);
+            }
         }
     }
 }

@@ -1,7 +1,7 @@
 """GPU parity of the centroid update of the Lloyd iterations after the first, which moves the member sums by the points that
 changed cluster: bit-identical to the oracle's sums in sequence order, also where fp64 rounds on the way (those clusters are
-summed afresh), with more points moving than a workgroup takes at a time, several groups of clusters to a block, blocks
-longer than the ids kept in LDS, empty clusters, and behind both assignment kernels."""
+summed afresh, from one list of members or several), with more points marked than a workgroup takes at a time (3072), many of
+them going to one cluster, several groups of clusters to a block, empty clusters, and behind both assignment kernels."""
 import math
 
 import numpy as np
@@ -18,6 +18,8 @@ def _keys(kind, U, n, seed):
         x = x[:, torch.randint(0, 11, (n,), generator=g)].contiguous()
     if kind == "half":
         x[:, :n // 2] = 0
+    if kind == "tiny":
+        x = torch.where(torch.rand(U, n, 128, generator=g) < 0.1, x * 2.0 ** -60, x)
     if kind == "wide":
         # magnitudes of 2^60 of either sign beside small ones in the same dims: a sum of them depends on its order
         huge = torch.where(torch.rand(U, n, 128, generator=g) < 0.5, 2.0 ** 60, -(2.0 ** 60))
@@ -27,13 +29,14 @@ def _keys(kind, U, n, seed):
 
 @pytest.mark.parametrize("kind,n,k,iters", [
     ("plain", 1500, 40, 6), ("plain", 700, 33, 4), ("plain", 4000, 300, 5), ("plain", 3000, 600, 3), ("plain", 14000, 9, 5),
-    ("few rows", 2000, 30, 5), ("few rows", 700, 20, 6), ("half", 3000, 60, 5), ("half", 9000, 60, 4), ("wide", 1500, 40, 6), ("wide", 700, 30, 4), ("wide", 14000, 40, 3)])
+    ("few rows", 2000, 30, 5), ("few rows", 700, 20, 6), ("half", 3000, 60, 5), ("half", 9000, 60, 4), ("wide", 1500, 40, 6), ("wide", 700, 30, 4), ("wide", 14000, 40, 3),
+    ("tiny", 2000, 40, 5), ("tiny", 14000, 300, 4), ("tiny", 66000, 300, 3)])
 def test_later_iterations(kind, n, k, iters):
     from paper_2506_13059_amd import binding as mp, inputs
     from oracle import mp_oracle as O
     from tests.gpu_util import f64, i32
     print(f"{kind} n={n} k={k}", flush=True)
-    U, kc = 2, max(1, k // 6)
+    U, kc = 1 if n > 20000 else 2, max(1, k // 6)
     K = _keys(kind, U, n, 900 + n + k)
     V = torch.randn(U, n, 128, generator=torch.Generator().manual_seed(5)).to(torch.bfloat16)
     blocks = mp.mp_plan_blocks(n, 0, 0, k, kc)
@@ -55,7 +58,7 @@ def test_later_iterations(kind, n, k, iters):
             rounded += sum(math.fsum(c) != sum(c.tolist()) for c in rows.T)
     # what the case is there for
     assert moved > 0 and (n < 14000 or moved > 3072)
-    assert (rounded > 0) == (kind == "wide")
+    assert (rounded > 0) == (kind in ("wide", "tiny"))
 
 
 def _quiet_start(U, n, seed):
