@@ -275,7 +275,7 @@ mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, hipStream_
         MP_TRY(build_lists(ctx, now, s));
         MP_HIPC(launch_cluster_means(pr.X, pr.x_unit_rows, pr.list, pr.list_stride, pr.start, pr.cnt_stride + 1,
                                      pr.k_first, pr.k_total, ctx->U, pr.C, pr.c_unit_rows, 0, pr.C, pr.c_unit_rows,
-                                     pr.sums ? pr.cnt : nullptr, pr.cnt_stride, 0, pr.sums, pr.sum_unit_rows, pr.range, s));
+                                     pr.sums ? pr.cnt : nullptr, pr.cnt_stride, 0, pr.sums, pr.sum_unit_rows, iters > 1 ? pr.range : nullptr, s));
     }
     return MP_OK;
 }
