@@ -229,7 +229,7 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     const size_t Lc = ctx->Lcap;
     A(lg, U * G * Lc); A(sc_keys, U * Lc); A(sc_wts, U * Lc); A(sc_ids, U * Lc); A(sc_aux, U * Lc); A(sc_aux2, U * Lc);
     A(sc_flags, U * Lc); A(key_c, U * Cc); A(key_f, U * F); A(key_mode, U * 2); A(flag_c, U * Cc); A(flag_f, U * F);
-    A(cand, U * F); A(n_cand, U); A(unprom_lse, U * G); A(rows, U * N); A(n_rows, U);
+    A(cand, U * F); A(n_cand, U); A(unprom_lse, U * G); A(rows, U * N); A(n_rows, U + 1);
     A(mp_rows, U * T); A(mp_scores, U * T * G); A(n_mp, U); A(counters, U * 4);
     A(partials, U * (size_t)ctx->Pcap * G * kPartStride);
     if (ctx->Tcap > 0) {
@@ -247,7 +247,7 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     if (e == hipSuccess) e = hipMemset(ctx->counters, 0, U * 4 * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->km_amb, 0, 2 * U * (size_t)ctx->max_blocks * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->n_mp, 0, U * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(ctx->n_rows, 0, U * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(ctx->n_rows, 0, (U + 1) * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->n_cand, 0, U * sizeof(int32_t));
     if (e != hipSuccess) {
         const mp_status st = (e == hipErrorOutOfMemory) ? MP_ENOMEM : MP_EHIP;

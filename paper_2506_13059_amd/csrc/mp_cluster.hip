@@ -390,7 +390,7 @@ mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void
                                  nullptr, s));
     if (bytes)   // (8-bit keys are residuals from the fine key centroids, which are final only now)
         MP_HIPC(launch_gather_quantize_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, ids, ids_stride, ctx->Kc, tab, n_pts, U,
-                                            ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, seq, s));
+                                            ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, seq, ctx->n_rows + U, s));
     if (two) {
         // the coarse tables: sums of the children's sums, in ascending fine id (no further pass over the rows)
         CoarseTables ct{};

@@ -128,7 +128,7 @@ struct mp_ctx {
     int32_t* n_cand = nullptr;     // [U]
     double* unprom_lse = nullptr;  // [U, G]
     int32_t* rows = nullptr;       // [U, Ncap] stored rows of the selected keys
-    int32_t* n_rows = nullptr;     // [U]
+    int32_t* n_rows = nullptr;     // [U], and whether a stored 8-bit row has had a value scale out of the ordinary (RowSource)
     int32_t* mp_rows = nullptr;    // [U, tab_rows]
     float* mp_scores = nullptr;    // [U, tab_rows, G]
     int32_t* n_mp = nullptr;       // [U]

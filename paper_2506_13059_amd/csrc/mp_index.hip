@@ -239,7 +239,7 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
                                             const uint4* __restrict__ Kc, long long kc_unit_rows, int n,
                                             uint2* __restrict__ dstK, uint2* __restrict__ dstV,
                                             float2* __restrict__ scales, long long dst_unit_rows, int dst_row0,
-                                            const SequenceCopy seq)
+                                            const SequenceCopy seq, int32_t* __restrict__ unusual)
 {
     const int u = blockIdx.y;
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -265,7 +265,10 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
     const long long row = (long long)u * dst_unit_rows + dst_row0 + p;
     dstK[row * 16 + c] = e4m3_codes8(k, ks);
     dstV[row * 16 + c] = e4m3_codes8(v, vs);
-    if (c == 0) scales[row] = make_float2(ks, vs);
+    if (c == 0) {
+        scales[row] = make_float2(ks, vs);
+        if (!(vs >= kSmallScale && vs < kLargeScale)) *unusual = 1;
+    }
 }
 
 // One wave per cluster of [k0, k): fp64 sum of the member rows in list order, mean rounded once to bf16.
@@ -298,8 +301,8 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     // the additions keep the members' order (a wave's time is the number of trips to memory it makes:
     // with 8 rows a trip the means of coarse clusters of some hundred rows took 160 us per call in an
     // online refresh, with 32 rows a trip a third of that).  The next 64 indices are asked for ahead, and a whole batch has no
-    // branch in front of each row: noting the range had made a cluster of thousands 12 % slower (2009 -> 2254 us for 60000
-    // members); a build of eight blocks of 131072 such keys, 128 clusters, 4620 -> 3655 us, of 32 blocks of 8192 keys 828 -> 796.
+    // branch in front of each row: noting the range had made a cluster of thousands 12 % slower (eight blocks of 131072 keys, the
+    // longest of 128 clusters, 2009 -> 2254 us); their build, five iterations, 4620 -> 3655 us, of 32 blocks of 8192 keys 828 -> 796.
     constexpr int kBatch = 32;
     auto members = [&](int base) { return base + lane < s1 ? (lp ? lp[base + lane] : base + lane) : 0; };
     int next = members(s0);
@@ -544,14 +547,15 @@ hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_
 hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                                        long long list_stride, const int32_t* ids, long long ids_stride,
                                        const uint16_t* Kc, long long kc_unit_rows, int n, int U, void* dstK, void* dstV,
-                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq, hipStream_t s)
+                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq,
+                                       int32_t* unusual, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     const long long threads = (long long)n * 16;
     hipLaunchKernelGGL(gather_quantize_rows_kernel, dim3((unsigned)((threads + 255) / 256), U), dim3(256), 0, s,
                        (const uint4*)srcK, (const uint4*)srcV, src_unit_rows, list, list_stride, ids, ids_stride,
                        (const uint4*)Kc, kc_unit_rows, n, (uint2*)dstK, (uint2*)dstV, (float2*)scales, dst_unit_rows,
-                       dst_row0, seq);
+                       dst_row0, seq, unusual);
     return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@ namespace mp {
 constexpr int kChunkRowsMin = 512;     // smallest chunk of the dense kernel: 4 waves, one strip of 128 rows each
 constexpr int kPartStride = 132;       // floats per (unit, chunk, head): m, l, pad, pad, acc[128]
 constexpr int kMaxSources = 4;
+constexpr float kSmallScale = 0x1p-80f, kLargeScale = 0x1p30f;      // (see mp_stream8.hip)
 
 // One stream of rows.  Row j of unit u lives at K + (u*unit_rows + idx)*128 (elements) where idx = rows ?
 // rows[u*rows_stride + j] : j.  The number of rows is *count_dev (clamped to count_max) or count_max.
@@ -27,7 +28,8 @@ struct RowSource {
     const float* scores;       // optional [U, rows_stride, G] ready-made logits in log2 units
     // optional, all three or none: K and V hold 128-byte rows of e4m3 codes; the value row idx stands for
     // code * row_scale[idx][1], the key row for (its cluster's centroid) + code * row_scale[idx][0], and the
-    // centroid's share of the logit is read ready-made: slot_base[row_slot[j]] for list position j
+    // centroid's share of the logit is read ready-made: slot_base[row_slot[j]] for list position j.  count_dev[n_units] is
+    // not zero if any row has had a value scale outside [kSmallScale, kLargeScale)
     const float* row_scale;    // [U, unit_rows, 2]
     const int32_t* row_slot;   // [U, rows_stride]
     const float* slot_base;    // [U, base_stride, 8] log2 units, column layout as written by the scoring kernel
@@ -204,7 +206,8 @@ hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_
 hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
                                        long long list_stride, const int32_t* ids, long long ids_stride,
                                        const uint16_t* Kc, long long kc_unit_rows, int n, int U, void* dstK, void* dstV,
-                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq, hipStream_t s);
+                                       float* scales, long long dst_unit_rows, int dst_row0, const SequenceCopy& seq,
+                                       int32_t* unusual, hipStream_t s);
 // mean_out row (out_row0 + id) = bf16(fp64 sum of the member rows in list order / count); sum_out (optional)
 // receives the fp64 sums themselves, row = id; range_out (optional) [U, sum_unit_rows] the exponent fields of a cluster's
 // largest magnitude (<< 16) and smallest nonzero one (subnormals count as 1; 255 where there is none).

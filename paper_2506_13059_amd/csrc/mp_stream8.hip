@@ -39,8 +39,9 @@ __device__ __forceinline__ bf16x8 widen_codes(u32x2 w)
 // The weights of the rows' codes are probabilities times value scales, of any magnitude, and the lowest bit of a bf16 part is
 // 2^-133 at best.  So from a scale below kSmallScale on a wave takes its weights, and the sums it has, kRaise times up, which
 // leaves every part its bits down to the smallest values; a scale from kLargeScale on ends that (below it a sum of 2^24 rows
-// taken up stays finite) and may be infinite.  Other scales cost a comparison a tile.
-constexpr float kSmallScale = 0x1p-80f, kLargeScale = 0x1p30f, kRaise = 0x1p64f;
+// taken up stays finite) and may be infinite.  A wave looks for such scales only where the index has had one (`unusual`, which the
+// quantiser notes): a comparison a tile alone made launches over a tile or two 0.2 us longer.
+constexpr float kRaise = 0x1p64f;
 enum class Weights { ordinary, raised, large };
 template <int G>
 __device__ __forceinline__ void scale_sums(StreamState<G>& st, float by)
@@ -108,9 +109,9 @@ __device__ __forceinline__ void tile_values8(StreamState<G>& st, const float (&p
 }
 
 // Listed 8-bit rows [w0, w1) through one wave (the counterpart of stream_tiles, whose comments on the pipeline hold here).
-// The wave's sums are still zero.
+// The wave's sums are still zero.  unusual: whether a value scale may lie outside [kSmallScale, kLargeScale).
 template <int G, typename Started>
-__device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, int w0, int w1,
+__device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSource& S, const ValuePassParams& p, int u, bool unusual, int w0, int w1,
                                               uint32_t ring, uint32_t strips, Started started)
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
@@ -138,7 +139,6 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
     const int col = head < kHalf ? head : 4 + head - kHalf;
     const uint32_t share_addr = ring + 2 * kCodes + (uint32_t)((col >> 2) * (kShares / 2) + (col & 3) * 4 + 4 * g * 16);
     const uint32_t scale_addr = ring + 2 * kCodes + kShares + (uint32_t)(4 * g * 8);
-    const uint32_t vs_addr = ring + 2 * kCodes + kShares + (uint32_t)((lane & 31) * 8 + 4);
     const int n_tiles = (w1 - w0 + kTile8 - 1) / kTile8;
 
     auto load_strip = [&](int s) {           // row numbers and slots [w0 + 64 s, +64), clamped to the last row
@@ -201,21 +201,21 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
         wait_vm<kAhead == 0 ? 4 : 8 + kKeyLoads>();
         u32x2 k[2][4];
         u32x4 sc[4];
-        float share[8], row_vs;                  // row_vs: the value scale of row lane & 31
+        float share[8];
         {
             const uint32_t a0 = k_addr + half, a1 = (k_addr ^ 32u) + half, a2 = (k_addr ^ 64u) + half, a3 = (k_addr ^ 96u) + half;
-            asm volatile("ds_read_b64 %0, %21\n\tds_read_b64 %1, %22\n\tds_read_b64 %2, %23\n\tds_read_b64 %3, %24\n\t"
-                         "ds_read_b64 %4, %21 offset:2048\n\tds_read_b64 %5, %22 offset:2048\n\tds_read_b64 %6, %23 offset:2048\n\t"
-                         "ds_read_b64 %7, %24 offset:2048\n\t"
-                         "ds_read_b128 %8, %25\n\tds_read_b128 %9, %25 offset:16\n\tds_read_b128 %10, %25 offset:128\n\t"
-                         "ds_read_b128 %11, %25 offset:144\n\t"
-                         "ds_read_b32 %12, %26\n\tds_read_b32 %13, %26 offset:16\n\tds_read_b32 %14, %26 offset:32\n\t"
-                         "ds_read_b32 %15, %26 offset:48\n\tds_read_b32 %16, %26 offset:256\n\tds_read_b32 %17, %26 offset:272\n\t"
-                         "ds_read_b32 %18, %26 offset:288\n\tds_read_b32 %19, %26 offset:304\n\tds_read_b32 %20, %27\n\ts_waitcnt lgkmcnt(0)"
+            asm volatile("ds_read_b64 %0, %20\n\tds_read_b64 %1, %21\n\tds_read_b64 %2, %22\n\tds_read_b64 %3, %23\n\t"
+                         "ds_read_b64 %4, %20 offset:2048\n\tds_read_b64 %5, %21 offset:2048\n\tds_read_b64 %6, %22 offset:2048\n\t"
+                         "ds_read_b64 %7, %23 offset:2048\n\t"
+                         "ds_read_b128 %8, %24\n\tds_read_b128 %9, %24 offset:16\n\tds_read_b128 %10, %24 offset:128\n\t"
+                         "ds_read_b128 %11, %24 offset:144\n\t"
+                         "ds_read_b32 %12, %25\n\tds_read_b32 %13, %25 offset:16\n\tds_read_b32 %14, %25 offset:32\n\t"
+                         "ds_read_b32 %15, %25 offset:48\n\tds_read_b32 %16, %25 offset:256\n\tds_read_b32 %17, %25 offset:272\n\t"
+                         "ds_read_b32 %18, %25 offset:288\n\tds_read_b32 %19, %25 offset:304\n\ts_waitcnt lgkmcnt(0)"
                          : "=&v"(k[0][0]), "=&v"(k[0][1]), "=&v"(k[0][2]), "=&v"(k[0][3]), "=&v"(k[1][0]), "=&v"(k[1][1]), "=&v"(k[1][2]),
                            "=&v"(k[1][3]), "=&v"(sc[0]), "=&v"(sc[1]), "=&v"(sc[2]), "=&v"(sc[3]), "=&v"(share[0]), "=&v"(share[1]),
-                           "=&v"(share[2]), "=&v"(share[3]), "=&v"(share[4]), "=&v"(share[5]), "=&v"(share[6]), "=&v"(share[7]), "=&v"(row_vs)
-                         : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(scale_addr + half), "v"(share_addr + half), "v"(vs_addr + half)
+                           "=&v"(share[2]), "=&v"(share[3]), "=&v"(share[4]), "=&v"(share[5]), "=&v"(share[6]), "=&v"(share[7])
+                         : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(scale_addr + half), "v"(share_addr + half)
                          : "memory");
         }
         if constexpr (kAhead == 2) {
@@ -241,14 +241,21 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
         }
         float pr[8];
         tile_softmax<G>(st, s, pr);
-        if (__builtin_expect(__any(!(row_vs >= kSmallScale && row_vs < kLargeScale)) && weights != Weights::large, 0)) {
-            const Weights now = __any(row_vs >= kLargeScale) ? Weights::large : Weights::raised;
+        if (__builtin_expect(unusual, 0)) {
+            float least = vs[0], most = vs[0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) {
+                least = fminf(least, vs[i]);
+                most = fmaxf(most, vs[i]);
+            }
+            const bool large = __any(most >= kLargeScale), small = __any(least < kSmallScale);
+            const Weights now = large || weights == Weights::large ? Weights::large : small ? Weights::raised : weights;
             if (now != weights) scale_sums(st, now == Weights::raised ? kRaise : weights == Weights::raised ? 1.f / kRaise : 1.f);
             weights = now;
-        }
-        if (__builtin_expect(weights == Weights::raised, 0)) {
+            if (weights == Weights::raised) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) vs[i] *= kRaise;
+                for (int i = 0; i < 8; ++i) vs[i] *= kRaise;
+            }
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) pr[i] *= vs[i];
@@ -282,9 +289,12 @@ __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassPa
     const uint32_t ring = lds0 + (uint32_t)(wave * kRing8), strips = lds0 + (uint32_t)(kWaves * kRing8 + wave * kStrips8);
     const uint32_t guest_strip = strips + 16 * kStrip;
     touch_arguments(p);
+    int unusual = 0;
     const StreamShare w = stream_share<kWaves>(p, [&](const RowSource& S, int u, int first) {
         fetch_strip(S.rows, S, u, first, strips);
-        if (S.row_slot) fetch_strip(S.row_slot, S, u, first, strips + 8 * kStrip);
+        if (!S.row_slot) return;
+        fetch_strip(S.row_slot, S, u, first, strips + 8 * kStrip);
+        unusual = ((const __attribute__((address_space(4))) int32_t*)S.count_dev)[p.n_units];
     });
     const RowSource& S = p.src[w.source];
     const int u = w.u;
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassPa
     auto guest = [&] { if (w.a < w.b) fetch_strip(p.src[0].rows, p.src[0], u, w.a, guest_strip); };
     if (w.w0 < w.w1) {
         if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
-        else if (S.row_scale) stream_tiles8<G>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
+        else if (S.row_scale) stream_tiles8<G>(st, S, p, u, unusual != 0, w.w0, w.w1, ring, strips, guest);
         else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
     } else {
         guest();

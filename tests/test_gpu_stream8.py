@@ -86,14 +86,22 @@ def test_values_of_any_magnitude(size):
         ctx.close()
 
 
+@pytest.mark.parametrize("appended", [False, True])
 @pytest.mark.parametrize("G", [2, 4, 8])
-def test_infinite_value(G):
+def test_infinite_value(G, appended):
     # a row with an infinity has an infinite scale, which leaves no dim of its unit's outputs finite, whichever kernel runs
+    from paper_2506_13059_amd import binding as mp
+
     def values(v):
-        v[0, 0, v.shape[2] // 3, 9] = float("inf")
+        v[0, 0, 697 if appended else 233, 9] = float("inf")
         return v
-    print(f"G={G}", flush=True)
+    print(f"G={G} appended={appended}", flush=True)
     ctx, q, K, V, kt, vt = _context(G, 700, 17, 90 + G, values=lambda v: values(v) if v.shape[2] == 700 else v)
+    if appended:
+        ctx.close()
+        ctx = mp.MpContext(1, 2 * G, 2, max_tokens=700, levels=1, max_fine=9, max_tail=17, kv_format=mp.MP_KV_E4M3)
+        ctx.mp_cluster_kv(*(x[:, :, :660].contiguous() for x in (K, V)), 7, 0, iters=2, seed=1)
+        ctx.mp_update_clusters(*(x[:, :, 660:].contiguous() for x in (K, V)), 1, 0, refine_iters=1, split_iters=1, seed=2)
     a = ctx.mp_decode_attention(q, 700, 0, kt, vt).view(2, G, 128)
     b = ctx.mp_decode_attention(q, 700, 0, _shifted(kt, 4), _shifted(vt, 2)).view(2, G, 128)
     torch.cuda.synchronize()
