@@ -119,8 +119,8 @@ inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
 
 // Selected keys stored as 8-bit rows, one query head to a unit: the vector-ALU kernel.  A row's sixteen columns of the matrix
 // product would hold three parts of one head; the conversions are for all sixteen.  Whole step, us, here / matrix cores, 1 head:
-// 32 units x 4096 keys 30.5 / 32.1, 64 x 4096 36.5 / 37.8, 128 x 4096 51.0 / 51.1; 2 heads: 8 x 4096 28.1 / 27.8, 32 x 4096 34.1 /
-// 34.7, 128 x 8192 87.5 / 85.6; 4 heads: 128 x 4096 65.4 / 53.4; 8 heads: 64 x 4096 65.7 / 45.0.
+// 8 units x 4096 keys 25.3 / 25.4, 32 x 4096 29.6 / 30.5, 64 x 4096 36.4 / 36.6, 128 x 4096 50.1 / 50.3; 2 heads: 8 x 4096 27.2 /
+// 26.4, 32 x 4096 32.0 / 31.4, 128 x 8192 77.8 / 74.6; 4 heads: 128 x 4096 64.3 / 52.0; 8 heads: 64 x 4096 67.3 / 42.3.
 inline bool bytes_on_vector_alu(int group) { return group == 1; }
 
 // Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one

@@ -10,8 +10,8 @@
 //                  and become bf16 there: one product of 32 rows each of the eight groups of dims
 // Bound by the memory system and its latency: two vector instructions a code pair are all that 8 bits cost, about 200 for 32
 // rows; the vector-ALU kernel needs 420 for 16.
-// Whole step, vector-ALU kernel -> here: 64 units, 3125 of 100003 keys and a tail of 139, 4 heads 54.7 -> 44.5 us; 64 x 4096, 8
-// heads 65.7 -> 45.0; 128 x 4096, 4 heads 65.4 -> 53.4 (one and two heads: bytes_on_vector_alu in mp_plan.h).
+// Whole step, vector-ALU kernel -> here: 64 units, 3125 of 100003 keys and a tail of 139, 4 heads 54.7 -> 44.2 us; 64 x 4096, 8
+// heads 67.3 -> 42.3; 128 x 4096, 4 heads 64.3 -> 52.0 (one and two heads: bytes_on_vector_alu in mp_plan.h).
 #include "mp_stream_tiles.h"
 
 namespace mp {
