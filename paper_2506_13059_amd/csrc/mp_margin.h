@@ -15,9 +15,14 @@ namespace mp {
 constexpr int kTiledSlotBits = 4;
 constexpr int kResidentSlotBits = 6;
 
+// Below the normal range of fp32 all of this is absolute: a step loses at most 2^-126 even if subnormal numbers are flushed, some
+// 140 steps and a product each 2^-117 a score, the index bits far less.  kNearFloor covers two scores of it (keys smaller than
+// 1e-14 then go to the exact pass, all of them).
+constexpr float kNearFloor = 0x1p-110f;
+
 // Scores whose index bits are four (2^-19 of at most 1.5 M each), or that carry none: two of them are off by less than
 // 3.6 * 2^-16 M (3.2 without index bits) together.  M is an fp32 sum, less than 2^-16 of it off.
-constexpr float near_margin(float m) { return m * (4.0f / 65536.0f); }
+constexpr float near_margin(float m) { return m * (4.0f / 65536.0f) + kNearFloor; }
 
 // Scores that carry six bits: 2^-17 of their size each, of which the size matters: of two scores, only one that is no
 // further from the best than the margin can have been confused with it, so 2^-16 |best| covers both.  3.2 * 2^-16 M +
@@ -25,7 +30,7 @@ constexpr float near_margin(float m) { return m * (4.0f / 65536.0f); }
 // point far from every centroid has scores down to -1.5 M.
 constexpr float near_margin_of_best(float m, float best)
 {
-    return (3.25f * m + (best < 0.0f ? -best : best)) * (1.0f / 65536.0f);
+    return (3.25f * m + (best < 0.0f ? -best : best)) * (1.0f / 65536.0f) + kNearFloor;
 }
 
 }  // namespace mp

@@ -72,3 +72,12 @@ def test_candidates_of_the_exact_pass(lib):
     # scores without index bits: whatever can be the nearest is within the margin of the best
     for M in (1.0, 9.0):
         assert lib.tiled(M * (1 - 100 * ULP), 0.0) > 2 * _accumulation_error(M, 131)
+
+
+@pytest.mark.parametrize("kernel,steps", [("tiled", 131), ("resident", 128)])
+def test_below_the_normal_range(lib, kernel, steps):
+    # products and sums may be flushed to zero there, and the index bits are most of what is left of a score
+    margin, bits = getattr(lib, kernel), getattr(lib, kernel + "_bits")()
+    for M in (0.0, 1e-44, 1e-38, 1e-30):
+        lost = 2 * (steps + 12) * 2 * 2.0 ** -126
+        assert margin(M, 0.0) > lost + 2 * _accumulation_error(M, steps) + 2.0 ** bits * 2.0 ** -149

@@ -16,6 +16,8 @@ def _keys(kind, U, n, seed):
     x = torch.randn(U, n, 128, generator=g)
     if kind == "few rows":
         x = x[:, torch.randint(0, 11, (n,), generator=g)].contiguous()
+    if kind in ("1e-20", "1e-36"):
+        x *= float(kind)
     if kind == "half":
         x[:, :n // 2] = 0
     if kind == "tiny":
@@ -30,6 +32,7 @@ def _keys(kind, U, n, seed):
 @pytest.mark.parametrize("kind,n,k,iters", [
     ("plain", 1500, 40, 6), ("plain", 700, 33, 4), ("plain", 4000, 300, 5), ("plain", 3000, 600, 3), ("plain", 14000, 9, 5),
     ("few rows", 2000, 30, 5), ("few rows", 700, 20, 6), ("half", 3000, 60, 5), ("half", 9000, 60, 4), ("wide", 1500, 40, 6), ("wide", 700, 30, 4), ("wide", 14000, 40, 3),
+    ("1e-20", 2000, 40, 4), ("1e-36", 2000, 40, 4), ("1e-36", 2000, 600, 3), ("1e-36", 700, 30, 4),
     ("tiny", 2000, 40, 5), ("tiny", 14000, 300, 4), ("tiny", 66000, 300, 3)])
 def test_later_iterations(kind, n, k, iters):
     from paper_2506_13059_amd import binding as mp, inputs
