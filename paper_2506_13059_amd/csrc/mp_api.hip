@@ -229,6 +229,11 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     const size_t Lc = ctx->Lcap;
     A(lg, U * G * Lc); A(sc_keys, U * Lc); A(sc_wts, U * Lc); A(sc_ids, U * Lc); A(sc_aux, U * Lc); A(sc_aux2, U * Lc);
     A(sc_flags, U * Lc); A(key_c, U * Cc); A(key_f, U * F); A(key_mode, U * 2); A(flag_c, U * Cc); A(flag_f, U * F);
+    if (score_helpers(ctx->U, ctx->n_cus, c.levels, 1) > 0) {
+        ctx->early_cap = std::min(ctx->Fcap, kHelpedClusters / ctx->U);
+        A(early, U * (size_t)ctx->early_cap * 8 * (size_t)((G + 3) / 4));
+        A(early_done, U);
+    }
     A(cand, U * F); A(n_cand, U); A(unprom_lse, U * G); A(rows, U * N); A(n_rows, U + 1);
     A(mp_rows, U * T); A(mp_scores, U * T * G); A(n_mp, U); A(counters, U * 4);
     A(partials, U * (size_t)ctx->Pcap * G * kPartStride);
@@ -246,6 +251,7 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->pin_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMemset(ctx->counters, 0, U * 4 * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->km_amb, 0, 2 * U * (size_t)ctx->max_blocks * sizeof(int32_t));
+    if (e == hipSuccess && ctx->early_done) e = hipMemset(ctx->early_done, 0, U * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->n_mp, 0, U * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->n_rows, 0, (U + 1) * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(ctx->n_cand, 0, U * sizeof(int32_t));
@@ -410,6 +416,8 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     sp.use_mp = use_mp; sp.counters = ctx->counters; sp.n_tail = n_tail;
     sp.lds_cap = std::min(1024, std::max(ctx->n_fine, std::max(ctx->n_coarse, 1)));
     sp.G = G; sp.U = U;
+    sp.early = ctx->early; sp.early_stride = ctx->early_cap; sp.early_done = ctx->early_done;
+    sp.helpers = ctx->early ? score_helpers(U, ctx->n_cus, ctx->cfg.levels, ctx->n_fine) : 0;
     if (app) {
         sp.app_n = app->n; sp.app_dst_rows = app->dst_rows; sp.app_row = app->row;
         for (int a = 0; a < app->n; ++a) { sp.app_src[a] = app->src[a]; sp.app_dst[a] = app->dst[a]; }

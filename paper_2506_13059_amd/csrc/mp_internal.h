@@ -115,6 +115,13 @@ struct ScoreParams {
     int use_mp;
     int32_t* counters;          // [U, 4]
     int n_tail;
+    // optional (two levels): workgroups per unit that work out e^l and the logits of all fine clusters while the coarse level
+    // is being scored (early_logits in mp_score.hip): how many, what they leave, and per unit how many of them are done -- zero
+    // before and after a launch
+    int helpers;
+    double* early;              // [U, early_stride, 2, heads in fours] logits, then e^l of a fine cluster
+    long long early_stride;
+    int32_t* early_done;        // [U]
     // optional: rows the caller hands over with this step (a generation loop's new token) are copied
     // into the tail buffers by the workgroup of their unit before anything else; the value pass,
     // a later launch, then finds them there.  app_n arrays (0 = none), 256-byte rows.

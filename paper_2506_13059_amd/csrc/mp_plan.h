@@ -123,6 +123,23 @@ inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
 // 26.4, 32 x 4096 32.0 / 31.4, 128 x 8192 77.8 / 74.6; 4 heads: 128 x 4096 64.3 / 52.0; 8 heads: 64 x 4096 67.3 / 42.3.
 inline bool bytes_on_vector_alu(int group) { return group == 1; }
 
+// Workgroups per unit that work out the logits of all fine clusters while the unit's own workgroup scores its coarse level (two
+// levels; 0: none).  They pay where they are done by the time the candidates are known: at most two rounds of 128 clusters
+// each, on compute units that are idle otherwise, and ten megabytes of centroid rows in all (more of them slow the coarse level's
+// down).  Whole step, us, without / with, four heads unless said otherwise: 1 unit x 1024 clusters 25.5 / 23.5; 8 x 256 22.9 /
+// 22.2, x 1024 27.7 / 25.6 (128 clusters a helper; 25.8 with 256, 28.5 with 512), x 1024 of 8 heads 31.5 / 29.1, x 2048 33.4 /
+// 28.0 (34.3 with 512 a helper), x 4096 37.6 / 33.1; 16 x 2048 31.3 / 29.7; 24 x 1562 41.3 / 37.3, of 8 heads 47.0 / 41.3; 32 x 1024 36.0 /
+// 34.4; 40 x 937 of 6 heads 41.7 / 40.2; 64 x 320 29.0 / 28.6; no gain: 64 x 640 37.6 / 37.9 (10.5 MB), 32 x 2048 of 5
+// heads 39.6 / 41.5 (16.8 MB).
+constexpr int kHelpedClusters = 40000;      // of all units together
+inline int score_helpers(int n_units, int n_compute_units, int levels, int n_fine)
+{
+    const int spare = n_units > 0 ? (n_compute_units - n_units) / n_units : 0;
+    if (levels != 2 || spare < 1 || (long long)n_units * n_fine > kHelpedClusters) return 0;
+    const int most = std::min(spare, (n_fine + 127) / 128);
+    return (n_fine + most - 1) / most <= 256 ? most : 0;
+}
+
 // Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one
 // workgroup per pair, or in a launch per step.  The workgroup's time grows with its clusters (each is one wave's walk over
 // all points and a trip to memory, sixteen or eight waves) and points, that of the steps with their number and, beyond one

@@ -36,6 +36,16 @@
 // opposite order, so that each of the two finds part of its rows already in the shared L2.  It never
 // communicates with the first.
 //
+// Helpers: where the units' fine clusters are few enough (score_helpers in mp_plan.h), further workgroups work out the
+// logits of ALL fine clusters of a unit, and their exponentials, while its own workgroup is busy with the coarse level
+// (early_logits).  They hand them over in global memory, past the L2 slices, which not all workgroups share: stored and loaded at
+// device scope, and each helper counts itself in once its stores have arrived.  The unit's workgroup looks at the count when
+// its candidates are known: if all helpers are done it loads 64 bytes a candidate (four heads) instead of the 256-byte row, its product
+// and its exponentials, else it works the level out for itself -- it does not wait for workgroups that may not have
+// started, so no order of dispatch is relied on, and the bits are the same either way.  Fine level of 256 candidates, 4 heads, up to the
+// exponentials 11.7k -> 6.7k cycles, of 390, 8 heads 24.7k -> 11.1k; whole step, 8 units of 1024 clusters 27.4 -> 25.4 us, 24 of
+// 1563 with 8 heads 47.3 -> 41.3.  In place of the shadow workgroup there.
+//
 // Outputs for the value pass: the flat list of stored rows of the selected clusters' keys, and one
 // "centroid term" entry (value-centroid row + ready-made logits) per cluster that stays behind at
 // either level (unpromising coarse clusters, unselected fine candidates).
@@ -78,6 +88,7 @@ struct Scratch {
     double bw[kWaves][8];             // ... the same sum by wave (register path: bs is its column sums)
     uint32_t far[2];                  // register path, per level: some logit needs a shift
     uint32_t tiny;                    // register path: some score left the range of a double
+    uint32_t early;                   // the helpers' logits are there
     // extremes of the keys, token total, "some score too small" flag and boundary-list length of the
     // level in progress, maintained with LDS atomics
     unsigned long long key_min, key_max;
@@ -1075,6 +1086,7 @@ __device__ __forceinline__ void fine_epilogue(const ScoreParams& p, const Arrays
 // unit), the chain of dependent instructions 22k, the expansion of 8192 row numbers 4k.
 // ================================================================================================
 constexpr int kFastChunks = 2;
+constexpr int kEarlyLooks = 4;        // further times the helpers' count is looked at (a trip each) before the level is worked out without them
 constexpr double kNoShift = 500.0;    // largest |logit| that is exponentiated without a shift
 constexpr int kRounds = 4;
 
@@ -1111,15 +1123,26 @@ __device__ __forceinline__ void for_rounds(F f)
     f(std::integral_constant<int, 3>{});
 }
 
+// What is handed from one workgroup to another inside a launch goes past the caches that they do not share.
+__device__ __forceinline__ double load_handed_over(const double* p)
+{
+    return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void hand_over(double* p, double v)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Scores and selection of one level (see score_level for the definitions); `behind`: the normaliser also covers
 // what the coarse level left behind (S.bm / S.bw).  `quiet`: store nothing in global memory, and ask for the
 // rows last round first (shadow workgroup).  `meanwhile` runs once the rows have been asked for.  Returns 1 for
 // linear-domain keys, 0 for logarithmic ones.
-template <int G, typename Meanwhile>
+template <int G, bool kHelped, typename Meanwhile>
 __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Scratch& S, const LevelTables& T, int n, int u, bool use_ids,
                                           bool coarse, bool behind, bool q_pending, const uint16_t (&qv)[(G + 3) / 4], bool quiet,
-                                          FastLevel<G>& st, Meanwhile meanwhile)
+                                          const double* handed, FastLevel<G>& st, Meanwhile meanwhile)
 {
+    const double* early = kHelped ? handed : nullptr;
     constexpr int GH = (G + 3) / 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 3, quad = lane >> 2;
@@ -1163,7 +1186,7 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
 #pragma unroll
     for (int i = 0; i < kRounds; ++i) {
         const int t = quiet ? kRounds - 1 - i : i;
-        if (t < R0) {
+        if (t < R0 && !early) {
             if (t == 0) request(0, 0, raw[0]);
             if (t == 1) request(0, 1, raw[1]);
             if (t == 2) request(0, 2, raw[2]);
@@ -1192,6 +1215,39 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
 
     // ---------------- logits ----------------
     bool far = false;
+    if (early) {
+        // (worked out by the helpers; every load on its way before the first is looked at)
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int nc = chunk_entries(n, c), R = chunk_rounds(n, c);
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) st.l[c][t][hg] = st.e[c][t][hg] = 0.0;
+                if (t < R) {
+                    const int x = min(wave * 16 * R + quad * R + t, nc - 1);
+                    const double* at = early + (long long)A.ids[c * kThreads + x] * (8 * GH) + j;
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) {
+                        st.l[c][t][hg] = load_handed_over(at + 4 * hg);
+                        st.e[c][t][hg] = load_handed_over(at + 4 * (GH + hg));
+                    }
+                }
+            });
+        }
+#pragma unroll
+        for (int c = 0; c < kFastChunks; ++c) {
+            const int R = chunk_rounds(n, c);
+            for_rounds([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t < R) {
+                    const bool part = quad_lane<t>(st.w[c]) != 0;
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) far |= part && !(fabs(st.l[c][t][hg]) <= kNoShift);
+                }
+            });
+        }
+    } else
 #pragma unroll
     for (int c = 0; c < kFastChunks; ++c) {
         const int R = chunk_rounds(n, c), Rn = c + 1 < kFastChunks ? chunk_rounds(n, c + 1) : 0;
@@ -1242,13 +1298,15 @@ __device__ __forceinline__ int fast_level(const ScoreParams& p, const Lds& L, Sc
             const int R = chunk_rounds(n, c);
             for_rounds([&](auto tc) {
                 constexpr int t = decltype(tc)::value;
+                if (t >= R) {
 #pragma unroll
-                for (int hg = 0; hg < GH; ++hg) st.e[c][t][hg] = 0.0;
-                if (t < R) {
+                    for (int hg = 0; hg < GH; ++hg) st.e[c][t][hg] = 0.0;
+                } else {
                     const uint32_t w = quad_lane<t>(st.w[c]);
 #pragma unroll
                     for (int hg = 0; hg < GH; ++hg) {
-                        const double x = exp_shifted(st.l[c][t][hg] - st.M[hg]);     // (an entry that takes no part: not used)
+                        // (an entry that takes no part: not used; a helper's e^l has no shift)
+                        const double x = early && trip == 0 ? st.e[c][t][hg] : exp_shifted(st.l[c][t][hg] - st.M[hg]);
                         st.e[c][t][hg] = w ? x : 0.0;
                         sw[hg] += (double)w * st.e[c][t][hg];
                     }
@@ -1715,29 +1773,101 @@ __device__ __forceinline__ void touch_rows(const ScoreParams& p, const int32_t* 
     if (x == 0xfff1fff2u && p.U < 0) p.counters[4 * u] = 0;
 }
 
+// Helper workgroup `share` of `shares` of a unit: the logits of its part of all fine clusters, by the very instructions of
+// fast_level, and their exponentials without a shift (fast_level does not look at those of a level that needs one).
+template <int G>
+__device__ __forceinline__ void early_logits(const ScoreParams& p, double* qB, const uint16_t* rows, int n, int share, int shares, int u,
+                                             const uint16_t (&qv)[(G + 3) / 4])
+{
+    constexpr int GH = (G + 3) / 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 3, quad = lane >> 2;
+    const int kA = lane >> 4, qA = 4 * (lane & 3) + ((lane >> 2) & 3), bsel = kA * 4 + j;
+    const int per = (n + shares - 1) / shares, a = share * per, b = min(a + per, n);
+    uint4 raw[kRounds][4];
+    auto request = [&](int x0, uint4 (&r)[4]) {
+        const uint4* kp = reinterpret_cast<const uint4*>(rows + (long long)min(x0 + qA, n - 1) * kHeadDim) + kA;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = kp[4 * k];
+    };
+    const int first = a + wave * 16;
+#pragma unroll
+    for (int t = 0; t < kRounds; ++t)
+        if (first + t * 16 * kWaves < b) request(first + t * 16 * kWaves, raw[t]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int hg = 0; hg < GH; ++hg) qB[tid + hg * kThreads] = query_operand<G>(qv[hg], hg, tid);
+    phase_sync<true>();
+    double* out = p.early + (long long)u * p.early_stride * (8 * GH) + j;
+    const double scale = p.scale;
+#pragma unroll 1
+    for (int x0 = first; x0 < b; x0 += kRounds * 16 * kWaves) {
+        for_rounds([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            const int xt = x0 + t * 16 * kWaves;
+            if (xt < b) {
+                double acc[GH];
+#pragma unroll
+                for (int hg = 0; hg < GH; ++hg) acc[hg] = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t w4[4] = {raw[t][k].x, raw[t][k].y, raw[t][k].z, raw[t][k].w};
+#pragma unroll
+                    for (int d = 0; d < 8; ++d) {
+                        const double v = (double)((d & 1) ? bf16hi_to_f32(w4[d >> 1]) : bf16lo_to_f32(w4[d >> 1]));
+#pragma unroll
+                        for (int hg = 0; hg < GH; ++hg)
+                            acc[hg] = __builtin_amdgcn_mfma_f64_4x4x4f64(v, qB[(hg * 32 + 8 * k + d) * 16 + bsel], acc[hg], 0, 0, 0);
+                    }
+                }
+                if (xt + kRounds * 16 * kWaves < b) request(xt + kRounds * 16 * kWaves, raw[t]);
+                if (xt + quad < b) {
+                    double* at = out + (long long)(xt + quad) * (8 * GH);
+#pragma unroll
+                    for (int hg = 0; hg < GH; ++hg) {
+                        const double l = acc[hg] * scale;
+                        hand_over(at + 4 * hg, l);
+                        hand_over(at + 4 * (GH + hg), exp_shifted(l));
+                    }
+                }
+            }
+        });
+    }
+    // every wave's stores have arrived before the workgroup counts itself in
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) __hip_atomic_fetch_add(p.early_done + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // What the first level's requests need, as scalars: they are in registers when a wave starts (see the build flags), while the
 // other arguments span several cache lines of a segment no one has read yet.  So the query and the first level's rows are
 // asked for at once, and the rest of the arguments, one request for each line, while those travel.  Together with a query
 // that nothing waits for in front of the rows: one level of 64 clusters, 1 unit: step 15.8 -> 15.6 us; 8 units x 4096 keys
 // 27.6 -> 27.2; 32 units x 4096, 5 heads 41.1 -> 39.7; 24 units, 8 heads 48.0 -> 47.2.
 // first_row: first row of the level in the unit's tables, 0 where there is no coarse level.
-template <int G>
+// kHelped: the launch may have helpers (a kernel of its own: in the other one the code for it costs 0.2 to 0.4 us a launch).
+template <int G, bool kHelped>
 __global__ __launch_bounds__(kThreads) void score_select_kernel(const uint16_t* q, const uint16_t* Kc, const int32_t* N,
                                                                 const int32_t* first_start, int U, int tab_rows, int first_row,
-                                                                int n_first, int first_stride, int lds_cap, const ScoreParams p)
+                                                                int n_first, int first_stride, int lds_cap, int helpers, int n_fine,
+                                                                const ScoreParams p)
 {
     constexpr int GH = (G + 3) / 4;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Scratch& S = *reinterpret_cast<Scratch*>(smem_raw);
     const Lds L = carve_lds<G>(smem_raw + align16(sizeof(Scratch)), lds_cap);
     const int u = blockIdx.x % U, tid = threadIdx.x;
-    const bool shadow = blockIdx.x >= (unsigned)U;     // second workgroup of the unit: warms the shared L2, stores nothing
+    // second workgroup of the unit: warms the shared L2, stores nothing (or, where there are helpers, it is one of them)
+    const bool shadow = blockIdx.x >= (unsigned)U;
     const long long tables = (long long)u * tab_rows + first_row;
     const LevelTables first{Kc + tables * kHeadDim, N + tables, first_start + (long long)u * first_stride};
 
     uint16_t qv[GH];    // this thread's elements of the query operand (one per head group; converted once they are needed)
 #pragma unroll
     for (int hg = 0; hg < GH; ++hg) qv[hg] = query_operand_element<G>(q, u, hg, tid);
+    if (kHelped && shadow) {
+        early_logits<G>(p, L.qB, Kc + (long long)u * tab_rows * kHeadDim, n_fine, (int)blockIdx.x / U - 1, helpers, u, qv);
+        return;
+    }
     // the step's new rows go to their place in the tail buffers: asked for here, stored at the end
     uint4 app = make_uint4(0, 0, 0, 0);
     bool appends = false;
@@ -1752,13 +1882,20 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const uint16_t* 
     uint32_t n_terms = 0;
     int n_f = n_first;
     const bool coarse_fast = n_first <= lds_cap;
+    int done = 0;
     FastLevel<G> fc;
     int slot_c[kFastChunks];
     if (two) {
         if (coarse_fast) {
-            const int lin = fast_level<G>(p, L, S, first, n_first, u, false, true, false, true, qv, shadow, fc, arguments);
+            const int lin = fast_level<G, false>(p, L, S, first, n_first, u, false, true, false, true, qv, shadow, nullptr, fc, arguments);
             if (tid == 0 && !shadow) p.key_mode[2 * u] = lin;
+            auto look = [&] { return __hip_atomic_load(p.early_done + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            if (kHelped && tid == 0) done = look();
             fast_candidates<G>(p, L, S, sc, fc, u, shadow, n_f, n_terms, slot_c);
+            if (kHelped && tid == 0) {
+                for (int i = 0; i < kEarlyLooks && done < helpers; ++i) done = look();
+                S.early = done >= helpers;
+            }
         } else {
             // (a shadow workgroup would race with the first one on the global working arrays: it leaves)
             if (shadow) return;
@@ -1797,7 +1934,8 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const uint16_t* 
             const long long t = (long long)u * tab_rows;
             fine = LevelTables{Kc + t * kHeadDim, N + t, p.fstart + (long long)u * p.fstart_stride};
         }
-        const int lin = fast_level<G>(p, L, S, fine, n_f, u, two, false, two, !two, qv, false, ff_state, coarse_terms);
+        const int lin = fast_level<G, kHelped>(p, L, S, fine, n_f, u, two, false, two, !two, qv, false,
+                                      kHelped && coarse_fast && S.early ? p.early + (long long)u * p.early_stride * (8 * GH) : nullptr, ff_state, coarse_terms);
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
         fast_epilogue<G>(p, L, S, sc, ff_state, u, n_f, two, n_terms);
     } else {
@@ -1818,6 +1956,8 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(const uint16_t* 
         if (tid == 0) p.key_mode[2 * u + 1] = lin;
         fine_epilogue<G>(p, Ag, S, sc, u, n_f, two, n_terms);
     }
+    // (whether or not they were waited for: when the last of them is done the count is zero again)
+    if (kHelped && tid == 0) __hip_atomic_fetch_add(p.early_done + u, -helpers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (appends)
         reinterpret_cast<uint4*>(p.app_dst[tid >> 4])[((long long)u * p.app_dst_rows + p.app_row) * 16 + (tid & 15)] = app;
 }
@@ -1831,21 +1971,21 @@ size_t score_smem_bytes(int G, int lds_cap)
            (size_t)lds_cap * (8 + 3 * 4) + 32;
 }
 
-template <int G>
+template <int G, bool kHelped>
 static hipError_t launch_score_g(const ScoreParams& p, int copies, hipStream_t s)
 {
     static size_t configured = 48 * 1024;
     const size_t smem = score_smem_bytes(G, p.lds_cap);
     if (smem > configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_select_kernel<G>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_select_kernel<G, kHelped>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         configured = smem;
     }
     const bool two = p.levels == 2;
-    hipLaunchKernelGGL((score_select_kernel<G>), dim3(p.U * copies), dim3(kThreads), smem, s, p.q, p.Kc, p.N,
+    hipLaunchKernelGGL((score_select_kernel<G, kHelped>), dim3(p.U * copies), dim3(kThreads), smem, s, p.q, p.Kc, p.N,
                        two ? p.cstart : p.fstart, p.U, (int)p.tab_rows, two ? p.fcap : 0, two ? p.n_coarse : p.n_fine,
-                       (int)(two ? p.cstart_stride : p.fstart_stride), p.lds_cap, p);
+                       (int)(two ? p.cstart_stride : p.fstart_stride), p.lds_cap, p.helpers, p.n_fine, p);
     return hipGetLastError();
 }
 
@@ -1853,16 +1993,17 @@ hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, hipStr
 {
     // a shadow workgroup per unit where the chip has compute units to spare and the second workgroup
     // of unit u (block u + U) lands on the same L2 slice as the first (blocks go round the 8 slices)
-    const int copies = (p.U % 8 == 0 && 2 * p.U <= n_compute_units) ? 2 : 1;
+    const bool helped = p.levels == 2 && p.helpers > 0;
+    const int copies = helped ? 1 + p.helpers : (p.U % 8 == 0 && 2 * p.U <= n_compute_units) ? 2 : 1;
     switch (p.G) {
-        case 1: return launch_score_g<1>(p, copies, s);
-        case 2: return launch_score_g<2>(p, copies, s);
-        case 3: return launch_score_g<3>(p, copies, s);
-        case 4: return launch_score_g<4>(p, copies, s);
-        case 5: return launch_score_g<5>(p, copies, s);
-        case 6: return launch_score_g<6>(p, copies, s);
-        case 7: return launch_score_g<7>(p, copies, s);
-        case 8: return launch_score_g<8>(p, copies, s);
+        case 1: return helped ? launch_score_g<1, true>(p, copies, s) : launch_score_g<1, false>(p, copies, s);
+        case 2: return helped ? launch_score_g<2, true>(p, copies, s) : launch_score_g<2, false>(p, copies, s);
+        case 3: return helped ? launch_score_g<3, true>(p, copies, s) : launch_score_g<3, false>(p, copies, s);
+        case 4: return helped ? launch_score_g<4, true>(p, copies, s) : launch_score_g<4, false>(p, copies, s);
+        case 5: return helped ? launch_score_g<5, true>(p, copies, s) : launch_score_g<5, false>(p, copies, s);
+        case 6: return helped ? launch_score_g<6, true>(p, copies, s) : launch_score_g<6, false>(p, copies, s);
+        case 7: return helped ? launch_score_g<7, true>(p, copies, s) : launch_score_g<7, false>(p, copies, s);
+        case 8: return helped ? launch_score_g<8, true>(p, copies, s) : launch_score_g<8, false>(p, copies, s);
         default: return hipErrorInvalidValue;
     }
 }
