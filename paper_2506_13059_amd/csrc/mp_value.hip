@@ -662,11 +662,14 @@ __global__ __launch_bounds__(256) void value_pass_kernel(const ValuePassParams p
 // flight together, with an online rescale between batches.  What bounds it is the number of trips to memory in a
 // row, so the launch splits the chunks until a share is one batch (up to eight shares): 118 chunks of 8 heads x 64
 // units took 37 us with one share.
-template <int kSplits>
+// kBatch: as few as the chunks need, since one past the last is a repeated load and an exponential like any other, and at most
+// eight a share up to 64 chunks.  Whole step with sixteen a share (shares as needed) / now, us: 2 chunks, 128 units of 4 heads 121.6 / 120.9; 4
+// chunks, 1 unit 15.6 / 14.8; 5 chunks, 64 units of 8-bit rows 44.3 / 43.5; 8 chunks, 32 units of 5 heads 38.4 / 38.0, 8 units, dense 13.6 / 13.2;
+// 11 chunks, 24 units of 8 heads 41.2 / 41.0; 32 chunks, 8 units of 4 heads 25.05 / 24.7.
+template <int kSplits, int kBatch>
 __global__ __launch_bounds__(128 * kSplits) void merge_kernel(const float* __restrict__ partials, int chunks_per_unit, int G,
                                                               uint16_t* __restrict__ out, float* __restrict__ lse)
 {
-    constexpr int kBatch = 16;
     __shared__ float share[kSplits > 1 ? kSplits : 1][kSplits > 1 ? 130 : 1];
     const int uh = blockIdx.x;
     const int u = uh / G, h = uh - u * G;
@@ -772,10 +775,13 @@ hipError_t launch_merge(const float* partials, int n_units, int chunks_per_unit,
     auto go = [&](auto kernel, int splits) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(128 * splits), 0, stream, partials, chunks_per_unit, G, out, lse);
     };
-    if (chunks_per_unit <= 16) go(merge_kernel<1>, 1);
-    else if (chunks_per_unit <= 32) go(merge_kernel<2>, 2);
-    else if (chunks_per_unit <= 64) go(merge_kernel<4>, 4);
-    else go(merge_kernel<8>, 8);
+    if (chunks_per_unit <= 2) go(merge_kernel<1, 2>, 1);
+    else if (chunks_per_unit <= 4) go(merge_kernel<1, 4>, 1);
+    else if (chunks_per_unit <= 8) go(merge_kernel<1, 8>, 1);
+    else if (chunks_per_unit <= 16) go(merge_kernel<2, 8>, 2);
+    else if (chunks_per_unit <= 32) go(merge_kernel<4, 8>, 4);
+    else if (chunks_per_unit <= 64) go(merge_kernel<8, 8>, 8);
+    else go(merge_kernel<8, 16>, 8);
     return hipGetLastError();
 }
 
