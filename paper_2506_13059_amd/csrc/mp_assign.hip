@@ -292,6 +292,9 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
 constexpr int kRowTile = 16;
 constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
 constexpr int kNearCap = 256;                    // (a multiple of sixteen)
+constexpr int kResidentMaxK = 512;
+constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
+constexpr int kChangedTwiceK = 288;              // 2 x (288 x 268 + 1.6 K)
 constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
 
 typedef const __attribute__((address_space(3))) bf16x8_t lds_frag;
@@ -322,14 +325,15 @@ __device__ __forceinline__ void merge_pair(float& best, float& second, uint32_t&
     best = fmaxf(best, best2);
 }
 
-// The nearest of the centroids in LDS (rows at lds0, -|c|^2/2 behind k_cap rows) for the 64 points first, first + 1, ...
+// The nearest of the centroids in LDS (rows at lds0, -|c|^2/2 at ci0) for the 64 points first, first + 1, ...
 // (clamped to `last`) of Xu: lane = point.  `near`: its two best scores are closer than the margin.
 struct Nearest {
     int j;
     bool near;
-    float best;      // the best score (its lowest bits carry the slot)
+    float best, second;      // the best scores (their lowest bits carry the slot)
+    float m;                 // what margins grow with: the largest of |x|^2 and c2max
 };
-__device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int first, int last, uint32_t lds0, int k_cap,
+__device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int first, int last, uint32_t lds0, uint32_t ci0,
                                                     int ntiles, float c2max)
 {
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -387,7 +391,7 @@ __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int
         }
     };
     auto tiles = [&](int ta, int tb) {
-        uint32_t fr[4], ci_at = lds0 + (uint32_t)(k_cap * 256 + (ta * kRowTile + 4 * g) * 4);
+        uint32_t fr[4], ci_at = ci0 + (uint32_t)((ta * kRowTile + 4 * g) * 4);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
             fr[ks] = lds0 + (uint32_t)(ta * kRowTile * 256 + c * 256 + ((g ^ c) & 3) * 16 + ((64 * ks) ^ ((c >> 2) * 64)));
@@ -447,9 +451,9 @@ __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int
     }
     const uint32_t slot = __float_as_uint(best[0]) & kSlotMask;
     const int tile = (int)(slot >> 2) + (int)(from[0] >> 2) * kHalfTiles, row_g = (int)(from[0] & 3u);
-    const float margin = near_margin_of_best(fmaxf(n2[0], c2max), best[0]);
+    const float m = fmaxf(n2[0], c2max), margin = near_margin_of_best(m, best[0]);
     // (written so that a point without any comparable score also goes to the exact pass)
-    return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin), best[0]};
+    return Nearest{tile * kRowTile + 4 * row_g + (int)(slot & 3u), !(best[0] - second[0] > margin), best[0], second[0], m};
 }
 
 // One 16-byte piece of a centroid row (16 lanes per row) to its place in LDS; the lane with the first piece writes
@@ -502,8 +506,10 @@ __device__ __forceinline__ int lane_id()
 // more, then two or three distances of 2 us) and about 100 to 140 to the second's (1044 us without near ties, 1142 to 1183
 // with them).
 // known: `best` is what nearest_of_chunk found, at most 2^-17 of its size off, and need not be looked for again.
-__device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, int k_cap,
-                                             int k, float c2max, bool known, float best)
+// id_of: the cluster whose centroid stands at a place of the rows.
+template <typename IdOf>
+__device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
+                                             int k, float c2max, bool known, float best, IdOf id_of)
 {
     const int lane = lane_id(), c = lane & 15, g = lane >> 4;
     const int ntiles = (k + kRowTile - 1) / kRowTile;
@@ -523,7 +529,7 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
     n2 += __shfl_xor(n2, 32, 64);
     const uint32_t at = lds0 + (uint32_t)(c * 256 + ((g ^ c) & 3) * 16), turn = (uint32_t)((c >> 2) * 64);
     auto scores = [&](int tile) {
-        f32x4_t acc = *reinterpret_cast<lds_four*>((uintptr_t)(lds0 + (uint32_t)(k_cap * 256 + (tile * kRowTile + 4 * g) * 4)));
+        f32x4_t acc = *reinterpret_cast<lds_four*>((uintptr_t)(ci0 + (uint32_t)((tile * kRowTile + 4 * g) * 4)));
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const bf16x8_t f = *reinterpret_cast<lds_frag*>((uintptr_t)(at + (uint32_t)(tile * kRowTile * 256) + ((uint32_t)(64 * ks) ^ turn)));
@@ -566,7 +572,8 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
                 mask &= mask - 1;
                 const int j = (t0 + (e >> 2)) * kRowTile + 4 * g + (e & 3);
                 const double d = exact_distance_lds(xrow, rows_lds, j);
-                if (d < bd) { bd = d; bj = j; }
+                const int id = id_of(j);
+                if (d < bd || (d == bd && id < bj)) { bd = d; bj = id; }
             }
         }
     }
@@ -579,6 +586,15 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
     return bj;
 }
 
+// The chunk a wave takes next: the first that no wave has, `first` the one behind those the waves start with.  (In turn, the waves of a
+// workgroup came to the barrier behind the chunks up to 40 us apart.)
+__device__ __forceinline__ int next_chunk(int* ticket, int first)
+{
+    int t = 0;
+    if (lane_id() == 0) t = atomicAdd(ticket, 1);
+    return first + __builtin_amdgcn_readfirstlane(t);
+}
+
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                                     const int32_t* __restrict__ blocks,
@@ -586,13 +602,13 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
                                                                     int32_t* __restrict__ assign, long long assign_stride,
                                                                     int32_t* __restrict__ amb_list, long long list_stride,
                                                                     int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap,
-                                                                    const MoveMarks mv)
+                                                                    const MoveMarks mv, const AssignState st)
 {
     extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
     __shared__ float wave_c2max[kW];
     __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them,
     __shared__ float near_best[kNearCap];                         // and their best scores
-    __shared__ int near_n;
+    __shared__ int near_n, ticket;
     const int u = blockIdx.z, b = blockIdx.y;
     // (this kernel leaves the counters of the other one alone; the next assignment step finds them zero all the same)
     if (b == 0 && blockIdx.x == 0)
@@ -628,7 +644,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     }
     c2max = wave_max_f32(c2max);
     if (lane == 0) wave_c2max[wave] = c2max;
-    if (tid == 0) near_n = 0;
+    if (tid == 0) near_n = ticket = 0;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
@@ -639,16 +655,18 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
 #pragma unroll 1
-    for (int chunk = chunk0 + wave; chunk < chunk1; chunk += kW) {
+    for (int chunk = chunk0 + wave; chunk < chunk1; chunk = next_chunk(&ticket, chunk0 + kW)) {
         const int t = x0 + chunk * 64 + lane;
         int old = 0;
         if (mv.marks) old = old_u[min(t, x1 - 1)];
-        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, k_cap, ntiles, c2max);
+        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, lds0 + k_cap * 256, ntiles, c2max);
         if (mv.marks) {
             const unsigned long long marked = __ballot(t < x1 && (r.near || old != k0 + r.j));
             if (lane == 0) marks[chunk] = marked;
         }
         if (t < x1) {
+            // (of a near tie the winner's score is no smaller than the best one, but for their errors, and no other is larger)
+            if (st.scores) st.scores[u * st.stride + t] = make_float2(r.best, r.near ? r.best : r.second);
             if (r.near) {
                 const int pos = atomicAdd(&near_n, 1);
                 if (pos < kNearCap) {
@@ -668,23 +686,233 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
     for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
         const int e = min(e0 + (lane_id() & 15), n - 1);
         const int t = e < kNearCap ? near_list[e] : more[e];
-        const int j = nearest_exact(Xu, t, rows_lds, lds0, k_cap, k1 - k0, c2max, e0 < kNearCap, e < kNearCap ? near_best[e] : 0.f);
+        const int j = nearest_exact(Xu, t, rows_lds, lds0, lds0 + k_cap * 256, k1 - k0, c2max, e0 < kNearCap, e < kNearCap ? near_best[e] : 0.f,
+                                    [](int place) { return place; });
         if (lane_id() < 16) assign_u[t] = k0 + j;
     }
 }
 
-constexpr int kResidentMaxK = 512;
-constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
-template <int kW>
-hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts, int max_k,
-                           int U, const uint16_t* C, long long c_unit_rows, int32_t* assign, long long assign_stride,
-                           int32_t* amb_list, long long list_stride, int32_t* cnt_next, int cnt_stride, const MoveMarks& mv,
-                           hipStream_t s)
+// The same step where the one before has left the scores it found (AssignState): a centroid that has not changed since scores
+// what it did, so the points have to be compared with the changed ones only.  Of a point there is the score of its cluster's
+// centroid, s, and a bound on the scores of all others, r >= what any of them scored.  With b the best and b2 the second best score
+// among the changed centroids (its own among them if that changed):
+//   - b is ahead of b2 and of r (and of s, if its own has not changed) by more than the margin: b's centroid is the one;
+//   - its own has not changed and s is ahead of b by more than the margin: it keeps its cluster, which won the comparison with
+//     the unchanged ones before, exactly where that was close;
+//   - otherwise it goes onto a list and is compared with all centroids afterwards (nearest_of_all).
+// The margins are those of two scores of one step (mp_margin.h): an older score has the error of its own centroid, which is still
+// one of the block, and the largest |c|^2 is taken over all of them.
+// 2048 blocks of 8192 keys, 256 centroids: 80 to 16 per cent of the centroids change in iterations 4 to 10, 3 to 0.5 per
+// cent of the points go onto the list, and a launch takes 1.2 to 0.99 ms (compared with all: 1.13 to 1.29, by the clock it gets).  Bound by
+// the keys it reads all the same: 0.81 ms without a single product, 0.93 with the points' ids and scores.  32 such blocks (of which 30 to 1 per cent
+// of the centroids change): 34 to 18.5 us, all 33; there a launch without products takes 16, and what a workgroup adds is the chain
+// of a point on its list, 10 us.
+// The changed centroids stand in front; the others' -|c|^2/2 is one that never wins while the points are compared with the changed
+// ones, tile by tile of sixteen.
+struct Decided {
+    int id;
+    float best, other;       // as in AssignState
+};
+template <typename IdOf>
+__device__ __forceinline__ Decided nearest_of_all(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
+                                                  int k, float c2max, IdOf id_of)
 {
-    static bool configured = false;
+    const int lane = lane_id(), c = lane & 15, g = lane >> 4;
+    const int ntiles = (k + kRowTile - 1) / kRowTile;
+    const uint4* xrow = reinterpret_cast<const uint4*>(Xu + (long long)t * 256);
+    bf16x8_t x[4];
+    float n2 = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const uint4 w = xrow[4 * ks + g];
+        x[ks] = __builtin_bit_cast(bf16x8_t, w);
+        n2 = dot2_bf16(w.x, w.x, n2);
+        n2 = dot2_bf16(w.y, w.y, n2);
+        n2 = dot2_bf16(w.z, w.z, n2);
+        n2 = dot2_bf16(w.w, w.w, n2);
+    }
+    n2 += __shfl_xor(n2, 16, 64);
+    n2 += __shfl_xor(n2, 32, 64);
+    const uint32_t at = lds0 + (uint32_t)(c * 256 + ((g ^ c) & 3) * 16), turn = (uint32_t)((c >> 2) * 64);
+    float best = -INFINITY, second = -INFINITY;
+    int place = 0;
+    for (int tile = 0; tile < ntiles; tile += 4) {
+        f32x4_t s[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int tl = min(tile + r, ntiles - 1);
+            s[r] = *reinterpret_cast<lds_four*>((uintptr_t)(ci0 + (uint32_t)((tl * kRowTile + 4 * g) * 4)));
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8_t f = *reinterpret_cast<lds_frag*>((uintptr_t)(at + (uint32_t)(tl * kRowTile * 256) + ((uint32_t)(64 * ks) ^ turn)));
+                s[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, x[ks], s[r], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (tile + r >= ntiles) continue;            // (uniform)
+                second = fmaxf(second, fminf(best, s[r][i]));
+                place = s[r][i] > best ? (tile + r) * kRowTile + 4 * g + i : place;
+                best = fmaxf(best, s[r][i]);
+            }
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+        const float ob = __shfl_xor(best, off, 64), os = __shfl_xor(second, off, 64);
+        const int op = __shfl_xor(place, off, 64);
+        second = fmaxf(fmaxf(second, os), fminf(best, ob));
+        place = ob > best ? op : place;                      // (equal ones are nearer than the margin)
+        best = fmaxf(best, ob);
+    }
+    const bool near = !(best - second > near_margin(fmaxf(n2, c2max)) + fabsf(best) * (1.0f / 65536.0f));
+    Decided d{id_of(min(place, k - 1)), best, near ? best : second};
+    if (__any(near)) {
+        const int id = nearest_exact(Xu, t, rows_lds, lds0, ci0, k, c2max, true, best, id_of);
+        if (near) d.id = id;
+    }
+    return d;
+}
+
+template <int kW>
+__global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
+                                                                   const int32_t* __restrict__ blocks,
+                                                                   const uint16_t* __restrict__ C, long long c_unit_rows,
+                                                                   int32_t* __restrict__ assign, long long assign_stride,
+                                                                   int32_t* __restrict__ amb_list, long long list_stride,
+                                                                   int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap,
+                                                                   const MoveMarks mv, const AssignState st)
+{
+    extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], [k_cap] -|c|^2/2, the same for changed ones only,
+    float* c_init = reinterpret_cast<float*>(rows_lds + k_cap * 256);
+    float* c_now = c_init + k_cap;
+    uint16_t* ids = reinterpret_cast<uint16_t*>(c_now + k_cap);   // [k_cap] the centroid at a place,
+    uint16_t* places = ids + k_cap;                               // [k_cap] the place of a centroid
+    __shared__ float wave_c2max[kW];
+    __shared__ int wave_changed[kW];
+    __shared__ int32_t list[kNearCap];                            // points to be compared with all centroids, the first of them
+    __shared__ int list_n, ticket;
+    const int u = blockIdx.z, b = blockIdx.y;
+    // (the counters of the other kernels, as in assign_resident_kernel)
+    if (b == 0 && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < cnt_stride; i += 64 * kW) cnt_next[u * cnt_stride + i] = 0;
+    const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2];
+    const int k = min(blocks[4 * b + 3] - k0, k_cap);             // (the launch guarantees the block has no more)
+    const int all_chunks = (x1 - x0 + 63) / 64;
+    const int per = (all_chunks + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int chunk0 = (int)blockIdx.x * per, chunk1 = min(chunk0 + per, all_chunks);
+    if (chunk0 >= chunk1) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) mv.moved_now[u * cnt_stride + b] = 0;
+    if (unchanged(mv, u, b, cnt_stride)) {
+        keep_chunks(mv, u, b, x0, x1, chunk0, chunk1, assign, assign_stride);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);
+
+    // ---- the block's centroids: asked for in the order of their ids, put in their places once it is known which have changed ----
+    const int ntiles = (k + kRowTile - 1) / kRowTile;
+    constexpr int kPieces = (kW == 8 ? kChangedTwiceK : kResidentMaxK) * 16 / (64 * kW);      // 16-byte pieces of a thread
+    uint4 w[kPieces];
+    const uint4* Cu = reinterpret_cast<const uint4*>(C + ((long long)u * c_unit_rows + k0) * kHeadDim);
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int e = tid + i * 64 * kW;
+        if (i * 64 * kW < k * 16) w[i] = Cu[min(e, k * 16 - 1)];
+    }
+    const bool mine = tid < k && st.changed[u * st.changed_stride + k0 + tid] != 0;
+    const unsigned long long which = __ballot(mine);
+    if (lane == 0) wave_changed[wave] = __popcll(which);
+    if (tid == 0) list_n = ticket = 0;
+    __syncthreads();
+    int n_changed = 0, before = 0;
+#pragma unroll
+    for (int i = 0; i < kW; ++i) {
+        const int c = wave_changed[i];
+        before += i < wave ? c : 0;
+        n_changed += c;
+    }
+    if (tid < k) {
+        const int rank = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(which >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)which, 0u));
+        const int place = mine ? rank : n_changed + tid - rank;
+        ids[place] = (uint16_t)tid;
+        places[tid] = (uint16_t)place;
+    }
+    __syncthreads();
+    float c2max = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int e = tid + i * 64 * kW, row = e >> 4, seg = e & 15;
+        if (row < ntiles * kRowTile) {
+            const bool exists = row < k;
+            const int place = exists ? places[row] : row;
+            const float s = place_centroid(rows_lds, c_init, place, seg, exists ? w[i] : make_uint4(0, 0, 0, 0), exists);
+            if (seg == 0) c_now[place] = place < n_changed ? -0.5f * s : kNoCentroid;
+            c2max = fmaxf(c2max, s);
+        }
+    }
+    c2max = wave_max_f32(c2max);
+    if (lane == 0) wave_c2max[wave] = c2max;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kW; ++i) c2max = fmaxf(c2max, wave_c2max[i]);
+
+    int32_t* assign_u = assign + u * assign_stride;
+    const int32_t* old_u = mv.old_ids + u * assign_stride;
+    float2* scores_u = st.scores + u * st.stride;
+    unsigned long long* marks = mv.marks + u * mv.stride + first_mark(x0, b);
+    int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
+    const uint32_t ci0 = lds0 + (uint32_t)(k_cap * 256);
+    const int tiles_changed = (n_changed + kRowTile - 1) / kRowTile;
+#pragma unroll 1
+    for (int chunk = chunk0 + wave; chunk < chunk1; chunk = next_chunk(&ticket, chunk0 + kW)) {
+        const int t = x0 + chunk * 64 + lane, tc = min(t, x1 - 1);
+        const int old = old_u[tc];
+        const float2 was = scores_u[tc];
+        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, ci0 + (uint32_t)(k_cap * 4), tiles_changed, c2max);
+        const bool own_changed = (int)places[old - k0] < n_changed;
+        const float others = fmaxf(own_changed ? was.y : fmaxf(was.x, was.y), r.second);
+        const bool won = r.best - others > near_margin_of_best(r.m, r.best);
+        const bool kept = !won && !own_changed && was.x - r.best > near_margin_of_best(r.m, was.x);
+        const int id = won ? k0 + ids[r.j] : old;
+        const unsigned long long marked = __ballot(t < x1 && (id != old || !(won || kept)));
+        if (lane == 0) marks[chunk] = marked;
+        if (t < x1) {
+            if (won || kept) {
+                assign_u[t] = id;
+                if (won || r.best > was.y) scores_u[t] = won ? make_float2(r.best, others) : make_float2(was.x, r.best);
+            } else {
+                const int pos = atomicAdd(&list_n, 1);
+                if (pos < kNearCap) list[pos] = t;
+                else more[pos] = t;
+            }
+        }
+    }
+    __syncthreads();
+    const int n = list_n;
+    for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
+        const int e = min(e0 + (lane_id() & 15), n - 1);
+        const int t = e < kNearCap ? list[e] : more[e];
+        const Decided d = nearest_of_all(Xu, t, rows_lds, lds0, ci0, k, c2max, [&](int place) { return (int)ids[place]; });
+        if (lane_id() < 16) {
+            assign_u[t] = k0 + d.id;
+            scores_u[t] = make_float2(d.best, d.other);
+        }
+    }
+}
+
+template <typename Kernel>
+hipError_t launch_resident(Kernel kernel, int waves, int bytes_per_row, bool& configured, const uint16_t* X, long long x_unit_rows,
+                           const int32_t* blocks_dev, int nb, int max_pts, int max_k, int U, const uint16_t* C, long long c_unit_rows,
+                           int32_t* assign, long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* cnt_next,
+                           int cnt_stride, const MoveMarks& mv, const AssignState& st, hipStream_t s)
+{
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&assign_resident_kernel<kW>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kResidentMaxK * 260);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           kResidentMaxK * bytes_per_row);
         if (e != hipSuccess) return e;
         configured = true;
     }
@@ -694,13 +922,13 @@ hipError_t launch_resident(const uint16_t* X, long long x_unit_rows, const int32
     // chip is idle otherwise, and its points' exact decisions are shared by all waves.  (A chunk a wave at least: 8192 points
     // x 512 centroids, 1 / 8 units, 338 / 456 us a build of five iterations against 264 / 397; the same with all keys
     // equal, every point decided exactly, 21.4 / 22.1 ms against 4.9 / 8.2.)
-    constexpr long long kSlots = 4096 / kW;                      // sixteen waves on each of 256 compute units
+    const long long kSlots = 4096 / waves;                       // sixteen waves on each of 256 compute units
     const long long groups = (long long)nb * U;
     const int chunks = (max_pts + 63) / 64;
     const long long want = groups <= kSlots ? kSlots / groups : (4 * kSlots + groups - 1) / groups;
     const int gx = (int)std::max<long long>(1, std::min<long long>(chunks, want));
-    hipLaunchKernelGGL(assign_resident_kernel<kW>, dim3(gx, nb, U), dim3(64 * kW), (size_t)k_cap * 260, s, X, x_unit_rows,
-                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, cnt_next, cnt_stride, k_cap, mv);
+    hipLaunchKernelGGL(kernel, dim3(gx, nb, U), dim3(64 * waves), (size_t)k_cap * bytes_per_row, s, X, x_unit_rows,
+                       blocks_dev, C, c_unit_rows, assign, assign_stride, amb_list, list_stride, cnt_next, cnt_stride, k_cap, mv, st);
     return hipGetLastError();
 }
 
@@ -760,7 +988,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
         for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[it & 1][w]);
         // ---- nearest centroid of every point ----
         for (int ch = wave; ch < chunks; ch += kW) {
-            const Nearest r = nearest_of_chunk(Xu, x0 + ch * 64, x0 + n - 1, lds0, p.k_cap, ntiles, c2max);
+            const Nearest r = nearest_of_chunk(Xu, x0 + ch * 64, x0 + n - 1, lds0, lds0 + p.k_cap * 256, ntiles, c2max);
             const int t = ch * 64 + lane;
             if (t < n) {
                 const uint16_t j = (uint16_t)min(r.j, k - 1);
@@ -776,7 +1004,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
         // ---- near ties ----
         for (int e0 = wave * 16; e0 < near_n; e0 += kW * 16) {
             const int t = near_pts[min(e0 + (lane & 15), near_n - 1)];
-            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, p.k_cap, k, c2max, false, 0.f);
+            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, lds0 + p.k_cap * 256, k, c2max, false, 0.f, [](int place) { return place; });
             if (lane < 16 && (it == 0 || asg[t] != j)) {
                 asg[t] = (uint16_t)j;
                 moved = 1;
@@ -1072,18 +1300,21 @@ hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int ma
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,
                          long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* amb_cnt,
-                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, hipStream_t s)
+                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, const AssignState& st, hipStream_t s)
 {
     if (nb <= 0 || max_pts <= 0 || U <= 0) return hipSuccess;
     if (nb > cnt_stride || U > 65535) return hipErrorInvalidValue;
     const int n_chunks = (max_pts + kPtsPerWg - 1) / kPtsPerWg;
-    if (max_k > 0 && max_k <= kResidentMaxK && max_pts >= 1024) {
+    if (assign_is_resident(max_pts, max_k)) {
         // two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen
-        auto go = [&](auto launch) {
-            return launch(X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows, assign, assign_stride, amb_list,
-                          list_stride, amb_cnt_next, cnt_stride, mv, s);
+        static bool configured[4] = {};
+        auto go = [&](auto kernel, int waves, int bytes_per_row, bool& set) {
+            return launch_resident(kernel, waves, bytes_per_row, set, X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows,
+                                   assign, assign_stride, amb_list, list_stride, amb_cnt_next, cnt_stride, mv, st, s);
         };
-        return max_k <= kResidentTwiceK ? go(launch_resident<8>) : go(launch_resident<16>);
+        if (st.changed)
+            return max_k <= kChangedTwiceK ? go(assign_changed_kernel<8>, 8, 268, configured[0]) : go(assign_changed_kernel<16>, 16, 268, configured[1]);
+        return max_k <= kResidentTwiceK ? go(assign_resident_kernel<8>, 8, 260, configured[2]) : go(assign_resident_kernel<16>, 16, 260, configured[3]);
     }
     hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
                        c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, mv);

@@ -229,12 +229,12 @@ inline int32_t* amb_counters(mp_ctx* ctx, int which)
     return ctx->km_amb + (size_t)((ctx->amb_turn ^ which) & 1) * ctx->U * ctx->max_blocks;
 }
 
-mp_status launch_assign(mp_ctx* ctx, const Problem& pr, const MoveMarks& mv, hipStream_t s)
+mp_status launch_assign(mp_ctx* ctx, const Problem& pr, const MoveMarks& mv, const AssignState& st, hipStream_t s)
 {
     // the member-list array is free during the assignment step and holds the points of the exact pass
     MP_HIPC(mp::launch_assign(pr.X, pr.x_unit_rows, pr.blocks_dev, pr.nb, pr.max_pts, pr.max_k, ctx->U, pr.C, pr.c_unit_rows,
                               pr.assign, pr.assign_stride, pr.list, pr.list_stride, amb_counters(ctx, 0), amb_counters(ctx, 1),
-                              ctx->max_blocks, mv, s));
+                              ctx->max_blocks, mv, st, s));
     ctx->amb_turn ^= 1;
     return MP_OK;
 }
@@ -251,31 +251,37 @@ mp_status build_lists(mp_ctx* ctx, const Problem& pr, hipStream_t s)
 // Lloyd iterations: assign, centroid <- bf16(mean of members); empty keeps.  The first one builds member lists and sums the
 // members; with pr.sums the later ones move the sums by the points that changed cluster (a launch less, and the few
 // per cent of the points that move instead of all).  The last assignment ends in pr.assign.
-mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, hipStream_t s)
+// From iteration `settled` on only the centroids that the one before changed are looked at, where the blocks allow it.
+mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, int settled, hipStream_t s)
 {
     Problem now = pr;
+    if (!pr.sums || !assign_keeps_state(pr.max_pts, pr.max_k)) settled = iters;
+    auto state = [&](int it) {
+        const bool uses = it >= settled, leaves = it + 1 >= settled && it + 1 < iters;
+        return AssignState{uses || leaves ? ctx->km_scores : nullptr, ctx->Ncap, uses ? ctx->km_changed : nullptr, ctx->Fcap};
+    };
     for (int it = 0; it < iters; ++it) {
         const int32_t* before = now.assign;
         if (pr.sums) now.assign = (iters - 1 - it) % 2 ? pr.other_assign : pr.assign;
         if (pr.sums && it > 0) {
             auto moved = [&](int i) { return ctx->km_moved + (size_t)(i & 1) * ctx->U * ctx->max_blocks; };
             const MoveMarks marks{before, ctx->km_marks, marks_of(ctx->Ncap, ctx->max_blocks), it > 1 ? moved(it - 1) : nullptr, moved(it)};
-            MP_TRY(launch_assign(ctx, now, marks, s));
+            MP_TRY(launch_assign(ctx, now, marks, state(it), s));
             MoveMeans mv{};
             mv.X = pr.X; mv.x_unit_rows = pr.x_unit_rows; mv.blocks = pr.blocks_dev;
             mv.old_ids = before; mv.new_ids = now.assign; mv.ids_stride = pr.assign_stride;
             mv.marks = marks.marks; mv.marks_stride = marks.stride;
             mv.moved = marks.moved_now; mv.moved_stride = ctx->max_blocks;
             mv.C = pr.C; mv.c_unit_rows = pr.c_unit_rows; mv.count = pr.cnt; mv.count_stride = pr.cnt_stride;
-            mv.sum = pr.sums; mv.sum_unit_rows = pr.sum_unit_rows; mv.range = pr.range; mv.range_stride = pr.sum_unit_rows;
+            mv.sum = pr.sums; mv.sum_unit_rows = pr.sum_unit_rows; mv.range = pr.range; mv.range_stride = pr.sum_unit_rows; mv.changed = it + 1 >= settled && it + 1 < iters ? ctx->km_changed : nullptr;
             MP_HIPC(launch_move_means(mv, pr.nb, pr.max_k, ctx->U, s));
             continue;
         }
-        MP_TRY(launch_assign(ctx, now, MoveMarks{}, s));
+        MP_TRY(launch_assign(ctx, now, MoveMarks{}, state(it), s));
         MP_TRY(build_lists(ctx, now, s));
         MP_HIPC(launch_cluster_means(pr.X, pr.x_unit_rows, pr.list, pr.list_stride, pr.start, pr.cnt_stride + 1,
                                      pr.k_first, pr.k_total, ctx->U, pr.C, pr.c_unit_rows, 0, pr.C, pr.c_unit_rows,
-                                     pr.sums ? pr.cnt : nullptr, pr.cnt_stride, 0, pr.sums, pr.sum_unit_rows, iters > 1 ? pr.range : nullptr, s));
+                                     pr.sums ? pr.cnt : nullptr, pr.cnt_stride, 0, pr.sums, pr.sum_unit_rows, iters > 1 ? pr.range : nullptr, settled == 1 ? ctx->km_changed : nullptr, s));
     }
     return MP_OK;
 }
@@ -384,10 +390,10 @@ mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void
     if (!fine_keys_are_means)
         MP_HIPC(launch_cluster_means((const uint16_t*)Xk, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
                                      ctx->Kc, tab, 0, key_fallback ? ctx->Kc : nullptr, tab, nullptr, 0, 0,
-                                     two ? ctx->sumK : nullptr, ctx->Fcap, nullptr, s));
+                                     two ? ctx->sumK : nullptr, ctx->Fcap, nullptr, nullptr, s));
     MP_HIPC(launch_cluster_means((const uint16_t*)Xv, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
                                  ctx->Vc, tab, 0, nullptr, 0, ctx->Ncl, tab, 0, two ? ctx->sumV : nullptr, ctx->Fcap,
-                                 nullptr, s));
+                                 nullptr, nullptr, s));
     if (bytes)   // (8-bit keys are residuals from the fine key centroids, which are final only now)
         MP_HIPC(launch_gather_quantize_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, ids, ids_stride, ctx->Kc, tab, n_pts, U,
                                             ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, seq, ctx->n_rows + U, s));
@@ -446,7 +452,7 @@ mp_status coarse_and_finalize(mp_ctx* ctx, const Range& r, int coarse_iters, int
                                seed_f0 < 0 ? pc.blocks_dev : ctx->blocks_dev + 8, ctx->km_seed_c, Ccap1, pc.C, pc.c_unit_rows);
             MP_HIPC(hipGetLastError());
         }
-        MP_TRY(lloyd_iterations(ctx, pc, coarse_iters, s));
+        MP_TRY(lloyd_iterations(ctx, pc, coarse_iters, coarse_iters, s));
         // km_plist[0..kf) = fine ids of the range grouped by coarse cluster (ascending inside): new order
         hipLaunchKernelGGL(invert_perm_kernel, dim3(blocks_for(kf, 256), U), dim3(256), 0, s, ctx->km_plist, Fcap, 0, kf,
                            r.f0, ctx->km_newid, Fcap);
@@ -510,7 +516,7 @@ mp_status cluster_range(mp_ctx* ctx, const Range& r, int iters, hipStream_t s)
                        ctx->km_seed_f, (long long)ctx->Fcap, pf.C, pf.c_unit_rows);
     MP_HIPC(hipGetLastError());
     pf.sums = ctx->sumK; pf.sum_unit_rows = ctx->Fcap; pf.range = ctx->km_range; pf.other_assign = ctx->km_assign2;
-    MP_TRY(lloyd_iterations(ctx, pf, iters, s));
+    MP_TRY(lloyd_iterations(ctx, pf, iters, 3, s));      // (from seeds: the first two updates change nearly all centroids)
     return coarse_and_finalize(ctx, r, iters, r.c0, -1, iters > 0, max_kf, max_kc, s);
 }
 
@@ -720,7 +726,7 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     // ---- one-shot assignment of the appended tokens + running mean of the touched centroids ----
     MP_HIPC(mp::launch_assign(ctx->Kfb, (long long)ctx->FBcap, ctx->blocks_dev, 1, n_new, 0, U, ctx->km_Cf, Fcap,
                               ctx->km_assign, Ncap, ctx->km_list, Ncap, amb_counters(ctx, 0), amb_counters(ctx, 1),
-                              ctx->max_blocks, MoveMarks{}, s));
+                              ctx->max_blocks, MoveMarks{}, AssignState{}, s));
     ctx->amb_turn ^= 1;
     hipLaunchKernelGGL(running_mean_kernel, dim3((kf + 3) / 4, U), dim3(256), 0, s, ctx->Kfb, (long long)ctx->FBcap,
                        nb_old, nb, ctx->km_assign, Ncap, f0, f1, lb.f1, ctx->Ncl, ctx->tab_rows, ctx->km_Cf, Fcap);
@@ -732,7 +738,7 @@ mp_status update_clusters_impl(mp_ctx* ctx, const void* k_new, const void* k_new
     pf.assign = ctx->km_assign; pf.assign_stride = Ncap; pf.list = ctx->km_list; pf.list_stride = Ncap;
     pf.cnt = ctx->km_cnt; pf.start = ctx->km_start; pf.cnt_stride = ctx->tab_rows;
     pf.sums = ctx->sumK; pf.sum_unit_rows = ctx->Fcap; pf.range = ctx->km_range; pf.other_assign = ctx->km_assign2;
-    MP_TRY(lloyd_iterations(ctx, pf, refine_iters, s));
+    MP_TRY(lloyd_iterations(ctx, pf, refine_iters, 1, s));
     // ---- coarse level: stored coarse key centroids, plus seeds taken from the new fine centroids ----
     mp_status st = coarse_and_finalize(ctx, r, std::max(1, refine_iters), lb.c1, lb.f1, refine_iters > 0, max_kf, max_kc, s);
     if (st != MP_OK) return st;

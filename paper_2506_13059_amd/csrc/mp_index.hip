@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
                                                            long long fb_unit_rows, int32_t* __restrict__ count_out,
                                                            long long count_stride, int count_off,
                                                            double* __restrict__ sum_out, long long sum_unit_rows,
-                                                           uint32_t* __restrict__ range_out)
+                                                           uint32_t* __restrict__ range_out, uint32_t* __restrict__ changed_out)
 {
     const int u = blockIdx.y;
     const int f = k0 + blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -355,7 +355,14 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     } else {
         outw = 0u;
     }
-    reinterpret_cast<uint32_t*>(mean_out + ((long long)u * out_unit_rows + out_row0 + f) * kHeadDim)[lane] = outw;
+    uint32_t* row = reinterpret_cast<uint32_t*>(mean_out + ((long long)u * out_unit_rows + out_row0 + f) * kHeadDim) + lane;
+    if constexpr (kRange) {
+        if (changed_out) {                                   // (centroids that an iteration replaces)
+            const bool differs = __any(*row != outw);
+            if (lane == 0) changed_out[u * sum_unit_rows + f] = differs ? 1u : 0u;
+        }
+    }
+    *row = outw;
     if (count_out && lane == 0) count_out[u * count_stride + count_off + f] = n;
     if (sum_out) reinterpret_cast<double2*>(sum_out + ((long long)u * sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a0, a1);
 }
@@ -563,13 +570,13 @@ hipError_t launch_cluster_means(const uint16_t* X, long long x_unit_rows, const 
                                 const int32_t* start, long long start_stride, int k0, int k, int U,
                                 uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
                                 long long fb_unit_rows, int32_t* count_out, long long count_stride, int count_off,
-                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, hipStream_t s)
+                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, uint32_t* changed_out, hipStream_t s)
 {
     if (k <= k0) return hipSuccess;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((k - k0 + 3) / 4, U), dim3(256), 0, s, X, x_unit_rows, list, list_stride, start,
                            start_stride, k0, k, mean_out, out_unit_rows, out_row0, fallback, fb_unit_rows, count_out,
-                           count_stride, count_off, sum_out, sum_unit_rows, range_out);
+                           count_stride, count_off, sum_out, sum_unit_rows, range_out, changed_out);
         return hipGetLastError();
     };
     return range_out ? go(cluster_mean_kernel<true>) : go(cluster_mean_kernel<false>);

@@ -148,6 +148,20 @@ struct MoveMarks {
                                    // were, and so is the assignment.  (no array: they may have changed in any case)
     int32_t* moved_now;            // the same of this step, cleared here and set by launch_move_means
 };
+// What an assignment step leaves for the next one, which then has to look at the centroids that have changed only: per point, the
+// score of its cluster's centroid and a bound on the scores of all others (see assign_changed_kernel).
+struct AssignState {
+    float2* scores;                // [U, stride] by point; none: nothing is kept
+    long long stride;
+    const uint32_t* changed;       // [U, changed_stride] by cluster: did its centroid change since the step that left `scores`?
+    long long changed_stride;      // (no array: the step looks at all centroids)
+};
+// Blocks of at most max_pts points and max_k centroids: whether their centroids stay in LDS, and whether steps keep and use such
+// a state.  (In smaller blocks a step is a chain of latencies, and that with a state is no shorter: builds of five iterations, us,
+// without / with: 1500 points x 93 centroids, 6 blocks 186 / 193; 1024 x 32, 24 blocks 187 / 194; 2000 x 60, 1 block 139.5 / 143, 64
+// blocks 277 / 265; 8192 x 256, 1 block 194 / 177; 8192 x 512, 64 blocks 977 / 911.)
+constexpr bool assign_is_resident(int max_pts, int max_k) { return max_k > 0 && max_k <= 512 && max_pts >= 1024; }
+constexpr bool assign_keeps_state(int max_pts, int max_k) { return assign_is_resident(max_pts, max_k) && (long long)max_pts * max_k >= 1 << 20; }
 constexpr int first_mark(int x0, int b) { return (x0 >> 6) + b; }
 inline long long marks_of(long long points, int blocks) { return (points >> 6) + blocks + 1; }
 // ------------------------------------------------------------------------------------------------
@@ -163,7 +177,7 @@ inline long long marks_of(long long points, int blocks) { return (points >> 6) +
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,
                          int max_k, int U, const uint16_t* C, long long c_unit_rows, int32_t* assign,
                          long long assign_stride, int32_t* amb_list, long long list_stride, int32_t* amb_cnt,
-                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, hipStream_t s);
+                         int32_t* amb_cnt_next, int cnt_stride, const MoveMarks& mv, const AssignState& st, hipStream_t s);
 // The coarse level of a range of blocks in one launch: `iters` Lloyd iterations over the fine working centroids X of each
 // block, then the fine clusters in their new order.  blocks: int32 [nb][4] = {first fine id, end, first coarse id, end}.
 struct CoarseLevel {
@@ -217,12 +231,13 @@ hipError_t launch_gather_quantize_rows(const void* srcK, const void* srcV, long 
                                        int32_t* unusual, hipStream_t s);
 // mean_out row (out_row0 + id) = bf16(fp64 sum of the member rows in list order / count); sum_out (optional)
 // receives the fp64 sums themselves, row = id; range_out (optional) [U, sum_unit_rows] the exponent fields of a cluster's
-// largest magnitude (<< 16) and smallest nonzero one (subnormals count as 1; 255 where there is none).
+// largest magnitude (<< 16) and smallest nonzero one (subnormals count as 1; 255 where there is none); changed_out (optional,
+// with range_out, mean_out holding the rows of before) [U, sum_unit_rows] whether the row is another one now.
 hipError_t launch_cluster_means(const uint16_t* X, long long x_unit_rows, const int32_t* list, long long list_stride,
                                 const int32_t* start, long long start_stride, int k0, int k, int U,
                                 uint16_t* mean_out, long long out_unit_rows, int out_row0, const uint16_t* fallback,
                                 long long fb_unit_rows, int32_t* count_out, long long count_stride, int count_off,
-                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, hipStream_t s);
+                                double* sum_out, long long sum_unit_rows, uint32_t* range_out, uint32_t* changed_out, hipStream_t s);
 // Later Lloyd iterations: sums, counts and centroids of the clusters whose members differ between old_ids and new_ids.
 // `range` is what launch_cluster_means left for the same points.
 struct MoveMeans {
@@ -244,6 +259,7 @@ struct MoveMeans {
     long long sum_unit_rows;
     const uint32_t* range;         // [U, range_stride]
     long long range_stride;
+    uint32_t* changed;             // [U, range_stride] by cluster, for blocks of which a point is marked: did its centroid change? (or null)
     int per;                       // clusters of a workgroup (set by the launch)
 };
 hipError_t launch_move_means(MoveMeans p, int nb, int max_k, int U, hipStream_t s);

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     __shared__ uint32_t points[kMoveRound];                  // of the block
     __shared__ uint32_t entries[2 * kMoveRound];             // point << 1 | it went (one that moves is in two clusters' entries)
     __shared__ int total[kMoveClusters], at[kMoveClusters], due[kMoveClusters];
-    __shared__ bool touched[kMoveClusters];
+    __shared__ bool touched[kMoveClusters], fresh[kMoveClusters];
     __shared__ int top, bottom, most, n_marked, n_points, n_few, n_many, held;
     const int b = blockIdx.y, u = blockIdx.z;
     asm volatile("" ::"s"(p.blocks), "s"(p.marks), "s"(p.sum), "s"(p.per));      // (the arguments' lines in one trip)
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
     const unsigned long long marks0 = chunk0 < chunks ? marks[chunk0] : 0ull;
     const int count0 = tid < m ? count[tid] : 0;
     if (tid == 0) { top = 0; bottom = 255; most = 0; n_marked = 0; }
-    if (tid < m) touched[tid] = false;
+    if (tid < m) touched[tid] = fresh[tid] = false;
     __syncthreads();
     {
         // range of the block's keys, marks of the block
@@ -119,14 +119,19 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
 #pragma unroll
         for (int i = 0; i < 4; ++i) sum_of(c)[i] = make_double2(a[2 * i], a[2 * i + 1]);
     };
-    auto store_mean = [&](int c, int members, const double (&a)[8]) {
+    // (the row a mean takes the place of is asked for with the sum: the next assignment looks at centroids that changed only)
+    auto mean_of = [&](int c) { return reinterpret_cast<uint4*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim) + part; };
+    auto store_mean = [&](int c, int members, const double (&a)[8], const uint4& before) {
         if (members == 0) return;                            // (an empty cluster keeps its centroid)
         const double den = (double)members, inv = 1.0 / den;
         uint32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             w[i] = (uint32_t)quotient_to_bf16(a[2 * i], den, inv) | ((uint32_t)quotient_to_bf16(a[2 * i + 1], den, inv) << 16);
-        reinterpret_cast<uint4*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim)[part] = make_uint4(w[0], w[1], w[2], w[3]);
+        *mean_of(c) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (!p.changed) return;
+        const unsigned long long differs = __ballot(w[0] != before.x || w[1] != before.y || w[2] != before.z || w[3] != before.w);
+        if (part == 0 && ((differs >> (lane & 48)) & 0xffffull) != 0) fresh[c] = true;
     };
     bool exact = true;
     for (int ca = 0; ca < chunks; ca += step) {
@@ -233,20 +238,24 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             for (int q = 0; q < kMoveBatch; ++q) add8(a, w[q]);
             return gone;
         };
-        auto store = [&](int c, int due_here, int gone, const double (&a)[8]) {
+        auto store = [&](int c, int due_here, int gone, const double (&a)[8], const uint4& before) {
             if (due_here != 0) store_sum(c, a);
             const int members_now = count[c] + due_here - 2 * gone;
             if (part == 0) {
                 count[c] = members_now;
                 touched[c] = true;
             }
-            if (last) store_mean(c, members_now, a);
+            if (last) store_mean(c, members_now, a, before);
         };
         // a cluster of many entries: every sixteen lanes of a wave take a quarter of them
         for (int d = wave; d < n_many; d += kMoveWaves) {
             const int c = due[kMoveClusters - 1 - d], due_here = total[c], first = at[c] - due_here;
             double a[8] = {};
-            if (lane < 16) read_sum(c, a);
+            uint4 before = make_uint4(0, 0, 0, 0);
+            if (lane < 16) {
+                read_sum(c, a);
+                if (p.changed) before = *mean_of(c);
+            }
             int gone = 0;
             for (int i0 = kMoveBatch * (lane >> 4); i0 < due_here; i0 += 4 * kMoveBatch) gone += take(a, first, i0, due_here);
 #pragma unroll
@@ -255,7 +264,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
                 for (int i = 0; i < 8; ++i) a[i] += __shfl_xor(a[i], off, 64);
                 gone += __shfl_xor(gone, off, 64);
             }
-            if (lane < 16) store(c, due_here, gone, a);
+            if (lane < 16) store(c, due_here, gone, a, before);
         }
         for (int d0 = 4 * wave; d0 < n_few; d0 += 4 * kMoveWaves) {
             const int d = d0 + (lane >> 4);
@@ -263,13 +272,19 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             const int c = due[d], due_here = total[c], first = at[c] - due_here;
             double a[8];
             read_sum(c, a);
+            uint4 before = make_uint4(0, 0, 0, 0);
+            if (p.changed) before = *mean_of(c);
             int gone = 0;
             for (int i0 = 0; i0 < due_here; i0 += kMoveBatch) gone += take(a, first, i0, due_here);
-            store(c, due_here, gone, a);
+            store(c, due_here, gone, a, before);
         }
         __syncthreads();
     }
-    if (exact) return;
+    auto say_changed = [&] { if (p.changed && tid < m) p.changed[u * p.range_stride + ka + tid] = fresh[tid] ? 1u : 0u; };
+    if (exact) {
+        say_changed();
+        return;
+    }
 
     // ---- the sums round: members one after the other, in sequence order, of every cluster that changed (as far as the
     // first round of moves tells; all of them where there are more).  A stable sort of a segment's points by cluster, each
@@ -376,11 +391,16 @@ __global__ __launch_bounds__(kMoveThreads, 4) void move_means_kernel(const MoveM
             if (lane == 0) count[c] = members;
             if (s0 + segment >= n && members > 0) {     // (an empty cluster keeps its centroid)
                 const double den = (double)members, inv = 1.0 / den;
-                reinterpret_cast<uint32_t*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim)[lane] =
-                    (uint32_t)quotient_to_bf16(a.x, den, inv) | ((uint32_t)quotient_to_bf16(a.y, den, inv) << 16);
+                uint32_t* row = reinterpret_cast<uint32_t*>(p.C + ((long long)u * p.c_unit_rows + ka + c) * kHeadDim) + lane;
+                const uint32_t w = (uint32_t)quotient_to_bf16(a.x, den, inv) | ((uint32_t)quotient_to_bf16(a.y, den, inv) << 16);
+                const bool differs = p.changed && __any(w != *row);
+                *row = w;
+                if (lane == 0 && differs) fresh[c] = true;
             }
         }
     }
+    __syncthreads();
+    say_changed();
 }
 
 }  // namespace
