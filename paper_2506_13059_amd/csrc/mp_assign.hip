@@ -294,6 +294,7 @@ constexpr int kHalfTiles = 16;                   // tiles whose slots fit the si
 constexpr int kNearCap = 256;                    // (a multiple of sixteen)
 constexpr int kResidentMaxK = 512;
 constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
+constexpr int kCoarseLds = 160 * 1024 - 2048;    // of a compute unit, less what the coarse level's kernel has besides
 constexpr int kChangedTwiceK = 288;              // 2 x (288 x 268 + 1.6 K)
 constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
 
@@ -325,15 +326,26 @@ __device__ __forceinline__ void merge_pair(float& best, float& second, uint32_t&
     best = fmaxf(best, best2);
 }
 
+// Where the points are: 16-byte piece i of point t (of the unit, or of the block where its points are in LDS).
+struct PointsInMemory {
+    const unsigned char* Xu;
+    __device__ __forceinline__ uint4 piece(int t, int i) const { return reinterpret_cast<const uint4*>(Xu + (long long)t * 256)[i]; }
+};
+struct PointsInLds {      // (256-byte rows swizzled as the centroids')
+    const unsigned char* rows;
+    __device__ __forceinline__ uint4 piece(int t, int i) const { return *reinterpret_cast<const uint4*>(rows + t * 256 + ((i ^ t) & 15) * 16); }
+};
+
 // The nearest of the centroids in LDS (rows at lds0, -|c|^2/2 at ci0) for the 64 points first, first + 1, ...
-// (clamped to `last`) of Xu: lane = point.  `near`: its two best scores are closer than the margin.
+// (clamped to `last`): lane = point.  `near`: its two best scores are closer than the margin.
 struct Nearest {
     int j;
     bool near;
     float best, second;      // the best scores (their lowest bits carry the slot)
     float m;                 // what margins grow with: the largest of |x|^2 and c2max
 };
-__device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int first, int last, uint32_t lds0, uint32_t ci0,
+template <typename Points>
+__device__ __forceinline__ Nearest nearest_of_chunk(const Points& X, int first, int last, uint32_t lds0, uint32_t ci0,
                                                     int ntiles, float c2max)
 {
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -343,9 +355,8 @@ __device__ __forceinline__ Nearest nearest_of_chunk(const unsigned char* Xu, int
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int t = min(first + 16 * q + c, last);
-        const uint4* xp = reinterpret_cast<const uint4*>(Xu + (long long)t * 256) + g;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) x[q][ks] = __builtin_bit_cast(bf16x8_t, xp[4 * ks]);
+        for (int ks = 0; ks < 4; ++ks) x[q][ks] = __builtin_bit_cast(bf16x8_t, X.piece(t, 4 * ks + g));
     }
     float best[4], second[4];
 #pragma unroll
@@ -472,12 +483,13 @@ __device__ __forceinline__ float place_centroid(unsigned char* rows_lds, float* 
 }
 
 // |x - c|^2 in fp64 as in exact_distance, the centroid in LDS
-__device__ __forceinline__ double exact_distance_lds(const uint4* xrow, const unsigned char* rows_lds, int j)
+template <typename Points>
+__device__ __forceinline__ double exact_distance_lds(const Points& X, int t, const unsigned char* rows_lds, int j)
 {
     double s = 0.0;
 #pragma unroll 4
     for (int i = 0; i < 16; ++i) {
-        const uint4 xw = xrow[i], cw = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((i ^ j) & 15) * 16);
+        const uint4 xw = X.piece(t, i), cw = *reinterpret_cast<const uint4*>(rows_lds + j * 256 + ((i ^ j) & 15) * 16);
         const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w}, x4[4] = {xw.x, xw.y, xw.z, xw.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -507,18 +519,17 @@ __device__ __forceinline__ int lane_id()
 // with them).
 // known: `best` is what nearest_of_chunk found, at most 2^-17 of its size off, and need not be looked for again.
 // id_of: the cluster whose centroid stands at a place of the rows.
-template <typename IdOf>
-__device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
+template <typename Points, typename IdOf>
+__device__ __forceinline__ int nearest_exact(const Points& X, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
                                              int k, float c2max, bool known, float best, IdOf id_of)
 {
     const int lane = lane_id(), c = lane & 15, g = lane >> 4;
     const int ntiles = (k + kRowTile - 1) / kRowTile;
-    const uint4* xrow = reinterpret_cast<const uint4*>(Xu + (long long)t * 256);
     bf16x8_t x[4];
     float n2 = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-        const uint4 w = xrow[4 * ks + g];
+        const uint4 w = X.piece(t, 4 * ks + g);
         x[ks] = __builtin_bit_cast(bf16x8_t, w);
         n2 = dot2_bf16(w.x, w.x, n2);
         n2 = dot2_bf16(w.y, w.y, n2);
@@ -571,7 +582,7 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
                 const int e = __ffsll(mask) - 1;
                 mask &= mask - 1;
                 const int j = (t0 + (e >> 2)) * kRowTile + 4 * g + (e & 3);
-                const double d = exact_distance_lds(xrow, rows_lds, j);
+                const double d = exact_distance_lds(X, t, rows_lds, j);
                 const int id = id_of(j);
                 if (d < bd || (d == bd && id < bj)) { bd = d; bj = id; }
             }
@@ -586,145 +597,23 @@ __device__ __forceinline__ int nearest_exact(const unsigned char* Xu, int t, con
     return bj;
 }
 
-// The chunk a wave takes next: the first that no wave has, `first` the one behind those the waves start with.  (In turn, the waves of a
-// workgroup came to the barrier behind the chunks up to 40 us apart.)
-__device__ __forceinline__ int next_chunk(int* ticket, int first)
-{
-    int t = 0;
-    if (lane_id() == 0) t = atomicAdd(ticket, 1);
-    return first + __builtin_amdgcn_readfirstlane(t);
-}
-
-template <int kW>
-__global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
-                                                                    const int32_t* __restrict__ blocks,
-                                                                    const uint16_t* __restrict__ C, long long c_unit_rows,
-                                                                    int32_t* __restrict__ assign, long long assign_stride,
-                                                                    int32_t* __restrict__ amb_list, long long list_stride,
-                                                                    int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap,
-                                                                    const MoveMarks mv, const AssignState st)
-{
-    extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
-    __shared__ float wave_c2max[kW];
-    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them,
-    __shared__ float near_best[kNearCap];                         // and their best scores
-    __shared__ int near_n, ticket;
-    const int u = blockIdx.z, b = blockIdx.y;
-    // (this kernel leaves the counters of the other one alone; the next assignment step finds them zero all the same)
-    if (b == 0 && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < cnt_stride; i += 64 * kW) cnt_next[u * cnt_stride + i] = 0;
-    const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2];
-    const int k1 = min(blocks[4 * b + 3], k0 + k_cap);            // (the launch guarantees the block has no more)
-    const int all_chunks = (x1 - x0 + 63) / 64;
-    const int per = (all_chunks + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int chunk0 = (int)blockIdx.x * per, chunk1 = min(chunk0 + per, all_chunks);
-    if (chunk0 >= chunk1) return;
-    if (mv.marks && blockIdx.x == 0 && threadIdx.x == 0) mv.moved_now[u * cnt_stride + b] = 0;
-    if (unchanged(mv, u, b, cnt_stride)) {
-        keep_chunks(mv, u, b, x0, x1, chunk0, chunk1, assign, assign_stride);
-        return;
-    }
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);
-    float* c_init = reinterpret_cast<float*>(rows_lds + k_cap * 256);
-
-    // ---- the block's centroids: 16 lanes per row, rows past the last centroid are zeros that can never win ----
-    const int ntiles = (k1 - k0 + kRowTile - 1) / kRowTile;
-    float c2max = 0.f;
-    {
-        const uint16_t* Cu = C + (long long)u * c_unit_rows * kHeadDim;
-        for (int e = tid; e < ntiles * kRowTile * 16; e += 64 * kW) {
-            const int row = e >> 4, seg = e & 15;
-            const bool exists = k0 + row < k1;
-            uint4 w = make_uint4(0, 0, 0, 0);
-            if (exists) w = reinterpret_cast<const uint4*>(Cu + (long long)(k0 + row) * kHeadDim)[seg];
-            c2max = fmaxf(c2max, place_centroid(rows_lds, c_init, row, seg, w, exists));
-        }
-    }
-    c2max = wave_max_f32(c2max);
-    if (lane == 0) wave_c2max[wave] = c2max;
-    if (tid == 0) near_n = ticket = 0;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
-
-    int32_t* assign_u = assign + u * assign_stride;
-    const int32_t* old_u = mv.old_ids + u * assign_stride;
-    unsigned long long* marks = mv.marks + u * mv.stride + first_mark(x0, b);
-    int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
-#pragma unroll 1
-    for (int chunk = chunk0 + wave; chunk < chunk1; chunk = next_chunk(&ticket, chunk0 + kW)) {
-        const int t = x0 + chunk * 64 + lane;
-        int old = 0;
-        if (mv.marks) old = old_u[min(t, x1 - 1)];
-        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, lds0 + k_cap * 256, ntiles, c2max);
-        if (mv.marks) {
-            const unsigned long long marked = __ballot(t < x1 && (r.near || old != k0 + r.j));
-            if (lane == 0) marks[chunk] = marked;
-        }
-        if (t < x1) {
-            // (of a near tie the winner's score is no smaller than the best one, but for their errors, and no other is larger)
-            if (st.scores) st.scores[u * st.stride + t] = make_float2(r.best, r.near ? r.best : r.second);
-            if (r.near) {
-                const int pos = atomicAdd(&near_n, 1);
-                if (pos < kNearCap) {
-                    near_list[pos] = t;
-                    near_best[pos] = r.best;
-                } else {
-                    more[pos] = t;
-                }
-            } else {
-                assign_u[t] = k0 + r.j;
-            }
-        }
-    }
-    __syncthreads();
-    // ---- near ties: here, where the centroids are, instead of in a launch that fetches them for every point ----
-    const int n = near_n;
-    for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
-        const int e = min(e0 + (lane_id() & 15), n - 1);
-        const int t = e < kNearCap ? near_list[e] : more[e];
-        const int j = nearest_exact(Xu, t, rows_lds, lds0, lds0 + k_cap * 256, k1 - k0, c2max, e0 < kNearCap, e < kNearCap ? near_best[e] : 0.f,
-                                    [](int place) { return place; });
-        if (lane_id() < 16) assign_u[t] = k0 + j;
-    }
-}
-
-// The same step where the one before has left the scores it found (AssignState): a centroid that has not changed since scores
-// what it did, so the points have to be compared with the changed ones only.  Of a point there is the score of its cluster's
-// centroid, s, and a bound on the scores of all others, r >= what any of them scored.  With b the best and b2 the second best score
-// among the changed centroids (its own among them if that changed):
-//   - b is ahead of b2 and of r (and of s, if its own has not changed) by more than the margin: b's centroid is the one;
-//   - its own has not changed and s is ahead of b by more than the margin: it keeps its cluster, which won the comparison with
-//     the unchanged ones before, exactly where that was close;
-//   - otherwise it goes onto a list and is compared with all centroids afterwards (nearest_of_all).
-// The margins are those of two scores of one step (mp_margin.h): an older score has the error of its own centroid, which is still
-// one of the block, and the largest |c|^2 is taken over all of them.
-// 2048 blocks of 8192 keys, 256 centroids: 80 to 16 per cent of the centroids change in iterations 4 to 10, 3 to 0.5 per
-// cent of the points go onto the list, and a launch takes 1.2 to 0.99 ms (compared with all: 1.13 to 1.29, by the clock it gets).  Bound by
-// the keys it reads all the same: 0.81 ms without a single product, 0.93 with the points' ids and scores.  32 such blocks (of which 30 to 1 per cent
-// of the centroids change): 34 to 18.5 us, all 33; there a launch without products takes 16, and what a workgroup adds is the chain
-// of a point on its list, 10 us.
-// The changed centroids stand in front; the others' -|c|^2/2 is one that never wins while the points are compared with the changed
-// ones, tile by tile of sixteen.
+// The nearest of all centroids for sixteen points a wave, lane (g, c) as in nearest_exact, which decides the near ties.  The same in
+// a point's four lanes.
 struct Decided {
     int id;
-    float best, other;       // as in AssignState
+    float best, other;       // the scores of an AssignState
 };
-template <typename IdOf>
-__device__ __forceinline__ Decided nearest_of_all(const unsigned char* Xu, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
+template <typename Points, typename IdOf>
+__device__ __forceinline__ Decided nearest_of_all(const Points& X, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
                                                   int k, float c2max, IdOf id_of)
 {
     const int lane = lane_id(), c = lane & 15, g = lane >> 4;
     const int ntiles = (k + kRowTile - 1) / kRowTile;
-    const uint4* xrow = reinterpret_cast<const uint4*>(Xu + (long long)t * 256);
     bf16x8_t x[4];
     float n2 = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-        const uint4 w = xrow[4 * ks + g];
+        const uint4 w = X.piece(t, 4 * ks + g);
         x[ks] = __builtin_bit_cast(bf16x8_t, w);
         n2 = dot2_bf16(w.x, w.x, n2);
         n2 = dot2_bf16(w.y, w.y, n2);
@@ -769,12 +658,135 @@ __device__ __forceinline__ Decided nearest_of_all(const unsigned char* Xu, int t
     const bool near = !(best - second > near_margin(fmaxf(n2, c2max)) + fabsf(best) * (1.0f / 65536.0f));
     Decided d{id_of(min(place, k - 1)), best, near ? best : second};
     if (__any(near)) {
-        const int id = nearest_exact(Xu, t, rows_lds, lds0, ci0, k, c2max, true, best, id_of);
+        const int id = nearest_exact(X, t, rows_lds, lds0, ci0, k, c2max, true, best, id_of);
         if (near) d.id = id;
     }
     return d;
 }
 
+// The chunk a wave takes next: the first that no wave has, `first` the one behind those the waves start with.  (In turn, the waves of a
+// workgroup came to the barrier behind the chunks up to 40 us apart.)
+__device__ __forceinline__ int next_chunk(int* ticket, int first)
+{
+    int t = 0;
+    if (lane_id() == 0) t = atomicAdd(ticket, 1);
+    return first + __builtin_amdgcn_readfirstlane(t);
+}
+
+template <int kW>
+__global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
+                                                                    const int32_t* __restrict__ blocks,
+                                                                    const uint16_t* __restrict__ C, long long c_unit_rows,
+                                                                    int32_t* __restrict__ assign, long long assign_stride,
+                                                                    int32_t* __restrict__ amb_list, long long list_stride,
+                                                                    int32_t* __restrict__ cnt_next, int cnt_stride, int k_cap,
+                                                                    const MoveMarks mv, const AssignState st)
+{
+    extern __shared__ __align__(256) unsigned char rows_lds[];    // [k_cap][256 bytes], then [k_cap] -|c|^2/2
+    __shared__ float wave_c2max[kW];
+    __shared__ int32_t near_list[kNearCap];                       // points for the exact pass, the first of them,
+    __shared__ float near_best[kNearCap];                         // and their best scores
+    __shared__ int near_n, ticket;
+    const int u = blockIdx.z, b = blockIdx.y;
+    // (this kernel leaves the counters of the other one alone; the next assignment step finds them zero all the same)
+    if (b == 0 && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < cnt_stride; i += 64 * kW) cnt_next[u * cnt_stride + i] = 0;
+    const int x0 = blocks[4 * b + 0], x1 = blocks[4 * b + 1], k0 = blocks[4 * b + 2];
+    const int k1 = min(blocks[4 * b + 3], k0 + k_cap);            // (the launch guarantees the block has no more)
+    const int all_chunks = (x1 - x0 + 63) / 64;
+    const int per = (all_chunks + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int chunk0 = (int)blockIdx.x * per, chunk1 = min(chunk0 + per, all_chunks);
+    if (chunk0 >= chunk1) return;
+    if (mv.marks && blockIdx.x == 0 && threadIdx.x == 0) mv.moved_now[u * cnt_stride + b] = 0;
+    if (unchanged(mv, u, b, cnt_stride)) {
+        keep_chunks(mv, u, b, x0, x1, chunk0, chunk1, assign, assign_stride);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PointsInMemory X_u{reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim)};
+    float* c_init = reinterpret_cast<float*>(rows_lds + k_cap * 256);
+
+    // ---- the block's centroids: 16 lanes per row, rows past the last centroid are zeros that can never win ----
+    const int ntiles = (k1 - k0 + kRowTile - 1) / kRowTile;
+    float c2max = 0.f;
+    {
+        const uint16_t* Cu = C + (long long)u * c_unit_rows * kHeadDim;
+        for (int e = tid; e < ntiles * kRowTile * 16; e += 64 * kW) {
+            const int row = e >> 4, seg = e & 15;
+            const bool exists = k0 + row < k1;
+            uint4 w = make_uint4(0, 0, 0, 0);
+            if (exists) w = reinterpret_cast<const uint4*>(Cu + (long long)(k0 + row) * kHeadDim)[seg];
+            c2max = fmaxf(c2max, place_centroid(rows_lds, c_init, row, seg, w, exists));
+        }
+    }
+    c2max = wave_max_f32(c2max);
+    if (lane == 0) wave_c2max[wave] = c2max;
+    if (tid == 0) near_n = ticket = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
+
+    int32_t* assign_u = assign + u * assign_stride;
+    const int32_t* old_u = mv.old_ids + u * assign_stride;
+    unsigned long long* marks = mv.marks + u * mv.stride + first_mark(x0, b);
+    int32_t* more = amb_list + u * list_stride + x0 + chunk0 * 64;     // the others: as many entries as this workgroup has points
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
+#pragma unroll 1
+    for (int chunk = chunk0 + wave; chunk < chunk1; chunk = next_chunk(&ticket, chunk0 + kW)) {
+        const int t = x0 + chunk * 64 + lane;
+        int old = 0;
+        if (mv.marks) old = old_u[min(t, x1 - 1)];
+        const Nearest r = nearest_of_chunk(X_u, x0 + chunk * 64, x1 - 1, lds0, lds0 + k_cap * 256, ntiles, c2max);
+        if (mv.marks) {
+            const unsigned long long marked = __ballot(t < x1 && (r.near || old != k0 + r.j));
+            if (lane == 0) marks[chunk] = marked;
+        }
+        if (t < x1) {
+            // (of a near tie the winner's score is no smaller than the best one, but for their errors, and no other is larger)
+            if (st.scores) st.scores[u * st.stride + t] = make_float2(r.best, r.near ? r.best : r.second);
+            if (r.near) {
+                const int pos = atomicAdd(&near_n, 1);
+                if (pos < kNearCap) {
+                    near_list[pos] = t;
+                    near_best[pos] = r.best;
+                } else {
+                    more[pos] = t;
+                }
+            } else {
+                assign_u[t] = k0 + r.j;
+            }
+        }
+    }
+    __syncthreads();
+    // ---- near ties: here, where the centroids are, instead of in a launch that fetches them for every point ----
+    const int n = near_n;
+    for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
+        const int e = min(e0 + (lane_id() & 15), n - 1);
+        const int t = e < kNearCap ? near_list[e] : more[e];
+        const int j = nearest_exact(X_u, t, rows_lds, lds0, lds0 + k_cap * 256, k1 - k0, c2max, e0 < kNearCap, e < kNearCap ? near_best[e] : 0.f,
+                                    [](int place) { return place; });
+        if (lane_id() < 16) assign_u[t] = k0 + j;
+    }
+}
+
+// The same step where the one before has left the scores it found (AssignState): a centroid that has not changed since scores
+// what it did, so the points have to be compared with the changed ones only.  Of a point there is the score of its cluster's
+// centroid, s, and a bound on the scores of all others, r >= what any of them scored.  With b the best and b2 the second best score
+// among the changed centroids (its own among them if that changed):
+//   - b is ahead of b2 and of r (and of s, if its own has not changed) by more than the margin: b's centroid is the one;
+//   - its own has not changed and s is ahead of b by more than the margin: it keeps its cluster, which won the comparison with
+//     the unchanged ones before, exactly where that was close;
+//   - otherwise it goes onto a list and is compared with all centroids afterwards (nearest_of_all).
+// The margins are those of two scores of one step (mp_margin.h): an older score has the error of its own centroid, which is still
+// one of the block, and the largest |c|^2 is taken over all of them.
+// 2048 blocks of 8192 keys, 256 centroids: 80 to 16 per cent of the centroids change in iterations 4 to 10, 3 to 0.5 per
+// cent of the points go onto the list, and a launch takes 1.2 to 0.99 ms (compared with all: 1.13 to 1.29, by the clock it gets).  Bound by
+// the keys it reads all the same: 0.81 ms without a single product, 0.93 with the points' ids and scores.  32 such blocks (of which 30 to 1 per cent
+// of the centroids change): 34 to 18.5 us, all 33; there a launch without products takes 16, and what a workgroup adds is the chain
+// of a point on its list, 10 us.
+// The changed centroids stand in front; the others' -|c|^2/2 is one that never wins while the points are compared with the changed
+// ones, tile by tile of sixteen.
 template <int kW>
 __global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
                                                                    const int32_t* __restrict__ blocks,
@@ -810,7 +822,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim);
+    const PointsInMemory X_u{reinterpret_cast<const unsigned char*>(X + (long long)u * x_unit_rows * kHeadDim)};
 
     // ---- the block's centroids: asked for in the order of their ids, put in their places once it is known which have changed ----
     const int ntiles = (k + kRowTile - 1) / kRowTile;
@@ -872,7 +884,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16
         const int t = x0 + chunk * 64 + lane, tc = min(t, x1 - 1);
         const int old = old_u[tc];
         const float2 was = scores_u[tc];
-        const Nearest r = nearest_of_chunk(Xu, x0 + chunk * 64, x1 - 1, lds0, ci0 + (uint32_t)(k_cap * 4), tiles_changed, c2max);
+        const Nearest r = nearest_of_chunk(X_u, x0 + chunk * 64, x1 - 1, lds0, ci0 + (uint32_t)(k_cap * 4), tiles_changed, c2max);
         const bool own_changed = (int)places[old - k0] < n_changed;
         const float others = fmaxf(own_changed ? was.y : fmaxf(was.x, was.y), r.second);
         const bool won = r.best - others > near_margin_of_best(r.m, r.best);
@@ -896,7 +908,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16
     for (int e0 = wave * 16; e0 < n; e0 += kW * 16) {
         const int e = min(e0 + (lane_id() & 15), n - 1);
         const int t = e < kNearCap ? list[e] : more[e];
-        const Decided d = nearest_of_all(Xu, t, rows_lds, lds0, ci0, k, c2max, [&](int place) { return (int)ids[place]; });
+        const Decided d = nearest_of_all(X_u, t, rows_lds, lds0, ci0, k, c2max, [&](int place) { return (int)ids[place]; });
         if (lane_id() < 16) {
             assign_u[t] = k0 + d.id;
             scores_u[t] = make_float2(d.best, d.other);
@@ -937,83 +949,86 @@ hipError_t launch_resident(Kernel kernel, int waves, int bytes_per_row, bool& co
 // order of the fine clusters, and the rows of the centroid tables that go with it.  One workgroup per (block, unit): a
 // block has some hundred points and some tens of centroids, which fit one compute unit, and every step of an iteration is a
 // few microseconds of latency when it is a launch of its own (assignment, exact pass, member lists, means: 30 us for 32
-// (block, unit) pairs, times ten iterations).  Here an iteration is five barriers, and the
+// (block, unit) pairs, times ten iterations).  Here an iteration is four barriers, and the
 // first that moves no point ends them (the rest would repeat it); the decisions and sums are those of the
-// separate kernels: near ties decided in fp64 as defined, members summed in ascending order in fp64, one rounding.
-// Bound by the latency of one pair's chain, a member row from memory being its longest link (hence the sixteen at once):
-// 11.8 us an iteration for 32 pairs of 256 points and 16 centroids.  A bound of two waves a SIMD does away with the spills
-// and is slower (1000 against 780 us for 2048 pairs).  Build of one 32K prompt: 1214 -> 1095 us; sixteen of 128K: 29.1 ->
-// 28.4 ms; refresh of eight 8K contexts: 970 -> 940 us.
+// separate kernels: near ties decided in fp64 as defined, members summed in ascending order in fp64, one rounding; only
+// clusters of which a point has come or gone are summed again.
+// Bound by the latency of one pair's chain.  So the points stand in LDS where they fit it beside the centroids (kInLds: rows for the products, the
+// exact distances and the sums without a trip to memory), and a wave takes sixteen of them (a pair has some four chunks of 64 for
+// its sixteen waves) and decides their near ties itself, with half the registers: 32 pairs of 256 points, 16 centroids and ten
+// iterations 103 -> 81 us, 2048 pairs 810 -> 530; 64 pairs, three iterations 49 -> 37 us.  (Chunks of 64 points with a list of near
+// ties behind a barrier, points in LDS: 85, 528 and 42 us.)
 // ------------------------------------------------------------------------------------------------
-template <int kW>
+template <int kW, bool kInLds>
 __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLevel p)
 {
-    extern __shared__ __align__(256) unsigned char rows_lds[];   // [k_cap][256 bytes], [k_cap] -|c|^2/2, then:
-    float* c_init = reinterpret_cast<float*>(rows_lds + p.k_cap * 256);
+    extern __shared__ __align__(256) unsigned char rows_lds[];   // [k_cap][256 bytes], kInLds: [n_cap][256 bytes] the points, [k_cap] -|c|^2/2, then:
+    unsigned char* points_lds = rows_lds + p.k_cap * 256;
+    float* c_init = reinterpret_cast<float*>(points_lds + (kInLds ? p.n_cap * 256 : 0));
     uint16_t* asg = reinterpret_cast<uint16_t*>(c_init + p.k_cap);    // [n_cap] cluster of each point
     uint16_t* order = asg + p.n_cap;                                  // [n_cap] points, cluster after cluster
-    uint16_t* near_pts = order + p.n_cap;                             // [n_cap]
-    __shared__ int count[kLevelMaxK], near_n, moved;
-    __shared__ float wave_c2max[2][kW];
+    __shared__ int count[kLevelMaxK], moved;
+    __shared__ bool touched[kLevelMaxK];                              // a point has come or gone
+    __shared__ float wave_c2max[kW];
     const int b = blockIdx.x, u = blockIdx.y;
     const int x0 = p.blocks[4 * b + 0], n = p.blocks[4 * b + 1] - x0, k0 = p.blocks[4 * b + 2], k = p.blocks[4 * b + 3] - k0;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned char* Xu = reinterpret_cast<const unsigned char*>(p.X) + (long long)u * p.x_unit_rows * 256;
-    const uint32_t* Xw = reinterpret_cast<const uint32_t*>(Xu) + (long long)x0 * 64;
+    const uint4* Xb = reinterpret_cast<const uint4*>(p.X) + ((long long)u * p.x_unit_rows + x0) * 16;
     uint4* Ku = reinterpret_cast<uint4*>(p.Kc) + (long long)u * p.tab_rows * 16;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)rows_lds;
+    const uint32_t ci0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)c_init;
     const int ntiles = (k + kRowTile - 1) / kRowTile;
     const int chunks = (n + 63) / 64;
+    using Points = std::conditional_t<kInLds, PointsInLds, PointsInMemory>;
+    const Points X{kInLds ? points_lds : reinterpret_cast<const unsigned char*>(Xb)};
+    // one row by a wave, a dword a lane
+    auto row_dword = [&](int t) {
+        if constexpr (kInLds) return *reinterpret_cast<const uint32_t*>(points_lds + t * 256 + (((lane >> 2) ^ t) & 15) * 16 + (lane & 3) * 4);
+        else return reinterpret_cast<const uint32_t*>(Xb)[(long long)t * 64 + lane];
+    };
 
-    // ---- first centroids: the stored ones of old clusters, seeds for the others ----
+    // ---- first centroids: the stored ones of old clusters, seeds for the others; the points ----
     float c2max = 0.f;
     for (int e = tid; e < ntiles * kRowTile * 16; e += 64 * kW) {
         const int row = e >> 4, seg = e & 15, j = k0 + row;
         uint4 w = make_uint4(0, 0, 0, 0);
         if (row < k) {
             if (j < p.old_end) w = Ku[(long long)(p.fcap + j) * 16 + seg];
-            else w = reinterpret_cast<const uint4*>(Xu)[(long long)((p.seed_x0 < 0 ? x0 : p.seed_x0) + p.seeds[u * p.seed_stride + j]) * 16 + seg];
+            else w = Xb[((long long)(p.seed_x0 < 0 ? 0 : p.seed_x0 - x0) + p.seeds[u * p.seed_stride + j]) * 16 + seg];
         }
         c2max = fmaxf(c2max, place_centroid(rows_lds, c_init, row, seg, w, row < k));
     }
+    if constexpr (kInLds)
+        for (int e = tid; e < n * 16; e += 64 * kW) {
+            const int t = e >> 4, seg = e & 15;
+            *reinterpret_cast<uint4*>(points_lds + t * 256 + ((seg ^ t) & 15) * 16) = Xb[e];
+        }
     c2max = wave_max_f32(c2max);
-    if (lane == 0) wave_c2max[0][wave] = c2max;
+    if (lane == 0) wave_c2max[wave] = c2max;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[w]);
 
     for (int it = 0; it < p.iters; ++it) {
-        if (tid == 0) near_n = moved = 0;
+        if (tid == 0) moved = 0;
+        for (int j = tid; j < k; j += 64 * kW) touched[j] = it == 0;
         __syncthreads();
-        c2max = 0.f;
-#pragma unroll
-        for (int w = 0; w < kW; ++w) c2max = fmaxf(c2max, wave_c2max[it & 1][w]);
-        // ---- nearest centroid of every point ----
-        for (int ch = wave; ch < chunks; ch += kW) {
-            const Nearest r = nearest_of_chunk(Xu, x0 + ch * 64, x0 + n - 1, lds0, lds0 + p.k_cap * 256, ntiles, c2max);
-            const int t = ch * 64 + lane;
-            if (t < n) {
-                const uint16_t j = (uint16_t)min(r.j, k - 1);
-                if (r.near) {
-                    near_pts[atomicAdd(&near_n, 1)] = (uint16_t)t;
-                } else if (it == 0 || asg[t] != j) {
-                    asg[t] = j;
-                    moved = 1;
-                }
-            }
-        }
-        __syncthreads();
-        // ---- near ties ----
-        for (int e0 = wave * 16; e0 < near_n; e0 += kW * 16) {
-            const int t = near_pts[min(e0 + (lane & 15), near_n - 1)];
-            const int j = nearest_exact(Xu, x0 + t, rows_lds, lds0, lds0 + p.k_cap * 256, k, c2max, false, 0.f, [](int place) { return place; });
-            if (lane < 16 && (it == 0 || asg[t] != j)) {
-                asg[t] = (uint16_t)j;
+        // ---- nearest centroid of every point, sixteen a wave: a pair has few chunks of 64, and the wave that finds a near tie decides it ----
+        for (int t0 = wave * 16; t0 < n; t0 += kW * 16) {
+            const int t = t0 + (lane & 15);
+            const Decided d = nearest_of_all(X, min(t, n - 1), rows_lds, lds0, ci0, k, c2max, [](int place) { return place; });
+            if (lane < 16 && t < n && (it == 0 || asg[t] != d.id)) {
+                if (it > 0) touched[asg[t]] = touched[d.id] = true;
+                asg[t] = (uint16_t)d.id;
                 moved = 1;
             }
         }
         __syncthreads();
         if (moved == 0) break;        // the same assignment as before: the same centroids, and so in every iteration after it
-        // ---- member lists: one wave per cluster finds its points 64 at a time ----
+        // ---- the clusters of which a point has come or gone: their members, one wave a cluster that finds them 64 at a time ----
         for (int j = wave; j < k; j += kW) {
+            if (!touched[j]) continue;
             int m = 0;
             for (int ch = 0; ch < chunks; ++ch) {
                 const int t = ch * 64 + lane;
@@ -1022,8 +1037,8 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
             if (lane == 0) count[j] = m;
         }
         __syncthreads();
-        float next_c2max = 0.f;
         for (int j = wave; j < k; j += kW) {
+            if (!touched[j]) continue;
             int pos = 0;                             // points of the clusters before this one
             for (int i = lane; i < j; i += 64) pos += count[i];
 #pragma unroll
@@ -1046,10 +1061,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
                 for (int q0 = 0; q0 < nm; q0 += kBatch) {
                     uint32_t w[kBatch];
 #pragma unroll
-                    for (int q = 0; q < kBatch; ++q) {
-                        const long long r = __builtin_amdgcn_readlane(member, (q0 + q) & 63);
-                        w[q] = (q0 + q < nm) ? Xw[r * 64 + lane] : 0u;
-                    }
+                    for (int q = 0; q < kBatch; ++q) w[q] = row_dword(__builtin_amdgcn_readlane(member, min(q0 + q, nm - 1)));
 #pragma unroll
                     for (int q = 0; q < kBatch; ++q) {
                         if (q0 + q < nm) {
@@ -1060,23 +1072,37 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
                 }
             }
             // new centroid (an empty cluster keeps its own), its place in LDS: dims 2 lane, 2 lane + 1
-            uint32_t* at = reinterpret_cast<uint32_t*>(rows_lds + j * 256 + (((lane >> 2) ^ j) & 15) * 16) + (lane & 3);
-            uint32_t row = *at;
             if (m > 0) {
                 const double den = (double)m;
-                row = (uint32_t)f64_to_bf16_rne(a0 / den) | ((uint32_t)f64_to_bf16_rne(a1 / den) << 16);
-                *at = row;
-            }
-            float s = dot2_bf16(row, row, 0.f);
+                const uint32_t row = (uint32_t)f64_to_bf16_rne(a0 / den) | ((uint32_t)f64_to_bf16_rne(a1 / den) << 16);
+                *(reinterpret_cast<uint32_t*>(rows_lds + j * 256 + (((lane >> 2) ^ j) & 15) * 16) + (lane & 3)) = row;
+                float s = dot2_bf16(row, row, 0.f);
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-            if (lane == 0) c_init[j] = -0.5f * s;
-            next_c2max = fmaxf(next_c2max, s);
+                for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+                if (lane == 0) c_init[j] = -0.5f * s;
+            }
         }
-        if (lane == 0) wave_c2max[(it + 1) & 1][wave] = next_c2max;
+        __syncthreads();
+        c2max = 0.f;
+        for (int j = lane; j < k; j += 64) c2max = fmaxf(c2max, -2.0f * c_init[j]);
+        c2max = wave_max_f32(c2max);
+    }
+    // ---- the new order (that of the last iteration has holes where clusters kept their members) ----
+    __syncthreads();
+    for (int j = wave; j < k; j += kW) {
+        int pos = 0;
+        for (int i = lane; i < j; i += 64) pos += count[i];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) pos += __shfl_xor(pos, off, 64);
+        for (int ch = 0; ch < chunks; ++ch) {
+            const int t = ch * 64 + lane;
+            const unsigned long long mine = __ballot(t < n && asg[t] == j);
+            if ((mine >> lane) & 1ull) order[pos + __popcll(mine & ((1ull << lane) - 1ull))] = (uint16_t)t;
+            pos += __popcll(mine);
+        }
     }
     __syncthreads();
-    // ---- the new order: list position -> old fine id, old -> new id, parents, and the rows of the tables ----
+    // ---- list position -> old fine id, old -> new id, parents, and the rows of the tables ----
     const int at0 = x0 - p.f0;
     for (int i = tid; i < n; i += 64 * kW) {
         const int t = order[i];
@@ -1086,7 +1112,7 @@ __global__ __launch_bounds__(64 * kW, 4) void coarse_level_kernel(const CoarseLe
     }
     for (int e = tid; e < n * 16; e += 64 * kW) {
         const int i = e >> 4, seg = e & 15;
-        Ku[(long long)(x0 + i) * 16 + seg] = reinterpret_cast<const uint4*>(Xu)[(long long)(x0 + order[i]) * 16 + seg];
+        Ku[(long long)(x0 + i) * 16 + seg] = X.piece(order[i], seg);
     }
     for (int e = tid; e < k * 16; e += 64 * kW) {
         const int j = e >> 4, seg = e & 15;
@@ -1265,23 +1291,23 @@ __global__ __launch_bounds__(256) void assign_recheck_kernel(const uint16_t* __r
 
 }  // namespace
 
-static size_t coarse_level_smem(int max_pts, int max_k)
+static size_t coarse_level_smem(int max_pts, int max_k, bool in_lds)
 {
     const size_t k_cap = (size_t)(max_k + kRowTile - 1) / kRowTile * kRowTile, n_cap = (size_t)(max_pts + 3) / 4 * 4;
-    return k_cap * 260 + n_cap * 6;
+    return k_cap * 260 + n_cap * (in_lds ? 260 : 4);
 }
 
-template <int kW>
+template <int kW, bool kInLds>
 static hipError_t launch_coarse_waves(const CoarseLevel& p, int nb, int U, size_t smem, hipStream_t s)
 {
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&coarse_level_kernel<kW>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)coarse_level_smem(kLevelMaxPts, kLevelMaxK));
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&coarse_level_kernel<kW, kInLds>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           kInLds ? kCoarseLds : (int)coarse_level_smem(kLevelMaxPts, kLevelMaxK, false));
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL(coarse_level_kernel<kW>, dim3(nb, U), dim3(64 * kW), smem, s, p);
+    hipLaunchKernelGGL((coarse_level_kernel<kW, kInLds>), dim3(nb, U), dim3(64 * kW), smem, s, p);
     return hipGetLastError();
 }
 
@@ -1292,9 +1318,12 @@ hipError_t launch_coarse_level(CoarseLevel p, int nb, int U, int max_pts, int ma
     p.k_cap = (max_k + kRowTile - 1) / kRowTile * kRowTile;
     p.n_cap = (max_pts + 3) / 4 * 4;
     // Sixteen waves where every pair has a compute unit of its own (a pair's time is what counts then: 104 against 132 us
-    // for 32 pairs and ten iterations where the line was drawn, 110 to 118 us in the build of a 32K prompt), else two workgroups of eight a compute unit (755 against 890 us for 2048 pairs).
-    const size_t smem = coarse_level_smem(max_pts, max_k);
-    return (long long)nb * U <= 256 ? launch_coarse_waves<16>(p, nb, U, smem, s) : launch_coarse_waves<8>(p, nb, U, smem, s);
+    // for 32 pairs and ten iterations), else two workgroups of eight a compute unit (755 against 890 us for 2048 pairs), with the
+    // points in LDS where two copies of them fit it.  (The four figures are from before the points stood there.)
+    const size_t smem = coarse_level_smem(max_pts, max_k, false), with_points = coarse_level_smem(max_pts, max_k, true);
+    static_assert((kLevelMaxPts + 64) * 260 <= kCoarseLds && (256 + 112) * 260 <= kCoarseLds, "whatever coarse_level_fits admits");
+    if ((long long)nb * U <= 256) return with_points <= kCoarseLds ? launch_coarse_waves<16, true>(p, nb, U, with_points, s) : hipErrorInvalidValue;
+    return with_points <= kCoarseLds / 2 ? launch_coarse_waves<8, true>(p, nb, U, with_points, s) : launch_coarse_waves<8, false>(p, nb, U, smem, s);
 }
 
 hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t* blocks_dev, int nb, int max_pts,

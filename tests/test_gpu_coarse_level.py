@@ -40,3 +40,10 @@ def test_more_pairs_than_compute_units():
 def test_every_point_a_near_tie(distinct):
     ctx, _, _ = _run_case(1, 2, 2, 600, 4, 2, 200, 40, 0, 0, iters=3, seed=52, distinct_rows=distinct)
     ctx.close()
+
+
+@pytest.mark.parametrize("W,fine", [(600, 250), (900, 262), (900, 400)])
+def test_many_pairs_with_and_without_points_in_lds(W, fine):
+    # 264 pairs of 8-wave workgroups: points in LDS up to 311 less the centroids
+    ctx, _, _ = _run_case(66, 4, 4, W, 40, 2, fine, 24, 0, 0, iters=3, seed=fine)
+    ctx.close()
