@@ -444,6 +444,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     // them empty, since only the host-known upper bound of their number can size the grid -- that take their
     // turn on the compute units before the long streams start.
     const bool terms_ride = use_mp && main_max > 0;
+    bool own_wave = false;      // the terms have one (mp_stream_terms.hip)
     int terms_src = -1;         // (the terms are the launch's first source: what a rider has to be)
     if (use_mp) {
         const int mp_max = ctx->n_fine + ctx->n_coarse;
@@ -473,6 +474,9 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
         r.count_dev = ctx->n_rows; r.count_max = main_max; r.scores = nullptr; r.chunk0 = chunk0;
         r.chunk_rows = crm; r.row0 = 0; r.n_chunks = ceil_div(main_max, crm); chunk0 += r.n_chunks;
         r.guest = (terms_ride && terms_src == 0) ? 1 : 0;
+        own_wave = on_matrix && !bytes && r.guest &&
+                   terms_have_a_wave((long long)U * chunk0, likely_terms(ctx->cfg.levels, ctx->n_tokens, ctx->n_fine, ctx->n_coarse, key_budget, coarse_budget),
+                                     r.n_chunks, crm);
     }
     vp.n_sources = ns;
     vp.chunks_per_unit = chunk0;
@@ -482,7 +486,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     MP_HIP(ctx, launch_score_select(sp, ctx->n_cus, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[2], s));
     if (chunk0 > 0)
-        MP_HIP(ctx, !on_matrix ? launch_value_pass(vp, G, s) : bytes && main_max > 0 ? launch_value_stream8(vp, G, s) : launch_value_stream(vp, G, s));
+        MP_HIP(ctx, !on_matrix ? launch_value_pass(vp, G, s) : bytes && main_max > 0 ? launch_value_stream8(vp, G, s) : own_wave ? launch_value_terms(vp, G, s) : launch_value_stream(vp, G, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[3], s));
     MP_HIP(ctx, launch_merge(ctx->partials, U, chunk0, G, (uint16_t*)out, lse, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[4], s));

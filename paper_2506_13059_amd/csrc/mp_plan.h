@@ -107,6 +107,24 @@ inline StreamPlan plan_streams(int n_units, long long first, long long tail, int
     return StreamPlan{even(first), even(tail)};
 }
 
+// Centroid terms that a decode step leaves to the value pass per unit, about (as if all clusters were of one size).
+inline long long likely_terms(int levels, int n_tokens, int n_fine, int n_coarse, int key_budget, int coarse_budget)
+{
+    const long long n = std::max(n_tokens, 1), candidates = levels == 2 ? std::min<long long>(coarse_budget, n) : n;
+    const long long taken = std::min<long long>(key_budget, candidates);
+    return (n_fine * (candidates - taken) + (levels == 2 ? n_coarse * (n - candidates) : 0)) / n;
+}
+
+// Whether the terms that ride along with the selected keys have a wave of their own (bf16 rows): where every workgroup has a compute
+// unit (its ten waves do not share one with ten others: 130 units, two workgroups each, 47.1 -> 47.4 to 48.8 us, 300 units 62.5 ->
+// 68.5), and one wave has no more to do than the others.  Whole step, us, riding / own wave: 1 unit of 4 heads x 512 keys 21.0 / 19.4; 8 x
+// 4096 24.5 / 23.5; 32 x 4096 of 5 heads 37.6 / 36.5; 32 x 2048 and a tail of 200 35.7 / 34.1; 100 x 2048 39.0 / 37.7; 128 x 8192 (256 terms,
+// 1024 keys a wave) 120.3 / 118.5; 64 x 1024 (136 terms, 64 keys a wave) 37.3 / 37.1; 128 x 2048 (544 terms, 256 keys a wave) 83 / 87.
+inline bool terms_have_a_wave(long long workgroups, long long terms, long long key_chunks, int chunk_rows)
+{
+    return workgroups <= kStreamWgs && 2 * terms <= key_chunks * chunk_rows;
+}
+
 // Dense calls of one or two heads to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one
 // chain of latencies, and its chain is shorter: no staging in LDS, and the work of an epilogue grows with the heads.  Us
 // on the device, here / matrix cores, 1 head: 1 unit x 8192 rows 9.4 / 10.2, 8 x 2000 10.9 / 11.6, 64 x 500 11.6 / 12.4, 128 x

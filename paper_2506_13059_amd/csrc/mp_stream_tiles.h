@@ -19,6 +19,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kTile = 16;                        // rows per tile
 constexpr int kPiece = kTile * 256;              // bytes of a tile's keys (or values)
 constexpr int kRing = 4 * kPiece;                // per wave: keys and values of two tiles
+constexpr int kScores = 1024;                    // in the place of a tile's keys: ready-made logits (512 bytes of eight heads)
+constexpr int kScoredRing = 2 * (kScores + kPiece);
 constexpr int kStrip = 64;                       // row numbers fetched at a time
 constexpr int kStripBytes = 12 * kStrip;         // per wave: two strips, and the first one of the launch's guest source
 
@@ -199,6 +201,7 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     const int vr = 4 * g + (c >> 2);
     const uint32_t v_addr = ring + (uint32_t)(vr * 256 + ((((c & 3) >> 1) ^ vr) & 1) * 16 + (c & 1) * 8 + (vr >> 1) * 32);   // ^ 32 d
     const int n_tiles = (w1 - w0 + kTile - 1) / kTile;
+    constexpr int kBehind = kScored ? kScores : kPiece, kSlot = kBehind + kPiece;      // the ring: two slots, values behind keys or logits
 
     auto load_strip = [&](int s) {          // row numbers [w0 + 64 s, +64), clamped to the last row
         if constexpr (kListed) {
@@ -229,16 +232,16 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
 #pragma unroll
             for (int i = 0; i < kKeyLoads; ++i) {
                 const int x = min((w0 + t * kTile) * G + 64 * i + lane, w1 * G - 1);
-                load_to_lds<4, false>(scores + x, ring + (uint32_t)((t & 1) * 2 * kPiece + i * 256));
+                load_to_lds<4, false>(scores + x, ring + (uint32_t)((t & 1) * kSlot + i * 256));
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Kb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + i * 1024));
+            for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Kb + off[i], ring + (uint32_t)((t & 1) * kSlot + i * 1024));
         }
     };
     auto load_values = [&](int t) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Vb + off[i], ring + (uint32_t)((t & 1) * 2 * kPiece + kPiece + i * 1024));
+        for (int i = 0; i < 4; ++i) load_to_lds<16, true>(Vb + off[i], ring + (uint32_t)((t & 1) * kSlot + kBehind + i * 1024));
     };
 
     // The value rows of tile t past the end of the wave's share (repeats of its last row) are zeroed: their probability is
@@ -272,7 +275,7 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
     // kAhead: how many tiles follow (two: two or more)
     auto tile = [&](int t, auto ahead) {
         constexpr int kAhead = decltype(ahead)::value;
-        const uint32_t half = (uint32_t)((t & 1) * 2 * kPiece);
+        const uint32_t half = (uint32_t)((t & 1) * kSlot);
         float s[4];
         wait_vm<kAhead == 0 ? 4 : 8 + kKeyLoads>();
         if constexpr (kScored) {
@@ -306,8 +309,8 @@ __device__ __forceinline__ void stream_tiles(StreamState<G>& st, const RowSource
         float pr[4];
         tile_softmax<G>(st, s, pr);
         wait_vm<kAhead == 2 ? 4 + 2 * kKeyLoads : kAhead * (4 + kKeyLoads)>();
-        if constexpr (kAhead == 0) clear_past_end(t, ring + half + kPiece);
-        tile_values<G>(st, pr, v_addr + half + kPiece, mask1, mask2);
+        if constexpr (kAhead == 0) clear_past_end(t, ring + half + kBehind);
+        tile_values<G>(st, pr, v_addr + half + kBehind, mask1, mask2);
         if constexpr (kAhead == 2) {
             load_values(t + 2);
             // the row numbers of tile t + 2, the last of its strip, have just been read: its slot takes the strip after next
@@ -418,7 +421,8 @@ __device__ __forceinline__ void combine_waves(const StreamState<G>& st, float* s
     float* sm_m = sm;                        // [kWaves][16]
     float* sm_l = sm + 16 * kWaves;
     constexpr int kCols = StreamState<G>::kThird ? 16 + 8 : 16;
-    float* sm_o = sm + 32 * kWaves;          // [kWaves][kCols][128]
+    float* sm_o = sm + 32 * kWaves;          // [kWaves][kCols][kRow]
+    constexpr int kRow = 132;                // (the four rows a store instruction has are four apart: at 128 they would meet in one bank)
     if (lane < 16) {
         sm_m[wave * 16 + lane] = st.m;
         sm_l[wave * 16 + lane] = l;
@@ -427,9 +431,9 @@ __device__ __forceinline__ void combine_waves(const StreamState<G>& st, float* s
     for (int d = 0; d < 8; ++d)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            sm_o[(wave * kCols + 4 * g + i) * 128 + 16 * d + c] = st.o[d][i];
+            sm_o[(wave * kCols + 4 * g + i) * kRow + 16 * d + c] = st.o[d][i];
             if constexpr (StreamState<G>::kThird)
-                if (g < 2) sm_o[(wave * kCols + 16 + 4 * g + i) * 128 + 16 * d + c] = st.o3[d][i];
+                if (g < 2) sm_o[(wave * kCols + 16 + 4 * g + i) * kRow + 16 * d + c] = st.o3[d][i];
         }
     __syncthreads();
     for (int o = tid; o < G * 128; o += 64 * kWaves) {
@@ -443,9 +447,9 @@ __device__ __forceinline__ void combine_waves(const StreamState<G>& st, float* s
         for (int w = 0; w < kWaves; ++w) {
             const float f = __builtin_amdgcn_exp2f(sm_m[w * 16 + h] - Ms);
             L = fmaf(sm_l[w * 16 + h], f, L);
-            float x = sm_o[(w * kCols + h) * 128 + d];
-            x += sm_o[(w * kCols + G + h) * 128 + d];
-            x += sm_o[(w * kCols + (StreamState<G>::kThird ? 16 : 2 * G) + h) * 128 + d];
+            float x = sm_o[(w * kCols + h) * kRow + d];
+            x += sm_o[(w * kCols + G + h) * kRow + d];
+            x += sm_o[(w * kCols + (StreamState<G>::kThird ? 16 : 2 * G) + h) * kRow + d];
             a = fmaf(x, f, a);
         }
         float* ph = part + h * kPartStride;
