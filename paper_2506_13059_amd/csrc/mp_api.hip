@@ -789,7 +789,7 @@ mp_status dense_impl(const char* who, const void* q, const void* k, const void* 
     p.src[0].count_max = n;
     p.src[0].chunk0 = 0;
     p.src[0].n_chunks = p.chunks_per_unit;
-    hipError_t e = on_matrix ? launch_value_stream(p, G, s) : launch_value_pass(p, G, s);
+    hipError_t e = on_matrix ? launch_value_dense(p, G, s) : launch_value_pass(p, G, s);
     if (e == hipSuccess) e = launch_merge(p.partials, U, p.chunks_per_unit, G, (uint16_t*)out, lse, s);
     if (e != hipSuccess) return fail(nullptr, MP_EHIP, "%s: %s", who, hipGetErrorString(e));
     return MP_OK;

@@ -55,6 +55,8 @@ struct ValuePassParams {
 hipError_t launch_value_pass(const ValuePassParams& p, int G, hipStream_t stream);
 // The same launch on the matrix cores: bf16 rows that start on 16 bytes, chunk_rows a multiple of 64.
 hipError_t launch_value_stream(const ValuePassParams& p, int G, hipStream_t stream);
+// ... of one source of rows in order, all of them (dense calls).
+hipError_t launch_value_dense(const ValuePassParams& p, int G, hipStream_t stream);
 // ... of a decode step whose centroid terms ride along with its selected keys: they have a wave of their own.
 hipError_t launch_value_terms(const ValuePassParams& p, int G, hipStream_t stream);
 // ... of which one source's rows are listed 8-bit rows.

@@ -127,9 +127,10 @@ inline bool terms_have_a_wave(long long workgroups, long long terms, long long k
 
 // Dense calls of one or two heads to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one
 // chain of latencies, and its chain is shorter: no staging in LDS, and the work of an epilogue grows with the heads.  Us
-// on the device, here / matrix cores, 1 head: 1 unit x 8192 rows 9.4 / 10.2, 8 x 2000 10.9 / 11.6, 64 x 500 11.6 / 12.4, 128 x
-// 500 13.2 / 14.1; 2 heads: 8 x 500 11.1 / 11.3, 64 x 500 12.1 / 12.7, 100 x 500 12.5 / 13.9; at 131072 rows in all the two meet
-// (64 x 2000 16.1 / 16.6, 128 x 2000 26.8 / 27.6; 32 x 8192, 1 head 28.1 / 26.4), and with three heads the matrix cores win.
+// on the device, here / matrix cores, 1 head: 1 unit x 8192 rows 8.7 / 9.1, 8 x 2000 8.3 / 8.8, 64 x 500 9.8 / 10.7, 128 x
+// 500 10.3 / 11.0, 64 x 2000 13.5 / 14.0, 128 x 2000 22.6 / 23.5; 2 heads, where the two are level since the matrix cores' kernel has
+// its arguments in registers: 8 x 2000 10.3 / 9.8, 8 x 8192 11.8 / 12.0, 64 x 500 11.1 / 11.1, 128 x 500 11.8 / 11.6, 64 x 2000 15.2 / 15.0, 128 x
+// 2000 26.2 / 25.6; with three heads the matrix cores win (8 x 2000 11.7 / 9.6).
 inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
 {
     return group <= 2 && n_units * n <= 131072;
