@@ -383,17 +383,27 @@ mp_status finalize_range(mp_ctx* ctx, const void* Xk, const void* Xs, const void
     so.fstart = ctx->fstart; so.perm = ctx->perm; so.fot = ctx->fot; so.cstart = ctx->cstart;
     MP_HIPC(launch_stored_order(so, U, s));
     const bool bytes = ctx->cfg.kv_format == MP_KV_E4M3;
-    if (!bytes)
-        MP_HIPC(launch_gather_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, n_pts, U, ctx->Kp, ctx->Vp, Ncap, pt0, seq, s));
     // (after a Lloyd iteration the working centroids already sitting in ctx->Kc ARE the member means of the
     // final assignment -- same members, same order of summation, same rounding: nothing to recompute)
-    if (!fine_keys_are_means)
+    const bool with_rows = !bytes && Xk == Xs;       // (key means on the way, of the very rows that are stored)
+    if (!fine_keys_are_means && !with_rows)
         MP_HIPC(launch_cluster_means((const uint16_t*)Xk, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
                                      ctx->Kc, tab, 0, key_fallback ? ctx->Kc : nullptr, tab, nullptr, 0, 0,
                                      two ? ctx->sumK : nullptr, ctx->Fcap, nullptr, nullptr, s));
-    MP_HIPC(launch_cluster_means((const uint16_t*)Xv, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
-                                 ctx->Vc, tab, 0, nullptr, 0, ctx->Ncl, tab, 0, two ? ctx->sumV : nullptr, ctx->Fcap,
-                                 nullptr, nullptr, s));
+    if (!bytes) {
+        StoredRows sr{};
+        sr.K = Xs; sr.V = Xv; sr.src_unit_rows = x_unit_rows; sr.list = ctx->km_list; sr.list_stride = Ncap;
+        sr.start = ctx->km_start; sr.start_stride = tab + 1; sr.f0 = f0; sr.f1 = f1; sr.n = n_pts;
+        sr.dstK = ctx->Kp; sr.dstV = ctx->Vp; sr.dst_unit_rows = Ncap; sr.dst_row0 = pt0; sr.seq = seq;
+        sr.value_means = ctx->Vc; sr.key_means = !fine_keys_are_means && with_rows ? ctx->Kc : nullptr; sr.key_keeps = key_fallback;
+        sr.counts = ctx->Ncl; sr.tab_rows = tab; sr.sum_unit_rows = ctx->Fcap;
+        if (two) { sr.value_sums = ctx->sumV; sr.key_sums = ctx->sumK; }
+        MP_HIPC(launch_stored_rows(sr, U, s));
+    } else {
+        MP_HIPC(launch_cluster_means((const uint16_t*)Xv, x_unit_rows, ctx->km_list, Ncap, ctx->km_start, tab + 1, f0, f1, U,
+                                     ctx->Vc, tab, 0, nullptr, 0, ctx->Ncl, tab, 0, two ? ctx->sumV : nullptr, ctx->Fcap,
+                                     nullptr, nullptr, s));
+    }
     if (bytes)   // (8-bit keys are residuals from the fine key centroids, which are final only now)
         MP_HIPC(launch_gather_quantize_rows(Xs, Xv, x_unit_rows, ctx->km_list, Ncap, ids, ids_stride, ctx->Kc, tab, n_pts, U,
                                             ctx->Kq, ctx->Vq, ctx->kv_scale, Ncap, pt0, seq, ctx->n_rows + U, s));

@@ -26,6 +26,7 @@ __device__ __forceinline__ uint4 load_once(const uint4* p)
     const u32x4_nt t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(p));
     return make_uint4(t.x, t.y, t.z, t.w);
 }
+__device__ __forceinline__ void store_once(uint32_t* p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_once(uint4* p, const uint4& v)
 {
     u32x4_nt t;

@@ -176,26 +176,7 @@ __device__ __forceinline__ void keep_in_sequence(const SequenceCopy& q, int u, l
     if (q.V) store_once(reinterpret_cast<uint4*>(q.V) + at, v);
 }
 
-// dst[u][p] = src[u][list[u][p]] for 256-byte rows; one thread moves 16 bytes.
-__global__ void gather_rows_kernel(const uint4* __restrict__ srcK, const uint4* __restrict__ srcV,
-                                   long long src_unit_rows, const int32_t* __restrict__ list, long long list_stride,
-                                   int n, uint4* __restrict__ dstK, uint4* __restrict__ dstV, long long dst_unit_rows,
-                                   int dst_row0, const SequenceCopy seq)
-{
-    const int u = blockIdx.y;
-    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long p = g >> 4;
-    const int c = (int)(g & 15);
-    if (p >= n) return;
-    const long long s = list[u * list_stride + p];
-    // (a pure stream: every line is read once and written once)
-    const uint4 k = load_once(&srcK[((long long)u * src_unit_rows + s) * 16 + c]), v = load_once(&srcV[((long long)u * src_unit_rows + s) * 16 + c]);
-    store_once(&dstK[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], k);
-    store_once(&dstV[((long long)u * dst_unit_rows + dst_row0 + p) * 16 + c], v);
-    keep_in_sequence(seq, u, s, c, k, v);
-}
-
-// The same gather into 8-bit storage.  A value row becomes 128 e4m3 codes (OCP format: bias 7,
+// The gather into 8-bit storage.  A value row becomes 128 e4m3 codes (OCP format: bias 7,
 // largest magnitude 448, no infinities) and one fp32 scale, scale = max|x| / 448 (1 for a zero row),
 // code = x / scale rounded to nearest even; both divisions are IEEE fp32.  A key row is stored the
 // same way as its residual from the key centroid of its fine cluster, x = fp32(k) - fp32(centroid):
@@ -271,31 +252,18 @@ __global__ void gather_quantize_rows_kernel(const uint4* __restrict__ srcK, cons
     }
 }
 
-// One wave per cluster of [k0, k): fp64 sum of the member rows in list order, mean rounded once to bf16.
-// Lane l owns dims 2l and 2l+1.  Empty cluster: `fallback` row if given (else zeros).
-// mean_out row index = out_row0 + cluster id.  count_out optional.
+// The fp64 sum of rows lp[s0 .. s1) (no list: s0 .. s1) of Xu in that order, by one wave: lane l has dims 2l and 2l+1.
+// passes(at, q, row, w) is told every row: it is number at + q of the list, and w the lane's dword of it.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-template <bool kRange>
-__global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
-                                                           const int32_t* __restrict__ list, long long list_stride,
-                                                           const int32_t* __restrict__ start, long long start_stride,
-                                                           int k0, int k, uint16_t* __restrict__ mean_out,
-                                                           long long out_unit_rows, int out_row0,
-                                                           const uint16_t* __restrict__ fallback,
-                                                           long long fb_unit_rows, int32_t* __restrict__ count_out,
-                                                           long long count_stride, int count_off,
-                                                           double* __restrict__ sum_out, long long sum_unit_rows,
-                                                           uint32_t* __restrict__ range_out, uint32_t* __restrict__ changed_out)
-{
-    const int u = blockIdx.y;
-    const int f = k0 + blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (f >= k) return;
-    const int s0 = start[u * start_stride + f], s1 = start[u * start_stride + f + 1];
-    const uint32_t* Xu = reinterpret_cast<const uint32_t*>(X + (long long)u * x_unit_rows * kHeadDim);
-    const int32_t* lp = list ? list + u * list_stride : nullptr;
+struct RowSum {
     double a0 = 0.0, a1 = 0.0;
-    u16x2 largest = {0, 0}, smallest = {0xffff, 0xffff};     // magnitudes, and nonzero magnitudes less one
+    u16x2 largest = {0, 0}, smallest = {0xffff, 0xffff};     // kRange: magnitudes, and nonzero magnitudes less one
+};
+template <bool kRange, typename Passes>
+__device__ __forceinline__ RowSum sum_of_rows(const uint32_t* __restrict__ Xu, const int32_t* __restrict__ lp, int s0, int s1, Passes passes)
+{
+    const int lane = threadIdx.x & 63;
+    RowSum a;
     // 64 member indices at a time (one per lane), then their rows kBatch at a time: the row numbers
     // reach every lane through a lane broadcast, so that kBatch row loads are in flight at once while
     // the additions keep the members' order (a wave's time is the number of trips to memory it makes:
@@ -303,6 +271,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     // online refresh, with 32 rows a trip a third of that).  The next 64 indices are asked for ahead, and a whole batch has no
     // branch in front of each row: noting the range had made a cluster of thousands 12 % slower (eight blocks of 131072 keys, the
     // longest of 128 clusters, 2009 -> 2254 us); their build, five iterations, 4620 -> 3655 us, of 32 blocks of 8192 keys 828 -> 796.
+    // (Zeros in the place of the rows past the end, instead of the branches: one cluster of 8192 350 -> 450 us.)
     constexpr int kBatch = 32;
     auto members = [&](int base) { return base + lane < s1 ? (lp ? lp[base + lane] : base + lane) : 0; };
     int next = members(s0);
@@ -320,12 +289,13 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) {
                 if (full || m + q < nm) {
-                    a0 += (double)bf16lo_to_f32(w[q]);
-                    a1 += (double)bf16hi_to_f32(w[q]);
+                    passes(base + m, q, __builtin_amdgcn_readlane(mine, (m + q) & 63), w[q]);
+                    a.a0 += (double)bf16lo_to_f32(w[q]);
+                    a.a1 += (double)bf16hi_to_f32(w[q]);
                     if constexpr (kRange) {
                         const u16x2 size = __builtin_bit_cast(u16x2, w[q] & 0x7fff7fffu);
-                        largest = __builtin_elementwise_max(largest, size);
-                        smallest = __builtin_elementwise_min(smallest, (u16x2)(size - (unsigned short)1));     // (zero: the largest number)
+                        a.largest = __builtin_elementwise_max(a.largest, size);
+                        a.smallest = __builtin_elementwise_min(a.smallest, (u16x2)(size - (unsigned short)1));     // (zero: the largest number)
                     }
                 }
             }
@@ -335,8 +305,43 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
             else batch(m, std::false_type{});
         }
     }
+    return a;
+}
+
+// Both dims of a lane: the sum over n rows (n > 0) divided once, rounded once to bf16.
+__device__ __forceinline__ uint32_t mean_dword(const RowSum& a, int n)
+{
+    const double den = (double)n;
+    return (uint32_t)f64_to_bf16_rne(a.a0 / den) | ((uint32_t)f64_to_bf16_rne(a.a1 / den) << 16);
+}
+
+// One wave per cluster of [k0, k): fp64 sum of the member rows in list order, mean rounded once to bf16.
+// Lane l owns dims 2l and 2l+1.  Empty cluster: `fallback` row if given (else zeros).
+// mean_out row index = out_row0 + cluster id.  count_out optional.
+template <bool kRange>
+__global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __restrict__ X, long long x_unit_rows,
+                                                           const int32_t* __restrict__ list, long long list_stride,
+                                                           const int32_t* __restrict__ start, long long start_stride,
+                                                           int k0, int k, uint16_t* __restrict__ mean_out,
+                                                           long long out_unit_rows, int out_row0,
+                                                           const uint16_t* __restrict__ fallback,
+                                                           long long fb_unit_rows, int32_t* __restrict__ count_out,
+                                                           long long count_stride, int count_off,
+                                                           double* __restrict__ sum_out, long long sum_unit_rows,
+                                                           uint32_t* __restrict__ range_out, uint32_t* __restrict__ changed_out)
+{
+    const int u = blockIdx.y;
+    // (units start at different clusters: workgroups 8 apart share an L2 slice, and the same cluster's of all units would meet there.
+    // 64 units of 8192 equal keys, five iterations: 8886 -> 8453 us)
+    const int f = k0 + (int)((blockIdx.x + (unsigned)u) % gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (f >= k) return;
+    const int s0 = start[u * start_stride + f], s1 = start[u * start_stride + f + 1];
+    const uint32_t* Xu = reinterpret_cast<const uint32_t*>(X + (long long)u * x_unit_rows * kHeadDim);
+    const int32_t* lp = list ? list + u * list_stride : nullptr;
+    const RowSum a = sum_of_rows<kRange>(Xu, lp, s0, s1, [](int, int, int, uint32_t) {});
     if constexpr (kRange) {
-        int hi = max((int)largest.x, (int)largest.y) >> 7, lo = min((int)smallest.x, (int)smallest.y);
+        int hi = max((int)a.largest.x, (int)a.largest.y) >> 7, lo = min((int)a.smallest.x, (int)a.smallest.y);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             hi = max(hi, __shfl_xor(hi, off, 64));
@@ -348,8 +353,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     const int n = s1 - s0;
     uint32_t outw;
     if (n > 0) {
-        const double inv = (double)n;
-        outw = (uint32_t)f64_to_bf16_rne(a0 / inv) | ((uint32_t)f64_to_bf16_rne(a1 / inv) << 16);
+        outw = mean_dword(a, n);
     } else if (fallback) {
         outw = reinterpret_cast<const uint32_t*>(fallback + ((long long)u * fb_unit_rows + f) * kHeadDim)[lane];
     } else {
@@ -364,7 +368,135 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     }
     *row = outw;
     if (count_out && lane == 0) count_out[u * count_stride + count_off + f] = n;
-    if (sum_out) reinterpret_cast<double2*>(sum_out + ((long long)u * sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a0, a1);
+    if (sum_out) reinterpret_cast<double2*>(sum_out + ((long long)u * sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a.a0, a.a1);
+}
+
+// Rows list[p0 .. min(p0 + kRows, end)) of X to places p0 ... of `to`, and those from row t0 on to `kept`, by one wave; sixteen
+// lanes a row.
+template <int kRows>
+struct RowMove {
+    int place, mine;
+    uint4 w[kRows / 4];
+    __device__ __forceinline__ void ask_members(const int32_t* __restrict__ list, int p0, int end)
+    {
+        place = p0;
+        mine = list[min(p0 + (int)(threadIdx.x & (kRows - 1)), end - 1)];
+    }
+    __device__ __forceinline__ int row(int i) const { return __shfl(mine, 4 * i + (int)((threadIdx.x & 63) >> 4), 64); }
+    __device__ __forceinline__ void ask_rows(const uint4* __restrict__ X)
+    {
+#pragma unroll
+        for (int i = 0; i < kRows / 4; ++i) w[i] = load_once(X + (long long)row(i) * 16 + (threadIdx.x & 15));
+    }
+    __device__ __forceinline__ void store(int end, uint4* __restrict__ to, uint4* __restrict__ kept, int t0) const
+    {
+        const int c = threadIdx.x & 15;
+#pragma unroll
+        for (int i = 0; i < kRows / 4; ++i) {
+            const int at = place + 4 * i + (int)((threadIdx.x & 63) >> 4), r = row(i);
+            if (at < end) {
+                store_once(to + (long long)at * 16 + c, w[i]);
+                if (kept && r >= t0) store_once(kept + (long long)(r - t0) * 16 + c, w[i]);
+            }
+        }
+    }
+};
+constexpr int kMoveRows = 32;
+
+// Rows to their stored places and the means of the values' clusters in one launch (bf16 storage).  One wave a cluster reads its
+// members once, stores them side by side and sums them as cluster_mean_kernel does; keys the same way where their means are
+// wanted too (p.key_means), else kMoveRows rows a wave by their places, in the workgroups behind those of the clusters.  Bound by
+// memory where the waves fill the chip: refresh of eight 8K contexts 626 -> 552 us (gather, key and value means were a launch each: 178 -> 125 us), build
+// of sixteen 128K prompts 20.30 -> 19.67 ms, resumed generation 1227 -> 1144 us.
+// A long cluster's sum is a chain of trips to memory, so its rows are moved by whichever of the workgroup's waves are done with theirs.
+__global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
+{
+    __shared__ int long_from[4], long_end[4], ticket[4];
+    const int u = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per_table = (p.f1 - p.f0 + 3) / 4, of_clusters = p.key_means ? 2 * per_table : per_table;
+    const int32_t* list = p.list + u * p.list_stride;
+    const bool by_place = (int)blockIdx.x >= of_clusters;
+    const int places = (p.n + 4 * kMoveRows - 1) / (4 * kMoveRows), group = (int)blockIdx.x - (by_place ? of_clusters : 0);
+    const bool keys = by_place ? group < places : group >= per_table;
+    const uint4* X = reinterpret_cast<const uint4*>(keys ? p.K : p.V) + (long long)u * p.src_unit_rows * 16;
+    uint4* to = reinterpret_cast<uint4*>(keys ? p.dstK : p.dstV) + ((long long)u * p.dst_unit_rows + p.dst_row0) * 16;
+    uint4* kept = reinterpret_cast<uint4*>(keys ? p.seq.K : p.seq.V);
+    if (kept) kept += (long long)u * p.seq.unit_rows * 16;
+    if (by_place) {
+        const int p0 = ((keys ? group : group - places) * 4 + wave) * kMoveRows;
+        if (p0 >= p.n) return;
+        RowMove<kMoveRows> m;
+        m.ask_members(list, p0, p.n);
+        m.ask_rows(X);
+        m.store(p.n, to, kept, p.seq.t0);
+        return;
+    }
+    // (units and tables start at different clusters: workgroups 8 apart share an L2 slice, and the same cluster's of all units would meet
+    // there.  All 8192 rows in one cluster, 8 / 64 units: 639 / 2412 us unturned, 345 / 541 turned)
+    const unsigned turned = (unsigned)(keys ? group - per_table + 4 : group) + (unsigned)u;
+    const int f = p.f0 + (int)(turned % (unsigned)per_table) * 4 + wave;
+    const int32_t* start = p.start + u * p.start_stride;
+    const int s0 = f < p.f1 ? start[f] : 0, s1 = f < p.f1 ? start[f + 1] : 0, n = s1 - s0;
+    const bool is_long = n > p.long_cluster;
+    if (lane == 0) {
+        long_from[wave] = is_long && !p.all_by_place ? s0 : 0;
+        long_end[wave] = is_long && !p.all_by_place ? s1 : 0;
+        ticket[wave] = 0;
+    }
+    __syncthreads();
+    if (f < p.f1) {
+        const uint32_t* Xd = reinterpret_cast<const uint32_t*>(X);
+        RowSum a;
+        if (is_long) {
+            a = sum_of_rows<false>(Xd, list, s0, s1, [](int, int, int, uint32_t) {});
+        } else {
+            uint32_t* to_d = reinterpret_cast<uint32_t*>(to);
+            uint32_t* kept_d = reinterpret_cast<uint32_t*>(kept);
+            a = sum_of_rows<false>(Xd, list, s0, s1, [&](int at, int q, int row, uint32_t w) {
+                store_once(to_d + (long long)at * 64 + (q * 64 + lane), w);
+                if (kept && row >= p.seq.t0) store_once(kept_d + (long long)(row - p.seq.t0) * 64 + lane, w);
+            });
+        }
+        const long long table = (long long)u * p.tab_rows + f;
+        uint32_t* mean = reinterpret_cast<uint32_t*>(keys ? p.key_means : p.value_means) + table * 64 + lane;
+        if (n > 0) *mean = mean_dword(a, n);
+        else if (!keys || !p.key_keeps) *mean = 0u;
+        if (!keys && lane == 0) p.counts[table] = n;
+        double* sums = keys ? p.key_sums : p.value_sums;
+        if (sums) reinterpret_cast<double2*>(sums + ((long long)u * p.sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a.a0, a.a1);
+    }
+#pragma unroll 1
+    for (int w = 0; w < 4; ++w) {
+        const int from = __builtin_amdgcn_readfirstlane(long_from[w]), end = __builtin_amdgcn_readfirstlane(long_end[w]);
+        // (a piece's rows are asked for in front of the stores of the one before: loads behind stores would wait for those)
+        constexpr int kPiece = 16;
+        const int pieces = (end - from + kPiece - 1) / kPiece;
+        auto next = [&] {
+            int t = 0;
+            if (lane == 0) t = atomicAdd(&ticket[w], 1);
+            return __builtin_amdgcn_readfirstlane(t);
+        };
+        auto members = [&](RowMove<kPiece>& m, int t) { m.ask_members(list, from + min(t, pieces - 1) * kPiece, end); };
+        if (pieces == 0) continue;
+        int t0 = next(), t1 = next();
+        if (t0 >= pieces) continue;
+        RowMove<kPiece> m0, m1;
+        members(m0, t0);
+        members(m1, t1);
+        m0.ask_rows(X);
+        while (true) {
+            const int t2 = next();
+            RowMove<kPiece> m2;
+            members(m2, t2);
+            if (t1 < pieces) m1.ask_rows(X);
+            m0.store(end, to, kept, p.seq.t0);
+            if (t1 >= pieces) break;
+            m0 = m1;
+            m1.place = m2.place;
+            m1.mine = m2.mine;
+            t1 = t2;
+        }
+    }
 }
 
 // Stored tables of the coarse clusters [c0, c1), keys (z = 0) and values, from those of their fine clusters (Sec. 3.4: a coarse
@@ -539,15 +671,20 @@ hipError_t launch_block_lists(const int32_t* ids, long long ids_stride, const in
     return hipGetLastError();
 }
 
-hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
-                              long long list_stride, int n, int U, void* dstK, void* dstV, long long dst_unit_rows,
-                              int dst_row0, const SequenceCopy& seq, hipStream_t s)
+// A cluster's wave that also stores its rows is the longer chain, and moves a row's bytes once less: it pays where the waves fill the chip.
+// Us, rows stored by place / by clusters, tables of keys and values given their clustering: 1 unit of 256 clusters 34.8 / 36.7, 2 of 256
+// 37.1 / 38.1, 4 of 256 42.3 / 41.9, 8 of 256 56.2 / 52.3, 64 of 256 217 / 185; builds of five iterations, values only: 1 x 46 148.4 / 154.4,
+// 8 x 128 284 / 287, 16 x 256 460 / 464, 8 x 1024 613.9 / 610.7, 64 x 256 817 / 807.
+constexpr int kFewClustersOfTwo = 768, kFewClustersOfOne = 6144;      // of all units
+hipError_t launch_stored_rows(StoredRows p, int U, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    const long long threads = (long long)n * 16;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((threads + 255) / 256), U), dim3(256), 0, s,
-                       (const uint4*)srcK, (const uint4*)srcV, src_unit_rows, list, list_stride, n, (uint4*)dstK,
-                       (uint4*)dstV, dst_unit_rows, dst_row0, seq);
+    if (p.n <= 0 || p.f1 <= p.f0) return hipSuccess;
+    p.long_cluster = std::max(128, 4 * (p.n / (p.f1 - p.f0)));
+    const int per_table = (p.f1 - p.f0 + 3) / 4, places = (p.n + 4 * kMoveRows - 1) / (4 * kMoveRows);
+    p.all_by_place = (long long)U * (p.f1 - p.f0) <= (p.key_means ? kFewClustersOfTwo : kFewClustersOfOne);
+    if (p.all_by_place) p.long_cluster = -1;
+    const int groups = per_table * (p.key_means ? 2 : 1) + places * (p.all_by_place ? 2 : p.key_means ? 0 : 1);
+    hipLaunchKernelGGL(stored_rows_kernel, dim3(groups, U), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

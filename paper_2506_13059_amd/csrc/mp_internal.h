@@ -221,10 +221,31 @@ struct SequenceCopy {
     int t0;
 };
 
-hipError_t launch_gather_rows(const void* srcK, const void* srcV, long long src_unit_rows, const int32_t* list,
-                              long long list_stride, int n, int U, void* dstK, void* dstV, long long dst_unit_rows,
-                              int dst_row0, const SequenceCopy& seq, hipStream_t s);
-// The same into 8-bit storage: dstK / dstV receive 128 e4m3 codes per row, scales [U, dst_unit_rows, 2] the
+// The stored rows of a range in cluster order, dst row dst_row0 + p = source row list[p] for p < n, and the tables of its fine
+// clusters [f0, f1), members list[start[f] .. start[f + 1]) ascending: means as launch_cluster_means gives them, counts, sums.
+struct StoredRows {
+    const void *K, *V;             // 256-byte rows
+    long long src_unit_rows;
+    const int32_t* list;
+    long long list_stride;
+    const int32_t* start;
+    long long start_stride;
+    int f0, f1, n;
+    void *dstK, *dstV;
+    long long dst_unit_rows;
+    int dst_row0;
+    SequenceCopy seq;
+    uint16_t *value_means, *key_means;   // [U, tab_rows, 128]; key means optional (the means of K's rows)
+    bool key_keeps;                // an empty cluster's key mean stays as it is (else zeros)
+    int32_t* counts;               // [U, tab_rows]
+    long long tab_rows;
+    double *value_sums, *key_sums; // [U, sum_unit_rows, 128], optional
+    long long sum_unit_rows;
+    bool all_by_place;             // set by the launch: a cluster's wave stores no rows,
+    int long_cluster;              // or not those of clusters of more members
+};
+hipError_t launch_stored_rows(StoredRows p, int U, hipStream_t s);
+// Rows in cluster order into 8-bit storage: dstK / dstV receive 128 e4m3 codes per row, scales [U, dst_unit_rows, 2] the
 // rows' fp32 scales {key, value} (scale = max|x| / 448, 1 for a zero row; code = round-to-nearest-even(x / scale)).
 // For a value row x is the row; for a key row x = fp32(key) - fp32(Kc[ids[point]]), the residual from the key
 // centroid of the point's fine cluster (ids [U, ids_stride] by local point, Kc [U, kc_unit_rows, 128] bf16).
