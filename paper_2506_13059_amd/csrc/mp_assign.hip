@@ -294,6 +294,7 @@ constexpr int kHalfTiles = 16;                   // tiles whose slots fit the si
 constexpr int kNearCap = 256;                    // (a multiple of sixteen)
 constexpr int kResidentMaxK = 512;
 constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
+constexpr int kWidePairs = 256;                  // (block, unit) pairs up to which workgroups have sixteen waves
 constexpr int kCoarseLds = 160 * 1024 - 2048;    // of a compute unit, less what the coarse level's kernel has besides
 constexpr int kChangedTwiceK = 288;              // 2 x (288 x 268 + 1.6 K)
 constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
@@ -1335,7 +1336,11 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
     if (nb > cnt_stride || U > 65535) return hipErrorInvalidValue;
     const int n_chunks = (max_pts + kPtsPerWg - 1) / kPtsPerWg;
     if (assign_is_resident(max_pts, max_k)) {
-        // two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen
+        // Two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen.  Up to 256 blocks
+        // of all units, sixteen take them in any case when all centroids are looked at: a wave has a chunk or two there, and half as many
+        // workgroups fetch the centroids.  Builds, us, eight / sixteen waves: 32 blocks of 8192 x 256 645 / 639 (keys without clusters 924 /
+        // 914), 8 of them 642 / 633, 64 1133 / 1118, 128 1688 / 1677, 256 2779 / 2762; 2048 19853 / 19933.  (Settled iterations: 32 of
+        // them 644 / 651, 2048 19842 / 20140, keys without clusters 924 / 925, 64 1133 / 1111.)
         static bool configured[4] = {};
         auto go = [&](auto kernel, int waves, int bytes_per_row, bool& set) {
             return launch_resident(kernel, waves, bytes_per_row, set, X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows,
@@ -1343,7 +1348,7 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
         };
         if (st.changed)
             return max_k <= kChangedTwiceK ? go(assign_changed_kernel<8>, 8, 268, configured[0]) : go(assign_changed_kernel<16>, 16, 268, configured[1]);
-        return max_k <= kResidentTwiceK ? go(assign_resident_kernel<8>, 8, 260, configured[2]) : go(assign_resident_kernel<16>, 16, 260, configured[3]);
+        return max_k <= kResidentTwiceK && (long long)nb * U > kWidePairs ? go(assign_resident_kernel<8>, 8, 260, configured[2]) : go(assign_resident_kernel<16>, 16, 260, configured[3]);
     }
     hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
                        c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, mv);
