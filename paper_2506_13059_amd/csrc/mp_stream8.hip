@@ -278,26 +278,51 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
     if (weights == Weights::raised) scale_sums(st, 1.f / kRaise);
 }
 
-// As value_stream_kernel; the selected keys are 8-bit rows, the centroid terms and the tail bf16 rows.
+// As value_stream_kernel; the selected keys, the launch's last source, are 8-bit rows, the centroid terms (src[0], which rides along) and the
+// tail bf16 rows.  rows, slots, counts, rows_stride, chunk0, chunk_rows: the keys' source, n_terms: the number of the terms (null: none), as scalars
+// of the launch, so that the first row numbers and the counts do not wait for the other arguments.
 template <int G>
-__global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassParams p)
+__global__ __launch_bounds__(256, 2) void value_stream8_kernel(const int32_t* rows, const int32_t* slots, const int32_t* counts, const int32_t* n_terms,
+                                                               int rows_stride, int n_units, int chunk0, int chunk_rows, const ValuePassParams p)
 {
     constexpr int kWaves = 4;
     extern __shared__ __align__(256) unsigned char ring_lds[];
-    const int tid = threadIdx.x, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)ring_lds;
     const uint32_t ring = lds0 + (uint32_t)(wave * kRing8), strips = lds0 + (uint32_t)(kWaves * kRing8 + wave * kStrips8);
     const uint32_t guest_strip = strips + 16 * kStrip;
+    StreamShare w;
+    w.chunk = blockIdx.x / n_units;
+    const int u = w.u = blockIdx.x - w.chunk * n_units;
+    const bool keys = w.chunk >= chunk0;     // (the others have rows of the tail)
+    typedef const __attribute__((address_space(4))) int32_t constant_int;
+    int counted = 0, unusual = 0, terms = 0;
+    if (keys) {
+        counted = ((constant_int*)counts)[u];
+        unusual = ((constant_int*)counts)[n_units];
+        if (n_terms) terms = ((constant_int*)n_terms)[u];
+        const int first = (w.chunk - chunk0) * chunk_rows + wave * ((chunk_rows / kWaves + kTile - 1) / kTile * kTile);
+        const long long at = (long long)u * rows_stride + min(first + (tid & 63), rows_stride - 1);
+        load_to_lds<4, false>(rows + at, strips);
+        load_to_lds<4, false>(slots + at, strips + 8 * kStrip);
+    }
     touch_arguments(p);
-    int unusual = 0;
-    const StreamShare w = stream_share<kWaves>(p, [&](const RowSource& S, int u, int first) {
-        fetch_strip(S.rows, S, u, first, strips);
-        if (!S.row_slot) return;
-        fetch_strip(S.row_slot, S, u, first, strips + 8 * kStrip);
-        unusual = ((const __attribute__((address_space(4))) int32_t*)S.count_dev)[p.n_units];
-    });
-    const RowSource& S = p.src[w.source];
-    const int u = w.u;
+    asm volatile("" ::"s"(counted), "s"(unusual), "s"(terms));
+    const RowSource& S = p.src[keys ? p.n_sources - 1 : p.n_sources - 2];
+    w.begin = (w.chunk - S.chunk0) * S.chunk_rows;
+    w.end = min(w.begin + S.chunk_rows, keys ? min(counted, S.count_max) : S.count_max);
+    const int wave_rows = (S.chunk_rows / kWaves + kTile - 1) / kTile * kTile;
+    w.w0 = w.begin + wave * wave_rows;
+    w.w1 = min(w.w0 + wave_rows, w.end);
+    w.g0 = w.g1 = 0;
+    if (n_terms && keys) {
+        const long long n = min(terms, p.src[0].count_max), k = w.chunk - S.chunk0;
+        w.g0 = (int)(n * k / S.n_chunks);
+        w.g1 = (int)(n * (k + 1) / S.n_chunks);
+    }
+    const int per = ((w.g1 - w.g0 + kWaves - 1) / kWaves + 15) & ~15;
+    w.a = w.g0 + wave * per;
+    w.b = min(w.a + per, w.g1);
     float* part = p.partials + ((long long)u * p.chunks_per_unit + w.chunk) * G * kPartStride;
     if (w.w0 >= w.w1) nothing_on_its_way();  // (what was asked for early is in place before its space is used or given back)
     if (w.begin >= w.end && w.g0 >= w.g1) {
@@ -311,8 +336,7 @@ __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const ValuePassPa
     clear_state(st);
     auto guest = [&] { if (w.a < w.b) fetch_strip(p.src[0].rows, p.src[0], u, w.a, guest_strip); };
     if (w.w0 < w.w1) {
-        if (S.scores) stream_tiles<G, true, true>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
-        else if (S.row_scale) stream_tiles8<G>(st, S, p, u, unusual != 0, w.w0, w.w1, ring, strips, guest);
+        if (keys) stream_tiles8<G>(st, S, p, u, unusual != 0, w.w0, w.w1, ring, strips, guest);
         else stream_tiles<G, false, false>(st, S, p, u, w.w0, w.w1, ring, strips, guest);
     } else {
         guest();
@@ -337,7 +361,9 @@ hipError_t launch_stream8_g(const ValuePassParams& p, hipStream_t s)
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((value_stream8_kernel<G>), dim3((unsigned)blocks), dim3(256), smem, s, p);
+    const RowSource& S = p.src[p.n_sources - 1];
+    hipLaunchKernelGGL((value_stream8_kernel<G>), dim3((unsigned)blocks), dim3(256), smem, s, S.rows, S.row_slot, S.count_dev,
+                       S.guest ? p.src[0].count_dev : nullptr, (int)S.rows_stride, p.n_units, S.chunk0, S.chunk_rows, p);
     return hipGetLastError();
 }
 
@@ -345,6 +371,14 @@ hipError_t launch_stream8_g(const ValuePassParams& p, hipStream_t s)
 
 hipError_t launch_value_stream8(const ValuePassParams& p, int G, hipStream_t s)
 {
+    // the terms, if they ride along, perhaps a tail, the selected keys
+    if (p.n_sources < 1 || p.n_sources > 3) return hipErrorInvalidValue;
+    const RowSource& S = p.src[p.n_sources - 1];
+    const int tails = p.n_sources - 1 - (S.guest ? 1 : 0);
+    if (!S.rows || !S.row_slot || !S.row_scale || !S.count_dev || S.row0 != 0 || S.rows_stride > 0x7fffffff || tails < 0 || tails > 1 ||
+        (S.guest && (!p.src[0].scores || !p.src[0].count_dev || p.src[0].n_chunks != 0)) ||
+        (tails == 1 && (p.src[p.n_sources - 2].rows || p.src[p.n_sources - 2].count_dev || p.src[p.n_sources - 2].row0 != 0)) || (tails == 0 && S.chunk0 != 0))
+        return hipErrorInvalidValue;
     switch (G) {
         case 2: return launch_stream8_g<2>(p, s);
         case 3: return launch_stream8_g<3>(p, s);
