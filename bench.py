@@ -245,7 +245,7 @@ def main():
         "input_generation_s": round(t_gen, 2),
         "paper_context": "paper reports up to 4.5x attention speedup vs FlashDecoding on an NVIDIA A6000 "
                          "(2.8x on A100), batch 16, 128K context",
-        "roofline": {"bound": "hbm", "kernel": "value_stream_kernel", "achieved": round(r0["vp_gbps"], 1),
+        "roofline": {"bound": "hbm", "kernel": "value_terms_kernel", "achieved": round(r0["vp_gbps"], 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(r0["vp_gbps"] / HBM_PEAK_GBPS, 4),
                      "traffic": measured_traffic(w.name, kb0),
                      "bytes_per_launch": int(r0["vp_bytes"]), "avg_launch_us": round(r0["stage_us"]["value"], 2)},

@@ -10,8 +10,8 @@
 //                  and become bf16 there: one product of 32 rows each of the eight groups of dims
 // Bound by the memory system and its latency: two vector instructions a code pair are all that 8 bits cost, about 200 for 32
 // rows; the vector-ALU kernel needs 420 for 16.
-// Whole step, vector-ALU kernel -> here: 64 units, 3125 of 100003 keys and a tail of 139, 4 heads 54.7 -> 44.2 us; 64 x 4096, 8
-// heads 67.3 -> 42.3; 128 x 4096, 4 heads 64.3 -> 52.0 (one and two heads: bytes_on_vector_alu in mp_plan.h).
+// Whole step, vector-ALU kernel -> here: 64 units, 3125 of 100003 keys and a tail of 139, 4 heads 54.7 -> 42.7 us; 64 x 4096, 8
+// heads 67.3 -> 42.3 and 128 x 4096, 4 heads 64.3 -> 52.0 when they were measured (one and two heads: bytes_on_vector_alu in mp_plan.h).
 #include "mp_stream_tiles.h"
 
 namespace mp {
@@ -280,7 +280,8 @@ __device__ __forceinline__ void stream_tiles8(StreamState<G>& st, const RowSourc
 
 // As value_stream_kernel; the selected keys, the launch's last source, are 8-bit rows, the centroid terms (src[0], which rides along) and the
 // tail bf16 rows.  rows, slots, counts, rows_stride, chunk0, chunk_rows: the keys' source, n_terms: the number of the terms (null: none), as scalars
-// of the launch, so that the first row numbers and the counts do not wait for the other arguments.
+// of the launch, so that the first row numbers and the counts do not wait for the other arguments (whole
+// step: 64 units, 3125 of 100003 keys and a tail 43.6 -> 42.7 us; 8 units x 4096 keys 24.1 -> 23.5; 32 units of 8 heads and a tail 36.7 -> 35.7).
 template <int G>
 __global__ __launch_bounds__(256, 2) void value_stream8_kernel(const int32_t* rows, const int32_t* slots, const int32_t* counts, const int32_t* n_terms,
                                                                int rows_stride, int n_units, int chunk0, int chunk_rows, const ValuePassParams p)
