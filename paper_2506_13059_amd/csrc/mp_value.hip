@@ -697,7 +697,7 @@ __global__ __launch_bounds__(128 * kSplits) void merge_kernel(const float* __res
         const float Mn = fmaxf(M, bm);
         if (Mn == -INFINITY) continue;                       // only empty chunks so far
         const float keep = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
-        a *= keep;
+        a = keep > 0.f ? a * keep : 0.f;                     // (what has vanished may hold an infinity or a NaN)
         L *= keep;
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
@@ -724,8 +724,10 @@ __global__ __launch_bounds__(128 * kSplits) void merge_kernel(const float* __res
 #pragma unroll
         for (int s = 0; s < kSplits; ++s) {
             const float w = (share[s][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(share[s][0] - Mt);
-            a = fmaf(share[s][2 + d], w, a);
-            L = fmaf(share[s][1], w, L);
+            if (w > 0.f) {                                   // (as inside a share)
+                a = fmaf(share[s][2 + d], w, a);
+                L = fmaf(share[s][1], w, L);
+            }
         }
         M = Mt;
     }
