@@ -602,7 +602,7 @@ __device__ __forceinline__ int nearest_exact(const Points& X, int t, const unsig
 // a point's four lanes.
 struct Decided {
     int id;
-    float best, other;       // the scores of an AssignState
+    float score, other;      // those of an AssignState
 };
 template <typename Points, typename IdOf>
 __device__ __forceinline__ Decided nearest_of_all(const Points& X, int t, const unsigned char* rows_lds, uint32_t lds0, uint32_t ci0,
@@ -656,8 +656,9 @@ __device__ __forceinline__ Decided nearest_of_all(const Points& X, int t, const 
         place = ob > best ? op : place;                      // (equal ones are nearer than the margin)
         best = fmaxf(best, ob);
     }
-    const bool near = !(best - second > near_margin(fmaxf(n2, c2max)) + fabsf(best) * (1.0f / 65536.0f));
-    Decided d{id_of(min(place, k - 1)), best, near ? best : second};
+    const float margin = near_margin(fmaxf(n2, c2max)) + fabsf(best) * (1.0f / 65536.0f);
+    const bool near = !(best - second > margin);
+    Decided d{id_of(min(place, k - 1)), kept_score(near, best, margin), near ? best : second};
     if (__any(near)) {
         const int id = nearest_exact(X, t, rows_lds, lds0, ci0, k, c2max, true, best, id_of);
         if (near) d.id = id;
@@ -744,8 +745,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
             if (lane == 0) marks[chunk] = marked;
         }
         if (t < x1) {
-            // (of a near tie the winner's score is no smaller than the best one, but for their errors, and no other is larger)
-            if (st.scores) st.scores[u * st.stride + t] = make_float2(r.best, r.near ? r.best : r.second);
+            if (st.scores) st.scores[u * st.stride + t] = make_float2(kept_score(r.near, r.best, near_margin_of_best(r.m, r.best)), r.near ? r.best : r.second);
             if (r.near) {
                 const int pos = atomicAdd(&near_n, 1);
                 if (pos < kNearCap) {
@@ -773,14 +773,14 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_resident_kernel(const uint1
 
 // The same step where the one before has left the scores it found (AssignState): a centroid that has not changed since scores
 // what it did, so the points have to be compared with the changed ones only.  Of a point there is the score of its cluster's
-// centroid, s, and a bound on the scores of all others, r >= what any of them scored.  With b the best and b2 the second best score
+// centroid, s, and a bound on the scores of all others, r >= what any of them scored (of a near tie, whose best score may be another's: s a margin below it, r that score).  With b the best and b2 the second best score
 // among the changed centroids (its own among them if that changed):
 //   - b is ahead of b2 and of r (and of s, if its own has not changed) by more than the margin: b's centroid is the one;
 //   - its own has not changed and s is ahead of b by more than the margin: it keeps its cluster, which won the comparison with
 //     the unchanged ones before, exactly where that was close;
 //   - otherwise it goes onto a list and is compared with all centroids afterwards (nearest_of_all).
-// The margins are those of two scores of one step (mp_margin.h): an older score has the error of its own centroid, which is still
-// one of the block, and the largest |c|^2 is taken over all of them.
+// The margins are those of two scores of one step (mp_margin.h): an older score that is compared as a centroid's own has the error of
+// that centroid, which is still one of the block, and the largest |c|^2 is taken over all of them.
 // 2048 blocks of 8192 keys, 256 centroids: 80 to 16 per cent of the centroids change in iterations 4 to 10, 3 to 0.5 per
 // cent of the points go onto the list, and a launch takes 1.2 to 0.99 ms (compared with all: 1.13 to 1.29, by the clock it gets).  Bound by
 // the keys it reads all the same: 0.81 ms without a single product, 0.93 with the points' ids and scores.  32 such blocks (of which 30 to 1 per cent
@@ -912,7 +912,7 @@ __global__ __launch_bounds__(64 * kW, 4) void assign_changed_kernel(const uint16
         const Decided d = nearest_of_all(X_u, t, rows_lds, lds0, ci0, k, c2max, [&](int place) { return (int)ids[place]; });
         if (lane_id() < 16) {
             assign_u[t] = k0 + d.id;
-            scores_u[t] = make_float2(d.best, d.other);
+            scores_u[t] = make_float2(d.score, d.other);
         }
     }
 }

@@ -33,4 +33,10 @@ constexpr float near_margin_of_best(float m, float best)
     return (3.25f * m + (best < 0.0f ? -best : best)) * (1.0f / 65536.0f) + kNearFloor;
 }
 
+// What a step keeps as the score of the centroid it chose, for a later step to compare with the scores of others.  The best score
+// is that centroid's own unless it was a near tie: then another one's, whose error goes with an M it may take with it when it
+// moves away.  The chosen one's true score is no lower than that one's, which is at least the best less its error, so the best less
+// the margin (more than twice that error) is below it with nothing left to allow for.
+constexpr float kept_score(bool near, float best, float margin) { return near ? best - margin : best; }
+
 }  // namespace mp
