@@ -724,10 +724,9 @@ __global__ __launch_bounds__(128 * kSplits) void merge_kernel(const float* __res
 #pragma unroll
         for (int s = 0; s < kSplits; ++s) {
             const float w = (share[s][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(share[s][0] - Mt);
-            if (w > 0.f) {                                   // (as inside a share)
-                a = fmaf(share[s][2 + d], w, a);
-                L = fmaf(share[s][1], w, L);
-            }
+            const float x = share[s][2 + d];
+            a = fmaf(w > 0.f ? x : 0.f, w, a);               // (a vanished share may hold an infinity or a NaN, too)
+            L = fmaf(share[s][1], w, L);
         }
         M = Mt;
     }
