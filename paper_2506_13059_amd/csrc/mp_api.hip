@@ -483,7 +483,9 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     if (chunk0 > ctx->Pcap) return fail(ctx, MP_ECAPACITY, "mp_decode_attention: %d chunks > workspace %d", chunk0, ctx->Pcap);
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[0], s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[1], s));
-    MP_HIP(ctx, launch_score_select(sp, ctx->n_cus, s));
+    if (ctx->helpers_test && sp.helpers) MP_HIP(ctx, launch_fill(ctx->early_done, U, ctx->helpers_test == 2 ? sp.helpers : -(1 << 20), s));
+    MP_HIP(ctx, launch_score_select(sp, ctx->n_cus, ctx->helpers_test != 2, s));
+    if (ctx->helpers_test == 1 && sp.helpers) MP_HIP(ctx, launch_fill(ctx->early_done, U, 0, s));
     if (ctx->timing) MP_HIP(ctx, hipEventRecord(ctx->ev[2], s));
     if (chunk0 > 0)
         MP_HIP(ctx, !on_matrix ? launch_value_pass(vp, G, s) : bytes && main_max > 0 ? launch_value_stream8(vp, G, s) : own_wave ? launch_value_terms(vp, G, s) : launch_value_stream(vp, G, s));
@@ -706,6 +708,17 @@ mp_status mp_get_counters(mp_ctx* ctx, int32_t* counters, void* stream)
     if (!ctx->has_index || !ctx->decoded) return fail(ctx, MP_ESTATE, "mp_get_counters: no decode call on this index yet");
     MP_HIP(ctx, hipMemcpyAsync(counters, ctx->counters, (size_t)ctx->U * 4 * sizeof(int32_t), hipMemcpyDeviceToDevice,
                                (hipStream_t)stream));
+    return MP_OK;
+}
+
+// For the library's own tests (so it is not declared with the rest): whether a unit's workgroup takes its helpers' logits or works the
+// level out for itself is a matter of time otherwise, and the results are the same.  how: 0 as planned; 1 it never takes them; 2 no helpers
+// are launched and it takes what those of the call before left (right for the same query only).  *n_helpers: per unit, as planned.
+mp_status mp_test_helpers(mp_ctx* ctx, int32_t how, int32_t* n_helpers)
+{
+    if (!ctx || !n_helpers || how < 0 || how > 2) return fail(ctx, MP_EINVAL, "mp_test_helpers: bad arguments");
+    ctx->helpers_test = how;
+    *n_helpers = ctx->early ? score_helpers(ctx->U, ctx->n_cus, ctx->cfg.levels, ctx->n_fine) : 0;
     return MP_OK;
 }
 

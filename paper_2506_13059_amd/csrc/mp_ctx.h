@@ -124,6 +124,7 @@ struct mp_ctx {
     double* early = nullptr;       // [U, early_cap, 2, G in fours] logits worked out beside the coarse level (see ScoreParams; where the plan has them)
     int32_t early_cap = 0;         // most fine clusters a unit can have there
     int32_t* early_done = nullptr; // [U] all zero between launches
+    int helpers_test = 0;          // mp_test_helpers
     unsigned long long* key_c = nullptr;   // [U, Ccap] keys the coarse clusters were ranked by in the last call
     unsigned long long* key_f = nullptr;   // [U, Fcap] the same for the fine level, by candidate position
     int32_t* key_mode = nullptr;   // [U, 2] what those keys are (see launch_scatter_selection)

@@ -635,7 +635,19 @@ __global__ __launch_bounds__(256) void scatter_selection_kernel(const int32_t* _
     }
 }
 
+__global__ __launch_bounds__(256) void fill_kernel(int32_t* __restrict__ dst, int n, int32_t value)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dst[i] = value;
+}
+
 }  // namespace
+
+hipError_t launch_fill(int32_t* dst, int n, int32_t value, hipStream_t s)
+{
+    hipLaunchKernelGGL(fill_kernel, dim3((n + 255) / 256), dim3(256), 0, s, dst, n, value);
+    return hipGetLastError();
+}
 
 hipError_t launch_scatter_selection(const int32_t* cand, long long cand_stride, const int32_t* n_cand_dev,
                                     int n_cand_fixed, const uint8_t* flag, const unsigned long long* keys,

@@ -138,8 +138,9 @@ struct ScoreParams {
     int G, U;
 };
 
-// n_compute_units: of the device the launch goes to (decides whether units get a second, shadow workgroup).
-hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, hipStream_t stream);
+// n_compute_units: of the device the launch goes to (decides whether units get a second, shadow workgroup).  helpers_run: no where
+// (tests) units' workgroups take what the helpers of the launch before left.
+hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, bool helpers_run, hipStream_t stream);
 size_t score_smem_bytes(int G, int cap);
 
 // Later assignment steps of a Lloyd sequence mark the points that may have changed cluster: bit i of marks[u][first_mark(x0,
@@ -332,6 +333,7 @@ struct CopyBatch {
     void add(void* dst, size_t dpitch, const void* src, size_t spitch, size_t width);
     hipError_t launch(int rows, hipStream_t s);
 };
+hipError_t launch_fill(int32_t* dst, int n, int32_t value, hipStream_t s);
 // Views of the last scoring launch, by cluster id.  keys [U, pos_stride] by position; key_mode[2*u + level]
 // says what they are: 0 = order-preserving image of the rank key r = log mean_h e^{l - LSE_h}; 1 = complement
 // of the bit pattern of sum_h e^{l - LSE_h} (then r = log(sum) - log G).  r_out receives r (NaN: took no part).

@@ -1989,12 +1989,12 @@ static hipError_t launch_score_g(const ScoreParams& p, int copies, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, hipStream_t s)
+hipError_t launch_score_select(const ScoreParams& p, int n_compute_units, bool helpers_run, hipStream_t s)
 {
     // a shadow workgroup per unit where the chip has compute units to spare and the second workgroup
     // of unit u (block u + U) lands on the same L2 slice as the first (blocks go round the 8 slices)
     const bool helped = p.levels == 2 && p.helpers > 0;
-    const int copies = helped ? 1 + p.helpers : (p.U % 8 == 0 && 2 * p.U <= n_compute_units) ? 2 : 1;
+    const int copies = helped ? 1 + (helpers_run ? p.helpers : 0) : (p.U % 8 == 0 && 2 * p.U <= n_compute_units) ? 2 : 1;
     switch (p.G) {
         case 1: return helped ? launch_score_g<1, true>(p, copies, s) : launch_score_g<1, false>(p, copies, s);
         case 2: return helped ? launch_score_g<2, true>(p, copies, s) : launch_score_g<2, false>(p, copies, s);

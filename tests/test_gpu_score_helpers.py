@@ -1,6 +1,7 @@
 """Scoring with helper workgroups (logits of all fine clusters worked out beside the coarse level): the rule on the CPU; the
-ranks and selections bit for bit those of a launch without helpers, at the edges of a helper's share; and steps one after the other,
-eager and from a graph."""
+ranks and selections bit for bit those of a launch without helpers, at the edges of a helper's share; what a unit's workgroup takes from
+them bit for bit what it works out for itself in the same launch, each way shown to have been gone; and steps one after the other, eager
+and from a graph."""
 import ctypes
 import os
 import subprocess
@@ -78,6 +79,45 @@ def test_same_bits_as_without_helpers(nf, nc, G, softness, empty):
             assert torch.equal(torch.nan_to_num(a[k], nan=7.0), torch.nan_to_num(b[k], nan=7.0)), k
         # (the value pass is cut differently: sums of fp32 in another order behind a bf16 output)
         assert (a["out"] - b["out"]).abs().max() <= 2.0 ** -7 * a["out"].abs().max()
+
+
+# Both ways of a unit's workgroup, each made certain: it never takes its helpers' logits, or it takes those that the helpers of an earlier call
+# with the same query left (with another query they give another result, so taken they are).  Both head groups, one and two chunks of candidates,
+# logits that need a shift, empty clusters.
+@pytest.mark.gpu
+@pytest.mark.parametrize("nf,nc,G,softness,empty", [(1, 1, 4, 0.2, False), (17, 3, 1, 0.2, False), (128, 9, 4, 0.2, True), (129, 40, 5, 0.2, False),
+                                                    (300, 20, 8, 0.2, False), (1024, 64, 4, 0.2, True), (1000, 30, 8, 6.0, False), (700, 30, 3, 6.0, True)])
+def test_handed_over_and_worked_out(nf, nc, G, softness, empty):
+    from paper_2506_13059_amd import binding as mp
+    U = 8
+    K, V, q, fot, cof, n = _clustered(U, G, nf, nc, 90 + nf, softness, empty)
+    ctx = mp.MpContext(1, U * G, U, max_tokens=n, levels=2, max_fine=nf, max_coarse=nc)
+    ctx.mp_set_clustering(K.view(1, U, n, 128), V.view(1, U, n, 128), fot, nf, cof, nc)
+    qs = [x.reshape(1, U * G, 128).contiguous() for x in q]
+    count = ctypes.c_int32()
+    how_many = lambda how: mp.lib().mp_test_helpers(ctx.h, how, ctypes.byref(count))      # noqa: E731
+
+    def step(how, x, kb, cb):
+        print(f"nf={nf} nc={nc} G={G} how={how} kb={kb} cb={cb}", flush=True)
+        assert how_many(how) == 0 and count.value == min(31, -(-nf // 128))
+        lse = torch.empty(1, U * G, device="cuda")
+        out = ctx.mp_decode_attention(x, kb, cb, lse=lse)
+        r = [out, lse, ctx.mp_get_counters(), *ctx.mp_get_selection().values()]
+        torch.cuda.synchronize()
+        return [t.view(torch.int64) if t.dtype == torch.float64 else t for t in r]
+
+    for i, (kb, cb) in enumerate([(n // 8, n // 3), (n // 3, n - 5), (n, n), (n // 8, 0)]):
+        x = qs[i % 3]
+        planned = step(0, x, kb, cb)
+        handed = step(2, x, kb, cb)
+        worked_out = step(1, x, kb, cb)
+        for a, b, c in zip(planned, handed, worked_out):
+            assert torch.equal(a, c) and torch.equal(b, c)
+        if kb < n and cb > 0 and nf > 1:
+            step(0, qs[(i + 1) % 3], kb, cb)
+            assert not torch.equal(step(2, x, kb, cb)[1], worked_out[1])
+    assert how_many(3) != 0 and how_many(0) == 0
+    ctx.close()
 
 
 @pytest.mark.gpu
