@@ -259,7 +259,7 @@ struct RowSum {
     double a0 = 0.0, a1 = 0.0;
     u16x2 largest = {0, 0}, smallest = {0xffff, 0xffff};     // kRange: magnitudes, and nonzero magnitudes less one
 };
-template <bool kRange, typename Passes>
+template <bool kRange, int kFew, typename Passes>
 __device__ __forceinline__ RowSum sum_of_rows(const uint32_t* __restrict__ Xu, const int32_t* __restrict__ lp, int s0, int s1, Passes passes)
 {
     const int lane = threadIdx.x & 63;
@@ -271,7 +271,8 @@ __device__ __forceinline__ RowSum sum_of_rows(const uint32_t* __restrict__ Xu, c
     // online refresh, with 32 rows a trip a third of that).  The next 64 indices are asked for ahead, and a whole batch has no
     // branch in front of each row: noting the range had made a cluster of thousands 12 % slower (eight blocks of 131072 keys, the
     // longest of 128 clusters, 2009 -> 2254 us); their build, five iterations, 4620 -> 3655 us, of 32 blocks of 8192 keys 828 -> 796.
-    // (Zeros in the place of the rows past the end, instead of the branches: one cluster of 8192 350 -> 450 us.)
+    // (Zeros in the place of the rows past the end, instead of the branches: one cluster of 8192 350 -> 450 us.)  kFew: up to so many rows
+    // are a batch of that size, which jumps over that many places instead of all of them.
     constexpr int kBatch = 32;
     auto members = [&](int base) { return base + lane < s1 ? (lp ? lp[base + lane] : base + lane) : 0; };
     int next = members(s0);
@@ -279,15 +280,16 @@ __device__ __forceinline__ RowSum sum_of_rows(const uint32_t* __restrict__ Xu, c
         const int nm = (s1 - base < 64) ? s1 - base : 64;
         const int mine = next;
         if (base + 64 < s1) next = members(base + 64);       // (arrives while these rows travel)
-        auto batch = [&](int m, auto full) {
-            uint32_t w[kBatch];
+        auto batch = [&](int m, auto full, auto most) {
+            constexpr int kMost = decltype(most)::value;
+            uint32_t w[kMost];
 #pragma unroll
-            for (int q = 0; q < kBatch; ++q) {
+            for (int q = 0; q < kMost; ++q) {
                 const long long r = __builtin_amdgcn_readlane(mine, (m + q) & 63);
                 w[q] = (full || m + q < nm) ? load_once(&Xu[r * 64 + lane]) : 0u;
             }
 #pragma unroll
-            for (int q = 0; q < kBatch; ++q) {
+            for (int q = 0; q < kMost; ++q) {
                 if (full || m + q < nm) {
                     passes(base + m, q, __builtin_amdgcn_readlane(mine, (m + q) & 63), w[q]);
                     a.a0 += (double)bf16lo_to_f32(w[q]);
@@ -301,8 +303,9 @@ __device__ __forceinline__ RowSum sum_of_rows(const uint32_t* __restrict__ Xu, c
             }
         };
         for (int m = 0; m < nm; m += kBatch) {
-            if (nm - m >= kBatch) batch(m, std::true_type{});
-            else batch(m, std::false_type{});
+            if (nm - m >= kBatch) batch(m, std::true_type{}, std::integral_constant<int, kBatch>{});
+            else if (kFew > 0 && nm - m <= kFew) batch(m, std::false_type{}, std::integral_constant<int, std::max(kFew, 1)>{});
+            else batch(m, std::false_type{}, std::integral_constant<int, kBatch>{});
         }
     }
     return a;
@@ -339,7 +342,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const uint16_t* __res
     const int s0 = start[u * start_stride + f], s1 = start[u * start_stride + f + 1];
     const uint32_t* Xu = reinterpret_cast<const uint32_t*>(X + (long long)u * x_unit_rows * kHeadDim);
     const int32_t* lp = list ? list + u * list_stride : nullptr;
-    const RowSum a = sum_of_rows<kRange>(Xu, lp, s0, s1, [](int, int, int, uint32_t) {});
+    const RowSum a = sum_of_rows<kRange, 0>(Xu, lp, s0, s1, [](int, int, int, uint32_t) {});
     if constexpr (kRange) {
         int hi = max((int)a.largest.x, (int)a.largest.y) >> 7, lo = min((int)a.smallest.x, (int)a.smallest.y);
 #pragma unroll
@@ -409,9 +412,12 @@ constexpr int kMoveRows = 32;
 // memory where the waves fill the chip: refresh of eight 8K contexts 626 -> 552 us (gather, key and value means were a launch each: 178 -> 125 us), build
 // of sixteen 128K prompts 20.30 -> 19.67 ms, resumed generation 1227 -> 1144 us.
 // A long cluster's sum is a chain of trips to memory, so its rows are moved by whichever of the workgroup's waves are done with theirs.
+// Where clusters have a row or two a wave is little more than its start and end: a workgroup without a long cluster has no barrier, and
+// few rows are a batch of four (tables of keys and values given their clustering, 64 units of 8192 rows and as many clusters 1330 -> 1192 us,
+// 4096 clusters 739 -> 681, 2048 392 -> 375; a launch each for rows and means 1115, 666, 403).
 __global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
 {
-    __shared__ int long_from[4], long_end[4], ticket[4];
+    __shared__ int ticket[4];
     const int u = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_table = (p.f1 - p.f0 + 3) / 4, of_clusters = p.key_means ? 2 * per_table : per_table;
     const int32_t* list = p.list + u * p.list_stride;
@@ -436,23 +442,36 @@ __global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
     const unsigned turned = (unsigned)(keys ? group - per_table + 4 : group) + (unsigned)u;
     const int f = p.f0 + (int)(turned % (unsigned)per_table) * 4 + wave;
     const int32_t* start = p.start + u * p.start_stride;
-    const int s0 = f < p.f1 ? start[f] : 0, s1 = f < p.f1 ? start[f + 1] : 0, n = s1 - s0;
-    const bool is_long = n > p.long_cluster;
-    if (lane == 0) {
-        long_from[wave] = is_long && !p.all_by_place ? s0 : 0;
-        long_end[wave] = is_long && !p.all_by_place ? s1 : 0;
-        ticket[wave] = 0;
+    // (all four clusters' places by every wave: only a workgroup with a long one has anything to say to its other waves)
+    int at[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) at[i] = start[min(f - wave + i, p.f1)];
+    int s0 = at[0], s1 = at[1];
+    bool with_long = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        with_long |= at[i + 1] - at[i] > p.long_cluster;
+        if (wave == i) {
+            s0 = at[i];
+            s1 = at[i + 1];
+        }
     }
-    __syncthreads();
+    const int n = s1 - s0;
+    const bool is_long = n > p.long_cluster;
+    with_long &= !p.all_by_place;
+    if (with_long) {
+        if (threadIdx.x < 4) ticket[threadIdx.x] = 0;
+        __syncthreads();
+    }
     if (f < p.f1) {
         const uint32_t* Xd = reinterpret_cast<const uint32_t*>(X);
         RowSum a;
         if (is_long) {
-            a = sum_of_rows<false>(Xd, list, s0, s1, [](int, int, int, uint32_t) {});
+            a = sum_of_rows<false, 0>(Xd, list, s0, s1, [](int, int, int, uint32_t) {});
         } else {
             uint32_t* to_d = reinterpret_cast<uint32_t*>(to);
             uint32_t* kept_d = reinterpret_cast<uint32_t*>(kept);
-            a = sum_of_rows<false>(Xd, list, s0, s1, [&](int at, int q, int row, uint32_t w) {
+            a = sum_of_rows<false, 4>(Xd, list, s0, s1, [&](int at, int q, int row, uint32_t w) {
                 store_once(to_d + (long long)at * 64 + (q * 64 + lane), w);
                 if (kept && row >= p.seq.t0) store_once(kept_d + (long long)(row - p.seq.t0) * 64 + lane, w);
             });
@@ -465,9 +484,11 @@ __global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
         double* sums = keys ? p.key_sums : p.value_sums;
         if (sums) reinterpret_cast<double2*>(sums + ((long long)u * p.sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a.a0, a.a1);
     }
+    if (!with_long) return;
 #pragma unroll 1
     for (int w = 0; w < 4; ++w) {
-        const int from = __builtin_amdgcn_readfirstlane(long_from[w]), end = __builtin_amdgcn_readfirstlane(long_end[w]);
+        const int from = start[min(f - wave + w, p.f1)], end = start[min(f - wave + w + 1, p.f1)];
+        if (end - from <= p.long_cluster) continue;
         // (a piece's rows are asked for in front of the stores of the one before: loads behind stores would wait for those)
         constexpr int kPiece = 16;
         const int pieces = (end - from + kPiece - 1) / kPiece;

@@ -104,3 +104,39 @@ def test_alone_and_among_others(given, lookup):
     for u in (0, 35, U - 1):
         for a, b in zip(many, index([u])):
             assert torch.equal(a[u], b[0])
+
+
+# many clusters of few rows (batches of up to four, and just above), some empty, workgroups without a long cluster; an update that refines
+# nothing (an empty cluster keeps its key centroid)
+@pytest.mark.parametrize("lookup", [False, True])
+@pytest.mark.parametrize("refine", [0, 1])
+def test_small_clusters(lookup, refine):
+    from paper_2506_13059_amd import binding as mp
+    U, F, new = 61, 396, 40
+    g = torch.Generator(device="cuda").manual_seed(9)
+    ids = torch.cat([torch.randint(0, F - 8, (U, 1400), generator=g, device="cuda"), torch.full((U, 100), F - 3, device="cuda")], 1).to(torch.int32)
+    n = ids.shape[1]
+    assert U * F > 6144 >= 8 * F      # (stored by the clusters' waves; alone by places)
+    K, V, Kl = _rows(U, n + new, 21), _rows(U, n + new, 22), _rows(U, n + new, 23) if lookup else None
+    cof = (torch.arange(F, device="cuda", dtype=torch.int32) // 8)[None].expand(U, -1)
+    C = F // 8 + 1
+    seeds = torch.tensor([[3, 30, 7]], dtype=torch.int32).expand(U, -1)
+
+    def index(units):
+        print(f"units={len(units)} lookup={lookup} refine={refine}", flush=True)
+        m = len(units)
+        at = lambda x, a, b: None if x is None else x[units, a:b].contiguous().view(m, 1, -1, 128)      # noqa: E731
+        ctx = mp.MpContext(m, 2, 1, max_tokens=n + new, levels=2, max_fine=F + 3, max_coarse=C, lookup_keys=lookup)
+        ctx.mp_set_clustering(at(K, 0, n), at(V, 0, n), ids[units].contiguous(), F, cof[units].contiguous(), C, k_lookup=at(Kl, 0, n))
+        _check(ctx, K[units, :n], V[units, :n], None if Kl is None else Kl[units, :n], ids[units], F)
+        out = [x.clone() for x in list(ctx.mp_get_centroids(0)) + list(ctx.mp_get_centroids(1))]
+        ctx.mp_update_clusters(at(K, n, n + new), at(V, n, n + new), 3, 0, refine_iters=refine, seeds=seeds[units], k_new_lookup=at(Kl, n, n + new))
+        out += list(ctx.mp_get_layout()) + list(ctx.mp_get_centroids(0)) + list(ctx.mp_get_centroids(1))
+        torch.cuda.synchronize()
+        ctx.close()
+        return [x.reshape(m, -1) for x in out]
+
+    many = index(list(range(U)))
+    for u in (0, U - 1):
+        for a, b in zip(many, index([u])):
+            assert torch.equal(a[u], b[0])
