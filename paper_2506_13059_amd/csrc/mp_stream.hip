@@ -1,5 +1,7 @@
 // Value pass on the matrix cores, for gfx950: the counterpart of value_pass_kernel (mp_value.hip) for groups of
-// query heads whose arithmetic a vector pipe cannot do at the rate the rows arrive.
+// query heads whose arithmetic a vector pipe cannot do at the rate the rows arrive.  The kernel here serves decode steps over bf16
+// rows whose centroid terms ride along with the selected keys or are left out, and steps that select no keys; the others and
+// dense calls have kernels of the same scheme (mp_stream_terms.hip, mp_stream_dense.hip, mp_stream8.hip).
 //
 // A wave streams tiles of 16 rows.  Rows go from global memory straight to LDS (global_load_lds, 16 bytes a lane,
 // four whole rows an instruction), into a ring of two tiles per wave, so that three of the four 4 KiB pieces are on
@@ -18,10 +20,10 @@
 //
 // What bounds it is the memory system: about 100 vector instructions a tile against 420 of the vector-ALU kernel (60 %
 // of a SIMD's issue slots at the dense rate with 4 heads, more than there are with 8).  Measured on the benchmark's
-// 8 GiB cache, dense, 1 / 4 / 5 / 6 / 8 heads: vector ALU 1259 / 1345 / 1367 / 1615 / 1763 us, here with the same
-// chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per compute unit (see plan_streams in mp_plan.h)
-// 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: the call 505 -> 301 to 306 us, 294 of them
-// this kernel; 8 units x 32768, 4 heads: 40.8 -> 26.0 us.
+// 8 GiB cache, dense, which this kernel served then (value_dense_kernel has the same tiles), 1 / 4 / 5 / 6 / 8 heads: vector ALU
+// 1259 / 1345 / 1367 / 1615 / 1763 us, here with the same chunks 1263 / 1341 / 1358 / 1382 / 1409 us, with one workgroup per
+// compute unit (see plan_streams in mp_plan.h) 1230 / 1228 / - / - / 1233 us = 7.0 TB/s; 64 units x 60013 rows, 8 heads: the
+// call 505 -> 301 to 306 us, 294 of them the kernel; 8 units x 32768, 4 heads: 40.8 -> 26.0 us.
 #include "mp_stream_tiles.h"
 
 namespace mp {
@@ -66,31 +68,22 @@ __global__ __launch_bounds__(64 * kWaves, 2) void value_stream_kernel(const Valu
     combine_waves<G, kWaves>(st, reinterpret_cast<float*>(ring_lds), part);
 }
 
-template <int G, int kWaves>
-hipError_t launch_stream_w(const ValuePassParams& p, unsigned blocks, hipStream_t s)
-{
-    static bool configured = false;
-    constexpr size_t smem = kWaves * (kRing + kStripBytes);
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&value_stream_kernel<G, kWaves>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
-    hipLaunchKernelGGL((value_stream_kernel<G, kWaves>), dim3(blocks), dim3(64 * kWaves), smem, s, p);
-    return hipGetLastError();
-}
-
-// Four waves a workgroup, or eight where the launch leaves half of the compute units idle and a wave's share is a
-// long chain of tiles all the same (dense calls over short contexts, whose workspace limits the chunks: 8 units x
-// 4096 rows, 4 / 8 heads: 13.4 / 15.3 us with four waves, 12.8 / 14.7 us with eight).  Elsewhere the two are within 1 %.
 template <int G>
 hipError_t launch_stream_g(const ValuePassParams& p, hipStream_t s)
 {
     const long long blocks = (long long)p.n_units * p.chunks_per_unit;
     if (blocks <= 0) return hipSuccess;
-    const bool eight = blocks <= 128 && p.src[p.n_sources - 1].chunk_rows >= 512;
-    return eight ? launch_stream_w<G, 8>(p, (unsigned)blocks, s) : launch_stream_w<G, 4>(p, (unsigned)blocks, s);
+    constexpr int kWaves = 4;
+    static bool configured = false;
+    constexpr size_t smem = kWaves * (kRing + kStripBytes);
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&value_stream_kernel<G, kWaves>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL((value_stream_kernel<G, kWaves>), dim3((unsigned)blocks), dim3(64 * kWaves), smem, s, p);
+    return hipGetLastError();
 }
 
 }  // namespace
