@@ -221,7 +221,8 @@ mp_status mp_create(const mp_config* cfg, mp_ctx** out)
     A(Kc, U * T * D); A(Vc, U * T * D); A(Ncl, U * T);
     A(Kfb, U * (size_t)ctx->FBcap * D); A(Vfb, U * (size_t)ctx->FBcap * D);
     if (c.lookup_keys) A(Kfs, U * (size_t)ctx->FBcap * D);
-    A(km_assign, U * N); A(km_assign2, U * N); A(km_marks, U * (size_t)mp::marks_of(ctx->Ncap, ctx->max_blocks)); A(km_moved, 2 * U * (size_t)ctx->max_blocks); A(km_range, U * F); A(km_scores, U * N); A(km_changed, U * F); A(km_list, U * N); A(km_cnt, U * T); A(km_start, U * (T + 2));
+    A(km_assign, U * N); A(km_assign2, U * N); A(km_marks, U * (size_t)mp::marks_of(ctx->Ncap, ctx->max_blocks)); A(km_moved, 2 * U * (size_t)ctx->max_blocks); A(km_range, U * F); A(km_list, U * N); A(km_cnt, U * T); A(km_start, U * (T + 2));
+    if (mp::assign_keeps_state(ctx->FBcap, std::min(ctx->Fcap, mp::kResidentMaxK))) { A(km_scores, U * N); A(km_changed, U * F); }     // (no block is longer)
     A(km_Cf, U * F * D); A(km_Cc, U * Cc * D); A(km_parent, U * F); A(km_plist, U * F); A(km_newid, U * F);
     A(km_seed_f, U * F); A(km_seed_c, U * Cc); A(blocks_dev, 3 * (size_t)ctx->max_blocks * 4);
     A(km_amb, 2 * U * (size_t)ctx->max_blocks);

@@ -292,7 +292,6 @@ __global__ __launch_bounds__(256) void assign_mfma_kernel(const uint16_t* __rest
 constexpr int kRowTile = 16;
 constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
 constexpr int kNearCap = 256;                    // (a multiple of sixteen)
-constexpr int kResidentMaxK = 512;
 constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
 constexpr int kWidePairs = 256;                  // (block, unit) pairs up to which workgroups have sixteen waves
 constexpr int kCoarseLds = 160 * 1024 - 2048;    // of a compute unit, less what the coarse level's kernel has besides

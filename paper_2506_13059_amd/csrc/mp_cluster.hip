@@ -255,7 +255,7 @@ mp_status build_lists(mp_ctx* ctx, const Problem& pr, hipStream_t s)
 mp_status lloyd_iterations(mp_ctx* ctx, const Problem& pr, int iters, int settled, hipStream_t s)
 {
     Problem now = pr;
-    if (!pr.sums || !assign_keeps_state(pr.max_pts, pr.max_k)) settled = iters;
+    if (!pr.sums || !ctx->km_scores || !assign_keeps_state(pr.max_pts, pr.max_k)) settled = iters;
     auto state = [&](int it) {
         const bool uses = it >= settled, leaves = it + 1 >= settled && it + 1 < iters;
         return AssignState{uses || leaves ? ctx->km_scores : nullptr, ctx->Ncap, uses ? ctx->km_changed : nullptr, ctx->Fcap};

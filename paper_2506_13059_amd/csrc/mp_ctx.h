@@ -94,8 +94,8 @@ struct mp_ctx {
     int32_t* km_assign2 = nullptr; // [U, Ncap] the iteration before, or after (used in turn; the last one ends in km_assign)
     unsigned long long* km_marks = nullptr;   // [U, marks_of(Ncap, max_blocks)] points that may have changed cluster
     int32_t* km_moved = nullptr;   // [2][U, max_blocks] did an assignment step move a point of the block? (used in turn)
-    float2* km_scores = nullptr;   // [U, Ncap] what an assignment step leaves for the next one (AssignState)
-    uint32_t* km_changed = nullptr;   // [U, Fcap] did a fine cluster's centroid change in the last update?
+    float2* km_scores = nullptr;   // [U, Ncap] what an assignment step leaves for the next one (AssignState; none where no block can be large enough)
+    uint32_t* km_changed = nullptr;   // [U, Fcap] ... and did a fine cluster's centroid change in the last update?
     uint32_t* km_range = nullptr;  // [U, Fcap] exponent range of a fine cluster's keys in the first Lloyd iteration
     int32_t* km_list = nullptr;    // [U, Ncap] member lists (during an assignment step: points of the exact pass)
     int32_t* km_amb = nullptr;     // [2][U, max_blocks] number of such points per block: two arrays used in turn, the one

@@ -165,7 +165,8 @@ struct AssignState {
 // a state.  (In smaller blocks a step is a chain of latencies, and that with a state is no shorter: builds of five iterations, us,
 // without / with: 1500 points x 93 centroids, 6 blocks 186 / 193; 1024 x 32, 24 blocks 187 / 194; 2000 x 60, 1 block 139.5 / 143, 64
 // blocks 277 / 265; 8192 x 256, 1 block 194 / 177; 8192 x 512, 64 blocks 977 / 911.)
-constexpr bool assign_is_resident(int max_pts, int max_k) { return max_k > 0 && max_k <= 512 && max_pts >= 1024; }
+constexpr int kResidentMaxK = 512;
+constexpr bool assign_is_resident(int max_pts, int max_k) { return max_k > 0 && max_k <= kResidentMaxK && max_pts >= 1024; }
 constexpr bool assign_keeps_state(int max_pts, int max_k) { return assign_is_resident(max_pts, max_k) && (long long)max_pts * max_k >= 1 << 20; }
 constexpr int first_mark(int x0, int b) { return (x0 >> 6) + b; }
 inline long long marks_of(long long points, int blocks) { return (points >> 6) + blocks + 1; }

@@ -56,3 +56,18 @@ def test_settled_iterations(kind, n, k, iters, refine):
         cl = O.update_unit(cl, f64(K)[0, n:], f64(V)[0, n:], new_f, 0, seeds[0], refine, 0, 0)
     for g, name in zip(got, ("fine_of_token", "Kc_f", "Vc_f", "N_f")):
         np.testing.assert_array_equal(g[0], cl[name], err_msg=name)
+
+
+def test_state_only_where_a_block_can_be_large_enough():
+    from paper_2506_13059_amd import binding as mp
+    n, W = 200000, 1024
+
+    def size(fine):
+        ctx = mp.MpContext(1, 1, 1, max_tokens=n, levels=1, max_fine=fine, block_w=W, block_alpha=W)
+        b = ctx.device_bytes()
+        ctx.close()
+        return b
+
+    # blocks of at most 2 W points: 512 clusters make 2^20 pairs, and the state is 8 bytes a token beside what a cluster costs anyway
+    a, b, c = (size(f) for f in (510, 511, 512))
+    assert abs((c - b) - (b - a) - 8 * n) < 0.01 * 8 * n
