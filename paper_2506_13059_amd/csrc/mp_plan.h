@@ -117,12 +117,19 @@ inline long long likely_terms(int levels, int n_tokens, int n_fine, int n_coarse
 
 // Whether the terms that ride along with the selected keys have a wave of their own (bf16 rows): where every workgroup has a compute
 // unit (its ten waves do not share one with ten others: 130 units, two workgroups each, 47.1 -> 47.4 to 48.8 us, 300 units 62.5 ->
-// 68.5), and one wave has no more to do than the others.  Whole step, us, riding / own wave: 1 unit of 4 heads x 512 keys 21.0 / 19.4; 8 x
-// 4096 24.5 / 23.5; 32 x 4096 of 5 heads 37.6 / 36.5; 32 x 2048 and a tail of 200 35.7 / 34.1; 100 x 2048 39.0 / 37.7; 128 x 8192 (256 terms,
-// 1024 keys a wave) 120.3 / 118.5; 64 x 1024 (136 terms, 64 keys a wave) 37.3 / 37.1; 128 x 2048 (544 terms, 256 keys a wave) 83 / 87.
+// 68.5; a tail of up to half a chunk, one workgroup a unit on top, can be what is too many: 24 units of 6250 keys and a tail of 201 have
+// 264); and where that wave has no more rows than the others, or than one fetch of row numbers brings, as far as one can tell.
+// Whole step, us, riding / own wave: 1 unit of 4 heads x 512 keys 21.0 / 19.4; 8 x 4096 24.5 / 23.5; 32 x 4096 of 5 heads 37.6 / 36.5; 32 x
+// 2048 and a tail of 200 35.7 / 34.1; 100 x 2048 39.0 / 37.7; 128 x 8192 (256 terms a workgroup, 1024 keys a wave) 120.3 / 118.5.
+// The line, one level, terms a workgroup by keys a wave, clusters of one size: 1 x 1024 (28 by 16) 25.15 / 24.13; 8 x 2048 (32 by 16)
+// 60.9 / 59.6; 8 x 4096 (59 by 32) 69.6 / 69.1; 64 x 4096 (237 by 256) 94.3 / 93.3; 128 x 2048 (250 by 256) 56.5 / 55.4, (300 by 256) 77.7 /
+// 77.8; 32 x 4096 (188 by 128) 109.0 / 109.3, of 8 heads 132.3 / 133.0.  Where a few large clusters are selected and hold half of all keys,
+// twice as many terms stay behind: 8 x 2048 (64 by 16) 51.5 / 51.6; 8 x 4096 (47 by 32) 46.9 / 46.0; 32 x 4096 (237 by 128) 66.3 / 66.4, (375
+// by 128) 94.4 / 96.3; 64 x 4096 (474 by 256) 87.0 / 89.9; 128 x 2048 (398 by 256) 53.4 / 54.7, (498 by 256) 57.6 / 60.7, (598 by 256) 74.1 / 78.5.
 inline bool terms_have_a_wave(long long workgroups, long long terms, long long key_chunks, int chunk_rows)
 {
-    return workgroups <= kStreamWgs && 2 * terms <= key_chunks * chunk_rows;
+    const int most = std::min(chunk_rows / 2, std::max(chunk_rows / 4, 64));
+    return workgroups <= kStreamWgs && terms <= key_chunks * most;
 }
 
 // Dense calls of one or two heads to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one

@@ -39,6 +39,9 @@ def test_rule(plan):
     assert h.terms(1, 4096, 64, 0, 256, 0) == 60 and h.terms(1, 4096, 64, 0, 99999, 0) == 0
     assert h.terms(2, 131072, 4096, 256, 8192, 16384) == 256 + 224 and h.terms(2, 1000, 100, 10, 500, 0) == 10
     assert h.own(256, 480, 2, 4096) and not h.own(257, 1, 2, 4096) and h.own(1, 32, 1, 64) and not h.own(1, 33, 1, 64)
+    # no more terms a workgroup than a wave has keys, or than one strip of row numbers
+    for rows, most in ((128, 64), (256, 64), (512, 128), (1024, 256)):
+        assert h.own(256, 2 * most, 2, rows) and not h.own(256, 2 * most + 1, 2, rows), rows
 
 
 def _case(U, G, nf, nc, n, seed):
@@ -70,7 +73,7 @@ def test_terms_beside_the_keys(U, nf, nc, n, kb, cb, G):
 
 
 # Clusters of four keys, so that budgets of whole clusters leave a known number of terms: `terms` a workgroup of the selected keys.
-MANY = [(128, 1024, 2, t) for t in (0, 1, 16, 17, 64, 65, 129, 250)] + [(100, 1000, 2, 129), (200, 448, 1, 193)]
+MANY = [(128, 1024, 2, t) for t in (0, 1, 16, 17, 64, 65, 128)] + [(128, 2048, 2, 250), (100, 2000, 2, 129), (200, 800, 1, 193)]
 
 
 def _sizes(kb, chunks, terms):
