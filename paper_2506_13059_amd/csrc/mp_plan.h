@@ -132,15 +132,16 @@ inline bool terms_have_a_wave(long long workgroups, long long terms, long long k
     return workgroups <= kStreamWgs && terms <= key_chunks * most;
 }
 
-// Dense calls of one or two heads to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one
-// chain of latencies, and its chain is shorter: no staging in LDS, and the work of an epilogue grows with the heads.  Us
-// on the device, here / matrix cores, 1 head: 1 unit x 8192 rows 8.7 / 9.1, 8 x 2000 8.3 / 8.8, 64 x 500 9.8 / 10.7, 128 x
-// 500 10.3 / 11.0, 64 x 2000 13.5 / 14.0, 128 x 2000 22.6 / 23.5; 2 heads, where the two are level since the matrix cores' kernel has
-// its arguments in registers: 8 x 2000 10.3 / 9.8, 8 x 8192 11.8 / 12.0, 64 x 500 11.1 / 11.1, 128 x 500 11.8 / 11.6, 64 x 2000 15.2 / 15.0, 128 x
-// 2000 26.2 / 25.6; with three heads the matrix cores win (8 x 2000 11.7 / 9.6).
+// Dense calls of one head to a unit over few rows: the vector-ALU kernel, in the same chunks.  Such a call is one chain of
+// latencies, and its chain is as short or shorter: no staging in LDS, and the work of an epilogue grows with the heads.  Us on the
+// device, here / matrix cores, 1 head: 8 units x 2000 rows 8.7 / 9.0, 8 x 8192 10.7 / 10.9, 32 x 4096 14.2 / 14.4, 64 x 500 9.9 / 10.2, 128 x 500
+// 10.8 / 10.9, 64 x 2000 14.6 / 14.4, 128 x 1000 14.75 / 14.3, 1 x 8192 9.2 / 9.1, 1 x 200 6.8 / 6.6; at 131072 rows in all the two have met
+// (32 x 8192 28.1 / 26.4 before the matrix cores' kernel had its arguments in registers).  With two heads the matrix cores win everywhere
+// since then: 1 x 200 7.9 / 6.9, 1 x 8192 10.6 / 9.4, 8 x 64 6.65 / 5.4, 8 x 2000 10.3 / 9.1, 8 x 8192 11.7 / 11.5, 32 x 4096 16.4 / 15.2, 64 x 500
+// 10.7 / 10.3, 64 x 2000 16.5 / 15.0, 128 x 100 7.7 / 6.6, 300 x 400 16.8 / 15.2.
 inline bool short_dense_on_vector_alu(int group, int n_units, long long n)
 {
-    return group <= 2 && n_units * n <= 131072;
+    return group == 1 && n_units * n <= 131072;
 }
 
 // Selected keys stored as 8-bit rows, one query head to a unit: the vector-ALU kernel.  A row's sixteen columns of the matrix

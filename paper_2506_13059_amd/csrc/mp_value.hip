@@ -1,7 +1,7 @@
 // Value pass on the vector ALU, and merge, for gfx950.  Launches over 8-bit rows of one head to a unit
 // (bytes_on_vector_alu in mp_plan.h), over rows that do not start on 16 bytes (a caller's tail or dense keys) and dense
-// calls of one or two heads to a unit over few rows (short_dense_on_vector_alu) come here; all others go to the
-// matrix-core kernels (mp_stream.hip, mp_stream8.hip).
+// calls of one head to a unit over few rows (short_dense_on_vector_alu) come here; all others go to the
+// matrix-core kernels (mp_stream.hip, mp_stream_terms.hip, mp_stream_dense.hip, mp_stream8.hip).
 //
 // The value pass is the byte mover of the decode step: it streams 256-byte key rows and value rows
 // (the keys of the selected clusters, the unclustered tail, or all keys for the dense comparison)

@@ -59,6 +59,33 @@ def test_dense_matches_oracle(B, Hq, Hkv, n):
     _check(out, lse, ref, ref_lse)
 
 
+# short calls of one head (vector ALU) and of two (matrix cores), at the edges of tiles, waves' shares and chunks; and the same rows off a
+# 16-byte boundary, which the vector ALU takes for any group, infinite values among them
+@pytest.mark.parametrize("G", [1, 2])
+@pytest.mark.parametrize("U,n", [(1, 1), (3, 15), (1, 16), (2, 17), (8, 63), (1, 64), (5, 65), (1, 127), (64, 129), (2, 513), (300, 40)])
+def test_short_calls_of_one_and_two_heads(U, n, G):
+    from paper_2506_13059_amd import binding as mp
+    print(f"case U={U} n={n} G={G}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(77 + n + G)
+    q = torch.randn(1, U * G, 128, generator=g, device="cuda").to(torch.bfloat16)
+    K, V = (torch.randn(1, U, n, 128, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    lse = torch.empty(1, U * G, dtype=torch.float32, device="cuda")
+    out = mp.mp_dense_attention(q, K, V, lse=lse)
+    ref, ref_lse = _oracle_full(q, K, V)
+    _check(out, lse, ref, ref_lse)
+
+    def off(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        return y.copy_(x)
+
+    V[0, 0, n // 2, 5], V[0, U - 1, 0, 9], V[0, U - 1, n - 1, 127] = math.inf, -math.inf, math.nan
+    out, want = mp.mp_dense_attention(q, K, V).double(), mp.mp_dense_attention(q, off(K), off(V)).double()
+    fin = torch.isfinite(want)
+    assert torch.equal(out.isnan(), want.isnan()) and torch.equal(out[out.isinf()], want[want.isinf()]) and not fin.all()
+    # bf16 outputs, half a unit in the last place of each, and fp32 sums
+    assert ((out - want).abs()[fin] <= 2.0 ** -7 * want.abs()[fin] + 1e-5 * want[fin].abs().max()).all()
+
+
 def test_dense_peaked_workload_keys():
     """Keys and queries from the benchmark's mixture recipe (logits of order 100)."""
     from paper_2506_13059_amd import binding as mp, inputs

@@ -96,8 +96,9 @@ def test_a_long_tail_does_not_spill_into_a_second_round(lib):
 
 
 def test_dense_calls_on_the_vector_alu(lib):
-    assert lib.short_dense(1, 1, 8192) and lib.short_dense(2, 128, 500) and lib.short_dense(2, 64, 2048)
-    assert not lib.short_dense(3, 1, 100) and not lib.short_dense(1, 64, 2049) and not lib.short_dense(2, 128, 1 << 40)
+    assert lib.short_dense(1, 1, 8192) and lib.short_dense(1, 128, 500) and lib.short_dense(1, 64, 2048)
+    assert not lib.short_dense(1, 64, 2049) and not lib.short_dense(1, 128, 1 << 40)
+    assert not any(lib.short_dense(g, u, n) for g in (2, 3) for u, n in ((1, 100), (8, 64), (64, 2000), (300, 400)))
 
 
 def test_coarse_level_in_one_launch_only_where_it_is_the_faster_way(lib):
