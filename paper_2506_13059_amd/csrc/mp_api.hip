@@ -762,8 +762,9 @@ size_t mp_dense_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_h
 {
     if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n < 0 || n_q_heads % n_kv_heads) return 0;
     const int U = batch * n_kv_heads, G = n_q_heads / n_kv_heads;
-    // the partials of the vector-ALU kernel's chunks (the matrix-core kernel would cut short contexts into more of
-    // them; it takes as many as fit: 8 units x 4096 rows, 4 heads: 12.8 us, 11.8 us with more room)
+    // the partials of the vector-ALU kernel's chunks (the matrix-core kernel would cut short contexts into more of them; it takes
+    // as many as fit: 8 units x 4096 rows, 4 heads: 10.1 us on the device, 7.3 with room for all; 8 heads: 12.6, 8.9; 8 x 8192, 4
+    // heads: 11.9, 10.2.  The size is kept all the same: it decides which shapes mp_dense_attention_static takes)
     const int cr = pick_chunk_rows(n, U);
     const int chunks = ceil_div(n > 0 ? n : 1, cr);
     return sizeof(float) * (size_t)U * chunks * G * kPartStride;

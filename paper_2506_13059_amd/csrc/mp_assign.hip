@@ -1337,9 +1337,10 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
     if (assign_is_resident(max_pts, max_k)) {
         // Two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen.  Up to 256 blocks
         // of all units, sixteen take them in any case when all centroids are looked at: a wave has a chunk or two there, and half as many
-        // workgroups fetch the centroids.  Builds, us, eight / sixteen waves: 32 blocks of 8192 x 256 645 / 639 (keys without clusters 924 /
-        // 914), 8 of them 642 / 633, 64 1133 / 1118, 128 1688 / 1677, 256 2779 / 2762; 2048 19853 / 19933.  (Settled iterations: 32 of
-        // them 644 / 651, 2048 19842 / 20140, keys without clusters 924 / 925, 64 1133 / 1111.)
+        // workgroups fetch the centroids.  Builds of ten iterations (three of these steps), us, eight / sixteen waves, two runs each that differ
+        // by up to 0.5 % (128 blocks: 1.3): 8 blocks of 8192 x 256 336 / 331, keys without clusters 601 / 593; 32 617 / 611 and 899 / 873; 64
+        // 885 / 872 and 1095 / 1081; 128 1408 / 1395 and 1629 / 1626; level at 256: 2499 / 2502 and 2663 / 2682; 2048 19853 / 19933.  (Settled
+        // iterations keep eight: 32 blocks 644 / 651, 2048 19842 / 20140, keys without clusters 924 / 925; 64, the one gain, 1133 / 1111.)
         static bool configured[4] = {};
         auto go = [&](auto kernel, int waves, int bytes_per_row, bool& set) {
             return launch_resident(kernel, waves, bytes_per_row, set, X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows,

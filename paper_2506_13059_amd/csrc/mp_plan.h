@@ -176,9 +176,10 @@ inline int score_helpers(int n_units, int n_compute_units, int levels, int n_fin
 //              512 x 48: 1328 / 1408,        x 64: 1437 / 1392, x 256: 1754 / 1295
 //   256 pairs  256 points x 96: 1352 / 1437, x 256: 1577 / 1586; 512 x 48: 2499 / 2682, x 128: 2683 / 2658
 //   1024 pairs 256 points x 64: 5035 / 5092, x 128: 5462 / 5428; 512 x 48: 8509 / 8640, x 64: 8983 / 8688
-// (Since the points stand in LDS one launch is the shorter way past these lines, too, keys with / without families: 1 pair 256 x 256
-// 293 / 448 and 459 / 586, 512 x 96 382 / 456 and 853 / 787, 64 pairs 512 x 128 1417 / 1489 and 2317 / 2348.  No workload here is there; the
-// lines stand where they were.)
+// These are from before the points stood in LDS and touched clusters alone were summed again.  With that, one launch is the shorter way at
+// five of six points past the lines, too, one launch / steps, keys with and without families: 1 pair 256 x 256 293 / 448 and 459 / 586, 512 x
+// 96 382 / 456 and 853 / 787, 64 pairs 512 x 128 1417 / 1489 and 2317 / 2348.  So the lines are safe and no longer where the two ways
+// meet; where that is has not been measured.
 // More than 512 points always take the steps (refreshes of 64 blocks of 256 .. 1100 points average 1133 us with the line
 // at 512 points, 1181 with it at 1024).
 constexpr int kLevelMaxPts = 512;
