@@ -422,8 +422,11 @@ constexpr int kMoveRows = 32;
 // of sixteen 128K prompts 20.30 -> 19.67 ms, resumed generation 1227 -> 1144 us.
 // A long cluster's sum is a chain of trips to memory, so its rows are moved by whichever of the workgroup's waves are done with theirs.
 // Where clusters have a row or two a wave is little more than its start and end: a workgroup without a long cluster has no barrier, and
-// few rows are a batch of four (tables of keys and values given their clustering, 64 units of 8192 rows and as many clusters 1330 -> 1192 us,
-// 4096 clusters 739 -> 681, 2048 392 -> 375; a launch each for rows and means 1115, 666, 403).
+// few rows are a batch of four.  Tables of keys and values given their clustering, two levels, 64 units of 8192 rows and as many clusters
+// 1330 -> 1192 us, with the sums past the caches 1168; 4096 clusters 739 -> 681 -> 660, 2048 392 -> 380 (a launch each for rows and means 1128,
+// 661, 408: only where most clusters have a single row, and sums, is that still the shorter way, by 2 to 4 %).
+// kSumsOnce: the sums go past the caches (kCachedSums).
+template <bool kSumsOnce>
 __global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
 {
     __shared__ int ticket[4];
@@ -491,7 +494,12 @@ __global__ __launch_bounds__(256) void stored_rows_kernel(const StoredRows p)
         else if (!keys || !p.key_keeps) *mean = 0u;
         if (!keys && lane == 0) p.counts[table] = n;
         double* sums = keys ? p.key_sums : p.value_sums;
-        if (sums) reinterpret_cast<double2*>(sums + ((long long)u * p.sum_unit_rows + f) * kHeadDim)[lane] = make_double2(a.a0, a.a1);
+        if (sums) {
+            double2* to_sums = reinterpret_cast<double2*>(sums + ((long long)u * p.sum_unit_rows + f) * kHeadDim) + lane;
+            const double2 both = make_double2(a.a0, a.a1);
+            if constexpr (kSumsOnce) store_once(reinterpret_cast<uint4*>(to_sums), __builtin_bit_cast(uint4, both));
+            else *to_sums = both;
+        }
     }
     if (!with_long) return;
 #pragma unroll 1
@@ -718,6 +726,10 @@ hipError_t launch_block_lists(const int32_t* ids, long long ids_stride, const in
 // 37.1 / 38.1, 4 of 256 42.3 / 41.9, 8 of 256 56.2 / 52.3, 64 of 256 217 / 185; builds of five iterations, values only: 1 x 46 148.4 / 154.4,
 // 8 x 128 284 / 287, 16 x 256 460 / 464, 8 x 1024 613.9 / 610.7, 64 x 256 817 / 807.
 constexpr int kFewClustersOfTwo = 768, kFewClustersOfOne = 6144;      // of all units
+// Clusters of all units whose sums (a kilobyte a table) do not stay in the 256 MiB last-level cache until the coarse tables are added up from
+// them: they are stored past it.  Us, through it / past it, two levels, both tables: 64 units of 2048 clusters 384 / 392, 16 of 8000 838 / 850, 64 of
+// 2730 493 / 481, 64 of 4096 678 / 660, 256 of 700 475 / 468, 32 of 8192 993 / 972, 128 of 3000 864 / 833.
+constexpr long long kCachedSums = 150000;
 hipError_t launch_stored_rows(StoredRows p, int U, hipStream_t s)
 {
     if (p.n <= 0 || p.f1 <= p.f0) return hipSuccess;
@@ -726,7 +738,9 @@ hipError_t launch_stored_rows(StoredRows p, int U, hipStream_t s)
     p.all_by_place = (long long)U * (p.f1 - p.f0) <= (p.key_means ? kFewClustersOfTwo : kFewClustersOfOne);
     if (p.all_by_place) p.long_cluster = -1;
     const int groups = per_table * (p.key_means ? 2 : 1) + places * (p.all_by_place ? 2 : p.key_means ? 0 : 1);
-    hipLaunchKernelGGL(stored_rows_kernel, dim3(groups, U), dim3(256), 0, s, p);
+    const bool past = (p.key_means ? p.key_sums : p.value_sums) && (long long)U * (p.f1 - p.f0) * (p.key_means ? 2 : 1) > 2 * kCachedSums;
+    if (past) hipLaunchKernelGGL(stored_rows_kernel<true>, dim3(groups, U), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(stored_rows_kernel<false>, dim3(groups, U), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

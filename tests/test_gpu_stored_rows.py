@@ -140,3 +140,33 @@ def test_small_clusters(lookup, refine):
     for u in (0, U - 1):
         for a, b in zip(many, index([u])):
             assert torch.equal(a[u], b[0])
+
+
+# so many clusters that their sums go past the caches, of both tables and (lookup keys) of the values' alone; a unit's tables, the coarse ones
+# added up from the sums among them, are those it has alone
+@pytest.mark.parametrize("U,lookup", [(305, False), (600, True)])
+def test_sums_past_the_caches(U, lookup):
+    from paper_2506_13059_amd import binding as mp
+    F, n, C = 512, 700, 64
+    assert U * F * (1 if lookup else 2) > 300000
+    g = torch.Generator(device="cuda").manual_seed(31)
+    ids = torch.randint(0, F, (U, n), generator=g, device="cuda").to(torch.int32)
+    K, V, Kl = _rows(U, n, 32), _rows(U, n, 33), _rows(U, n, 34) if lookup else None
+    cof = (torch.arange(F, device="cuda", dtype=torch.int32) // 8)[None].expand(U, -1)
+
+    def index(units):
+        print(f"units={len(units)} lookup={lookup}", flush=True)
+        m = len(units)
+        at = lambda x: None if x is None else x[units].contiguous().view(m, 1, -1, 128)      # noqa: E731
+        ctx = mp.MpContext(m, 2, 1, max_tokens=n, levels=2, max_fine=F, max_coarse=C, lookup_keys=lookup)
+        ctx.mp_set_clustering(at(K), at(V), ids[units].contiguous(), F, cof[units].contiguous(), C, k_lookup=at(Kl))
+        _check(ctx, K[units], V[units], None if Kl is None else Kl[units], ids[units], F)
+        out = [x.clone().reshape(m, -1) for x in list(ctx.mp_get_centroids(0)) + list(ctx.mp_get_centroids(1))]
+        torch.cuda.synchronize()
+        ctx.close()
+        return out
+
+    many = index(list(range(U)))
+    for u in (0, U // 2, U - 1):
+        for a, b in zip(many, index([u])):
+            assert torch.equal(a[u], b[0])
