@@ -418,7 +418,7 @@ static mp_status decode_impl(mp_ctx* ctx, const void* q, const void* q_lookup, c
     sp.lds_cap = std::min(1024, std::max(ctx->n_fine, std::max(ctx->n_coarse, 1)));
     sp.G = G; sp.U = U;
     sp.early = ctx->early; sp.early_stride = ctx->early_cap; sp.early_done = ctx->early_done;
-    sp.helpers = ctx->early ? score_helpers(U, ctx->n_cus, ctx->cfg.levels, ctx->n_fine) : 0;
+    sp.helpers = ctx->early && helpers_pay(U, ctx->n_tokens, ctx->n_fine, coarse_budget) ? score_helpers(U, ctx->n_cus, ctx->cfg.levels, ctx->n_fine) : 0;
     if (app) {
         sp.app_n = app->n; sp.app_dst_rows = app->dst_rows; sp.app_row = app->row;
         for (int a = 0; a < app->n; ++a) { sp.app_src[a] = app->src[a]; sp.app_dst[a] = app->dst[a]; }

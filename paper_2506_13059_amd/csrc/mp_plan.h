@@ -167,6 +167,18 @@ inline int score_helpers(int n_units, int n_compute_units, int levels, int n_fin
     return (n_fine + most - 1) / most <= 256 ? most : 0;
 }
 
+// Whether they are launched.  A unit takes their logits if its candidates fit the register path (1024), as many as a budget of keys is likely
+// to leave (with a sixteenth to spare: a unit has a few less or more).  With more candidates they only bring the rows nearer, which pays up
+// to 32768 clusters of all units: without / with, all clusters candidates, 1 unit x 4096 105.0 / 103.0; 8 x 2048 67.4 / 65.7, x 4096 107.7 /
+// 105.8; 9 x 2048 69.7 / 68.4, x 4096 109.8 / 118.8, of 2 heads 133.2 / 139; 16 x 2048 71.4 / 69.9; 24 x 1300 63.4 / 62.0, x 1600 of 8
+// heads 79.0 / 79.6; 28 x 1300 65.7 / 65.6; 9 x 4096, 1169 candidates 60.5 / 61.2, 877 47.4 / 39.4; 24 x 1600 of 8 heads, 952 49.6 / 39.3.
+inline bool helpers_pay(int n_units, int n_tokens, int n_fine, int coarse_budget)
+{
+    const int n = std::max(n_tokens, 1);
+    const long long candidates = (long long)n_fine * std::min(coarse_budget, n) / n;
+    return candidates <= 1024 + 64 || (long long)n_units * n_fine <= 32768;
+}
+
 // Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one
 // workgroup per pair, or in a launch per step.  The workgroup's time grows with its clusters (each is one wave's walk over
 // all points and a trip to memory, sixteen or eight waves) and points, that of the steps with their number and, beyond one

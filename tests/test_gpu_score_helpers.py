@@ -32,6 +32,17 @@ def test_rule(tmp_path):
     assert h(8, 256, 2, 1024) == 8 and h(24, 256, 2, 1563) == 9 and h(64, 256, 2, 320) == 3 and h(32, 256, 2, 2048) == 0
 
 
+def test_launched_where_they_are_taken_or_warm_the_caches(tmp_path):
+    src, so = tmp_path / "p.cpp", tmp_path / "p.so"
+    src.write_text(f'#include "{HEADER}"\nextern "C" int pay(int u, int n, int f, int cb) {{ return mp::helpers_pay(u, n, f, cb); }}\n')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", str(so), str(src)])
+    pay = ctypes.CDLL(str(so)).pay
+    assert pay(9, 41807, 4096, 9000) and not pay(9, 41807, 4096, 12000) and not pay(9, 41807, 4096, 1 << 30)
+    assert pay(9, 41807, 2048, 41807) and pay(8, 32768, 4096, 32768) and not pay(24, 40000, 1600, 40000) and pay(24, 40000, 1600, 24000)
+    assert pay(4, 16384, 8192, 16384) and not pay(5, 16384, 8192, 16384) and pay(5, 16384, 8192, 2176) and not pay(5, 16384, 8192, 2178)
+    assert pay(1, 0, 1, 0)
+
+
 def _clustered(U, G, nf, nc, seed, softness=0.2, empty=False):
     from paper_2506_13059_amd import inputs
     n = 3 * nf + 40
