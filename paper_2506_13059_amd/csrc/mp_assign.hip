@@ -293,7 +293,6 @@ constexpr int kRowTile = 16;
 constexpr int kHalfTiles = 16;                   // tiles whose slots fit the six bits
 constexpr int kNearCap = 256;                    // (a multiple of sixteen)
 constexpr int kResidentTwiceK = 304;             // 2 x (304 x 260 + 2.6 K) bytes of the compute unit's 160 KiB
-constexpr int kWidePairs = 256;                  // (block, unit) pairs up to which workgroups have sixteen waves
 constexpr int kCoarseLds = 160 * 1024 - 2048;    // of a compute unit, less what the coarse level's kernel has besides
 constexpr int kChangedTwiceK = 288;              // 2 x (288 x 268 + 1.6 K)
 constexpr uint32_t kSlotMask = (1u << kResidentSlotBits) - 1u;
@@ -1336,11 +1335,15 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
     const int n_chunks = (max_pts + kPtsPerWg - 1) / kPtsPerWg;
     if (assign_is_resident(max_pts, max_k)) {
         // Two workgroups of eight waves a compute unit where two copies of the centroids fit its LDS, else one of sixteen.  Up to 256 blocks
-        // of all units, sixteen take them in any case when all centroids are looked at: a wave has a chunk or two there, and half as many
-        // workgroups fetch the centroids.  Builds of ten iterations (three of these steps), us, eight / sixteen waves, two runs each that differ
-        // by up to 0.5 % (128 blocks: 1.3): 8 blocks of 8192 x 256 336 / 331, keys without clusters 601 / 593; 32 617 / 611 and 899 / 873; 64
-        // 885 / 872 and 1095 / 1081; 128 1408 / 1395 and 1629 / 1626; level at 256: 2499 / 2502 and 2663 / 2682; 2048 19853 / 19933.  (Settled
-        // iterations keep eight: 32 blocks 644 / 651, 2048 19842 / 20140, keys without clusters 924 / 925; 64, the one gain, 1133 / 1111.)
+        // of all units, sixteen take them in any case when all centroids are looked at (waves_for_blocks): a wave has a chunk or two there,
+        // and half as many workgroups fetch the centroids -- but where that would leave a fifth of the waves out (129 to 170 blocks, 86 to
+        // 102: one and two of the larger workgroups a block, three and five of the smaller), chunks and near ties wait for the waves there are:
+        // 160 blocks of 8192 x 256 1759 / 1811, keys without clusters 2001 / 2047, few different keys 1868 / 2213; 96 1183 / 1189, 1408 / 1417, 1226 / 1314;
+        // 129 of 1024 x 60, three iterations 194 / 198, 222 / 224, 238 / 257.
+        // Elsewhere, builds of ten iterations (three of these steps), us, eight / sixteen waves, two runs each that differ by up to 0.5 %
+        // (128 blocks: 1.3): 8 blocks of 8192 x 256 336 / 331, keys without clusters 601 / 593; 32 617 / 611 and 899 / 873; 64 885 / 872 and
+        // 1095 / 1081; 72 1003 / 989 and 1222 / 1206; 104 1273 / 1263 and 1502 / 1492; 192 2119 / 2096 and 2300 / 2268; level at 256: 2499 /
+        // 2502 and 2663 / 2682; 2048 19853 / 19933.  (Settled iterations keep eight: 32 blocks 644 / 651, 2048 19842 / 20140, keys without clusters 924 / 925; 64, the one gain, 1133 / 1111.)
         static bool configured[4] = {};
         auto go = [&](auto kernel, int waves, int bytes_per_row, bool& set) {
             return launch_resident(kernel, waves, bytes_per_row, set, X, x_unit_rows, blocks_dev, nb, max_pts, max_k, U, C, c_unit_rows,
@@ -1348,7 +1351,7 @@ hipError_t launch_assign(const uint16_t* X, long long x_unit_rows, const int32_t
         };
         if (st.changed)
             return max_k <= kChangedTwiceK ? go(assign_changed_kernel<8>, 8, 268, configured[0]) : go(assign_changed_kernel<16>, 16, 268, configured[1]);
-        return max_k <= kResidentTwiceK && (long long)nb * U > kWidePairs ? go(assign_resident_kernel<8>, 8, 260, configured[2]) : go(assign_resident_kernel<16>, 16, 260, configured[3]);
+        return max_k <= kResidentTwiceK && waves_for_blocks((long long)nb * U) == 8 ? go(assign_resident_kernel<8>, 8, 260, configured[2]) : go(assign_resident_kernel<16>, 16, 260, configured[3]);
     }
     hipLaunchKernelGGL(assign_mfma_kernel, dim3(n_chunks, nb, U), dim3(256), 0, s, X, x_unit_rows, blocks_dev, C,
                        c_unit_rows, assign, assign_stride, amb_list, list_stride, amb_cnt, cnt_stride, mv);

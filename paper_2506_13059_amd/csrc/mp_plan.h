@@ -179,6 +179,14 @@ inline bool helpers_pay(int n_units, int n_tokens, int n_fine, int coarse_budget
     return candidates <= 1024 + 64 || (long long)n_units * n_fine <= 32768;
 }
 
+// Waves of a workgroup of an assignment step that looks at all centroids, where two workgroups of eight fit a compute unit: sixteen up to
+// 256 (block, unit) pairs, unless whole workgroups of them come to less than four fifths of the waves that eight come to.
+inline int waves_for_blocks(long long pairs)
+{
+    if (pairs < 1 || pairs > 256) return 8;
+    return 5 * (256 / pairs) > 2 * (512 / pairs) ? 16 : 8;
+}
+
 // Whether the coarse level of (block, unit) pairs of at most max_pts fine and max_k coarse clusters runs in one launch, one
 // workgroup per pair, or in a launch per step.  The workgroup's time grows with its clusters (each is one wave's walk over
 // all points and a trip to memory, sixteen or eight waves) and points, that of the steps with their number and, beyond one

@@ -1,4 +1,4 @@
-"""GPU parity of the two workgroup widths of `assign_resident_kernel` (sixteen waves up to 256 blocks of all units, eight above): a unit has
+"""GPU parity of the two workgroup widths of `assign_resident_kernel` (sixteen waves for one block of all units, eight for 258): a unit has
 the same index alone and among 257 others, at the edges of centroid tiles and chunks of points.  (Alone it is compared with the oracle
 in test_gpu_kmeans.py and test_gpu_assign.py.)  Bit-identical."""
 import pytest

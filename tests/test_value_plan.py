@@ -21,6 +21,7 @@ extern "C" void plan(int units, long long first, long long tail, int most, int* 
 }}
 extern "C" int short_dense(int group, int units, long long n) {{ return mp::short_dense_on_vector_alu(group, units, n); }}
 extern "C" int coarse_level(long long pairs, int pts, int k) {{ return mp::coarse_level_fits(pairs, pts, k); }}
+extern "C" int waves(long long pairs) {{ return mp::waves_for_blocks(pairs); }}
 extern "C" int most_selected(int levels, int kb, int cb, int n) {{ return mp::most_selected(levels, kb, cb, n); }}
 ''')
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", str(so), str(src)])
@@ -99,6 +100,13 @@ def test_dense_calls_on_the_vector_alu(lib):
     assert lib.short_dense(1, 1, 8192) and lib.short_dense(1, 128, 500) and lib.short_dense(1, 64, 2048)
     assert not lib.short_dense(1, 64, 2049) and not lib.short_dense(1, 128, 1 << 40)
     assert not any(lib.short_dense(g, u, n) for g in (2, 3) for u, n in ((1, 100), (8, 64), (64, 2000), (300, 400)))
+
+
+def test_waves_of_an_assignments_workgroups(lib):
+    narrow = [p for p in range(1, 400) if lib.waves(ctypes.c_longlong(p)) == 8]
+    assert narrow == [*range(86, 103), *range(129, 171), *range(257, 400)] and lib.waves(ctypes.c_longlong(1)) == 16
+    for p in range(1, 257):         # whole workgroups, of sixteen on 256 places or of eight on 512: at least three quarters of the others' waves
+        assert p in narrow or 4 * 16 * (256 // p) >= 3 * 8 * (512 // p), p
 
 
 def test_coarse_level_in_one_launch_only_where_it_is_the_faster_way(lib):
